@@ -87,7 +87,8 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  *                         per feature gradient: 6*B^2*d flop instead of 12.  Shape limits of MATERIALIZED
  *                         (a batch that is not whole 256-row tiles is padded in the workspace as there).  Inputs whose rows' or columns' largest logits lie more than about
  *                         60 (base 2) under the largest positive-pair logit are handed over, inside the same
- *                         call, to the MATERIALIZED kernels, so the workspace is sized for those as well.
+ *                         call, to the MATERIALIZED kernels, so the workspace is sized for those as well.  A
+ *                         batch too small to gain from it (B*B*d < 1e10) goes to those kernels at once.
  * DISCO_PATH_AUTO         the fastest path that supports the arguments: SYMMETRIC (N = 1) or
  *                         MATERIALIZED when their shape limits hold, else NAIVE.  Feature widths that are not
  *                         a multiple of 64, fp32 inputs, and ragged shares of blocks smaller than
@@ -192,6 +193,7 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
  * replaced.  Stages of DISCO_PATH_MATERIALIZED (DISCO_STAGES_MATERIALIZED = 6):
  *   1 row norms + positive-pair logits   2 logit tiles + softmax numerators   3 row merge + scaled transpose
  *   4 key-side gradient GEMM             5 query-side split GEMM              6 query finalize + scalars
+ * (Stages 4 and 5 are one launch while stage timing is off, two while it is on.)
  * Stages of DISCO_PATH_NAIVE (DISCO_STAGES_NAIVE = 5): similarity, row softmax, scalars, key grad, query grad.
  * Stages of DISCO_PATH_FUSED (DISCO_STAGES_FUSED = 5): row norms + positive-pair logits, streaming forward
  *   (row sums only), row merge + scaled transpose, all key panels (recompute + both gradient GEMMs),

@@ -16,6 +16,7 @@ void stage_mark(hipStream_t st, int k) {
   void** ev = g_stage_events.load(std::memory_order_acquire);
   if (ev && k < g_stage_count.load(std::memory_order_acquire) && ev[k]) (void)hipEventRecord(static_cast<hipEvent_t>(ev[k]), st);
 }
+bool stage_marks_on() { return g_stage_events.load(std::memory_order_acquire) != nullptr; }
 }  // namespace disco
 
 extern "C" int disco_set_stage_events(void** events, int count) {

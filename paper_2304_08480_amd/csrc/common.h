@@ -44,6 +44,7 @@ __host__ __device__ inline float loss_norm(int64_t B, int variant) { return (var
 
 // Benchmark stage timing (see disco_set_stage_events): records events[k] on `st` if it exists.
 void stage_mark(hipStream_t st, int k);
+bool stage_marks_on();
 
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 

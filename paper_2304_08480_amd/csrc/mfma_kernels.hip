@@ -19,7 +19,7 @@
 // query tile and k_logit_repair redoes that tile with the true row maximum as its reference (a slow path for
 // inputs that are not CLIP-like; it returns at once when nothing is flagged).
 //
-// One 256x256x64 NT tile main loop (mfma_tile.h: 8 waves, each 128x64 = 4x2 MFMA 32x32x16 blocks, operands
+// One NT tile main loop (mfma_tile.h: 256x256x64 by 8 waves, or 128x128x64 by 4, of MFMA 32x32x16 blocks, operands
 // loaded global -> LDS directly into a ring of five units) serves all three contractions; operands whose
 // reduction index is not the contiguous one in memory are read from LDS with transposing loads.
 #include "common.h"
@@ -33,16 +33,23 @@ using namespace tile;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float REF_HEADROOM = 100.f;                    // largest exponent (base 2) a stored numerator may reach
 
-constexpr int E_ROW_BYTES = BM * 2;                      // row of the bf16 tile copy in LDS (swizzled, not padded)
-constexpr int E_TILE_BYTES = BN * E_ROW_BYTES;            // 128 KiB
-constexpr int LOGIT_SMEM_BYTES = E_TILE_BYTES > SMEM_BYTES ? E_TILE_BYTES : SMEM_BYTES;
-constexpr int GEMM_SMEM_BYTES = OUT_SMEM_BYTES > SMEM_BYTES ? OUT_SMEM_BYTES : SMEM_BYTES;
+constexpr int BM = 256, BN = 256, NTHREADS = Cfg<256>::NTHREADS;     // the symmetric path's tiles
+
+// The tile kernels come in two sizes, T = 256 (one workgroup of 8 waves per compute unit) and T = 128 (4 waves, two
+// workgroups per compute unit); make_plan chooses.
+template <int T>
+constexpr int E_ROW_BYTES = T * 2;                       // row of the bf16 tile copy in LDS (swizzled, not padded)
+template <int T>
+constexpr int E_TILE_BYTES = T * E_ROW_BYTES<T>;         // 128 KiB at T = 256
+template <int T>
+constexpr int LOGIT_SMEM_BYTES = E_TILE_BYTES<T> > Cfg<T>::SMEM_BYTES ? E_TILE_BYTES<T> : Cfg<T>::SMEM_BYTES;
+template <int T>
+constexpr int GEMM_SMEM_BYTES = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SMEM_BYTES<T> : Cfg<T>::SMEM_BYTES;
 
 // Workgroup id -> tile, keeping the workgroups that share an XCD's L2 on neighbouring tiles.
 // Workgroups are dealt round-robin to the 8 XCDs; XCD x takes the x-th contiguous eighth of the
 // (padded) tile list.  Returns false for padding.
-__device__ __forceinline__ bool xcd_linear(int total, int& lin) {
-  const int w = blockIdx.x;
+__device__ __forceinline__ bool xcd_linear(int w, int total, int& lin) {
   const int chunk = (total + 7) / 8;
   lin = (w & 7) * chunk + (w >> 3);
   return (w >> 3) < chunk && lin < total;
@@ -66,12 +73,12 @@ struct BlockPtrs {
   const uint16_t* X;     // b x d, the rank's rows (zero rows past the real ones)
   const uint16_t* Y;     // B x d (zero rows past the real ones)
   uint16_t* E;           // b x W stored numerators of one key panel, in 16-byte atoms (e_index)
-  float* lpart;          // (B/128) x b partial row sums (label column excluded)
+  float* lpart;          // (2B/T) x b partial row sums (label column excluded) of logit tiles of size T
   float* ediag;          // b: numerator of the label column
   float* zd2;            // b: z2 of the positive pair
   float* xnorm;          // b: |x_i|
   float* ref2;           // b: exponent reference of the row (written by the statistics pass, replaced by a repair)
-  int* tileflag;         // b / 256: set when a row of that query tile has lost its row total to underflow
+  int* tileflag;         // b / T: set when a row of that query tile has lost its row total to underflow
   const float* ymax_parts; // NORM_BLOCKS partial maxima of |y_j|^2
   float* beta;           // b
   float* gdiag;          // b: P_label - 1
@@ -79,6 +86,7 @@ struct BlockPtrs {
   float* rowds;          // b
   uint16_t* Xs;          // d x b: (beta_i x_i)^T in bf16
   float* part;           // splitK x b x d partial query-side products
+  float* kpart;          // key_splits x B x d partial key-side products (only where the plan splits that reduction)
   float* gq;             // query-side gradient destination (gI for block A, gT for block C), B x d
   float* gk;             // key-side gradient destination, B x d
 };
@@ -89,7 +97,7 @@ struct Blocks {
   const int* gate;       // nullptr: the kernel always runs; else it runs only while *gate == gate_value (the symmetric
   int gate_value;        // full-loss path hands over to the two-block path through this flag)
   int64_t rows, keys;    // the rank's rows and the batch as the caller has them.  The kernels' own b / B arguments are
-                         // these rounded up to whole 256-row tiles; where they differ (a ragged share), X and Y are
+                         // these rounded up to whole tiles; where they differ (a ragged share), X and Y are
                          // zero-padded copies, query rows >= rows and key columns >= keys are padding
 };
 
@@ -110,7 +118,7 @@ __device__ __forceinline__ float row_reference(float zd2, float xnorm, float yma
 }
 
 constexpr int NORM_BLOCKS = 512;     // workgroups per matrix that take row norms = partial maxima per matrix
-static_assert(NORM_BLOCKS == NTHREADS, "the logit kernel folds the partial maxima one per thread");
+static_assert(NORM_BLOCKS == 512, "the logit kernels fold the partial maxima one or two per thread");
 
 // Preparation, two kinds of workgroup in one launch (they are independent of each other):
 //  * blockIdx.x < 2 NORM_BLOCKS: partial maximum over rows of |row|^2 of I (first NORM_BLOCKS workgroups) or T,
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(256) void k_prep(Blocks bl, const uint16_t* I, cons
   const int64_t rb = (bp + 3) / 4;                      // row workgroups per block
   const int64_t q = (int64_t)blockIdx.x - 2 * NORM_BLOCKS;
   if (q == 0)
-    for (int64_t it = threadIdx.x; it < bp / BN; it += 256) { bl.z[0].tileflag[it] = 0; bl.z[1].tileflag[it] = 0; }
+    for (int64_t it = threadIdx.x; it < bp / 128; it += 256) { bl.z[0].tileflag[it] = 0; bl.z[1].tileflag[it] = 0; }
   const BlockPtrs& p = bl.z[q / rb];
   const int64_t i = (q % rb) * 4 + wave;
   if (i >= bp) return;
@@ -234,54 +242,56 @@ __global__ __launch_bounds__(256) void k_pad_operands(const uint16_t* I, const u
 // are added into rs / kept in ed (registers of the lane, indexed like ref2) instead of being written to lpart / ediag.
 // jl0: first key column of the tile relative to the panel of width W that p.E holds.  STREAM: streaming stores
 // (written once, read by later kernels: keeps the operand tiles in L2).  STAGE: also leave the bf16 tile in LDS,
-// row-major 256 x 256 (8-byte granules XOR-swizzled with the row: conflict-free 8-byte writes and 16-byte reads),
+// row-major T x T (8-byte granules XOR-swizzled with the row: conflict-free 8-byte writes and 16-byte reads),
 // for a caller that wants sums down its columns.
 constexpr int64_t NO_SELF = -((int64_t)1 << 40);
 
-// Do label columns or left-out columns of the 256 query rows from global row g on fall among key rows [j0, j0 + BM)?
+// Do label columns or left-out columns of the T query rows from global row g on fall among key rows [j0, j0 + T)?
 // (Only such tiles pay for finding those columns.  The rows of a tile of the two-view loss may lie in both views.)
+template <int T>
 __device__ __forceinline__ bool tile_has_marked_columns(int64_t g, int64_t B, int variant, int64_t j0) {
-  auto hits = [&](int64_t lo, int64_t hi) { return lo < j0 + BM && j0 < hi; };      // key rows [lo, hi)
-  if (variant != LOSS_NTXENT) return hits(g, g + BN);
+  auto hits = [&](int64_t lo, int64_t hi) { return lo < j0 + T && j0 < hi; };       // key rows [lo, hi)
+  if (variant != LOSS_NTXENT) return hits(g, g + T);
   const int64_t M = B / 2;
-  bool h = hits(g, g + BN);                                                          // the rows' own columns
-  const int64_t hi1 = g + BN < M ? g + BN : M;                                       // rows of view one: label g' + M
+  bool h = hits(g, g + T);                                                           // the rows' own columns
+  const int64_t hi1 = g + T < M ? g + T : M;                                         // rows of view one: label g' + M
   if (g < hi1) h = h || hits(g + M, hi1 + M);
   const int64_t lo2 = g > M ? g : M;                                                 // rows of view two: label g' - M
-  if (lo2 < g + BN) h = h || hits(lo2 - M, g + BN - M);
+  if (lo2 < g + T) h = h || hits(lo2 - M, g + T - M);
   return h;
 }
 
 enum { MASK_NONE = 0, MASK_DIAG = 1, MASK_EDGE = 2 };     // MASK_EDGE: label / left-out columns and padding columns
 
-template <bool STATS, bool STORE, int MASK, bool LOCAL = false, bool STAGE = false, bool STREAM = true>
-__device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, f32x16 (&acc)[4][2], char* smem, int64_t b, float s2, int64_t i0,
+template <int T, bool STATS, bool STORE, int MASK, bool LOCAL = false, bool STAGE = false, bool STREAM = true>
+__device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::NFA>& acc, char* smem, int64_t b, float s2, int64_t i0,
                                                int64_t j0, int64_t g0, int variant, int64_t nkeys, const float (&ref2)[2],
                                                int64_t jl0, int64_t W, float* rs = nullptr, float* ed = nullptr) {
   constexpr bool DIAG = MASK != MASK_NONE, EDGE = MASK == MASK_EDGE;
+  constexpr int WTM = Cfg<T>::WTM, NFA = Cfg<T>::NFA;      // a wave's key columns: 128 (T = 256) or 64
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3, half = lane >> 5;
+  const int wm = wave / Cfg<T>::WN, wn = wave % Cfg<T>::WN, half = lane >> 5;
 #pragma unroll
   for (int bn = 0; bn < 2; ++bn) {
     const int il = wn * 64 + bn * 32 + (lane & 31);
     const int64_t i = i0 + il;
     const float ref = ref2[bn];
     // label column of row i, relative to this lane's first key column of the tile (any value outside
-    // [0, 128) means the label is not among this lane's columns)
-    const int64_t dl64 = (DIAG ? label_row(g0 + i, nkeys, variant) : 0) - (j0 + wm * 128 + half * 4);
-    const int dl = dl64 >= 0 && dl64 < 128 ? (int)dl64 : -1;
-    const int64_t dm64 = (variant == LOSS_NTXENT ? g0 + i : NO_SELF) - (j0 + wm * 128 + half * 4);
-    const int dm = dm64 >= 0 && dm64 < 128 ? (int)dm64 : -1;
-    // first padding column, relative like dl (128: none among this lane's columns)
-    const int64_t jl64 = nkeys - (j0 + wm * 128 + half * 4);
-    const int jlim = jl64 >= 128 ? 128 : jl64 > 0 ? (int)jl64 : 0;
+    // [0, WTM) means the label is not among this lane's columns)
+    const int64_t dl64 = (DIAG ? label_row(g0 + i, nkeys, variant) : 0) - (j0 + wm * WTM + half * 4);
+    const int dl = dl64 >= 0 && dl64 < WTM ? (int)dl64 : -1;
+    const int64_t dm64 = (variant == LOSS_NTXENT ? g0 + i : NO_SELF) - (j0 + wm * WTM + half * 4);
+    const int dm = dm64 >= 0 && dm64 < WTM ? (int)dm64 : -1;
+    // first padding column, relative like dl (WTM: none among this lane's columns)
+    const int64_t jl64 = nkeys - (j0 + wm * WTM + half * 4);
+    const int jlim = jl64 >= WTM ? WTM : jl64 > 0 ? (int)jl64 : 0;
     float rowsum = 0.f;
-    char* lrow = smem + il * E_ROW_BYTES;
+    char* lrow = smem + il * E_ROW_BYTES<T>;
     // this lane's atom of the wave's first key piece pair: row i, key piece (jl0 + 128 wm) / 8 + half
-    uint16_t* erow = STORE ? p.E + ((i >> 6) * (W >> 3) + ((jl0 + wm * 128) >> 3) + half) * 512 + (i & 63) * 8 : nullptr;
+    uint16_t* erow = STORE ? p.E + ((i >> 6) * (W >> 3) + ((jl0 + wm * WTM) >> 3) + half) * 512 + (i & 63) * 8 : nullptr;
 #pragma unroll
-    for (int bm = 0; bm < 4; ++bm) {
-      const int jl = wm * 128 + bm * 32 + half * 4;
+    for (int bm = 0; bm < NFA; ++bm) {
+      const int jl = wm * WTM + bm * 32 + half * 4;
       u32x2 pk[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -328,7 +338,7 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, f32x16 (&acc)
       rs[bn] += rowsum;
     } else if (STATS) {
       rowsum += __shfl_xor(rowsum, 32);
-      if (half == 0) p.lpart[((j0 >> 7) + wm) * b + i] = rowsum;
+      if (half == 0) p.lpart[((T == 256 ? j0 >> 7 : j0 >> 6) + wm) * b + i] = rowsum;
     }
   }
 }
@@ -345,8 +355,8 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, f32x16 (&acc)
 // b: the rank's rows rounded up to whole tiles; B: the key rows that exist (the panel widths cover them rounded up to
 // whole tiles); g0: global row of the rank's first row.  RAGGED: the last key tile may hold padding columns (the
 // instance without it keeps the tile walk free of that variant of the epilogue and of the registers it costs).
-template <bool STATS, bool STORE, bool RAGGED = false>
-__global__ __launch_bounds__(NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, int64_t B, int64_t d, int64_t g0, float s2,
+template <int T, bool STATS, bool STORE, bool RAGGED = false>
+__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, int64_t B, int64_t d, int64_t g0, float s2,
                                                           int64_t jp0, int64_t W, int sbi, int sbj, int nblk) {
   if (gated_off(bl)) return;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -357,17 +367,18 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, 
   // workgroup stays on one XCD's contiguous eighth of the tile list.  The list runs over super-blocks of
   // sbi query tiles x sbj key tiles (sbi sbj <= 32; 8 x 4 where the shape allows, see superblock_tile): the
   // workgroups an XCD runs at one time then share sbi + sbj operand tiles in its L2.
-  const int nI = (int)(b / BN), nJ = (int)(W / BM);
+  const int nI = (int)(b / T), nJ = (int)(W / T);
   const int total = nI * nJ;
   const int chunk = (total + 7) >> 3, padded = chunk << 3;
-  const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) & 3;
-  // max_j |y_j| of each block's key matrix, folded from the partial maxima (one per thread)
+  const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) % Cfg<T>::WN;
+  // max_j |y_j| of each block's key matrix, folded from the partial maxima (one per thread, T = 128: two)
   float ymax_z[2];
   {
     float* red = reinterpret_cast<float*>(smem);
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
       float m = bl.z[z].ymax_parts[threadIdx.x];
+      if (T == 128) m = fmaxf(m, bl.z[z].ymax_parts[threadIdx.x + 256]);
       for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
       if (lane == 0) red[z * 8 + (threadIdx.x >> 6)] = m;
     }
@@ -376,7 +387,7 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, 
     for (int z = 0; z < 2; ++z) {
       float m = red[z * 8];
 #pragma unroll
-      for (int w = 1; w < 8; ++w) m = fmaxf(m, red[z * 8 + w]);
+      for (int w = 1; w < Cfg<T>::WAVES; ++w) m = fmaxf(m, red[z * 8 + w]);
       ymax_z[z] = sqrtf(m);
     }
     __syncthreads();
@@ -389,7 +400,7 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, 
     if ((u >> 3) >= chunk || lin >= total) continue;                  // padding of the eighths (workgroup-uniform)
     int it, jt;
     superblock_tile(lin, nI, nJ, sbi, sbj, it, jt);
-    const int64_t i0 = (int64_t)it * BN, j0 = jp0 + (int64_t)jt * BM;
+    const int64_t i0 = (int64_t)it * T, j0 = jp0 + (int64_t)jt * T;
 
     // exponent reference of this lane's two query rows, fetched before the main loop so that the loads are
     // not waited for in the epilogue
@@ -402,20 +413,20 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, 
         ref2[bn] = STATS ? row_reference(p.zd2[i], p.xnorm[i], ymax, s2) : p.ref2[i];
       }
     }
-    f32x16 acc[4][2];
+    Acc<Cfg<T>::NFA> acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Cfg<T>::NFA; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
 
     // Only the tiles that the label diagonal (or the left-out diagonal) crosses, or that hold padding columns, pay
     // for finding those columns.
-    const bool diag = tile_has_marked_columns(g0 + i0, B, bl.variant, j0);
-    if (diag || (RAGGED && j0 + BM > B)) logit_epilogue<STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
-    else logit_epilogue<STATS, STORE, MASK_NONE>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    const bool diag = tile_has_marked_columns<T>(g0 + i0, B, bl.variant, j0);
+    if (diag || (RAGGED && j0 + T > B)) logit_epilogue<T, STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    else logit_epilogue<T, STATS, STORE, MASK_NONE>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
   }
 }
 
@@ -435,7 +446,7 @@ __device__ __forceinline__ float row_outputs(const BlockPtrs& p, int64_t i, floa
 
 // Xs[k][i] = bf16(scale_i x_ik) for the nrows (a multiple of 64) rows from i0 on, scale = the nrows floats at `scale`
 // in LDS (nullptr: 1): the key-side contraction's right operand, with its reduction index contiguous.  All NTH threads
-// of the workgroup (512 or 1024), 64 x 64 pieces through `tile` (64 x 65 floats of LDS).  The pieces of up to eight
+// of the workgroup (256, 512 or 1024), 64 x 64 pieces through `tile` (64 x 65 floats of LDS).  The pieces of up to eight
 // 64-feature tiles are fetched before the first is turned round, so that their loads are in flight together.
 template <int NTH>
 __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t b, int64_t d, int64_t i0, int nrows, const float* scale,
@@ -486,8 +497,9 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
 // exponent reference every row shares; bad_flag: where that path records that a row or column total was lost
 // (the per-rank paths flag the row's query tile for repair instead).  d > 0: the workgroup goes on to write its
 // rows of Xs = (beta x)^T (a query tile that is repaired afterwards rewrites its rows there); d = 0: not.
+// tile_rows: rows of a query tile of the logit kernel (what the repair flags count).
 __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, int64_t b, int nparts0, int nparts1, float s2,
-                                                    const float* global_ref, int* bad_flag, int64_t d) {
+                                                    const float* global_ref, int* bad_flag, int64_t d, int tile_rows) {
   if (gated_off(bl)) return;
   const int nparts = blockIdx.y ? nparts1 : nparts0;
   __shared__ float red[16][64];
@@ -542,7 +554,7 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, int64_t b, int np
       // the row's query tile is redone against the true row maximum.  Also catches non-finite totals.
       if (!(tot >= ROW_TOTAL_FLOOR)) {
         if (bad_flag) *bad_flag = 1;
-        else p.tileflag[i >> 8] = 1;
+        else p.tileflag[i / tile_rows] = 1;
       }
     }
   }
@@ -554,38 +566,39 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, int64_t b, int np
 // second sweep forms the numerators (stored to E when STORE) and the row sums against it, and the rows'
 // beta, P_label - 1 and cross-entropy are written directly.  Workgroups of tiles that are not flagged return
 // at once, which is the normal case: the kernel then costs one launch.
-template <bool STORE>
-__global__ __launch_bounds__(NTHREADS) void k_logit_repair(Blocks bl, int64_t b, int64_t B, int64_t d, int rank, float s2) {
+template <int T, bool STORE>
+__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_repair(Blocks bl, int64_t b, int64_t B, int64_t d, int rank, float s2) {
   if (gated_off(bl)) return;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int nI = (int)(b / BN), nJ = (int)(B / BM);
+  const int nI = (int)(b / T), nJ = (int)(B / T);
   const int z = blockIdx.x / nI, it = blockIdx.x % nI;
   const BlockPtrs& p = bl.z[z];
   if (p.tileflag[it] == 0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 2, wn = wave & 3, half = lane >> 5;
-  const int64_t i0 = (int64_t)it * BN;
+  constexpr int WTM = Cfg<T>::WTM, NFA = Cfg<T>::NFA;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / Cfg<T>::WN, wn = wave % Cfg<T>::WN, half = lane >> 5;
+  const int64_t i0 = (int64_t)it * T;
   const int64_t g0 = (int64_t)rank * bl.rows;             // global row of the rank's first row
-  float* red = reinterpret_cast<float*>(smem);            // [2][256] exchange between the two key halves
-  f32x16 acc[4][2];
+  float* red = reinterpret_cast<float*>(smem);            // [2][T] exchange between the two key halves
+  Acc<NFA> acc;
   float ref2[2] = {-INFINITY, -INFINITY};
   for (int jt = 0; jt < nJ; ++jt) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NFA; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<FMT_K, FMT_K, true>(p.Y + (int64_t)jt * BM * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
-    const int64_t j0 = (int64_t)jt * BM;
+    mainloop<T, FMT_K, FMT_K, true>(p.Y + (int64_t)jt * T * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    const int64_t j0 = (int64_t)jt * T;
     // the left-out column and the padding columns take no part in the maximum
-    const bool has_self = bl.variant == LOSS_NTXENT && (g0 + i0 < j0 + BM) && (j0 < g0 + i0 + BN);
-    const int64_t jl64 = bl.keys - (j0 + wm * 128 + half * 4);
-    const int jlim = jl64 >= 128 ? 128 : jl64 > 0 ? (int)jl64 : 0;
+    const bool has_self = bl.variant == LOSS_NTXENT && (g0 + i0 < j0 + T) && (j0 < g0 + i0 + T);
+    const int64_t jl64 = bl.keys - (j0 + wm * WTM + half * 4);
+    const int jlim = jl64 >= WTM ? WTM : jl64 > 0 ? (int)jl64 : 0;
 #pragma unroll
     for (int bn = 0; bn < 2; ++bn) {
-      const int64_t dm64 = g0 + i0 + wn * 64 + bn * 32 + (lane & 31) - (j0 + wm * 128 + half * 4);
+      const int64_t dm64 = g0 + i0 + wn * 64 + bn * 32 + (lane & 31) - (j0 + wm * WTM + half * 4);
 #pragma unroll
-      for (int bm = 0; bm < 4; ++bm)
+      for (int bm = 0; bm < NFA; ++bm)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int jl = bm * 32 + (e >> 2) * 8 + (e & 3);
@@ -597,30 +610,30 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_repair(Blocks bl, int64_t b,
 #pragma unroll
   for (int bn = 0; bn < 2; ++bn) {
     ref2[bn] = fmaxf(ref2[bn], __shfl_xor(ref2[bn], 32));
-    if (half == 0) red[wm * 256 + wn * 64 + bn * 32 + lane] = ref2[bn];
+    if (half == 0) red[wm * T + wn * 64 + bn * 32 + lane] = ref2[bn];
   }
   __syncthreads();
 #pragma unroll
   for (int bn = 0; bn < 2; ++bn) {
     const int il = wn * 64 + bn * 32 + (lane & 31);
-    ref2[bn] = fmaxf(red[il], red[256 + il]);
+    ref2[bn] = fmaxf(red[il], red[T + il]);
     if (wm == 0 && half == 0) p.ref2[i0 + il] = ref2[bn];
   }
   __syncthreads();                                         // red is read before the main loop reuses the LDS
 
   float rs[2] = {0.f, 0.f}, ed[2] = {0.f, 0.f};
   for (int jt = 0; jt < nJ; ++jt) {
-    const int64_t j0 = (int64_t)jt * BM;
+    const int64_t j0 = (int64_t)jt * T;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NFA; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
-    const bool diag = tile_has_marked_columns(g0 + i0, bl.keys, bl.variant, j0) || j0 + BM > bl.keys;
-    if (diag) logit_epilogue<true, STORE, MASK_EDGE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
-    else logit_epilogue<true, STORE, MASK_NONE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
+    mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    const bool diag = tile_has_marked_columns<T>(g0 + i0, bl.keys, bl.variant, j0) || j0 + T > bl.keys;
+    if (diag) logit_epilogue<T, true, STORE, MASK_EDGE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
+    else logit_epilogue<T, true, STORE, MASK_NONE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
   }
   // row totals: the four lanes (two key halves x two lane halves) that share a row; exactly one of them met the label
   __syncthreads();
@@ -629,8 +642,8 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_repair(Blocks bl, int64_t b,
     rs[bn] += __shfl_xor(rs[bn], 32);
     ed[bn] += __shfl_xor(ed[bn], 32);
     if (half == 0) {
-      red[wm * 256 + wn * 64 + bn * 32 + lane] = rs[bn];
-      red[512 + wm * 256 + wn * 64 + bn * 32 + lane] = ed[bn];
+      red[wm * T + wn * 64 + bn * 32 + lane] = rs[bn];
+      red[2 * T + wm * T + wn * 64 + bn * 32 + lane] = ed[bn];
     }
   }
   __syncthreads();
@@ -638,16 +651,16 @@ __global__ __launch_bounds__(NTHREADS) void k_logit_repair(Blocks bl, int64_t b,
 #pragma unroll
     for (int bn = 0; bn < 2; ++bn) {
       const int il = wn * 64 + bn * 32 + lane;
-      const float off = red[il] + red[256 + il], e = red[512 + il] + red[768 + il];
+      const float off = red[il] + red[T + il], e = red[2 * T + il] + red[3 * T + il];
       p.ediag[i0 + il] = e;
       float beta = 0.f;
       if (i0 + il < bl.rows) beta = row_outputs(p, i0 + il, off, e, off + e);
       else { p.beta[i0 + il] = 0.f; p.gdiag[i0 + il] = 0.f; p.ce[i0 + il] = 0.f; }
-      red[1024 + il] = beta;
+      red[4 * T + il] = beta;
     }
   }
   // the rows' share of Xs = (beta x)^T, written by k_row_merge with the betas that have just been replaced
-  scale_transpose_rows<NTHREADS>(p, b, d, i0, BN, red + 1024, reinterpret_cast<float (*)[65]>(red + 1280));
+  scale_transpose_rows<Cfg<T>::NTHREADS>(p, b, d, i0, T, red + 4 * T, reinterpret_cast<float (*)[65]>(red + 5 * T));
 }
 
 // Xs = X^T for one block without any scaling (the symmetric full loss folds both normalisations into the stored
@@ -658,67 +671,86 @@ __global__ __launch_bounds__(1024) void k_transpose(Blocks bl, int64_t b, int64_
   scale_transpose_rows<1024>(bl.z[0], b, d, (int64_t)blockIdx.x * 64, 64, nullptr, tile);
 }
 
-// Key-side gradient without its label-column term: gk[j][k] (+)= cs * sum_i E[i][j] Xs[k][i].
-// (The term [j = label_i] gdiag_i x_ik is added by k_query_finalize, which owns the rank's rows.)
+// The two gradient contractions of every block, in one launch: they are independent of each other, so where neither has
+// the workgroups to fill the chip they fill it together, and neither waits for the other's last workgroups (one launch
+// against two: 56 us against 68 a call at b = 512, B = 1024, d = 256; 4060 against 4098 for the symmetric B = 32768).
+// blockIdx.x < q_wgs: query-side workgroups, the rest key-side ones (q_wgs is a multiple of 8, so that both parts keep
+// their workgroup -> XCD mapping).
+//
+// Key side, without its label-column term: gk[j][k] (+)= cs * sum_i E[i][j] Xs[k][i].
+// (The term [j = label_i] gdiag_i x_ik is added by the finalize kernel, which owns the rank's rows.)
 // GEMM M = key rows j (operand E read transposed), N = feature index k, reduction over the rank's rows.
-template <bool ACCUMULATE>
-__global__ __launch_bounds__(NTHREADS) void k_key_grad(Blocks bl, int64_t b, int64_t d, float cs, int64_t jp0, int64_t W,
-                                                       int nM, int nN) {
-  if (gated_off(bl)) return;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const BlockPtrs& p = bl.z[blockIdx.y];
-  int lin;
-  if (!xcd_linear(nM * nN, lin)) return;
-  const int nt = lin % nN, mt = lin / nN;
-  const int64_t jl0 = (int64_t)mt * BM, k0 = (int64_t)nt * BN;     // key rows jp0 + jl0 .. of the panel
-  f32x16 acc[4][2];
-  const int ncols = d - k0 < BN ? (int)(d - k0) : BN;              // the last column tile may be partial (d % 64 == 0)
-  mainloop<FMT_RA, FMT_K, false, true>(p.E + (jl0 >> 6) * 4096, (W >> 6) * 4096, p.Xs + k0 * b, b, (int)(b / BK), smem, acc, ncols);
-  const int64_t left = bl.keys - (jp0 + jl0);                      // key rows that exist from this tile's first one on
-  store_tile_f32<ACCUMULATE>(acc, smem, p.gk + (jp0 + jl0) * d + k0, d, cs, ncols, left < BM ? (int)left : BM);
-}
-
-// Query-side products, split over the key index: part[ks][i][k] = sum_{j in split ks} E[i][j] y_jk.
+// KMODE: KEY_WRITE / KEY_ADD overwrite gk / add to it; KEY_SPLIT leaves the unscaled sums of key_splits ranges of the rows
+// in kpart for the finalize kernel (wanted where B x d has too few tiles and the rank many rows).
+//
+// Query side, split over the key index: part[ks][i][k] = sum_{j in split ks} E[i][j] y_jk.
 // GEMM M = query rows i, N = feature index k (operand Y read transposed), reduction over key rows.
-// One-dimensional grid over (block z, split ks, row tile mt, column tile nt).  A "slice" is one (z, ks): all
-// its workgroups read the same rows of Y, so slices are pinned to XCDs (workgroups are dealt round-robin to
-// the 8 XCDs): with S = 2 splitk slices, either S/8 slices per XCD one after the other (S a multiple of 8), or
-// 8/S XCDs per slice sharing its tiles (S divides 8).  Then Y comes in from the fabric once per slice instead
+// A "slice" is one (z, ks): all its workgroups read the same rows of Y, so slices are pinned to XCDs (workgroups are dealt
+// round-robin to the 8 XCDs): with S = nblk splitk slices, either S/8 slices per XCD one after the other (S a multiple of
+// 8), or 8/S XCDs per slice sharing its tiles (S divides 8).  Then Y comes in from the fabric once per slice instead
 // of once per XCD.  Any other S falls back to slices laid out contiguously.
-template <bool ACCUMULATE>
-__global__ __launch_bounds__(NTHREADS) void k_query_partial(Blocks bl, int64_t b, int64_t d, int64_t jp0, int64_t W, int nM,
-                                                            int nN, int splitk, int ktiles_per_split) {
+struct GradShape {
+  int64_t b, B, d, jp0, W;          // b, B: rounded up to whole tiles; key panel [jp0, jp0 + W)
+  int nMq, nMk, nN;                 // row tiles of the query and key sides, column tiles
+  int splitk, ktps;                 // query side: splits of the W keys, K-steps per split
+  int key_splits, key_ktps;         // key side: splits of the b rows, K-steps per split
+  int q_wgs;
+};
+enum { KEY_WRITE = 0, KEY_ADD = 1, KEY_SPLIT = 2 };
+
+template <int T, int KMODE, bool QADD>
+__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_grads(Blocks bl, GradShape g, float cs) {
   if (gated_off(bl)) return;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int T = nM * nN, S = bl.nblk * splitk;
-  const int w = blockIdx.x, xcd = w & 7, r = w >> 3;
-  int slice, tile;
-  if (S % 8 == 0) {
-    slice = xcd + 8 * (r / T);
-    tile = r % T;
-  } else if (8 % S == 0) {
-    const int G = 8 / S;
-    slice = xcd % S;
-    tile = xcd / S + G * r;
-  } else {
-    slice = w / T;
-    tile = w % T;
+  const int64_t b = g.b, d = g.d, W = g.W;
+  Acc<Cfg<T>::NFA> acc;
+  if ((int)blockIdx.x < g.q_wgs) {
+    const int tiles = g.nMq * g.nN, S = bl.nblk * g.splitk;
+    const int w = blockIdx.x, xcd = w & 7, r = w >> 3;
+    int slice, tile;
+    if (S % 8 == 0) {
+      slice = xcd + 8 * (r / tiles);
+      tile = r % tiles;
+    } else if (8 % S == 0) {
+      const int G = 8 / S;
+      slice = xcd % S;
+      tile = xcd / S + G * r;
+    } else {
+      slice = w / tiles;
+      tile = w % tiles;
+    }
+    if (slice >= S || tile >= tiles) return;
+    const BlockPtrs& p = bl.z[slice / g.splitk];
+    const int ks = slice % g.splitk;
+    const int nt = tile % g.nN, mt = tile / g.nN;
+    const int64_t i0 = (int64_t)mt * T, k0 = (int64_t)nt * T;
+    const int kt_total = (int)(W / BK);
+    const int kt0 = ks * g.ktps;
+    int kts = kt_total - kt0;
+    if (kts > g.ktps) kts = g.ktps;
+    const int ncols = d - k0 < T ? (int)(d - k0) : T;               // the last column tile may be partial (d % 64 == 0)
+    // (kts >= 1: the plan's split count is the number of splits that hold at least one K-step)
+    mainloop<T, FMT_KA, FMT_R, false, true>(p.E + ((i0 >> 6) * (W >> 6) + kt0) * 4096, (W >> 6) * 4096,
+                                            p.Y + (g.jp0 + (int64_t)kt0 * BK) * d + k0, d, kts, smem, acc, ncols);
+    store_tile_f32<T, QADD>(acc, smem, p.part + (int64_t)ks * b * d + i0 * d + k0, d, 1.0f, ncols);
+    return;
   }
-  if (slice >= S || tile >= T) return;
-  const BlockPtrs& p = bl.z[slice / splitk];
-  const int ks = slice % splitk;
-  const int nt = tile % nN, mt = tile / nN;
-  const int64_t i0 = (int64_t)mt * BM, k0 = (int64_t)nt * BN;
-  const int kt_total = (int)(W / BK);
-  const int kt0 = ks * ktiles_per_split;
-  int kts = kt_total - kt0;
-  if (kts > ktiles_per_split) kts = ktiles_per_split;
-  f32x16 acc[4][2];
-  const int ncols = d - k0 < BN ? (int)(d - k0) : BN;              // the last column tile may be partial (d % 64 == 0)
-  // (kts >= 1: the plan's split count is the number of splits that hold at least one K-step)
-  mainloop<FMT_KA, FMT_R, false, true>(p.E + ((i0 >> 6) * (W >> 6) + kt0) * 4096, (W >> 6) * 4096,
-                                   p.Y + (jp0 + (int64_t)kt0 * BK) * d + k0, d, kts, smem, acc, ncols);
-  store_tile_f32<ACCUMULATE>(acc, smem, p.part + (int64_t)ks * b * d + i0 * d + k0, d, 1.0f, ncols);
+  const int tiles = g.nMk * g.nN * g.key_splits, per_block = (tiles + 7) / 8 * 8;
+  const int w = blockIdx.x - g.q_wgs, z = w / per_block;
+  int lin;
+  if (!xcd_linear(w - z * per_block, tiles, lin)) return;
+  const BlockPtrs& p = bl.z[z];
+  const int nt = lin % g.nN, t2 = lin / g.nN, mt = t2 % g.nMk, ks = t2 / g.nMk;
+  const int64_t jl0 = (int64_t)mt * T, k0 = (int64_t)nt * T;        // key rows jp0 + jl0 .. of the panel
+  const int ncols = d - k0 < T ? (int)(d - k0) : T;
+  const int kt0 = ks * g.key_ktps;
+  int kts = (int)(b / BK) - kt0;
+  if (kts > g.key_ktps) kts = g.key_ktps;
+  mainloop<T, FMT_RA, FMT_K, false, true>(p.E + (jl0 >> 6) * 4096 + (int64_t)kt0 * (W >> 6) * 4096, (W >> 6) * 4096,
+                                          p.Xs + k0 * b + (int64_t)kt0 * BK, b, kts, smem, acc, ncols);
+  const int64_t left = bl.keys - (g.jp0 + jl0);                      // key rows that exist from this tile's first one on
+  float* out = KMODE == KEY_SPLIT ? p.kpart + ((int64_t)ks * g.B + jl0) * d + k0 : p.gk + (g.jp0 + jl0) * d + k0;
+  store_tile_f32<T, KMODE == KEY_ADD>(acc, smem, out, d, KMODE == KEY_SPLIT ? 1.0f : cs, ncols, left < T ? (int)left : T);
 }
 
 // Sum over the split-K slices ks0, ks0 + step, ... (< splitk), in that order, of the 16-byte piece of row i at feature
@@ -736,69 +768,105 @@ __device__ __forceinline__ f32x4 sum_slices(const float* part, int64_t pitch, in
   return u;
 }
 
+// What the finalize kernels add up for a row, besides its own terms.
+struct FinalizeShape {
+  int64_t b, bp;        // the rank's rows; row pitch of part
+  int64_t B, Bp;        // all rows; row pitch of kpart
+  int64_t d;
+  int rank, splitk, key_splits, accumulate;
+};
+
 // Everything that lands in the rank's own rows, for both blocks at once.  With lab = label of local row i:
 //   gI[lab] += cs (beta^A_i sum_ks part^A + gdiag^A_i T[lab])    query side of block A (Eq. 4)
 //            + cs gdiag^C_i T[lab]                                label-column term of block C's key side
 //   gT[lab] += cs (beta^C_i sum_ks part^C + gdiag^C_i I[lab]) + cs gdiag^A_i I[lab]
-// and the rows' shares of d/ds, <query-side vector, x_i>, per block.  Fixed summation order.  One wave per row; ROWWG
-// (small shares, where rows / 4 workgroups would leave most of the chip idle while each wave walks all the split-K
-// slices): one workgroup per row, its four waves each add every fourth slice and wave 0 combines them.
-// b: the real rows; bp: row pitch of the partial products.
-template <bool ROWWG>
-__global__ __launch_bounds__(256) void k_query_finalize(Blocks bl, int64_t b, int64_t bp, int64_t d, int rank, float cs, int splitk) {
+// and the rows' shares of d/ds, <query-side vector, x_i>, per block.  Fixed summation order.
+// KSPLIT (the key-side contraction was split, k_grads<.., KEY_SPLIT>): the kernel runs over all B rows and starts each from
+//   gI[j] = [accumulate] gI[j] + cs sum_ks kpart^C[ks][j],  gT[j] likewise from kpart^A.
+// One wave per row; ROWWG (few rows, where rows / 4 workgroups would leave most of the chip idle while each wave walks
+// all the split-K slices): one workgroup per row, its four waves each add every fourth slice and wave 0 combines them.
+template <bool ROWWG, bool KSPLIT>
+__global__ __launch_bounds__(256) void k_finalize(Blocks bl, FinalizeShape f, float cs) {
   if (gated_off(bl)) return;
-  __shared__ f32x4 others[ROWWG ? 3 : 1][2][64];
+  constexpr int NSUM = KSPLIT ? 4 : 2;
+  __shared__ f32x4 others[ROWWG ? 3 : 1][NSUM][64];
   const BlockPtrs& pa = bl.z[0];
   const BlockPtrs& pc = bl.z[1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i = ROWWG ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
-  if (i >= b) return;                                   // ROWWG: the whole workgroup
-  const int64_t lab = (int64_t)rank * b + i;
-  const float beta_a = pa.beta[i], gd_a = pa.gdiag[i], beta_c = pc.beta[i], gd_c = pc.gdiag[i];
+  const int64_t row = ROWWG ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+  if (row >= (KSPLIT ? f.B : f.b)) return;              // ROWWG: the whole workgroup
+  const int64_t i = KSPLIT ? row - (int64_t)f.rank * f.b : row;         // local row
+  const int64_t lab = KSPLIT ? row : (int64_t)f.rank * f.b + row;       // global row
+  const bool own = !KSPLIT || (i >= 0 && i < f.b);
+  float beta_a = 0.f, gd_a = 0.f, beta_c = 0.f, gd_c = 0.f;
+  if (own) { beta_a = pa.beta[i]; gd_a = pa.gdiag[i]; beta_c = pc.beta[i]; gd_c = pc.gdiag[i]; }
+  const int64_t d = f.d;
+  const int first = ROWWG ? wave : 0, step = ROWWG ? 4 : 1;
   float dot_a = 0.f, dot_c = 0.f;
   for (int64_t kc = 0; kc < d; kc += 256) {
     const int64_t k = kc + lane * 4;
     const bool on = k < d;
-    f32x4 ua = {0.f, 0.f, 0.f, 0.f}, uc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 u[NSUM];                                       // query side of A and C, key side of A and C
+#pragma unroll
+    for (int q = 0; q < NSUM; ++q) u[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (on) {
-      ua = sum_slices(pa.part, bp, i, d, k, ROWWG ? wave : 0, ROWWG ? 4 : 1, splitk);
-      uc = sum_slices(pc.part, bp, i, d, k, ROWWG ? wave : 0, ROWWG ? 4 : 1, splitk);
+      if (own) {
+        u[0] = sum_slices(pa.part, f.bp, i, d, k, first, step, f.splitk);
+        u[1] = sum_slices(pc.part, f.bp, i, d, k, first, step, f.splitk);
+      }
+      if constexpr (KSPLIT) {
+        u[2] = sum_slices(pa.kpart, f.Bp, row, d, k, first, step, f.key_splits);
+        u[3] = sum_slices(pc.kpart, f.Bp, row, d, k, first, step, f.key_splits);
+      }
     }
     if (ROWWG) {
-      if (wave > 0) { others[wave - 1][0][lane] = ua; others[wave - 1][1][lane] = uc; }
+      if (wave > 0)
+#pragma unroll
+        for (int q = 0; q < NSUM; ++q) others[wave - 1][q][lane] = u[q];
       __syncthreads();
       if (wave == 0)
 #pragma unroll
-        for (int w = 0; w < 3; ++w) { ua += others[w][0][lane]; uc += others[w][1][lane]; }
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+          for (int q = 0; q < NSUM; ++q) u[q] += others[w][q][lane];
       __syncthreads();                                  // read before the next piece overwrites it
       if (wave > 0) continue;
     }
     if (!on) continue;
-    const u32x2 iw = *reinterpret_cast<const u32x2*>(pa.X + i * d + k);        // I[lab]
-    const u32x2 tw = *reinterpret_cast<const u32x2*>(pc.X + i * d + k);        // T[lab]
-    const float iv[4] = {bf16_lo(iw[0]), bf16_hi(iw[0]), bf16_lo(iw[1]), bf16_hi(iw[1])};
-    const float tv[4] = {bf16_lo(tw[0]), bf16_hi(tw[0]), bf16_lo(tw[1]), bf16_hi(tw[1])};
-    f32x4 gi = *reinterpret_cast<f32x4*>(pa.gq + lab * d + k);
-    f32x4 gt = *reinterpret_cast<f32x4*>(pc.gq + lab * d + k);
+    f32x4 gi = {0.f, 0.f, 0.f, 0.f}, gt = {0.f, 0.f, 0.f, 0.f};
+    if (!KSPLIT || f.accumulate) {
+      gi = *reinterpret_cast<f32x4*>(pa.gq + lab * d + k);
+      gt = *reinterpret_cast<f32x4*>(pc.gq + lab * d + k);
+    }
+    if constexpr (KSPLIT) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float ga = fmaf(beta_a, ua[e], gd_a * tv[e]);
-      const float gc = fmaf(beta_c, uc[e], gd_c * iv[e]);
-      gi[e] = fmaf(cs * gd_c, tv[e], fmaf(cs, ga, gi[e]));
-      gt[e] = fmaf(cs * gd_a, iv[e], fmaf(cs, gc, gt[e]));
-      dot_a = fmaf(ga, iv[e], dot_a);
-      dot_c = fmaf(gc, tv[e], dot_c);
+      for (int e = 0; e < 4; ++e) { gt[e] = fmaf(cs, u[2][e], gt[e]); gi[e] = fmaf(cs, u[3][e], gi[e]); }
+    }
+    if (own) {
+      const u32x2 iw = *reinterpret_cast<const u32x2*>(pa.X + i * d + k);        // I[lab]
+      const u32x2 tw = *reinterpret_cast<const u32x2*>(pc.X + i * d + k);        // T[lab]
+      const float iv[4] = {bf16_lo(iw[0]), bf16_hi(iw[0]), bf16_lo(iw[1]), bf16_hi(iw[1])};
+      const float tv[4] = {bf16_lo(tw[0]), bf16_hi(tw[0]), bf16_lo(tw[1]), bf16_hi(tw[1])};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ga = fmaf(beta_a, u[0][e], gd_a * tv[e]);
+        const float gc = fmaf(beta_c, u[1][e], gd_c * iv[e]);
+        gi[e] = fmaf(cs * gd_c, tv[e], fmaf(cs, ga, gi[e]));
+        gt[e] = fmaf(cs * gd_a, iv[e], fmaf(cs, gc, gt[e]));
+        dot_a = fmaf(ga, iv[e], dot_a);
+        dot_c = fmaf(gc, tv[e], dot_c);
+      }
     }
     *reinterpret_cast<f32x4*>(pa.gq + lab * d + k) = gi;
     *reinterpret_cast<f32x4*>(pc.gq + lab * d + k) = gt;
   }
-  if (ROWWG && wave > 0) return;
+  if (!own || (ROWWG && wave > 0)) return;
   dot_a = wave_sum(dot_a);
   dot_c = wave_sum(dot_c);
   if (lane == 0) { pa.rowds[i] = dot_a; pc.rowds[i] = dot_c; }
 }
 
-// shares up to this many rows finalize with one workgroup per row
+// up to this many rows finalize with one workgroup per row
 constexpr int64_t FINALIZE_ROWWG_MAX = 1024;
 
 // The same for the two-view loss (one block, X = Y = Z, gq = gk = gZ).  With g = rank b + i the row's own global row
@@ -808,38 +876,51 @@ constexpr int64_t FINALIZE_ROWWG_MAX = 1024;
 // The second line lands in another row, lab.  If lab belongs to this rank too, the wave that owns it adds the term
 // (seen from there it reads gdiag_i' Z[lab'] with i' its positive, since the positive of the positive is the row
 // itself); otherwise the wave of row i writes it.  Every row of gZ so has exactly one writer in this kernel.
-// b: the real rows; bp: row pitch of the partial products.
-__global__ __launch_bounds__(256) void k_query_finalize_ntxent(Blocks bl, int64_t b, int64_t bp, int64_t B, int64_t d, int rank, float cs, int splitk) {
+// KSPLIT: the kernel runs over all B rows as above, every row adds what its positive owes it and nobody writes
+// another's row.
+template <bool KSPLIT>
+__global__ __launch_bounds__(256) void k_finalize_ntxent(Blocks bl, FinalizeShape f, float cs) {
   if (gated_off(bl)) return;
   const BlockPtrs& p = bl.z[0];
   const int lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= b) return;
-  const int64_t g = (int64_t)rank * b + i, lab = label_row(g, B, LOSS_NTXENT);
-  const int64_t ip = lab - (int64_t)rank * b;                         // local index of the positive, if it is local
-  const bool pos_local = ip >= 0 && ip < b;
-  const float beta = p.beta[i], gd = p.gdiag[i], gd_pos = pos_local ? p.gdiag[ip] : 0.f;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= (KSPLIT ? f.B : f.b)) return;
+  const int64_t i = KSPLIT ? row - (int64_t)f.rank * f.b : row;
+  const int64_t g = KSPLIT ? row : (int64_t)f.rank * f.b + row, lab = label_row(g, f.B, LOSS_NTXENT);
+  const bool own = !KSPLIT || (i >= 0 && i < f.b);
+  const int64_t ip = lab - (int64_t)f.rank * f.b;                     // local index of the positive, if it is local
+  const bool pos_local = ip >= 0 && ip < f.b;
+  const bool owes = !KSPLIT && !pos_local;                            // this wave writes its term into row lab
+  const float beta = own ? p.beta[i] : 0.f, gd = own ? p.gdiag[i] : 0.f, gd_pos = pos_local ? p.gdiag[ip] : 0.f;
   const uint16_t* Zfull = p.Y;
+  const int64_t d = f.d;
   float dot = 0.f;
   for (int64_t k = lane * 4; k < d; k += 256) {
-    const f32x4 u = sum_slices(p.part, bp, i, d, k, 0, 1, splitk);
+    f32x4 u = {0.f, 0.f, 0.f, 0.f};
+    if (own) u = sum_slices(p.part, f.bp, i, d, k, 0, 1, f.splitk);
     const u32x2 zw = *reinterpret_cast<const u32x2*>(Zfull + g * d + k);        // Z[g]
     const u32x2 pw = *reinterpret_cast<const u32x2*>(Zfull + lab * d + k);      // Z[lab]
     const float zv[4] = {bf16_lo(zw[0]), bf16_hi(zw[0]), bf16_lo(zw[1]), bf16_hi(zw[1])};
     const float pv[4] = {bf16_lo(pw[0]), bf16_hi(pw[0]), bf16_lo(pw[1]), bf16_hi(pw[1])};
-    f32x4 own = *reinterpret_cast<f32x4*>(p.gq + g * d + k);
-    f32x4 oth = {0.f, 0.f, 0.f, 0.f};
-    if (!pos_local) oth = *reinterpret_cast<f32x4*>(p.gq + lab * d + k);
+    f32x4 mine = {0.f, 0.f, 0.f, 0.f}, oth = {0.f, 0.f, 0.f, 0.f};
+    if (!KSPLIT || f.accumulate) mine = *reinterpret_cast<f32x4*>(p.gq + g * d + k);
+    if (owes) oth = *reinterpret_cast<f32x4*>(p.gq + lab * d + k);
+    if constexpr (KSPLIT) {
+      const f32x4 kv = sum_slices(p.kpart, f.Bp, row, d, k, 0, 1, f.key_splits);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine[e] = fmaf(cs, kv[e], mine[e]);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float ga = fmaf(beta, u[e], gd * pv[e]);
-      own[e] = fmaf(cs * gd_pos, pv[e], fmaf(cs, ga, own[e]));        // + what the local positive owes this row
+      mine[e] = fmaf(cs * gd_pos, pv[e], fmaf(cs, ga, mine[e]));      // + what the local positive owes this row
       oth[e] = fmaf(cs * gd, zv[e], oth[e]);
       dot = fmaf(ga, zv[e], dot);
     }
-    *reinterpret_cast<f32x4*>(p.gq + g * d + k) = own;
-    if (!pos_local) *reinterpret_cast<f32x4*>(p.gq + lab * d + k) = oth;
+    *reinterpret_cast<f32x4*>(p.gq + g * d + k) = mine;
+    if (owes) *reinterpret_cast<f32x4*>(p.gq + lab * d + k) = oth;
   }
+  if (!own) return;
   dot = wave_sum(dot);
   if (lane == 0) p.rowds[i] = dot;
 }
@@ -926,7 +1007,7 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
   const int chunk = (total + 7) >> 3, padded = chunk << 3;
   const float ref = *rglobal;
   const float ref2[2] = {ref, ref};
-  float* colpart = reinterpret_cast<float*>(smem + E_TILE_BYTES);       // [8 waves][256 keys]
+  float* colpart = reinterpret_cast<float*>(smem + E_TILE_BYTES<256>);       // [8 waves][256 keys]
   for (int u = blockIdx.x; u < padded; u += gridDim.x) {
     const int lin = (u & 7) * chunk + (u >> 3);
     if ((u >> 3) >= chunk || lin >= total) continue;
@@ -940,12 +1021,12 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    mainloop<256, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
     // the label of query row i is key row i: only the tiles on the diagonal contain label columns
     // (ordinary stores: the matrix is read again by the combining pass and the two contractions)
     if (it == jt || (RAGGED && j0 + BM > bl.keys))
-      logit_epilogue<true, true, RAGGED ? MASK_EDGE : MASK_DIAG, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
-    else logit_epilogue<true, true, MASK_NONE, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
+      logit_epilogue<256, true, true, RAGGED ? MASK_EDGE : MASK_DIAG, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
+    else logit_epilogue<256, true, true, MASK_NONE, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
     lds_barrier();
     const int t = threadIdx.x;
     const int chunk16 = t & 31, r0 = t >> 5;
@@ -953,7 +1034,7 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
 #pragma unroll 8
     for (int r = 0; r < 16; ++r) {
       const int row = r * 16 + r0;
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(smem + row * E_ROW_BYTES + ((chunk16 ^ ((row & 31) >> 1)) << 4));
+      const u32x4 raw = *reinterpret_cast<const u32x4*>(smem + row * E_ROW_BYTES<256> + ((chunk16 ^ ((row & 31) >> 1)) << 4));
       const u32x4 val = (row & 1) ? u32x4{raw[2], raw[3], raw[0], raw[1]} : raw;
       if (RAGGED && i0 + row >= bl.rows) continue;
 #pragma unroll
@@ -1052,54 +1133,30 @@ __global__ __launch_bounds__(256) void k_sym_finalize(Blocks bl, int64_t B, int6
 constexpr int NROWARRAYS = 7;
 
 struct Plan {
-  int64_t b, B, d;       // b and B rounded up to whole 256-row tiles: what the tile kernels and the layout below see
+  int64_t b, B, d;       // b and B rounded up to whole tiles: what the tile kernels and the layout below see
   int64_t b_real, B_real;
   bool ragged;           // b or B was rounded up: the kernels read zero-padded copies of the operands (off_pad)
   int64_t W;             // key panel width (B for the materialized path)
   int npanels;
-  int nparts;            // B / 128
-  int nMq, nN, splitk, ktps;
-  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_ymax, off_flags, off_ref, off_pad, total;
+  int tl, tg;            // tile size of the logit kernels and of the gradient kernel (256 or 128)
+  int nparts;            // partial row sums per row: one per tl / 2 keys
+  int nMq, nMk, nN;      // gradient tiles: query rows, key rows of a panel, columns
+  int splitk, ktps;      // query-side split, K-steps per split
+  int key_splits, key_ktps;
+  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ymax, off_flags, off_ref, off_pad, total;
   size_t rows_stride;    // bytes of one b-float row array (aligned)
 };
 
 // Key panels of the fused path: at most 16384 keys wide (so that one panel of both blocks' numerators
 // stays within the 256 MiB last-level cache at the paper's rank shares) and at least two of them.
-int fused_panels(int64_t B) {
+int fused_panels(int64_t B, int unit) {
   for (int n = 2; n <= 4096; ++n)
-    if (B % ((int64_t)n * BM) == 0 && B / n <= 16384) return n;
+    if (B % ((int64_t)n * unit) == 0 && B / n <= 16384) return n;
   return 1;
 }
 
-Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2) {
-  Plan pl;
-  pl.B_real = B; pl.b_real = B / N; pl.d = d;
-  pl.b = (pl.b_real + BN - 1) / BN * BN;
-  pl.B = (B + BM - 1) / BM * BM;
-  pl.ragged = pl.b != pl.b_real || pl.B != pl.B_real;
-  B = pl.B;
-  const int64_t b = pl.b;
-  pl.npanels = fused ? fused_panels(B) : 1;
-  pl.W = B / pl.npanels;
-  pl.nparts = (int)(B / 128);
-  pl.nMq = (int)(b / BM);
-  pl.nN = (int)((d + BN - 1) / BN);
-  const int tiles = pl.nMq * pl.nN;
-  const int kt_total = (int)(pl.W / BK);
-  // Split of the query-side reduction: the 2 * tiles * sk workgroups run in rounds of one per compute unit (256 on
-  // this chip), each taking kt_total / sk K-steps of about 1.1 us, and the sk partial tiles are written once and
-  // read once at about 4 TB/s.  Take the sk with the least estimated time.
-  int sk = 1;
-  double best = 1e300;
-  for (int c = 1; c <= 32 && c <= kt_total; ++c) {
-    const int ktps = (kt_total + c - 1) / c;
-    const int eff = (kt_total + ktps - 1) / ktps;                    // splits that are not empty
-    const int rounds = (nblk * tiles * eff + 255) / 256;
-    const double cost = rounds * ktps * 1.1 + eff * (2.0 * b * d * 4.0 * 2.0) / 4e6;
-    if (cost < best) { best = cost; sk = c; }
-  }
-  pl.ktps = (kt_total + sk - 1) / sk;
-  pl.splitk = (kt_total + pl.ktps - 1) / pl.ktps;
+void layout(Plan& pl) {
+  const int64_t b = pl.b, B = pl.B, d = pl.d;
   size_t o = 0;
   pl.off_E = o;      o += 2 * align_up((size_t)b * pl.W * 2);
   pl.off_lpart = o;  o += 2 * align_up((size_t)pl.nparts * b * 4);
@@ -1107,13 +1164,107 @@ Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2) {
   pl.off_rows = o;   o += 2 * NROWARRAYS * pl.rows_stride;   // ediag, zd2, xnorm, beta, gdiag, ce, rowds
   pl.off_Xs = o;     o += 2 * align_up((size_t)d * b * 2);
   pl.off_part = o;   o += 2 * align_up((size_t)pl.splitk * b * d * 4);
+  pl.off_kpart = o;
+  if (pl.key_splits > 1) o += 2 * align_up((size_t)pl.key_splits * B * d * 4);
   pl.off_ymax = o;   o += align_up((size_t)2 * NORM_BLOCKS * 4);         // partial maxima of the row norms
-  pl.off_flags = o;  o += 2 * align_up((size_t)(b / BN) * 4);            // repair flags, one per query tile
+  pl.off_flags = o;  o += 2 * align_up((size_t)(b / 128) * 4);           // repair flags, one per query tile
   pl.off_ref = o;    o += 2 * pl.rows_stride;                            // exponent references of the rows
   pl.off_pad = o;                                                        // padded I, T, I_r, T_r of a ragged share
   if (pl.ragged) o += 2 * align_up((size_t)B * d * 2) + 2 * align_up((size_t)b * d * 2);
   pl.total = o;
-  return pl;
+}
+
+// b and B rounded to whole tiles of the two tile sizes, and what follows from them.
+void round_shape(Plan& pl, bool fused) {
+  const int unit = pl.tl > pl.tg ? pl.tl : pl.tg;
+  pl.b = (pl.b_real + unit - 1) / unit * unit;
+  pl.B = (pl.B_real + unit - 1) / unit * unit;
+  pl.ragged = pl.b != pl.b_real || pl.B != pl.B_real;
+  pl.npanels = fused ? fused_panels(pl.B, unit) : 1;
+  pl.W = pl.B / pl.npanels;
+  pl.nparts = (int)(pl.B / (pl.tl / 2));
+  pl.nMq = (int)(pl.b / pl.tg);
+  pl.nMk = (int)(pl.W / pl.tg);
+  pl.nN = (int)((pl.d + pl.tg - 1) / pl.tg);
+}
+
+// Time estimates in microseconds that make_plan compares, for a chip of 256 compute units.  What they rest on (measured):
+// a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
+// every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
+// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.
+constexpr double CHIP_CUS = 256.0;
+constexpr double BYTES_PER_US = 4.5e6;
+
+double step_us(int T, double wgs) {
+  const double slots = T == 256 ? CHIP_CUS : 2 * CHIP_CUS, few = T == 256 ? 1.15 : 0.57, full = T == 256 ? 1.7 : 1.03;
+  const double f = (wgs - slots / 4) / (slots * 3 / 4);
+  return few + (full - few) * (f < 0 ? 0 : f > 1 ? 1 : f);
+}
+
+double logits_us(const Plan& pl, int nblk) {
+  const double slots = pl.tl == 256 ? CHIP_CUS : 2 * CHIP_CUS, tiles = (double)nblk * (pl.b / pl.tl) * (pl.B / pl.tl);
+  const double tile = (double)(pl.d / BK) * step_us(pl.tl, tiles) + (pl.tl == 256 ? 5.5 : 2.5);
+  const double rounds = (double)(int64_t)((tiles + slots - 1) / slots), bytes = 2.0 * nblk * pl.b * pl.B;
+  return rounds * tile > bytes / BYTES_PER_US ? rounds * tile : bytes / BYTES_PER_US;
+}
+
+// the gradient kernel with sk and ks splits, and the finalize kernel's share of reading them back
+double grads_us(const Plan& pl, int nblk, int ktps, int sk, int kktps, int ks) {
+  const double slots = pl.tg == 256 ? CHIP_CUS : 2 * CHIP_CUS, fix = pl.tg == 256 ? 8.0 : 3.0;
+  const double nq = (double)nblk * pl.nMq * pl.nN * sk, nk = (double)nblk * pl.nMk * pl.nN * ks, n = nq + nk;
+  const double step = step_us(pl.tg, n), lq = ktps * step + fix, lk = kktps * step + fix, longest = lq > lk ? lq : lk;
+  const int slices = nblk * sk;                                      // see k_grads: slices that map onto the 8 XCDs share their L2
+  const double spread = slices % 8 == 0 || 8 % slices == 0 ? 1.0 : 1.12;
+  // query workgroups first, in rounds of `slots`; the slots that the last of these rounds leaves free start on the key side
+  const int s0 = (int)slots, rounds = (int)nq / s0, rest = (int)nq % s0;
+  int k = (int)nk / s0;                                              // key workgroups one after the other on such a slot
+  auto done = [&] { const double late = k - lq / lk; return k * (double)(s0 - rest) + (late > 0 ? (int)late : 0) * (double)rest; };
+  while (done() < nk) ++k;
+  const double tail = k * lk > (rest ? lq : 0.0) ? k * lk : lq;
+  // (a last query round that fills part of the chip overlaps with the key side less well than that: b = 4096, B = 32768,
+  // d = 512 takes 946 us with 2 query splits, half a round, and 837 with 4, one round)
+  const double compute = spread * (n <= slots ? longest : rounds * lq + (k || rest ? tail : 0.0) + (rest ? 0.3 * lq * (1.0 - rest / slots) : 0.0));
+  const double part = 4.0 * nblk * pl.b * pl.d * sk, key = 4.0 * nblk * pl.W * pl.d * ks;
+  const double moved = (4.0 * nblk * pl.b * pl.W + key) / BYTES_PER_US;
+  const double splits = (2.0 * part + (ks > 1 ? key + key / ks : 0.0)) / BYTES_PER_US;     // partial sums out and back: not hidden
+  return (compute > moved ? compute : moved) + splits;
+}
+
+void split(int total, int want, int& splits, int& per) {
+  per = (total + want - 1) / want;
+  splits = (total + per - 1) / per;                                  // those that are not empty
+}
+
+// tile: 0, or the size that the caller's kernels are written for.
+Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2, int tile = 0) {
+  static const int Q_SPLITS[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
+  Plan best;
+  double best_us = 1e300;
+  bool best_fits = false;
+  for (int tl = 128; tl <= 256; tl += 128)
+    for (int tg = 128; tg <= 256; tg += 128) {
+      if (tile && (tl != tile || tg != tile)) continue;
+      Plan pl;
+      pl.B_real = B; pl.b_real = B / N; pl.d = d; pl.tl = tl; pl.tg = tg;
+      round_shape(pl, fused);
+      const double base = logits_us(pl, nblk) * (fused ? 2 : 1);
+      const int kt_q = (int)(pl.W / BK), kt_k = (int)(pl.b / BK);
+      for (int sk : Q_SPLITS) {
+        if (sk > kt_q) break;
+        split(kt_q, sk, pl.splitk, pl.ktps);
+        for (int ks : K_SPLITS) {
+          if (ks > 1 && (fused || tile || ks > kt_k)) break;
+          split(kt_k, ks, pl.key_splits, pl.key_ktps);
+          const double us = base + pl.npanels * grads_us(pl, nblk, pl.ktps, pl.splitk, pl.key_ktps, pl.key_splits);
+          if (best_fits && us >= best_us) continue;
+          layout(pl);
+          // a call whose workspace can stay within the library's static array stays within it
+          const bool fits = pl.total <= DISCO_STATIC_SCRATCH_BYTES;
+          if (fits > best_fits || (fits == best_fits && us < best_us)) { best = pl; best_us = us; best_fits = fits; }
+        }
+      }
+    }
+  return best;
 }
 
 // Query tiles per super-block of the logit tile walk (superblock_tile): the largest power of two <= 8 that divides
@@ -1137,20 +1288,74 @@ bool allow_lds(K kernel, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
+// Launchers of one tile size; the LDS limit of the kernels is raised once per process (one device per process here).
+template <int T>
+struct TileKernels {
+  static bool lds_ok() {
+    static const bool ok =
+        allow_lds(k_logit_tiles<T, true, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, false>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, true, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_repair<T, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_repair<T, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_grads<T, KEY_WRITE, false>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false>, GEMM_SMEM_BYTES<T>) &&
+        allow_lds(k_grads<T, KEY_WRITE, true>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true>, GEMM_SMEM_BYTES<T>) &&
+        allow_lds(k_grads<T, KEY_SPLIT, false>, GEMM_SMEM_BYTES<T>);
+    return ok;
+  }
+  // logit tiles of the key panel [jp0, jp0 + W): statistics, stored numerators or both
+  static void logits(bool stats, bool store, const Plan& pl, const Blocks& bl, int64_t g0, float s2, int64_t jp0, int64_t W, int cus, hipStream_t st) {
+    const int nI = (int)(pl.b / T), nJ = (int)(W / T);
+    // super-block shape of the tile walk: sbi query tiles, then as many key tiles as keep it within 32 tiles
+    const int sbi = superblock_width(nI), sbj = 32 / sbi < nJ ? 32 / sbi : nJ;
+    const int tiles = bl.nblk * ((nI * nJ + 7) / 8 * 8);  // every block, each padded to a multiple of 8
+    const int slots = cus * (T == 256 ? 1 : 2);
+    const dim3 grid((unsigned)(tiles < slots ? tiles : slots));
+    auto go = [&](auto kernel) { kernel<<<grid, Cfg<T>::NTHREADS, LOGIT_SMEM_BYTES<T>, st>>>(bl, pl.b, pl.B_real, pl.d, g0, s2, jp0, W, sbi, sbj, bl.nblk); };
+    if (stats && store) { if (pl.ragged) go(k_logit_tiles<T, true, true, true>); else go(k_logit_tiles<T, true, true>); }
+    else if (stats) { if (pl.ragged) go(k_logit_tiles<T, true, false, true>); else go(k_logit_tiles<T, true, false>); }
+    else { if (pl.ragged) go(k_logit_tiles<T, false, true, true>); else go(k_logit_tiles<T, false, true>); }
+  }
+  static void repair(bool store, const Plan& pl, const Blocks& bl, int rank, float s2, hipStream_t st) {
+    const dim3 grid((unsigned)(bl.nblk * (pl.b / T)));
+    auto go = [&](auto kernel) { kernel<<<grid, Cfg<T>::NTHREADS, LOGIT_SMEM_BYTES<T>, st>>>(bl, pl.b, pl.B, pl.d, rank, s2); };
+    if (store) go(k_logit_repair<T, true>); else go(k_logit_repair<T, false>);
+  }
+  // both gradient contractions over the key panel [jp0, jp0 + W); part: 0 both, 1 key side only, 2 query side only
+  static void grads(int part, bool key_add, bool query_add, const Plan& pl, const Blocks& bl, float cs, int64_t jp0, hipStream_t st) {
+    GradShape g;
+    g.b = pl.b; g.B = pl.B; g.d = pl.d; g.jp0 = jp0; g.W = pl.W;
+    g.nMq = pl.nMq; g.nMk = pl.nMk; g.nN = pl.nN;
+    g.splitk = pl.splitk; g.ktps = pl.ktps; g.key_splits = pl.key_splits; g.key_ktps = pl.key_ktps;
+    const int qT = pl.nMq * pl.nN, qS = bl.nblk * pl.splitk;
+    g.q_wgs = part == 1 ? 0 : qS % 8 == 0 ? qT * qS : 8 % qS == 0 ? 8 * ((qT + 8 / qS - 1) / (8 / qS)) : (qS * qT + 7) / 8 * 8;   // see the kernel's slice -> XCD mapping
+    const int k_wgs = part == 2 ? 0 : bl.nblk * ((pl.nMk * pl.nN * pl.key_splits + 7) / 8 * 8);
+    auto go = [&](auto kernel) { kernel<<<dim3((unsigned)(g.q_wgs + k_wgs)), Cfg<T>::NTHREADS, GEMM_SMEM_BYTES<T>, st>>>(bl, g, cs); };
+    if (pl.key_splits > 1) go(k_grads<T, KEY_SPLIT, false>);
+    else if (query_add) { if (key_add) go(k_grads<T, KEY_ADD, true>); else go(k_grads<T, KEY_WRITE, true>); }
+    else { if (key_add) go(k_grads<T, KEY_ADD, false>); else go(k_grads<T, KEY_WRITE, false>); }
+  }
+};
+
+void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, float cs, hipStream_t st) {
+  FinalizeShape f;
+  f.b = pl.b_real; f.bp = pl.b; f.B = pl.B_real; f.Bp = pl.B; f.d = pl.d;
+  f.rank = pr.rank; f.splitk = pl.splitk; f.key_splits = pl.key_splits; f.accumulate = pr.accumulate;
+  const bool ks = pl.key_splits > 1;
+  const int64_t rows = ks ? pl.B_real : pl.b_real;
+  const bool rowwg = pr.variant != LOSS_NTXENT && rows <= FINALIZE_ROWWG_MAX;
+  auto go = [&](auto kernel) { kernel<<<dim3((unsigned)(rowwg ? rows : (rows + 3) / 4)), 256, 0, st>>>(bl, f, cs); };
+  if (pr.variant == LOSS_NTXENT) { if (ks) go(k_finalize_ntxent<true>); else go(k_finalize_ntxent<false>); }
+  else if (rowwg) { if (ks) go(k_finalize<true, true>); else go(k_finalize<true, false>); }
+  else { if (ks) go(k_finalize<false, true>); else go(k_finalize<false, false>); }
+}
+
 // gate / gate_value: see Blocks.  marks: record the benchmark's stage events.
 int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_value = 0, bool marks = true) {
-  // the tile kernels use more LDS than the default limit; raised once per process (one device per process here)
-  static const bool lds_ok = allow_lds(k_logit_tiles<true, true>, LOGIT_SMEM_BYTES) && allow_lds(k_logit_tiles<true, false>, LOGIT_SMEM_BYTES) &&
-                             allow_lds(k_logit_tiles<false, true>, LOGIT_SMEM_BYTES) && allow_lds(k_logit_tiles<true, true, true>, LOGIT_SMEM_BYTES) &&
-                             allow_lds(k_logit_tiles<true, false, true>, LOGIT_SMEM_BYTES) && allow_lds(k_logit_tiles<false, true, true>, LOGIT_SMEM_BYTES) &&
-                             allow_lds(k_logit_repair<false>, LOGIT_SMEM_BYTES) &&
-                             allow_lds(k_logit_repair<true>, LOGIT_SMEM_BYTES) && allow_lds(k_key_grad<false>, GEMM_SMEM_BYTES) &&
-                             allow_lds(k_key_grad<true>, GEMM_SMEM_BYTES) && allow_lds(k_query_partial<false>, GEMM_SMEM_BYTES) &&
-                             allow_lds(k_query_partial<true>, GEMM_SMEM_BYTES);
-  if (!lds_ok) return DISCO_ERR_HIP;
   const int nblk = loss_blocks(pr.variant);
   const Plan pl = make_plan(pr.B, pr.d, pr.N, fused, nblk);
-  const int persistent_wgs = compute_units();
+  if ((pl.tl == 256 || pl.tg == 256) && !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
+  if ((pl.tl == 128 || pl.tg == 128) && !TileKernels<128>::lds_ok()) return DISCO_ERR_HIP;
+  const int cus = compute_units();
   const int64_t b = pl.b, B = pl.B, d = pl.d, W = pl.W;     // whole tiles; the real sizes are pl.b_real, pl.B_real
   char* ws = static_cast<char*>(pr.ws);
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
@@ -1185,10 +1390,11 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
     p.ce = reinterpret_cast<float*>(rows + 5 * pl.rows_stride);
     p.rowds = reinterpret_cast<float*>(rows + 6 * pl.rows_stride);
     p.ref2 = reinterpret_cast<float*>(ws + pl.off_ref + (size_t)z * pl.rows_stride);
-    p.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + z * align_up((size_t)(b / BN) * 4));
+    p.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + z * align_up((size_t)(b / 128) * 4));
     p.ymax_parts = wgmax + (z == 0 ? NORM_BLOCKS : 0);     // block A's keys are T, block C's are I
     p.Xs = reinterpret_cast<uint16_t*>(ws + pl.off_Xs + z * align_up((size_t)d * b * 2));
     p.part = reinterpret_cast<float*>(ws + pl.off_part + z * align_up((size_t)pl.splitk * b * d * 4));
+    p.kpart = reinterpret_cast<float*>(ws + pl.off_kpart + z * align_up((size_t)pl.key_splits * B * d * 4));
     p.gq = z == 0 ? pr.gI : pr.gT;
     p.gk = z == 0 ? pr.gT : pr.gI;
   }
@@ -1197,83 +1403,66 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   const float c = loss_norm(pl.B_real, pr.variant);
   const float cs = c * pr.s;
   hipStream_t st = pr.stream;
-  const int nI = (int)(b / BN);
-  // super-block shape of the logit tile walk: sbi query tiles, then as many key tiles as keep it within 32 tiles
-  const int sbi = superblock_width(nI);
-  auto logit_grid = [&](int64_t keys, int& sbj) {
-    const int nJ = (int)(keys / BM);
-    sbj = 32 / sbi < nJ ? 32 / sbi : nJ;
-    const int tiles2 = nblk * ((nI * nJ + 7) / 8 * 8);  // every block, each padded to a multiple of 8
-    return dim3((unsigned)(tiles2 < persistent_wgs ? tiles2 : persistent_wgs));
-  };
-  const int nMk = (int)(W / BM);
-  const dim3 key_grid((unsigned)(((nMk * pl.nN + 7) / 8) * 8), (unsigned)nblk);
-  // k_query_partial's grid: see its slice -> XCD mapping
-  const int qT = pl.nMq * pl.nN, qS = nblk * pl.splitk;
-  const int q_wgs = qS % 8 == 0 ? 8 * qT * (qS / 8) : 8 % qS == 0 ? 8 * ((qT + 8 / qS - 1) / (8 / qS)) : (qS * qT + 7) / 8 * 8;
-  const dim3 q_grid((unsigned)q_wgs);
   const int64_t g0 = (int64_t)pr.rank * pl.b_real;       // global row of the rank's first row
   int stage = 0;
+  auto mark = [&] { if (marks) stage_mark(st, stage++); };
 
-  if (marks) stage_mark(st, stage++);
+  mark();
   if (pl.ragged)
-    k_pad_operands<<<dim3((unsigned)(8 * persistent_wgs)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, b, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
+    k_pad_operands<<<dim3((unsigned)(8 * cus)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, b, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
   k_prep<<<dim3((unsigned)(2 * NORM_BLOCKS + nblk * ((b + 3) / 4))), 256, 0, st>>>(bl, I, T, pl.B_real, pl.b_real, b, d, pr.rank, s2, wgmax);
-  if (marks) stage_mark(st, stage++);
-
-  int sbj;
-  if (fused) {
-    const dim3 g = logit_grid(B, sbj);
-    if (pl.ragged) k_logit_tiles<true, false, true><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, 0, B, sbi, sbj, nblk);
-    else k_logit_tiles<true, false><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, 0, B, sbi, sbj, nblk);
-  } else {
-    const dim3 g = logit_grid(B, sbj);
-    if (pl.ragged) k_logit_tiles<true, true, true><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, 0, B, sbi, sbj, nblk);
-    else k_logit_tiles<true, true><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, 0, B, sbi, sbj, nblk);
-  }
-  if (marks) stage_mark(st, stage++);
-  k_row_merge<<<dim3((unsigned)(b / 64), (unsigned)nblk), 1024, 0, st>>>(bl, b, pl.nparts, pl.nparts, s2, nullptr, nullptr, d);
-  if (fused) k_logit_repair<false><<<dim3((unsigned)(nblk * nI)), NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, B, d, pr.rank, s2);
-  else k_logit_repair<true><<<dim3((unsigned)(nblk * nI)), NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, B, d, pr.rank, s2);
-  if (marks) stage_mark(st, stage++);
-
+  mark();
+  if (pl.tl == 256) TileKernels<256>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
+  else TileKernels<128>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
+  mark();
+  k_row_merge<<<dim3((unsigned)(b / 64), (unsigned)nblk), 1024, 0, st>>>(bl, b, pl.nparts, pl.nparts, s2, nullptr, nullptr, d, pl.tl);
+  if (pl.tl == 256) TileKernels<256>::repair(!fused, pl, bl, pr.rank, s2, st);
+  else TileKernels<128>::repair(!fused, pl, bl, pr.rank, s2, st);
+  mark();
   for (int pnl = 0; pnl < pl.npanels; ++pnl) {
     const int64_t jp0 = (int64_t)pnl * W;
     if (fused) {
-      const dim3 g = logit_grid(W, sbj);
-      if (pl.ragged) k_logit_tiles<false, true, true><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, jp0, W, sbi, sbj, nblk);
-      else k_logit_tiles<false, true><<<g, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, b, pl.B_real, d, g0, s2, jp0, W, sbi, sbj, nblk);
+      if (pl.tl == 256) TileKernels<256>::logits(false, true, pl, bl, g0, s2, jp0, W, cus, st);
+      else TileKernels<128>::logits(false, true, pl, bl, g0, s2, jp0, W, cus, st);
     }
-    if (pr.accumulate)
-      k_key_grad<true><<<key_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(bl, b, d, cs, jp0, W, nMk, pl.nN);
-    else
-      k_key_grad<false><<<key_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(bl, b, d, cs, jp0, W, nMk, pl.nN);
-    if (!fused) if (marks) stage_mark(st, stage++);
-    if (pnl > 0)
-      k_query_partial<true><<<q_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(bl, b, d, jp0, W, pl.nMq, pl.nN, pl.splitk, pl.ktps);
-    else
-      k_query_partial<false><<<q_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(bl, b, d, jp0, W, pl.nMq, pl.nN, pl.splitk, pl.ktps);
+    auto grads = [&](int part) {
+      if (pl.tg == 256) TileKernels<256>::grads(part, pr.accumulate != 0, pnl > 0, pl, bl, cs, jp0, st);
+      else TileKernels<128>::grads(part, pr.accumulate != 0, pnl > 0, pl, bl, cs, jp0, st);
+    };
+    if (fused || !marks || !stage_marks_on()) {
+      grads(0);
+    } else {                                              // a launch of its own for each side, so that each can be timed
+      grads(1);
+      mark();
+      grads(2);
+    }
   }
-  if (marks) stage_mark(st, stage++);
-  if (pr.variant == LOSS_NTXENT) k_query_finalize_ntxent<<<dim3((unsigned)((pl.b_real + 3) / 4)), 256, 0, st>>>(bl, pl.b_real, b, pl.B_real, d, pr.rank, cs, pl.splitk);
-  else if (pl.b_real <= FINALIZE_ROWWG_MAX) k_query_finalize<true><<<dim3((unsigned)pl.b_real), 256, 0, st>>>(bl, pl.b_real, b, d, pr.rank, cs, pl.splitk);
-  else k_query_finalize<false><<<dim3((unsigned)((pl.b_real + 3) / 4)), 256, 0, st>>>(bl, pl.b_real, b, d, pr.rank, cs, pl.splitk);
+  if (!fused && !stage_marks_on()) ++stage;
+  mark();
+  finalize(pr, pl, bl, cs, st);
   k_scalars<<<1, 1024, 0, st>>>(bl, pl.b_real, c, pr.accumulate, pr.loss, pr.gs);
-  if (marks) stage_mark(st, stage++);
+  mark();
   return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
 }
 
 // The symmetric full loss (see the kernels above): one matrix of numerators, both directions' statistics, one
 // combined gradient matrix, two contractions; then, behind the flag, the two-block path for inputs it cannot take.
+// A small batch is not worth the path's two fixed costs, the pass over the matrix that combines the gradients and the
+// empty launches of the two-block path behind it (about 45 us together): the 6 B^2 d flop it saves pay for them from about
+// B^2 d = 1e10 on.  (Measured, symmetric / two-block in us: B = 2816, d = 640: 133 / 110; 4375, 320: 193 / 156;
+// 3964, 256: 158 / 112; 6912, 320: 274 / 293; 8728, 320: 397 / 498.)
+bool sym_two_block(int64_t B, int64_t d) { return (double)B * B * d < 1e10; }
+
 size_t sym_tail(int64_t B, int64_t d) {
-  const size_t a = make_plan(B, d, 1, false, 1).total, c = make_plan(B, d, 1, false, 2).total;
+  const size_t a = make_plan(B, d, 1, false, 1, 256).total, c = make_plan(B, d, 1, false, 2).total;
   return a > c ? a : c;
 }
 
 int mfma_sym_run_impl(const Problem& pr) {
-  static const bool lds_ok = allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES) && allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES);
-  if (!lds_ok) return DISCO_ERR_HIP;
-  const Plan pl = make_plan(pr.B, pr.d, 1, false, 1);
+  static const bool lds_ok = allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES<256>) && allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES<256>);
+  if (!lds_ok || !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
+  if (sym_two_block(pr.B, pr.d)) return mfma_run(pr, false);
+  const Plan pl = make_plan(pr.B, pr.d, 1, false, 1, 256);
   const int persistent_wgs = compute_units();
   const int64_t B = pl.B, d = pl.d, Br = pl.B_real;        // whole tiles / the rows that exist
   char* ws = static_cast<char*>(pr.ws);
@@ -1326,7 +1515,7 @@ int mfma_sym_run_impl(const Problem& pr) {
   q.ce = reinterpret_cast<float*>(rows1 + 5 * pl.rows_stride);
   q.rowds = reinterpret_cast<float*>(rows1 + 6 * pl.rows_stride);
   q.ref2 = reinterpret_cast<float*>(ws + pl.off_ref + pl.rows_stride);
-  q.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + align_up((size_t)(B / BN) * 4));
+  q.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + align_up((size_t)(B / 128) * 4));
 
   const float s2 = pr.s * LOG2E;
   const float c = loss_norm(Br, LOSS_CLIP);
@@ -1337,9 +1526,6 @@ int mfma_sym_run_impl(const Problem& pr) {
   const int sbj = 32 / sbi < nT ? 32 / sbi : nT;
   const int tiles = (nT * nT + 7) / 8 * 8;
   const dim3 logit_grid((unsigned)(tiles < persistent_wgs ? tiles : persistent_wgs));
-  const dim3 key_grid((unsigned)(((nT * pl.nN + 7) / 8) * 8), 1);
-  const int qT = pl.nMq * pl.nN, qS = pl.splitk;
-  const int q_wgs = qS % 8 == 0 ? 8 * qT * (qS / 8) : 8 % qS == 0 ? 8 * ((qT + 8 / qS - 1) / (8 / qS)) : (qS * qT + 7) / 8 * 8;
   int stage = 0;
 
   stage_mark(st, stage++);
@@ -1347,12 +1533,12 @@ int mfma_sym_run_impl(const Problem& pr) {
   k_prep<<<dim3((unsigned)(2 * NORM_BLOCKS + (B + 3) / 4)), 256, 0, st>>>(bl, I, T, Br, Br, B, d, 0, s2, wgmax);
   k_sym_ref<<<1, 1024, 0, st>>>(p.zd2, Br, wgmax, s2, rglobal, gate);
   stage_mark(st, stage++);
-  if (pl.ragged) k_sym_logit<true><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
-  else k_sym_logit<false><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
+  if (pl.ragged) k_sym_logit<true><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES<256>, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
+  else k_sym_logit<false><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES<256>, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
   stage_mark(st, stage++);
   Blocks both = bl;
   both.nblk = 2;
-  k_row_merge<<<dim3((unsigned)((B + 63) / 64), 2), 1024, 0, st>>>(both, B, pl.nparts, nT, s2, rglobal, gate, 0);
+  k_row_merge<<<dim3((unsigned)((B + 63) / 64), 2), 1024, 0, st>>>(both, B, pl.nparts, nT, s2, rglobal, gate, 0, BN);
   Blocks go = bl;                                   // from here on only while no total was lost
   go.gate = gate;
   go.gate_value = 0;
@@ -1360,10 +1546,16 @@ int mfma_sym_run_impl(const Problem& pr) {
   stage_mark(st, stage++);
   k_sym_combine<<<dim3((unsigned)(8 * persistent_wgs)), 256, 0, st>>>(go, B);
   stage_mark(st, stage++);
-  if (pr.accumulate) k_key_grad<true><<<key_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(go, B, d, cs, 0, B, nT, pl.nN);
-  else k_key_grad<false><<<key_grid, NTHREADS, GEMM_SMEM_BYTES, st>>>(go, B, d, cs, 0, B, nT, pl.nN);
+  auto grads = [&](int part) { TileKernels<256>::grads(part, pr.accumulate != 0, false, pl, go, cs, 0, st); };
+  if (stage_marks_on()) {
+    grads(1);
+    stage_mark(st, stage++);
+    grads(2);
+  } else {
+    grads(0);
+    ++stage;
+  }
   stage_mark(st, stage++);
-  k_query_partial<false><<<dim3((unsigned)q_wgs), NTHREADS, GEMM_SMEM_BYTES, st>>>(go, B, d, 0, B, pl.nMq, pl.nN, pl.splitk, pl.ktps);
   stage_mark(st, stage++);
   k_sym_finalize<<<dim3((unsigned)((Br + 3) / 4)), 256, 0, st>>>(go, Br, B, d, cs, pl.splitk, pr.accumulate);
   Blocks go2 = go;
@@ -1393,7 +1585,9 @@ size_t mfma_stored_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant)
 size_t mfma_fused_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, true, loss_blocks(variant)).total; }
 int mfma_stored_run(const Problem& pr) { return mfma_run(pr, false); }
 int mfma_fused_run(const Problem& pr) { return mfma_run(pr, true); }
-size_t mfma_sym_workspace_bytes(int64_t B, int64_t d) { return sym_tail(B, d) + 256; }
+size_t mfma_sym_workspace_bytes(int64_t B, int64_t d) {
+  return sym_two_block(B, d) ? make_plan(B, d, 1, false, 2).total : sym_tail(B, d) + 256;
+}
 int mfma_sym_run(const Problem& pr) { return mfma_sym_run_impl(pr); }
 
 }  // namespace disco

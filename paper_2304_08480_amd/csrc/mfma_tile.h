@@ -1,4 +1,4 @@
-// Device-side building blocks of the bf16 MFMA path: the 256x256x64 NT tile main loop, the operand
+// Device-side building blocks of the bf16 MFMA path: the T x T x 64 NT tile main loop (T = 256 or 128), the operand
 // tile formats and the tile store of the fp32 outputs (through LDS).  Included by mfma_kernels.hip only.
 //
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
@@ -16,7 +16,14 @@
 // 32 KiB units, each holding one operand of one K-step: A(kt), B(kt), A(kt+1), B(kt+1) resident or landing,
 // plus one unit being refilled (see kloop).
 //
-// Operand tile formats in one unit:
+// T = 128 is the same loop at half the size: 4 waves of 64 x 64, waves 0-1 loading A and 2-3 B, units of 16 KiB, so that
+// two workgroups share a compute unit (80 KiB of LDS each).  It moves twice the bytes per MFMA, which the compute unit's
+// load path (about 64 B/clk) cannot hide: where the chip is full a K-step of two such workgroups takes 1.03 us against
+// 1.7 us for a 256-tile of twice their work (b = 4096, B = 32768, d = 512: 1011 us a call against 835).  What it is for is
+// calls whose 256-tiles leave compute units idle, whose reductions are a few K-steps, or whose feature width fills half a
+// 256-tile: 37 us against 56 at b = 512, B = 1024, d = 256; 83 against 123 at b = 1550, B = 6200, d = 256.
+//
+// Operand tile formats in one unit (T = 256; T = 128 has half the rows or half the row length):
 //   format K - the operand's reduction index is contiguous in memory (element (r,k) at base[r*ld + k]):
 //              256 rows of 128 bytes, 16-byte chunks XOR-swizzled with bits 1..3 of the row so that the
 //              16 consecutive rows a quarter-wave reads (same chunk) hit 16 different bank groups of the
@@ -60,17 +67,28 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
-constexpr int NTHREADS = 512;                     // 8 waves: 2 (M) x 4 (N), wave tile 128 x 64
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int UNIT_BYTES = BM * BK * 2;           // 32 KiB: one operand, one K-step
+constexpr int BK = 64;
 constexpr int NUNITS = 5;
-constexpr int SMEM_BYTES = NUNITS * UNIT_BYTES;   // all 160 KiB of the CU's LDS
 constexpr int NLD = 8;                            // load instructions per loading wave and unit
+
+// T x T output tile: 256 (8 waves, 2 along M x 4 along N, wave tile 128 x 64) or 128 (4 waves, 2 x 2, wave tile 64 x 64)
+template <int T>
+struct Cfg {
+  static_assert(T == 128 || T == 256);
+  static constexpr int WAVES = T / 32, NTHREADS = WAVES * 64;
+  static constexpr int WN = WAVES / 2;                    // waves along N; also the waves that load one operand
+  static constexpr int WTM = T / 2;                       // a wave's rows of the A side (64 of the B side)
+  static constexpr int NFA = WTM / 32;                    // its 32-row fragments of the A side (2 of the B side)
+  static constexpr int UNIT_BYTES = T * BK * 2;           // one operand, one K-step: 32 or 16 KiB
+  static constexpr int SMEM_BYTES = NUNITS * UNIT_BYTES;  // the ring: all 160 KiB of the CU's LDS, or half of it
+};
+template <int NFA>
+using Acc = f32x16[NFA][2];
 
 enum { FMT_K = 0, FMT_R = 1, FMT_KA = 2, FMT_RA = 3 };
 // bytes between the LDS destinations of a wave's consecutive load instructions (FMT_KA: the wave loads the 8 column
-// pieces of its row group, which lie 4 KiB apart; else its instructions fill 8 KiB contiguously)
-constexpr int lds_step(int f) { return f == FMT_KA ? 4096 : 1024; }
+// pieces of its row group, which lie 16 T bytes apart; else its instructions fill 8 KiB contiguously)
+constexpr int lds_step(int f, int T) { return f == FMT_KA ? 16 * T : 1024; }
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -92,16 +110,20 @@ __device__ __forceinline__ u32x2 ds_read64_tr(uint32_t addr) {
   return v;
 }
 
-// Operand fragments of one 16-wide sub-step: 4 for the A side (rows 32 i), 2 for the B side.
+// Operand fragments of one 16-wide sub-step: NFA (4 or 2) for the A side (rows 32 i), 2 for the B side.
+template <int NFA>
 struct Frags {
-  u32x4 a[4], b[2];
+  u32x4 a[NFA], b[2];
 };
 // All LDS reads issued so far have returned; ties the registers to the wait so no MFMA moves above it.
-__device__ __forceinline__ void wait_frags(Frags& f) {
+__device__ __forceinline__ void wait_frags(Frags<4>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1])
                :
                : "memory");
+}
+__device__ __forceinline__ void wait_frags(Frags<2>& f) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]) : : "memory");
 }
 
 // A pointer that is the same in every lane, handed to the compiler as scalar registers: the loads below then take
@@ -112,24 +134,24 @@ __device__ __forceinline__ const char* uniform_ptr(const void* p) {
   return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
-// ---- per-lane addressing of one operand
-template <int FMT, int NFRAG>
+// ---- per-lane addressing of one operand of a T x T tile
+template <int T, int FMT, int NFRAG>
 struct Operand {
   uint32_t ld_off[NLD];     // byte offset of this lane's global chunk for the wave's load instructions
   uint32_t rd[4];           // FMT_K/KA: rd[ks] base for sub-step ks; FMT_R: rd[i] base for fragment i; FMT_RA: rd[h]
                             // base of the fragment's first (h = 0) and second (h = 1) transposing read
   uint32_t lds_q;           // LDS byte offset (inside the operand tile) of the wave's first load instruction
 
-  // lw: index 0..3 of this wave among the four that load this operand; row0: first tile row of this
+  // lw: index of this wave among the T / 64 that load this operand; row0: first tile row of this
   // wave's fragments (multiple of 32); ld in elements; nvalid: tile rows that exist in memory (a multiple of
-  // 8, at most 256): loads of the rows past them are redirected to the last existing rows, so that they
+  // 8, at most T): loads of the rows past them are redirected to the last existing rows, so that they
   // stay in bounds (the caller does not use the output rows or columns they feed)
-  __device__ __forceinline__ void init(int64_t ld, int lw, int lane, int row0, int nvalid = BM) {
+  __device__ __forceinline__ void init(int64_t ld, int lw, int lane, int row0, int nvalid = T) {
     const int wave = lw;
     lds_q = FMT == FMT_KA ? wave * 1024 : NLD * wave * 1024;
 #pragma unroll
     for (int n = 0; n < NLD; ++n) {
-      const int q = NLD * wave + n;               // which 1 KiB slice of the 32 KiB tile
+      const int q = NLD * wave + n;               // which 1 KiB slice of the operand's unit
       if (FMT == FMT_K) {
         const int rho = 8 * q + (lane >> 3), pc = lane & 7;
         const int ch = (pc ^ ((rho >> 1) & 7)) << 3;
@@ -141,7 +163,8 @@ struct Operand {
         const int c = q;                            // this instruction's column piece; lane = position in it
         ld_off[n] = (uint32_t)((c * 512 + (lane ^ ((c & 3) << 2)) * 8) * 2);
       } else {
-        const int kap = 2 * q + (lane >> 5), pcw = lane & 31;
+        constexpr int PPR = T / 8;                  // 16-byte pieces per reduction row of the unit
+        const int kap = (64 / PPR) * q + lane / PPR, pcw = lane % PPR;
         const int c0 = (((pcw >> 1) ^ ((kap & 3) << 1)) << 1) | (pcw & 1);
         const int c = (c0 << 3) < nvalid ? c0 : (nvalid >> 3) - 1;
         ld_off[n] = (uint32_t)(((int64_t)kap * ld + (c << 3)) * 2);
@@ -154,7 +177,7 @@ struct Operand {
     } else if (FMT == FMT_KA) {
       const int row = row0 + (lane & 31), kc = lane >> 5;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) rd[ks] = (uint32_t)((ks * 2 + kc) * 4096 + row * 16);
+      for (int ks = 0; ks < 4; ++ks) rd[ks] = (uint32_t)((ks * 2 + kc) * (16 * T) + row * 16);
     } else if (FMT == FMT_RA) {
       const int grp = lane >> 4, L = lane & 15, piece = L & 3;     // piece: 8-byte quarter of a 16-row (32-byte) group
       const int c = ((row0 + (grp & 1) * 16) >> 3) + (piece >> 1);   // + 4 per fragment: c % 4 unchanged
@@ -169,7 +192,7 @@ struct Operand {
 #pragma unroll
       for (int i = 0; i < NFRAG; ++i) {
         const int G = (row0 + 32 * i + (grp & 1) * 16) >> 4;
-        rd[i] = (uint32_t)(kap * 512 + ((G ^ ((kap & 3) << 1)) << 5) + 8 * (L & 3));
+        rd[i] = (uint32_t)(kap * (2 * T) + ((G ^ ((kap & 3) << 1)) << 5) + 8 * (L & 3));
       }
     }
   }
@@ -181,7 +204,7 @@ struct Operand {
     for (int n = 0; n < NLD; ++n) {
       const char* gp = ub + ld_off[n];
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
-                                       (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT)), 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT, T)), 16, 0, 0);
     }
   }
 };
@@ -189,70 +212,76 @@ struct Operand {
 __device__ __forceinline__ u32x4 join(u32x2 lo, u32x2 hi) { return u32x4{lo[0], lo[1], hi[0], hi[1]}; }
 
 // fragment i of sub-step KS from the operand tile at LDS byte address `tile`
-template <int FMT, int NFRAG, int KS, int I>
-__device__ __forceinline__ u32x4 read_frag(const Operand<FMT, NFRAG>& op, uint32_t tile) {
-  if (FMT == FMT_K) return ds_read128<I * 4096>(tile + op.rd[KS]);
-  if (FMT == FMT_KA) return ds_read128<I * 512>(tile + op.rd[KS]);
-  if (FMT == FMT_RA) return join(ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[0]), ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[1]));
-  return join(ds_read64_tr<KS * 8192>(tile + op.rd[I]), ds_read64_tr<KS * 8192 + 2048>(tile + op.rd[I]));
+template <int KS, int I, int T, int FMT, int NFRAG>
+__device__ __forceinline__ u32x4 read_frag(const Operand<T, FMT, NFRAG>& op, uint32_t tile) {
+  if constexpr (FMT == FMT_K) return ds_read128<I * 4096>(tile + op.rd[KS]);
+  else if constexpr (FMT == FMT_KA) return ds_read128<I * 512>(tile + op.rd[KS]);
+  else if constexpr (FMT == FMT_RA) return join(ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[0]), ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[1]));
+  else return join(ds_read64_tr<KS * 32 * T>(tile + op.rd[I]), ds_read64_tr<KS * 32 * T + 8 * T>(tile + op.rd[I]));
 }
-template <int FA, int FB, int KS>
-__device__ __forceinline__ void read_frags(Frags& f, const Operand<FA, 4>& a, const Operand<FB, 2>& b, uint32_t ta, uint32_t tb) {
-  f.a[0] = read_frag<FA, 4, KS, 0>(a, ta);
-  f.b[0] = read_frag<FB, 2, KS, 0>(b, tb);
-  f.a[1] = read_frag<FA, 4, KS, 1>(a, ta);
-  f.b[1] = read_frag<FB, 2, KS, 1>(b, tb);
-  f.a[2] = read_frag<FA, 4, KS, 2>(a, ta);
-  f.a[3] = read_frag<FA, 4, KS, 3>(a, ta);
+template <int KS, int T, int FA, int FB, int NFA>
+__device__ __forceinline__ void read_frags(Frags<NFA>& f, const Operand<T, FA, NFA>& a, const Operand<T, FB, 2>& b, uint32_t ta, uint32_t tb) {
+  f.a[0] = read_frag<KS, 0>(a, ta);
+  f.b[0] = read_frag<KS, 0>(b, tb);
+  f.a[1] = read_frag<KS, 1>(a, ta);
+  f.b[1] = read_frag<KS, 1>(b, tb);
+  if constexpr (NFA == 4) {
+    f.a[2] = read_frag<KS, 2>(a, ta);
+    f.a[3] = read_frag<KS, 3>(a, ta);
+  }
 }
 __device__ __forceinline__ void mfma1(f32x16& c, const u32x4& a, const u32x4& b) {
   c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 // acc = a * b (the matrix instruction takes a literal zero for its addend: no registers are cleared)
-__device__ __forceinline__ void mfma_block_first(const Frags& f, f32x16 (&acc)[4][2]) {
+template <int NFA>
+__device__ __forceinline__ void mfma_block_first(const Frags<NFA>& f, Acc<NFA>& acc) {
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NFA; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[i]), __builtin_bit_cast(bf16x8, f.b[j]), zero, 0, 0, 0);
 }
-__device__ __forceinline__ void mfma_block(const Frags& f, f32x16 (&acc)[4][2]) {
+template <int NFA>
+__device__ __forceinline__ void mfma_block(const Frags<NFA>& f, Acc<NFA>& acc) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NFA; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) mfma1(acc[i][j], f.a[i], f.b[j]);
 }
-// the 8 MFMAs of a sub-step with this wave's 8 load instructions of one unit interleaved (two after each of the
+// the 8 (4) MFMAs of a sub-step with this wave's 8 load instructions of one unit interleaved (two after each of the
 // first four: how they are spread over the sub-step makes no measurable difference).  The wave runs this
 // sub-step at raised priority: it then wins the SIMD's issue slots from the other wave group's wave, its loads
 // leave early in the K-step and have the longest time to land (query-side GEMM 6 % faster, logit kernel 1 %;
 // raising the priority of every MFMA block instead is 1-4 % slower everywhere)
-template <int FMT, int NFRAG>
-__device__ __forceinline__ void mfma_block_loads(const Frags& f, f32x16 (&acc)[4][2], const Operand<FMT, NFRAG>& op,
+template <int T, int FMT, int NFRAG, int NFA>
+__device__ __forceinline__ void mfma_block_loads(const Frags<NFA>& f, Acc<NFA>& acc, const Operand<T, FMT, NFRAG>& op,
                                                  const uint16_t* base, char* lds) {
   char* l0 = lds + __builtin_amdgcn_readfirstlane(op.lds_q);
   const char* ub = uniform_ptr(base);
 #define DISCO_LD(n)                                                                                                         \
   __builtin_amdgcn_global_load_lds(                                                                                         \
       (const __attribute__((address_space(1))) void*)(ub + op.ld_off[n]),                                                   \
-      (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT)), 16, 0, 0)
+      (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT, T)), 16, 0, 0)
   __builtin_amdgcn_s_setprio(1);
   mfma1(acc[0][0], f.a[0], f.b[0]); DISCO_LD(0); DISCO_LD(1);
   mfma1(acc[0][1], f.a[0], f.b[1]); DISCO_LD(2); DISCO_LD(3);
   mfma1(acc[1][0], f.a[1], f.b[0]); DISCO_LD(4); DISCO_LD(5);
   mfma1(acc[1][1], f.a[1], f.b[1]); DISCO_LD(6); DISCO_LD(7);
-  mfma1(acc[2][0], f.a[2], f.b[0]);
-  mfma1(acc[2][1], f.a[2], f.b[1]);
-  mfma1(acc[3][0], f.a[3], f.b[0]);
-  mfma1(acc[3][1], f.a[3], f.b[1]);
+  if constexpr (NFA == 4) {
+    mfma1(acc[2][0], f.a[2], f.b[0]);
+    mfma1(acc[2][1], f.a[2], f.b[1]);
+    mfma1(acc[3][0], f.a[3], f.b[0]);
+    mfma1(acc[3][1], f.a[3], f.b[1]);
+  }
   __builtin_amdgcn_s_setprio(0);
 #undef DISCO_LD
 }
 
 __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u >= NUNITS ? u - NUNITS : u; }
 
-// The K loop of one wave group.  GROUP 0 (waves 0-3) loads the A units, GROUP 1 (waves 4-7) the B units.
+// The K loop of one wave group.  GROUP 0 (the lower half of the waves) loads the A units, GROUP 1 the B units.
 //
 // Ring of five units; the operand tiles are laid into it in the order A0 B0 A1 B1 A2 B2 ..., item n in
 // unit n mod 5.  K-step kt computes from A(kt), B(kt) in four 16-wide sub-steps, each fetching the next
@@ -275,17 +304,18 @@ __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
 // WRITE_FIRST: the first K-step is peeled off the loop and writes the accumulators (acc = product, acc need not be
 // initialised); else every K-step adds to them (acc += product).  Peeling gains 2-5 % on the gradient GEMMs; in the
 // logit kernel it costs the epilogue registers it does not have.
-template <int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST>
+template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST>
 __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp, int64_t ldb,
-                                      int ktiles, char* smem, f32x16 (&acc)[4][2], int nvalid_b) {
+                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b) {
+  constexpr int NFA = Cfg<T>::NFA, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t stepA = kstep_elems<FA>(lda);
   const int64_t stepB = kstep_elems<FB>(ldb);
   const int last = ktiles - 1;
-  Operand<FA, 4> oa;
-  Operand<FB, 2> ob;
-  oa.init(lda, wave & 3, lane, (wave >> 2) * 128);
-  ob.init(ldb, wave & 3, lane, (wave & 3) * 64, nvalid_b);
+  Operand<T, FA, NFA> oa;
+  Operand<T, FB, 2> ob;
+  oa.init(lda, wave % WN, lane, (wave / WN) * Cfg<T>::WTM);
+  ob.init(ldb, wave % WN, lane, (wave % WN) * 64, nvalid_b);
   const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;   // LDS byte address
   const int k1 = last < 1 ? last : 1;
   if (GROUP == 0) {
@@ -297,8 +327,8 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   }
   wait_vmcnt<NLD>();
   lds_barrier();
-  Frags f0, f1;
-  read_frags<FA, FB, 0>(f0, oa, ob, smem_addr, smem_addr + UNIT_BYTES);
+  Frags<NFA> f0, f1;
+  read_frags<0>(f0, oa, ob, smem_addr, smem_addr + UNIT_BYTES);
   wait_frags(f0);
 
   int rA = 0;                                       // unit of A(kt); B(kt) is the next unit of the ring
@@ -310,20 +340,20 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     const uint32_t ta = smem_addr + (uint32_t)(rA * UNIT_BYTES), tb = smem_addr + (uint32_t)(rB * UNIT_BYTES);             \
     const int kload = kt + 2 < ktiles ? kt + 2 : last;                                                                     \
     /* sub-step 0 */                                                                                                       \
-    read_frags<FA, FB, 1>(f1, oa, ob, ta, tb);                                                                             \
+    read_frags<1>(f1, oa, ob, ta, tb);                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
     FIRST_BLOCK(f0, acc);                                                                                                  \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(f1);                                                                                                        \
     /* sub-step 1 */                                                                                                       \
-    read_frags<FA, FB, 2>(f0, oa, ob, ta, tb);                                                                             \
+    read_frags<2>(f0, oa, ob, ta, tb);                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
     if (GROUP == 0) mfma_block_loads(f1, acc, oa, A + kload * stepA, smem + lA * UNIT_BYTES);                              \
     else mfma_block(f1, acc);                                                                                              \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(f0);                                                                                                        \
     /* sub-step 2 */                                                                                                       \
-    read_frags<FA, FB, 3>(f1, oa, ob, ta, tb);                                                                             \
+    read_frags<3>(f1, oa, ob, ta, tb);                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
     mfma_block(f0, acc);                                                                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
@@ -332,7 +362,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     asm volatile("s_barrier" ::: "memory");                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     /* sub-step 3 */                                                                                                       \
-    read_frags<FA, FB, 0>(f0, oa, ob, smem_addr + (uint32_t)(nA * UNIT_BYTES), smem_addr + (uint32_t)(nB * UNIT_BYTES));   \
+    read_frags<0>(f0, oa, ob, smem_addr + (uint32_t)(nA * UNIT_BYTES), smem_addr + (uint32_t)(nB * UNIT_BYTES));   \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
     if (GROUP == 1) mfma_block_loads(f1, acc, ob, Bp + kload * stepB, smem + rA * UNIT_BYTES);                             \
     else mfma_block(f1, acc);                                                                                              \
@@ -358,56 +388,62 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   lds_barrier();
 }
 
-// acc[bm][bn] (+)= A_tile(256 x K) * B_tile(256 x K)^T for this wave's 128 x 64 piece (WRITE_FIRST: =, see kloop).
+// acc[bm][bn] (+)= A_tile(T x K) * B_tile(T x K)^T for this wave's T/2 x 64 piece (WRITE_FIRST: =, see kloop).
 //   FA / FB : tile format of the A / B operand (FMT_K: element (r,k) at base[r*ld + k]; FMT_R: at base[k*ld + r];
 //             FMT_KA / FMT_RA: the same for storage in 16-byte atoms, see the top of this file).
 //   A, Bp   : element (row 0, k 0) of the workgroup's operand tiles; ktiles = K / 64 >= 1.
-//   smem    : SMEM_BYTES of LDS, 16-byte aligned; on return no load is in flight and every wave has passed
+//   smem    : Cfg<T>::SMEM_BYTES of LDS, 16-byte aligned; on return no load is in flight and every wave has passed
 //             a barrier, so the caller may reuse it at once.
-//   nvalid_b: rows of the B tile that exist in memory (multiple of 8, <= 256); the output columns from
+//   nvalid_b: rows of the B tile that exist in memory (multiple of 8, <= T); the output columns from
 //             nvalid_b on are then meaningless and must not be stored.
-template <int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false>
+template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp,
-                                         int64_t ldb, int ktiles, char* smem, f32x16 (&acc)[4][2], int nvalid_b = BN) {
-  if (threadIdx.x < NTHREADS / 2) kloop<FA, FB, 0, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
-  else kloop<FA, FB, 1, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
+                                         int64_t ldb, int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b = T) {
+  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
+  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
 }
 
-// Writes a workgroup's 256 x 256 fp32 accumulator tile to row-major global memory through LDS, so that
-// every global store is a full 1 KiB row segment (the accumulator layout would give 4-byte elements per
-// lane).  Two passes of 128 rows; LDS rows padded to 1056 bytes so that the two half-waves of a 4-byte
+// Writes a workgroup's T x T fp32 accumulator tile to row-major global memory through LDS, so that
+// every global store is a full 1 KiB (T = 128: 512-byte) row segment (the accumulator layout would give 4-byte elements
+// per lane).  Passes of 128 rows; LDS rows padded by 32 bytes so that the two half-waves of a 4-byte
 // write land on different banks.  out points at the tile's first element; value = scale * acc (+ old);
 // only the first ncols columns (a multiple of 4) of the first nrows rows are touched.
-constexpr int OUT_ROW_BYTES = BN * 4 + 32;
-constexpr int OUT_SMEM_BYTES = 128 * OUT_ROW_BYTES;       // 132 KiB
+template <int T>
+constexpr int OUT_ROW_BYTES = T * 4 + 32;
+template <int T>
+constexpr int OUT_SMEM_BYTES = 128 * OUT_ROW_BYTES<T>;       // 132 KiB (T = 128: 68 KiB)
 
-template <bool ACCUMULATE, bool ROWMASK>
-__device__ __forceinline__ void store_tile_f32_rows(f32x16 (&acc)[4][2], char* smem, float* out, int64_t ld, float scale, int ncols, int nrows) {
+template <int T, bool ACCUMULATE, bool ROWMASK>
+__device__ __forceinline__ void store_tile_f32_rows(Acc<Cfg<T>::NFA>& acc, char* smem, float* out, int64_t ld, float scale, int ncols, int nrows) {
+  constexpr int WN = Cfg<T>::WN, NFA = Cfg<T>::NFA, RB = OUT_ROW_BYTES<T>;
+  constexpr int CPR = T / 4, RSTEP = Cfg<T>::NTHREADS / CPR;      // 16-byte pieces per row, rows the workgroup stores at a time (8)
+  constexpr int PASSES = T / 128;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave >> 2, wn = wave & 3, half = lane >> 5;
-  const int chunk = t & 63, r0 = t >> 6;
+  const int wm = wave / WN, wn = wave % WN, half = lane >> 5;
+  const int chunk = t % CPR, r0 = t / CPR;
   const bool live = chunk * 4 < ncols;             // this thread's four columns exist (ncols is a multiple of 4)
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < PASSES; ++h) {
     // when accumulating, the old values are requested eight rows at a time, the first eight before the
     // staging so that their latency is paid under the LDS traffic
     f32x4 old[8];
     if (ACCUMULATE && live) {
 #pragma unroll
       for (int r = 0; r < 8; ++r)
-        if (!ROWMASK || h * 128 + r * 8 + r0 < nrows) old[r] = *reinterpret_cast<const f32x4*>(out + (int64_t)(h * 128 + r * 8 + r0) * ld + chunk * 4);
+        if (!ROWMASK || h * 128 + r * RSTEP + r0 < nrows) old[r] = *reinterpret_cast<const f32x4*>(out + (int64_t)(h * 128 + r * RSTEP + r0) * ld + chunk * 4);
     }
     lds_barrier();
-    if (wm == h) {
+    if (PASSES == 1 || wm == h) {
+      const int rbase = PASSES == 1 ? wm * Cfg<T>::WTM : 0;
 #pragma unroll
       for (int bn = 0; bn < 2; ++bn)
 #pragma unroll
-        for (int bm = 0; bm < 4; ++bm)
+        for (int bm = 0; bm < NFA; ++bm)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int row = bm * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
+            const int row = rbase + bm * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
             const int col = wn * 64 + bn * 32 + (lane & 31);
-            *reinterpret_cast<float*>(smem + row * OUT_ROW_BYTES + col * 4) = scale * acc[bm][bn][e];
+            *reinterpret_cast<float*>(smem + row * RB + col * 4) = scale * acc[bm][bn][e];
           }
     }
     lds_barrier();
@@ -415,16 +451,16 @@ __device__ __forceinline__ void store_tile_f32_rows(f32x16 (&acc)[4][2], char* s
     for (int q = 0; q < 2; ++q) {
       f32x4 v[8];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) v[r] = *reinterpret_cast<const f32x4*>(smem + ((q * 8 + r) * 8 + r0) * OUT_ROW_BYTES + chunk * 16);
+      for (int r = 0; r < 8; ++r) v[r] = *reinterpret_cast<const f32x4*>(smem + ((q * 8 + r) * RSTEP + r0) * RB + chunk * 16);
       if (ACCUMULATE && q == 1 && live) {
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-          if (!ROWMASK || h * 128 + (8 + r) * 8 + r0 < nrows) old[r] = *reinterpret_cast<const f32x4*>(out + (int64_t)(h * 128 + (8 + r) * 8 + r0) * ld + chunk * 4);
+          if (!ROWMASK || h * 128 + (8 + r) * RSTEP + r0 < nrows) old[r] = *reinterpret_cast<const f32x4*>(out + (int64_t)(h * 128 + (8 + r) * RSTEP + r0) * ld + chunk * 4);
       }
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        const bool there = live && (!ROWMASK || h * 128 + (q * 8 + r) * 8 + r0 < nrows);
-        float* g = out + (int64_t)(h * 128 + (q * 8 + r) * 8 + r0) * ld + chunk * 4;
+        const bool there = live && (!ROWMASK || h * 128 + (q * 8 + r) * RSTEP + r0 < nrows);
+        float* g = out + (int64_t)(h * 128 + (q * 8 + r) * RSTEP + r0) * ld + chunk * 4;
         if (ACCUMULATE && there) v[r] += old[r];
         if (there) *reinterpret_cast<f32x4*>(g) = v[r];
       }
@@ -433,11 +469,11 @@ __device__ __forceinline__ void store_tile_f32_rows(f32x16 (&acc)[4][2], char* s
 }
 
 // (a tile whose rows all exist takes the instance without the per-row tests)
-template <bool ACCUMULATE>
-__device__ __forceinline__ void store_tile_f32(f32x16 (&acc)[4][2], char* smem, float* out, int64_t ld, float scale, int ncols = BN,
-                                               int nrows = BM) {
-  if (nrows >= BM) store_tile_f32_rows<ACCUMULATE, false>(acc, smem, out, ld, scale, ncols, nrows);
-  else store_tile_f32_rows<ACCUMULATE, true>(acc, smem, out, ld, scale, ncols, nrows);
+template <int T, bool ACCUMULATE>
+__device__ __forceinline__ void store_tile_f32(Acc<Cfg<T>::NFA>& acc, char* smem, float* out, int64_t ld, float scale, int ncols = T,
+                                               int nrows = T) {
+  if (nrows >= T) store_tile_f32_rows<T, ACCUMULATE, false>(acc, smem, out, ld, scale, ncols, nrows);
+  else store_tile_f32_rows<T, ACCUMULATE, true>(acc, smem, out, ld, scale, ncols, nrows);
 }
 
 }  // namespace tile
