@@ -67,7 +67,8 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
 /*
  * DISCO_PATH_NAIVE        fp32 arithmetic (fp32 matrix instruction for fp32 features, vector-ALU FMA for
  *                         part of the bf16 case), fp32 logit blocks kept in the workspace (2*b*B*4
- *                         bytes: the paper's 2B^2/N memory model, Sec. 4.1).  Any B, d, N; either dtype.
+ *                         bytes, rows rounded up to whole 16-byte pieces: the paper's 2B^2/N memory model,
+                         Sec. 4.1).  Any B, d, N; either dtype.
  * DISCO_PATH_MATERIALIZED bf16 MFMA tiles.  The logit blocks are computed once; the un-normalised
  *                         softmax numerators are kept in bf16 (2*b*B*2 bytes) and feed the two
  *                         gradient contractions (12*b*B*d flop).  Needs dtype bf16, d % 64 == 0,
@@ -194,7 +195,8 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
  *   1 row norms + positive-pair logits   2 logit tiles + softmax numerators   3 row merge + scaled transpose
  *   4 key-side gradient GEMM             5 query-side split GEMM              6 query finalize + scalars
  * (Stages 4 and 5 are one launch while stage timing is off, two while it is on.)
- * Stages of DISCO_PATH_NAIVE (DISCO_STAGES_NAIVE = 5): similarity, row softmax, scalars, key grad, query grad.
+ * Stages of DISCO_PATH_NAIVE (DISCO_STAGES_NAIVE = 5): similarity, row softmax, scalars, key grad, query grad.  (Calls whose
+ *   two gradient sides share a launch, with the scalars in it, have all three in the fourth interval.)
  * Stages of DISCO_PATH_FUSED (DISCO_STAGES_FUSED = 5): row norms + positive-pair logits, streaming forward
  *   (row sums only), row merge + scaled transpose, all key panels (recompute + both gradient GEMMs),
  *   query finalize + scalars.

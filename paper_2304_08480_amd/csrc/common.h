@@ -48,7 +48,7 @@ bool stage_marks_on();
 
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
-size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant = LOSS_CLIP);
+size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant = LOSS_CLIP);
 int naive_run(const Problem& p);
 
 // the bf16 tile kernels can take the shape (materialized path; a rank share that is not a whole number of 256-row

@@ -242,12 +242,12 @@ __device__ __forceinline__ void row_visit(float* w, int64_t B, int head, F f) {
 // d/ds:  sum_j (P_ij - [j=label]) * W_ij.
 // variant LOSS_NTXENT: the positive is the other view's row and column `self` (the row itself) takes no part:
 // it is left out of the maximum and the sums and its gradient entry is 0.
-__global__ __launch_bounds__(256) void naive_row_softmax(float* ws, int64_t b, int64_t B, int rank, float s,
+__global__ __launch_bounds__(256) void naive_row_softmax(float* ws, int64_t b, int64_t B, int64_t pitch, int rank, float s,
                                                           float* row_ce, float* row_ds, int variant) {
   __shared__ float red[4];
   const int z = blockIdx.y;
   const int64_t i = blockIdx.x;
-  const int64_t row0 = ((int64_t)z * b + i) * B;
+  const int64_t row0 = ((int64_t)z * b + i) * pitch;
   float* w = ws + row0;
   const int64_t to_boundary = (4 - (row0 & 3)) & 3;
   const int head = (int)(to_boundary < B ? to_boundary : B);
@@ -338,15 +338,321 @@ __global__ __launch_bounds__(256) void naive_query_grad(const void* I, const voi
       [&](int64_t m, int64_t n, float a) { out[m * d + n] += cs * a; });
 }
 
+// ------------------------------------------------------------------------------------------------
+// Small calls: the same four contractions in two launches around the softmax, on 32 R x 32 R output tiles (R = 1 or 2).
+// What bounds such a call is latency: launches, and the reduction that one workgroup walks alone (a rank of B = 256,
+// N = 4, d = 512 is four 128 x 128 similarity tiles, each a chain of 32 LDS round trips).  So the tiles are small, the
+// NW waves of a workgroup split the reduction among them and load their operands from memory straight into the
+// registers of the fp32 matrix instruction (no LDS, no barrier until the partial tiles are added up at the end), and
+// the next piece's loads are in flight while one is multiplied.  Key side and query side share a launch: a tile of
+// gradient rows adds up both (the query side only where the rows are the rank's own), so every row has one writer.
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+// Four consecutive values from element idx on.  VEC: they start on a 16-byte (bf16: 8-byte) boundary.
+template <int DT, bool VEC>
+__device__ __forceinline__ f32x4 load_feat4(const void* base, int64_t idx) {
+  if constexpr (!VEC) {
+    return f32x4{load_feat<DT>(base, idx), load_feat<DT>(base, idx + 1), load_feat<DT>(base, idx + 2), load_feat<DT>(base, idx + 3)};
+  } else if constexpr (DT == DISCO_BF16) {
+    const u32x2 w = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(base) + idx);
+    return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),
+                 __uint_as_float(w[1] & 0xffff0000u)};
+  } else {
+    return *reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + idx);
+  }
+}
+
+__device__ __forceinline__ int upper_half() { return (threadIdx.x >> 5) & 1; }
+
+// acc[u][v] += sum over k in [k0, k1) of A(row block u, k) B(k, column block v), one value of each operand per lane and
+// instruction: the lanes of the lower half supply reduction indices k .. k + 3 of an 8-deep piece, the upper half
+// k + 4 .. k + 7 (any assignment does as long as both operands share it).  A.get4(u, k) / B.get4(v, k): this lane's four
+// values of row (column) block u of the piece that starts at k, the same k in all lanes; get1(u, k): the value at k.
+template <int R, class LA, class LB>
+__device__ __forceinline__ void wave_product(f32x16 (&acc)[R][R], int64_t k0, int64_t k1, const LA& A, const LB& B) {
+  constexpr int U = 4;                                  // 8-deep pieces fetched at a time
+  struct Regs { f32x4 a[U][R], b[U][R]; };
+  auto fetch = [&](Regs& g, int64_t k) {
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+#pragma unroll
+      for (int u = 0; u < R; ++u) { g.a[c][u] = A.get4(u, k + c * 8); g.b[c][u] = B.get4(u, k + c * 8); }
+  };
+  int64_t k = k0;
+  if (k + 8 * U <= k1) {
+    Regs cur;
+    fetch(cur, k);
+    for (;;) {
+      const bool more = k + 16 * U <= k1;
+      Regs nxt;
+      if (more) fetch(nxt, k + 8 * U);
+#pragma unroll
+      for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int v = 0; v < R; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(cur.a[c][u][e], cur.b[c][v][e], acc[u][v], 0, 0, 0);
+      k += 8 * U;
+      if (!more) break;
+      cur = nxt;
+    }
+  }
+  for (; k < k1; k += 8) {                              // what is left, element by element: past k1 both operands count as 0
+    float a[R][4], b[R][4];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t kk = k + upper_half() * 4 + e, kc = kk < k1 ? kk : k1 - 1;
+        const float x = A.get1(u, kc), y = B.get1(u, kc);
+        a[u][e] = kk < k1 ? x : 0.f;
+        b[u][e] = kk < k1 ? y : 0.f;
+      }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int v = 0; v < R; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][e], b[v][e], acc[u][v], 0, 0, 0);
+  }
+}
+
+// Adds up the waves' partial tiles in wave order and hands every entry to out(row, column, value), rows and columns
+// relative to the tile; 32 consecutive columns per half-wave.
+template <int R, int NW, class FOut>
+__device__ __forceinline__ void join_waves(const f32x16 (&acc)[R][R], float (*red)[R * R * 16][64], FOut out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+#pragma unroll
+    for (int v = 0; v < R; ++v)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[wave][(u * R + v) * 16 + r][lane] = acc[u][v][r];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < R * R * 16 / NW; ++q) {
+    const int idx = q * NW + wave, uv = idx >> 4, r = idx & 15;
+    float s = red[0][idx][lane];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[w][idx][lane];
+    out((uv / R) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), (uv % R) * 32 + (lane & 31), s);
+  }
+}
+
+template <int R>
+__device__ __forceinline__ void clear(f32x16 (&acc)[R][R]) {
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+#pragma unroll
+    for (int v = 0; v < R; ++v)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[u][v][r] = 0.f;
+}
+
+// This wave's part [k0, k1) of a reduction of length K (8-deep pieces dealt in runs).
+template <int NW>
+__device__ __forceinline__ void wave_range(int64_t K, int64_t& k0, int64_t& k1) {
+  const int64_t per = ((K + 7) / 8 + NW - 1) / NW * 8;
+  k0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * per;
+  k1 = k0 + per < K ? k0 + per : K;
+}
+
+// Operand whose reduction index is contiguous: element (row, k) at base[row ld + k], one row per lane and block.
+template <int DT, bool VEC, int R>
+struct AlongK {
+  const void* base;
+  int64_t off[R];
+  __device__ __forceinline__ AlongK(const void* p, int64_t ld, int64_t row0, int64_t rows) : base(p) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int64_t row = row0 + u * 32 + (threadIdx.x & 31);
+      off[u] = (row < rows ? row : rows - 1) * ld;       // a row past the end repeats the last; its results are not stored
+    }
+  }
+  __device__ __forceinline__ f32x4 get4(int u, int64_t k) const { return load_feat4<DT, VEC>(base, off[u] + upper_half() * 4 + k); }
+  __device__ __forceinline__ float get1(int u, int64_t k) const { return load_feat<DT>(base, off[u] + k); }
+};
+// Operand whose row (column) index is contiguous: element (k, col) at base[k ld + col].
+template <int DT, int R>
+struct AcrossK {
+  const void* base;
+  int64_t ld, col[R], up;
+  __device__ __forceinline__ AcrossK(const void* p, int64_t pitch, int64_t col0, int64_t cols) : base(p), ld(pitch), up(upper_half() * 4 * pitch) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int64_t c = col0 + u * 32 + (threadIdx.x & 31);
+      col[u] = c < cols ? c : cols - 1;
+    }
+  }
+  __device__ __forceinline__ float get1(int u, int64_t k) const { return load_feat<DT>(base, k * ld + col[u]); }
+  __device__ __forceinline__ f32x4 get4(int u, int64_t k) const {
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = load_feat<DT>(base, (k + e) * ld + (col[u] + up));
+    return v;
+  }
+};
+// Rows of the gradient matrix of the rank's own rows, by global row: rows of other ranks that share the tile count as 0.
+// VEC: the pitch is a multiple of 4 floats.
+template <bool VEC, int R>
+struct OwnRows {
+  AlongK<DISCO_F32, VEC, R> rows;
+  bool own[R];
+  __device__ __forceinline__ OwnRows(const float* W, int64_t pitch, int64_t local0, int64_t b)
+      : rows(W, pitch, 0, 1) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int64_t i = local0 + u * 32 + (threadIdx.x & 31);
+      own[u] = i >= 0 && i < b;
+      rows.off[u] = (own[u] ? i : 0) * pitch;
+    }
+  }
+  __device__ __forceinline__ f32x4 get4(int u, int64_t k) const {
+    const f32x4 v = rows.get4(u, k);
+    return own[u] ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ float get1(int u, int64_t k) const { const float v = rows.get1(u, k); return own[u] ? v : 0.f; }
+};
+
+struct SmallShape {
+  int64_t b, B, d, pitch;        // pitch: floats between the rows of a block's matrix
+  int rank, nb, variant, accumulate;
+};
+__device__ __forceinline__ const void* feat_rows(const void* M, int64_t row, int64_t d, int dt) {
+  return static_cast<const char*>(M) + (size_t)(row * d) * (dt == DISCO_BF16 ? 2 : 4);
+}
+
+template <int DT, bool VEC, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void small_similarity(const void* I, const void* T, SmallShape f, float* ws) {
+  __shared__ float red[NW][R * R * 16][64];
+  const int z = blockIdx.z;
+  const int64_t m0 = (int64_t)blockIdx.y * 32 * R, n0 = (int64_t)blockIdx.x * 32 * R;
+  const AlongK<DT, VEC, R> A(feat_rows(z == 0 ? I : T, f.rank * f.b, f.d, DT), f.d, m0, f.b), Bm(z == 0 ? T : I, f.d, n0, f.B);
+  f32x16 acc[R][R];
+  clear(acc);
+  int64_t k0, k1;
+  wave_range<NW>(f.d, k0, k1);
+  wave_product<R>(acc, k0, k1, A, Bm);
+  float* W = ws + (size_t)z * f.b * f.pitch;
+  join_waves<R, NW>(acc, red, [&](int r, int c, float v) {
+    if (m0 + r < f.b && n0 + c < f.B) W[(m0 + r) * f.pitch + n0 + c] = v;
+  });
+}
+
+// Workgroup 0 adds up loss and d/ds; the others take gradient tiles (row tile, column tile, block z = whose key side):
+// rows [m0, m0 + 32 R) of gT (z = 0) or gI (z = 1), key side of block z plus, in the rank's own rows, the query side of
+// the other block (of the same one for the two-view loss).  The row tiles start at the rank's own rows, whose
+// reduction is the longest.
+template <int DT, bool WVEC, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void small_grads(const void* I, const void* T, SmallShape f, const float* ws, float cs, float c,
+                                                       const float* row_ce, const float* row_ds, float* loss, float* gs, float* gI, float* gT) {
+  __shared__ float red[NW][R * R * 16][64];
+  if (blockIdx.x == 0) {
+    float a = 0.f, g = 0.f;
+    for (int64_t i = threadIdx.x; i < f.nb * f.b; i += 64 * NW) { a += row_ce[i]; g += row_ds[i]; }
+    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); g += __shfl_xor(g, o); }
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6][0][0] = a; red[threadIdx.x >> 6][0][1] = g; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < NW; ++w) { a += red[w][0][0]; g += red[w][0][1]; }
+      *loss = (f.accumulate ? *loss : 0.f) + c * a;
+      *gs = (f.accumulate ? *gs : 0.f) + c * g;
+    }
+    return;
+  }
+  const int nM = (int)((f.B + 32 * R - 1) / (32 * R)), nN = (int)((f.d + 32 * R - 1) / (32 * R));
+  const int w = blockIdx.x - 1, r0 = f.rank * (int)f.b;
+  // tiles of all blocks in order of their distance from the own rows
+  const int mt_rel = w / (nN * f.nb), rest = w - mt_rel * nN * f.nb, z = rest / nN;
+  const int mt = (mt_rel + r0 / (32 * R)) % nM;
+  const int64_t m0 = (int64_t)mt * 32 * R, n0 = (int64_t)(rest % nN) * 32 * R;
+  f32x16 acc[R][R];
+  clear(acc);
+  int64_t k0, k1;
+  wave_range<NW>(f.b, k0, k1);
+  wave_product<R>(acc, k0, k1, AcrossK<DISCO_F32, R>(ws + (size_t)z * f.b * f.pitch, f.pitch, m0, f.B),
+                  AcrossK<DT, R>(feat_rows(z == 0 ? I : T, r0, f.d, DT), f.d, n0, f.d));
+  if (m0 < r0 + f.b && m0 + 32 * R > r0) {
+    const int zq = f.nb == 1 ? 0 : 1 - z;
+    wave_range<NW>(f.B, k0, k1);
+    wave_product<R>(acc, k0, k1, OwnRows<WVEC, R>(ws + (size_t)zq * f.b * f.pitch, f.pitch, m0 - r0, f.b),
+                    AcrossK<DT, R>(zq == 0 ? T : I, f.d, n0, f.d));
+  }
+  float* out = z == 0 ? gT : gI;
+  join_waves<R, NW>(acc, red, [&](int r, int col, float v) {
+    if (m0 + r >= f.B || n0 + col >= f.d) return;
+    float* p = out + (m0 + r) * f.d + n0 + col;
+    *p = (f.accumulate ? *p : 0.f) + cs * v;
+  });
+}
+
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 }  // namespace
 
-size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) {
-  (void)d;
+namespace {
+
+// Which calls the small kernels take, by multiply-adds per contraction.  (Old and new kernels in us, d = 512: fp32 B = 256,
+// N = 4: 96 -> 18; 2048, 8: 210 -> 83; 8192, 8: 798 -> 644; 16384, 8: 2940 -> 2469; 32768, 8: 9000 -> 9815.  bf16
+// features: B = 2048, d = 200, N = 16: 276 -> 73; 4096, 500, 8: 826 -> 289; 8192, 1000, 8: 1881 -> 2107.)
+bool small_call(int64_t b, int64_t B, int64_t d, int dtype) {
+  return (double)b * B * d <= (dtype == DISCO_BF16 ? 3e9 : 2e10);
+}
+
+size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
+
+// Floats between the rows of a block's matrix: whole 16-byte pieces for the small kernels, except where that alone would
+// take a call out of the static scratch array.
+int64_t row_pitch(int64_t b, int64_t B, int64_t d, int dtype, size_t nb) {
+  const int64_t padded = (B + 3) / 4 * 4;
+  const size_t rows = 2 * align_up(nb * b * sizeof(float));
+  if (!small_call(b, B, d, dtype)) return B;
+  return matrix_bytes(nb, b, padded) + rows > DISCO_STATIC_SCRATCH_BYTES && matrix_bytes(nb, b, B) + rows <= DISCO_STATIC_SCRATCH_BYTES ? B : padded;
+}
+
+template <int DT>
+void small_run(const Problem& p, float* W, float* row_ce, float* row_ds, float c) {
+  SmallShape f;
+  f.b = p.b; f.B = p.B; f.d = p.d; f.nb = loss_blocks(p.variant);
+  f.pitch = row_pitch(p.b, p.B, p.d, DT, f.nb);
+  f.rank = p.rank; f.variant = p.variant; f.accumulate = p.accumulate;
+  const unsigned nb = (unsigned)f.nb;
+  // 16-byte pieces of a feature row (8-byte ones in bf16)
+  const uintptr_t align = reinterpret_cast<uintptr_t>(p.I) | reinterpret_cast<uintptr_t>(p.T);
+  const bool vec = p.d % 4 == 0 && align % (DT == DISCO_BF16 ? 8 : 16) == 0;
+  // 64 x 64 tiles (four waves) once they give every compute unit one, else 32 x 32 (eight waves)
+  auto big = [&](int64_t rows, int64_t cols) { return (int64_t)nb * cdiv(rows, 64) * cdiv(cols, 64) >= 256; };
+  auto sim = [&](auto kernel, int tile, int waves) {
+    kernel<<<dim3(cdiv(p.B, tile), cdiv(p.b, tile), nb), 64 * waves, 0, p.stream>>>(p.I, p.T, f, W);
+  };
+  auto grads = [&](auto kernel, int tile, int waves) {
+    kernel<<<dim3(1 + nb * cdiv(p.B, tile) * cdiv(p.d, tile)), 64 * waves, 0, p.stream>>>(p.I, p.T, f, W, c * p.s, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT);
+  };
+  stage_mark(p.stream, 0);
+  if (big(p.b, p.B)) { if (vec) sim(small_similarity<DT, true, 2, 4>, 64, 4); else sim(small_similarity<DT, false, 2, 4>, 64, 4); }
+  else { if (vec) sim(small_similarity<DT, true, 1, 8>, 32, 8); else sim(small_similarity<DT, false, 1, 8>, 32, 8); }
+  stage_mark(p.stream, 1);
+  naive_row_softmax<<<dim3((unsigned)p.b, nb), 256, 0, p.stream>>>(W, p.b, p.B, f.pitch, p.rank, p.s, row_ce, row_ds, p.variant);
+  stage_mark(p.stream, 2);
+  stage_mark(p.stream, 3);
+  const bool wvec = f.pitch % 4 == 0;
+  if (big(p.B, p.d)) { if (wvec) grads(small_grads<DT, true, 2, 4>, 64, 4); else grads(small_grads<DT, false, 2, 4>, 64, 4); }
+  else { if (wvec) grads(small_grads<DT, true, 1, 8>, 32, 8); else grads(small_grads<DT, false, 1, 8>, 32, 8); }
+  stage_mark(p.stream, 4);
+  stage_mark(p.stream, 5);
+}
+
+}  // namespace
+
+size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant) {
   int64_t b = B / N;
   const size_t nb = (size_t)loss_blocks(variant);
-  return align_up(nb * b * B * sizeof(float)) + 2 * align_up(nb * b * sizeof(float));
+  return matrix_bytes(nb, b, row_pitch(b, B, d, dtype, nb)) + 2 * align_up(nb * b * sizeof(float));
 }
 
 int naive_run(const Problem& p) {
@@ -354,18 +660,23 @@ int naive_run(const Problem& p) {
   float* W = static_cast<float*>(p.ws);
   char* base = static_cast<char*>(p.ws);
   const unsigned nb = (unsigned)loss_blocks(p.variant);
-  float* row_ce = reinterpret_cast<float*>(base + align_up((size_t)nb * b * B * sizeof(float)));
+  float* row_ce = reinterpret_cast<float*>(base + matrix_bytes(nb, b, row_pitch(b, B, d, p.dtype, nb)));
   float* row_ds = reinterpret_cast<float*>(reinterpret_cast<char*>(row_ce) + align_up((size_t)nb * b * sizeof(float)));
   const float c = loss_norm(B, p.variant);
   const float cs = c * p.s;
 
-  stage_mark(p.stream, 0);
   const bool bf = p.dtype == DISCO_BF16;
+  if (small_call(b, B, d, p.dtype)) {
+    if (bf) small_run<DISCO_BF16>(p, W, row_ce, row_ds, c);
+    else small_run<DISCO_F32>(p, W, row_ce, row_ds, c);
+    return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
+  }
+  stage_mark(p.stream, 0);
   const dim3 sim_grid(cdiv(B, TS), cdiv(b, TS), nb);
   if (bf) naive_similarity<DISCO_BF16><<<sim_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W);
   else naive_similarity<DISCO_F32><<<sim_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W);
   stage_mark(p.stream, 1);
-  naive_row_softmax<<<dim3((unsigned)b, nb), 256, 0, p.stream>>>(W, b, B, p.rank, p.s, row_ce, row_ds, p.variant);
+  naive_row_softmax<<<dim3((unsigned)b, nb), 256, 0, p.stream>>>(W, b, B, B, p.rank, p.s, row_ce, row_ds, p.variant);
   stage_mark(p.stream, 2);
   naive_scalars<<<1, 256, 0, p.stream>>>(row_ce, row_ds, (int64_t)nb * b, c, p.accumulate, p.loss, p.gs);
   stage_mark(p.stream, 3);
