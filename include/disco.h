@@ -65,10 +65,11 @@ typedef enum {
 typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
 
 /*
- * DISCO_PATH_NAIVE        fp32 arithmetic (fp32 matrix instruction for fp32 features, vector-ALU FMA for
- *                         part of the bf16 case), fp32 logit blocks kept in the workspace (2*b*B*4
- *                         bytes, rows rounded up to whole 16-byte pieces: the paper's 2B^2/N memory model,
-                         Sec. 4.1).  Any B, d, N; either dtype.
+ * DISCO_PATH_NAIVE        fp32 arithmetic, either on the fp32 matrix instruction or (large calls) on the bf16 one with
+ *                         every fp32 operand split exactly into three bf16 planes.  Any B, d, N; either dtype.  Asked
+ *                         for by name it stays within the fp32 logit blocks' memory (2*b*B*4 bytes, rows rounded up
+ *                         to whole 16-byte pieces: the paper's 2B^2/N memory model, Sec. 4.1); where AUTO resolves to
+ *                         it, a large call takes up to 8 GiB where the blocks need less, and is faster.
  * DISCO_PATH_MATERIALIZED bf16 MFMA tiles.  The logit blocks are computed once; the un-normalised
  *                         softmax numerators are kept in bf16 (2*b*B*2 bytes) and feed the two
  *                         gradient contractions (12*b*B*d flop).  Needs dtype bf16, d % 64 == 0,
@@ -93,8 +94,8 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  * DISCO_PATH_AUTO         the fastest path that supports the arguments: SYMMETRIC (N = 1) or
  *                         MATERIALIZED when their shape limits hold, else NAIVE.  Feature widths that are not
  *                         a multiple of 64, fp32 inputs, and ragged shares of blocks smaller than
- *                         b*B = 2^18 logits (launch-bound either way) therefore run on the vector ALUs, for
- *                         large shapes an order of magnitude slower; disco_resolve_path tells which path a
+ *                         b*B = 2^18 logits (launch-bound either way) therefore run in fp32 arithmetic, for
+ *                         large shapes three to six times slower; disco_resolve_path tells which path a
  *                         call takes.
  */
 typedef enum {
@@ -171,7 +172,8 @@ DISCO_API int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t r
  * process ends).  The call allocates and frees nothing; on its first use on a device it looks the array's
  * address up once (not a stream operation: make one call outside any capture first, as for the MFMA paths).
  * Returns DISCO_ERR_WORKSPACE, before any launch, when the arguments need more than the array holds
- * (disco_workspace_bytes(...) > disco_static_scratch_bytes()), DISCO_ERR_HIP when the address lookup fails.
+ * (disco_workspace_bytes(...) of the path that the call resolves to > disco_static_scratch_bytes()), DISCO_ERR_HIP when
+ * the address lookup fails.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different streams or
  * threads) race on it and must be serialised by the caller; nothing in it needs to start at zero, each call
  * overwrites what it reads.
@@ -196,7 +198,7 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
  *   4 key-side gradient GEMM             5 query-side split GEMM              6 query finalize + scalars
  * (Stages 4 and 5 are one launch while stage timing is off, two while it is on.)
  * Stages of DISCO_PATH_NAIVE (DISCO_STAGES_NAIVE = 5): similarity, row softmax, scalars, key grad, query grad.  (Calls whose
- *   two gradient sides share a launch, with the scalars in it, have all three in the fourth interval.)
+ *   two gradient sides share a launch have both in the fourth interval; the scalars are in that one or in the last.)
  * Stages of DISCO_PATH_FUSED (DISCO_STAGES_FUSED = 5): row norms + positive-pair logits, streaming forward
  *   (row sums only), row merge + scaled transpose, all key panels (recompute + both gradient GEMMs),
  *   query finalize + scalars.

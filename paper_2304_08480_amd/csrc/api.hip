@@ -72,8 +72,9 @@ int resolve(int64_t B, int64_t d, int32_t N, int dtype, int path, int variant = 
   }
 }
 
-size_t workspace_need(int r, int64_t B, int64_t d, int32_t N, int dtype, int variant) {
-  if (r == DISCO_PATH_NAIVE) return naive_workspace_bytes(B, d, N, dtype, variant);
+// path: what the caller asked for, r: what it resolves to
+size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant) {
+  if (r == DISCO_PATH_NAIVE) return naive_workspace_bytes(B, d, N, dtype, variant, path == DISCO_PATH_NAIVE);
   // (the bf16 paths lay their workspace out for two blocks; the one-block loss uses the first half of each part)
   if (r == DISCO_PATH_MATERIALIZED) return mfma_stored_workspace_bytes(B, d, N, variant);
   if (r == DISCO_PATH_FUSED) return mfma_fused_workspace_bytes(B, d, N, variant);
@@ -89,7 +90,7 @@ extern "C" int disco_resolve_path(int64_t B, int64_t d, int32_t N, int dtype, in
 
 extern "C" size_t disco_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path) {
   const int r = resolve(B, d, N, dtype, path);
-  return r > 0 ? workspace_need(r, B, d, N, dtype, LOSS_CLIP) : 0;
+  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_CLIP) : 0;
 }
 
 extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N,
@@ -99,7 +100,7 @@ extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64
   int r = resolve(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(r, B, d, N, dtype, LOSS_CLIP);
+  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_CLIP);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(I) && aligned16(T) && aligned16(gI) && aligned16(gT))) return DISCO_ERR_UNSUPPORTED;
@@ -108,6 +109,7 @@ extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64
   p.variant = LOSS_CLIP;
   p.I = I; p.T = T; p.B = B; p.d = d; p.rank = rank; p.N = N; p.b = B / N; p.s = s; p.dtype = dtype;
   p.accumulate = accumulate ? 1 : 0;
+  p.lean = path == DISCO_PATH_NAIVE;
   p.loss = loss; p.gI = gI; p.gT = gT; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
@@ -130,7 +132,7 @@ extern "C" int ntxent_resolve_path(int64_t B, int64_t d, int32_t N, int dtype, i
 
 extern "C" size_t ntxent_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path) {
   const int r = resolve(B, d, N, dtype, path, LOSS_NTXENT);
-  return r > 0 ? workspace_need(r, B, d, N, dtype, LOSS_NTXENT) : 0;
+  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT) : 0;
 }
 
 extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t rank, int32_t N, float s, int dtype,
@@ -140,7 +142,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   const int r = resolve(B, d, N, dtype, path, LOSS_NTXENT);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(r, B, d, N, dtype, LOSS_NTXENT);
+  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(Z) && aligned16(gZ))) return DISCO_ERR_UNSUPPORTED;
@@ -148,6 +150,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   p.variant = LOSS_NTXENT;
   p.I = Z; p.T = Z; p.B = B; p.d = d; p.rank = rank; p.N = N; p.b = B / N; p.s = s; p.dtype = dtype;
   p.accumulate = accumulate ? 1 : 0;
+  p.lean = path == DISCO_PATH_NAIVE;
   p.loss = loss; p.gI = gZ; p.gT = gZ; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);

@@ -19,6 +19,7 @@ struct Problem {
   float s;
   int dtype;
   int accumulate;
+  bool lean;          // fp32 path: see naive_workspace_bytes
   float* loss;
   float* gI;
   float* gT;
@@ -48,8 +49,16 @@ bool stage_marks_on();
 
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
-size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant = LOSS_CLIP);
+// The fp32 path.  lean: within the memory of its fp32 logit blocks (what DISCO_PATH_NAIVE by name asks for).
+size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean);
 int naive_run(const Problem& p);
+
+// Its large calls (split_kernels.hip): shapes they take, gradients they can store, their estimated time and workspace with the
+// workspace kept within `limit` (*bytes = 0: impossible), and the call in that plan.
+bool split_supported(int64_t B, int64_t b);
+bool split_aligned(const Problem& p);
+double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, size_t* bytes);
+int split_run(const Problem& p, size_t limit);
 
 // the bf16 tile kernels can take the shape (materialized path; a rank share that is not a whole number of 256-row
 // tiles is zero-padded in the workspace) / the share is whole tiles (what the fused and symmetric paths need too)

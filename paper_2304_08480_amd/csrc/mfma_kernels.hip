@@ -46,28 +46,6 @@ constexpr int LOGIT_SMEM_BYTES = E_TILE_BYTES<T> > Cfg<T>::SMEM_BYTES ? E_TILE_B
 template <int T>
 constexpr int GEMM_SMEM_BYTES = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SMEM_BYTES<T> : Cfg<T>::SMEM_BYTES;
 
-// Workgroup id -> tile, keeping the workgroups that share an XCD's L2 on neighbouring tiles.
-// Workgroups are dealt round-robin to the 8 XCDs; XCD x takes the x-th contiguous eighth of the
-// (padded) tile list.  Returns false for padding.
-__device__ __forceinline__ bool xcd_linear(int w, int total, int& lin) {
-  const int chunk = (total + 7) / 8;
-  lin = (w & 7) * chunk + (w >> 3);
-  return (w >> 3) < chunk && lin < total;
-}
-
-// Tile (it, jt) at position lin of the walk over super-blocks of sbi query tiles x sbj key tiles: bands of sbj key
-// tiles one after the other, inside a band the super-blocks along the query tiles, inside a super-block the query
-// tile runs fastest.  The last super-block of either direction may be partial.
-__device__ __forceinline__ void superblock_tile(int lin, int nI, int nJ, int sbi, int sbj, int& it, int& jt) {
-  const int band = sbj * nI;
-  const int jb = lin / band, r = lin - jb * band;
-  const int hj = nJ - jb * sbj < sbj ? nJ - jb * sbj : sbj;
-  const int ib = r / (sbi * hj), r2 = r - ib * sbi * hj;
-  const int wi = nI - ib * sbi < sbi ? nI - ib * sbi : sbi;
-  it = ib * sbi + r2 % wi;
-  jt = jb * sbj + r2 / wi;
-}
-
 // ------------------------------------------------------------------------------------------------
 struct BlockPtrs {
   const uint16_t* X;     // b x d, the rank's rows (zero rows past the real ones)
@@ -1186,19 +1164,6 @@ void round_shape(Plan& pl, bool fused) {
   pl.nMq = (int)(pl.b / pl.tg);
   pl.nMk = (int)(pl.W / pl.tg);
   pl.nN = (int)((pl.d + pl.tg - 1) / pl.tg);
-}
-
-// Time estimates in microseconds that make_plan compares, for a chip of 256 compute units.  What they rest on (measured):
-// a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
-// every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
-// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.
-constexpr double CHIP_CUS = 256.0;
-constexpr double BYTES_PER_US = 4.5e6;
-
-double step_us(int T, double wgs) {
-  const double slots = T == 256 ? CHIP_CUS : 2 * CHIP_CUS, few = T == 256 ? 1.15 : 0.57, full = T == 256 ? 1.7 : 1.03;
-  const double f = (wgs - slots / 4) / (slots * 3 / 4);
-  return few + (full - few) * (f < 0 ? 0 : f > 1 ? 1 : f);
 }
 
 double logits_us(const Plan& pl, int nblk) {

@@ -85,6 +85,19 @@ struct Cfg {
 template <int NFA>
 using Acc = f32x16[NFA][2];
 
+// Plane products of an operand pair of PA and PB planes (PS of kloop), smallest first.  Planes 0, 1, 2 of a value carry its
+// leading, middle and last 8 significand bits, so with three planes on both sides the products left out (1 x 2, 2 x 1 and
+// 2 x 2) are below 2^-26 of the value's own product, under the rounding of the fp32 sum.
+template <int PA, int PB, bool SWEEPS_ = false>
+struct Planes {
+  static constexpr bool SWEEPS = SWEEPS_;
+  static_assert((PA == 1 && PB == 1) || (PA == 3 && (PB == 1 || PB == 3)));
+  static constexpr int N = PA == 1 ? 1 : PB == 1 ? 3 : 6;
+  // two bits per product
+  static constexpr uint32_t A = PA == 1 ? 0u : PB == 1 ? (2u | 1u << 2 | 0u << 4) : (2u | 0u << 2 | 1u << 4 | 1u << 6 | 0u << 8 | 0u << 10);
+  static constexpr uint32_t B = PB == 1 ? 0u : (0u | 2u << 2 | 1u << 4 | 0u << 6 | 1u << 8 | 0u << 10);
+};
+
 enum { FMT_K = 0, FMT_R = 1, FMT_KA = 2, FMT_RA = 3 };
 // bytes between the LDS destinations of a wave's consecutive load instructions (FMT_KA: the wave loads the 8 column
 // pieces of its row group, which lie 16 T bytes apart; else its instructions fill 8 KiB contiguously)
@@ -296,6 +309,12 @@ __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u 
 // So an A load has six sub-steps to land and a B load four.  Loads past the end are clamped to the last
 // K-step (redundant, never out of range, into a unit nobody reads again).
 // READS_FIRST: issue a sub-step's LDS reads ahead of its MFMAs (otherwise the compiler places them).
+//
+// PS: the operands may be kept as several bf16 planes (a value is the sum of its planes), `plane_a` / `plane_b` elements
+// apart, and PS lists the plane products that make up one K-step's worth of the reduction: the loop then runs PS::N
+// times the K-steps: the products of one 64-deep piece one after the other, so that each plane's piece comes from L2 when it
+// is read again, or (PS::SWEEPS) one product over the whole reduction after the other, so that the smallest products are
+// added up while the sum is small and only the last sweep rounds at the size of the result.
 template <int FMT>
 __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
   return FMT == FMT_K ? BK : FMT == FMT_KA ? 4096 : FMT == FMT_R ? (int64_t)BK * ld : ld;
@@ -304,14 +323,30 @@ __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
 // WRITE_FIRST: the first K-step is peeled off the loop and writes the accumulators (acc = product, acc need not be
 // initialised); else every K-step adds to them (acc += product).  Peeling gains 2-5 % on the gradient GEMMs; in the
 // logit kernel it costs the epilogue registers it does not have.
-template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST>
+template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS>
 __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp, int64_t ldb,
-                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b) {
+                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b) {
   constexpr int NFA = Cfg<T>::NFA, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t stepA = kstep_elems<FA>(lda);
   const int64_t stepB = kstep_elems<FB>(ldb);
   const int last = ktiles - 1;
+  // operand tiles of step kt: with several planes, product q of a 64-deep piece
+  const int pieces = ktiles / PS::N;
+  const uint32_t inv = 0xffffffffu / (uint32_t)pieces + 1u;      // (kt pieces < 2^32: the high half of kt inv is the quotient)
+  struct Step { int piece, q; };
+  auto step_of = [&](int kt) {
+    const int x = !PS::SWEEPS ? kt / PS::N : pieces == 1 ? kt : (int)__umulhi((uint32_t)kt, inv), y = kt - x * (PS::SWEEPS ? pieces : PS::N);
+    return PS::SWEEPS ? Step{y, x} : Step{x, y};
+  };
+  auto tile_a = [&](int kt) {
+    if constexpr (PS::N == 1) return A + kt * stepA;
+    else { const auto [piece, q] = step_of(kt); return A + piece * stepA + (PS::A >> (2 * q) & 3) * plane_a; }
+  };
+  auto tile_b = [&](int kt) {
+    if constexpr (PS::N == 1) return Bp + kt * stepB;
+    else { const auto [piece, q] = step_of(kt); return Bp + piece * stepB + (PS::B >> (2 * q) & 3) * plane_b; }
+  };
   Operand<T, FA, NFA> oa;
   Operand<T, FB, 2> ob;
   oa.init(lda, wave % WN, lane, (wave / WN) * Cfg<T>::WTM);
@@ -319,11 +354,11 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;   // LDS byte address
   const int k1 = last < 1 ? last : 1;
   if (GROUP == 0) {
-    oa.load(A, smem);
-    oa.load(A + k1 * stepA, smem + 2 * UNIT_BYTES);
+    oa.load(tile_a(0), smem);
+    oa.load(tile_a(k1), smem + 2 * UNIT_BYTES);
   } else {
-    ob.load(Bp, smem + UNIT_BYTES);
-    ob.load(Bp + k1 * stepB, smem + 3 * UNIT_BYTES);
+    ob.load(tile_b(0), smem + UNIT_BYTES);
+    ob.load(tile_b(k1), smem + 3 * UNIT_BYTES);
   }
   wait_vmcnt<NLD>();
   lds_barrier();
@@ -348,7 +383,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     /* sub-step 1 */                                                                                                       \
     read_frags<2>(f0, oa, ob, ta, tb);                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 0) mfma_block_loads(f1, acc, oa, A + kload * stepA, smem + lA * UNIT_BYTES);                              \
+    if (GROUP == 0) mfma_block_loads(f1, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                                  \
     else mfma_block(f1, acc);                                                                                              \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(f0);                                                                                                        \
@@ -364,7 +399,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     /* sub-step 3 */                                                                                                       \
     read_frags<0>(f0, oa, ob, smem_addr + (uint32_t)(nA * UNIT_BYTES), smem_addr + (uint32_t)(nB * UNIT_BYTES));   \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 1) mfma_block_loads(f1, acc, ob, Bp + kload * stepB, smem + rA * UNIT_BYTES);                             \
+    if (GROUP == 1) mfma_block_loads(f1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                                  \
     else mfma_block(f1, acc);                                                                                              \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(f0);                                                                                                        \
@@ -391,16 +426,17 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
 // acc[bm][bn] (+)= A_tile(T x K) * B_tile(T x K)^T for this wave's T/2 x 64 piece (WRITE_FIRST: =, see kloop).
 //   FA / FB : tile format of the A / B operand (FMT_K: element (r,k) at base[r*ld + k]; FMT_R: at base[k*ld + r];
 //             FMT_KA / FMT_RA: the same for storage in 16-byte atoms, see the top of this file).
-//   A, Bp   : element (row 0, k 0) of the workgroup's operand tiles; ktiles = K / 64 >= 1.
+//   A, Bp   : element (row 0, k 0) of the workgroup's operand tiles; ktiles = PS::N K / 64 >= 1.
 //   smem    : Cfg<T>::SMEM_BYTES of LDS, 16-byte aligned; on return no load is in flight and every wave has passed
 //             a barrier, so the caller may reuse it at once.
 //   nvalid_b: rows of the B tile that exist in memory (multiple of 8, <= T); the output columns from
 //             nvalid_b on are then meaningless and must not be stored.
-template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false>
+template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false, class PS = Planes<1, 1>>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp,
-                                         int64_t ldb, int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b = T) {
-  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
-  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b);
+                                         int64_t ldb, int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b = T,
+                                         int64_t plane_a = 0, int64_t plane_b = 0) {
+  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST, PS>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b);
+  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST, PS>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b);
 }
 
 // Writes a workgroup's T x T fp32 accumulator tile to row-major global memory through LDS, so that
@@ -474,6 +510,41 @@ __device__ __forceinline__ void store_tile_f32(Acc<Cfg<T>::NFA>& acc, char* smem
                                                int nrows = T) {
   if (nrows >= T) store_tile_f32_rows<T, ACCUMULATE, false>(acc, smem, out, ld, scale, ncols, nrows);
   else store_tile_f32_rows<T, ACCUMULATE, true>(acc, smem, out, ld, scale, ncols, nrows);
+}
+
+// Workgroup id -> tile, keeping the workgroups that share an XCD's L2 on neighbouring tiles.
+// Workgroups are dealt round-robin to the 8 XCDs; XCD x takes the x-th contiguous eighth of the
+// (padded) tile list.  Returns false for padding.
+__device__ __forceinline__ bool xcd_linear(int w, int total, int& lin) {
+  const int chunk = (total + 7) / 8;
+  lin = (w & 7) * chunk + (w >> 3);
+  return (w >> 3) < chunk && lin < total;
+}
+
+// Tile (it, jt) at position lin of the walk over super-blocks of sbi query tiles x sbj key tiles: bands of sbj key
+// tiles one after the other, inside a band the super-blocks along the query tiles, inside a super-block the query
+// tile runs fastest.  The last super-block of either direction may be partial.
+__device__ __forceinline__ void superblock_tile(int lin, int nI, int nJ, int sbi, int sbj, int& it, int& jt) {
+  const int band = sbj * nI;
+  const int jb = lin / band, r = lin - jb * band;
+  const int hj = nJ - jb * sbj < sbj ? nJ - jb * sbj : sbj;
+  const int ib = r / (sbi * hj), r2 = r - ib * sbi * hj;
+  const int wi = nI - ib * sbi < sbi ? nI - ib * sbi : sbi;
+  it = ib * sbi + r2 % wi;
+  jt = jb * sbj + r2 / wi;
+}
+
+// Time estimates in microseconds that the plans compare, for a chip of 256 compute units.  What they rest on (measured):
+// a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
+// every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
+// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.
+constexpr double CHIP_CUS = 256.0;
+constexpr double BYTES_PER_US = 4.5e6;
+
+inline double step_us(int T, double wgs) {
+  const double slots = T == 256 ? CHIP_CUS : 2 * CHIP_CUS, few = T == 256 ? 1.15 : 0.57, full = T == 256 ? 1.7 : 1.03;
+  const double f = (wgs - slots / 4) / (slots * 3 / 4);
+  return few + (full - few) * (f < 0 ? 0 : f > 1 ? 1 : f);
 }
 
 }  // namespace tile

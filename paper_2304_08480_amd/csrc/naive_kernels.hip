@@ -19,184 +19,6 @@ __device__ __forceinline__ float load_feat(const void* base, int64_t idx) {
   return static_cast<const float*>(base)[idx];
 }
 
-// Generic tiled product  out(m,n) = sum_k A(m,k) * Bm(k,n)  for one TM x TN output tile (TM, TN: 64 or 128), on the
-// vector ALUs.  A and Bm are accessor functors (any layout, any dtype); entries outside the ranges count as 0.
-// 256 threads as 16 x 16; a thread owns (TM/16) x (TN/16) outputs in pieces of 4: rows ty*4 + u (+ 64 for the second
-// piece), columns tx*4 + v (+ 64), so that its LDS reads are 16-byte vectors, a wave's column reads are 256
-// contiguous bytes and its row reads 4 broadcast pieces: one LDS read per 8 (128 x 128: 16) multiply-adds.
-// TK: reduction step.  AK / BK: the reduction index is the contiguous one in the memory behind A(m, k) / Bm(k, n);
-// the fill loops run consecutive threads along it, otherwise along m / n, so that the loads coalesce either way.
-template <int TM, int TN, int TK, bool AK, bool BK, class FA, class FB, class FOut>
-__device__ __forceinline__ void tile_product_valu(int64_t M, int64_t Nn, int64_t K, int64_t m0, int64_t n0,
-                                                  FA A, FB Bm, FOut out) {
-  typedef __attribute__((ext_vector_type(4))) float f32x4;
-  constexpr int PM = TM / 64, PN = TN / 64;             // pieces of 4 rows / columns per thread
-  __shared__ __attribute__((aligned(16))) float As[TK][TM + 4];
-  __shared__ __attribute__((aligned(16))) float Bs[TK][TN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  float acc[PM * 4][PN * 4] = {};
-  for (int64_t k0 = 0; k0 < K; k0 += TK) {
-    for (int e = tid; e < TM * TK; e += 256) {
-      const int kk = AK ? e % TK : e / TM, mm = AK ? e / TK : e % TM;
-      const int64_t m = m0 + mm, k = k0 + kk;
-      As[kk][mm] = (m < M && k < K) ? A(m, k) : 0.f;
-    }
-    for (int e = tid; e < TK * TN; e += 256) {
-      const int kk = BK ? e % TK : e / TN, nn = BK ? e / TK : e % TN;
-      const int64_t n = n0 + nn, k = k0 + kk;
-      Bs[kk][nn] = (n < Nn && k < K) ? Bm(k, n) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      f32x4 a[PM], bb[PN];
-#pragma unroll
-      for (int p = 0; p < PM; ++p) a[p] = *reinterpret_cast<const f32x4*>(&As[kk][p * 64 + ty * 4]);
-#pragma unroll
-      for (int p = 0; p < PN; ++p) bb[p] = *reinterpret_cast<const f32x4*>(&Bs[kk][p * 64 + tx * 4]);
-#pragma unroll
-      for (int u = 0; u < PM * 4; ++u)
-#pragma unroll
-        for (int v = 0; v < PN * 4; ++v) acc[u][v] = fmaf(a[u / 4][u % 4], bb[v / 4][v % 4], acc[u][v]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < PM * 4; ++u)
-#pragma unroll
-    for (int v = 0; v < PN * 4; ++v) {
-      int64_t m = m0 + (u / 4) * 64 + ty * 4 + u % 4, n = n0 + (v / 4) * 64 + tx * 4 + v % 4;
-      if (m < M && n < Nn) out(m, n, acc[u][v]);
-    }
-}
-
-// The same product on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums).  256 threads as
-// 2 x 2 waves, each wave a (TM/2) x (TN/2) part of the tile in 32 x 32 accumulator blocks.  One instruction takes
-// A[32 rows][2 k] and B[2 k][32 columns], one value per lane: lane l supplies row (column) l % 32 of reduction index
-// l / 32, and holds of the 32 x 32 result the entries (row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32), r < 16.
-// The fill fetches a whole reduction step into registers before it writes any of it to LDS (all loads in flight at
-// once; the accumulators live in the other half of the register file, so there is room).  LDS row pitch TM + 1: a
-// k-contiguous fill writes 32 consecutive k of one row, all banks once; an operand read takes 32 consecutive floats.
-template <int TM, int TN, int TK, bool AK, bool BK, class FA, class FB, class FOut>
-__device__ __forceinline__ void tile_product_mfma(int64_t M, int64_t Nn, int64_t K, int64_t m0, int64_t n0,
-                                                  FA A, FB Bm, FOut out) {
-  typedef __attribute__((ext_vector_type(16))) float f32x16;
-  constexpr int WM = TM / 2, WN = TN / 2, NBM = WM / 32, NBN = WN / 32;
-  __shared__ float As[TK][TM + 1];
-  __shared__ float Bs[TK][TN + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1, l32 = lane & 31, lh = lane >> 5;
-  f32x16 acc[NBM][NBN];
-#pragma unroll
-  for (int u = 0; u < NBM; ++u)
-#pragma unroll
-    for (int v = 0; v < NBN; ++v)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[u][v][r] = 0.f;
-  for (int64_t k0 = 0; k0 < K; k0 += TK) {
-    {
-      constexpr int NA = TM * TK / 256, NB = TN * TK / 256;
-      float ra[NA], rb[NB];
-#pragma unroll
-      for (int r = 0; r < NA; ++r) {
-        const int e = tid + r * 256, kk = AK ? e % TK : e / TM, mm = AK ? e / TK : e % TM;
-        const int64_t m = m0 + mm, k = k0 + kk;
-        ra[r] = (m < M && k < K) ? A(m, k) : 0.f;
-      }
-#pragma unroll
-      for (int r = 0; r < NB; ++r) {
-        const int e = tid + r * 256, kk = BK ? e % TK : e / TN, nn = BK ? e / TK : e % TN;
-        const int64_t n = n0 + nn, k = k0 + kk;
-        rb[r] = (n < Nn && k < K) ? Bm(k, n) : 0.f;
-      }
-#pragma unroll
-      for (int r = 0; r < NA; ++r) {
-        const int e = tid + r * 256;
-        As[AK ? e % TK : e / TM][AK ? e / TK : e % TM] = ra[r];
-      }
-#pragma unroll
-      for (int r = 0; r < NB; ++r) {
-        const int e = tid + r * 256;
-        Bs[BK ? e % TK : e / TN][BK ? e / TK : e % TN] = rb[r];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; kk += 2) {
-      float a[NBM], bb[NBN];
-#pragma unroll
-      for (int u = 0; u < NBM; ++u) a[u] = As[kk + lh][wr * WM + u * 32 + l32];
-#pragma unroll
-      for (int v = 0; v < NBN; ++v) bb[v] = Bs[kk + lh][wc * WN + v * 32 + l32];
-#pragma unroll
-      for (int u = 0; u < NBM; ++u)
-#pragma unroll
-        for (int v = 0; v < NBN; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], bb[v], acc[u][v], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < NBM; ++u)
-#pragma unroll
-    for (int v = 0; v < NBN; ++v)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t m = m0 + wr * WM + u * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), n = n0 + wc * WN + v * 32 + l32;
-        if (m < M && n < Nn) out(m, n, acc[u][v][r]);
-      }
-}
-
-// Which product runs where (measured at B = 32768, d = 512, b = 4096; ms for the two logit blocks):
-//  * fp32 features: the matrix-core product everywhere (similarities 2.6 against 4.0 on the vector ALUs, key side 2.6
-//    against 4.4, query side 3.2 against 4.6);
-//  * bf16 features (the widths the MFMA path does not take): their 2-byte loads make the batched fill slow, and the
-//    vector-ALU product with its element-by-element fill wins for the similarities (3.5 against 5.0) and the key
-//    side (4.3 against 5.2); the query side, whose left operand is the fp32 matrix in the workspace, stays on the
-//    matrix cores (5.0 against 5.4).
-// Output tiles: 128 x 128 where the grid is large (b x B similarities, B x d key-side gradient), 64 x 64 for the
-// b x d query-side gradient, whose grid would not fill the chip otherwise.
-constexpr int TS = 128;
-constexpr int TQ = 64;
-
-// AKV: the left operand's fill order on the vector-ALU variant (the key side runs 8 % faster there with consecutive
-// threads along the reduction index although its left operand is contiguous along m)
-template <int DT, int TM, int TN, bool AK, bool BK, bool AKV, class FA, class FB, class FOut>
-__device__ __forceinline__ void tile_product(int64_t M, int64_t Nn, int64_t K, int64_t m0, int64_t n0, FA A, FB Bm, FOut out) {
-  if constexpr (DT == DISCO_F32) tile_product_mfma<TM, TN, 16, AK, BK>(M, Nn, K, m0, n0, A, Bm, out);
-  else tile_product_valu<TM, TN, 16, AKV, BK>(M, Nn, K, m0, n0, A, Bm, out);
-}
-
-struct BlockView {
-  const void* X;   // b x d local rows (already offset to the rank's first row)
-  const void* Y;   // B x d
-  float* W;        // b x B fp32: raw similarities, later softmax - onehot
-};
-
-__device__ __forceinline__ BlockView block_view(const void* I, const void* T, int dtype, int64_t b, int64_t B,
-                                                int64_t d, int rank, float* ws, int z) {
-  size_t esz = dtype == DISCO_BF16 ? 2 : 4;
-  const char* Ir = static_cast<const char*>(I) + (size_t)rank * b * d * esz;
-  const char* Tr = static_cast<const char*>(T) + (size_t)rank * b * d * esz;
-  BlockView v;
-  v.X = z == 0 ? Ir : Tr;
-  v.Y = z == 0 ? T : I;
-  v.W = ws + (size_t)z * b * B;
-  return v;
-}
-
-// Step 1 (Alg. 1 "scaled dot product similarities", without the multiplier): W[i][j] = <X_i, Y_j>.
-template <int DT>
-__global__ __launch_bounds__(256) void naive_similarity(const void* I, const void* T, int dtype, int64_t b,
-                                                         int64_t B, int64_t d, int rank, float* ws) {
-  BlockView v = block_view(I, T, dtype, b, B, d, rank, ws, blockIdx.z);
-  int64_t m0 = (int64_t)blockIdx.y * TS, n0 = (int64_t)blockIdx.x * TS;
-  tile_product<DT, TS, TS, true, true, true>(
-      b, B, d, m0, n0, [&](int64_t m, int64_t k) { return load_feat<DT>(v.X, m * d + k); },
-      [&](int64_t k, int64_t n) { return load_feat<DT>(v.Y, n * d + k); },
-      [&](int64_t m, int64_t n, float a) { v.W[m * B + n] = a; });
-}
-
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* red) {
   for (int o = 32; o > 0; o >>= 1) {
     float w = __shfl_xor(v, o);
@@ -282,60 +104,6 @@ __global__ __launch_bounds__(256) void naive_row_softmax(float* ws, int64_t b, i
     row_ce[(size_t)z * b + i] = (el > 0.5f * tot) ? log1pf(off / el) : logf(tot) - (zl - mx);
     row_ds[(size_t)z * b + i] = ds;
   }
-}
-
-// Step 3: loss_r = c * sum ce, gs_r = c * sum ds  (Alg. 1 `(loss_i + loss_t)/2` with c = 1/(2B)).
-// One workgroup, fixed summation order.
-__global__ __launch_bounds__(256) void naive_scalars(const float* row_ce, const float* row_ds, int64_t n, float c,
-                                                      int accumulate, float* loss, float* gs) {
-  __shared__ float red[4];
-  float a = 0.f, g = 0.f;
-  for (int64_t i = threadIdx.x; i < n; i += 256) { a += row_ce[i]; g += row_ds[i]; }
-  a = block_reduce(a, false, red);
-  g = block_reduce(g, false, red);
-  if (threadIdx.x == 0) {
-    *loss = (accumulate ? *loss : 0.f) + c * a;
-    *gs = (accumulate ? *gs : 0.f) + c * g;
-  }
-}
-
-// Step 4, key side (inter-rank term of Eq. 5 plus the key-side intra term): for every global row j
-//   gT[j] (+)= c s sum_i G^A[i][j] I_r[i]      (z = 0)
-//   gI[j] (+)= c s sum_i G^C[i][j] T_r[i]      (z = 1)
-template <int DT>
-__global__ __launch_bounds__(256) void naive_key_grad(const void* I, const void* T, int dtype, int64_t b, int64_t B,
-                                                       int64_t d, int rank, float* ws, float cs, int accumulate,
-                                                       float* gI, float* gT) {
-  const int z = blockIdx.z;
-  BlockView v = block_view(I, T, dtype, b, B, d, rank, ws, z);
-  float* out = z == 0 ? gT : gI;
-  // the B key rows run along grid.x (up to 2^31 - 1 workgroups), the feature columns along grid.y
-  int64_t m0 = (int64_t)blockIdx.x * TS, n0 = (int64_t)blockIdx.y * TS;
-  tile_product<DT, TS, TS, false, false, true>(
-      B, d, b, m0, n0, [&](int64_t m, int64_t k) { return v.W[k * B + m]; },
-      [&](int64_t k, int64_t n) { return load_feat<DT>(v.X, k * d + n); },
-      [&](int64_t m, int64_t n, float a) {
-        float prev = accumulate ? out[m * d + n] : 0.f;
-        out[m * d + n] = prev + cs * a;
-      });
-}
-
-// Step 5, query side (the intra-rank terms of Eq. 4 that land in the rank's own rows):
-//   gI[R_r][i] += c s sum_j G^A[i][j] T[j]     (z = 0)
-//   gT[R_r][i] += c s sum_j G^C[i][j] I[j]     (z = 1)
-// Runs after naive_key_grad on the same stream, so the rows already hold the key-side part.
-template <int DT>
-__global__ __launch_bounds__(256) void naive_query_grad(const void* I, const void* T, int dtype, int64_t b,
-                                                         int64_t B, int64_t d, int rank, float* ws, float cs,
-                                                         float* gI, float* gT) {
-  const int z = blockIdx.z;
-  BlockView v = block_view(I, T, dtype, b, B, d, rank, ws, z);
-  float* out = (z == 0 ? gI : gT) + (size_t)rank * b * d;
-  int64_t m0 = (int64_t)blockIdx.y * TQ, n0 = (int64_t)blockIdx.x * TQ;
-  tile_product_mfma<TQ, TQ, 32, true, false>(
-      b, d, B, m0, n0, [&](int64_t m, int64_t k) { return v.W[m * B + k]; },
-      [&](int64_t k, int64_t n) { return load_feat<DT>(v.Y, k * d + n); },
-      [&](int64_t m, int64_t n, float a) { out[m * d + n] += cs * a; });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -597,29 +365,45 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 namespace {
 
-// Which calls the small kernels take, by multiply-adds per contraction.  (Old and new kernels in us, d = 512: fp32 B = 256,
-// N = 4: 96 -> 18; 2048, 8: 210 -> 83; 8192, 8: 798 -> 644; 16384, 8: 2940 -> 2469; 32768, 8: 9000 -> 9815.  bf16
-// features: B = 2048, d = 200, N = 16: 276 -> 73; 4096, 500, 8: 826 -> 289; 8192, 1000, 8: 1881 -> 2107.)
-bool small_call(int64_t b, int64_t B, int64_t d, int dtype) {
-  return (double)b * B * d <= (dtype == DISCO_BF16 ? 3e9 : 2e10);
+size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
+size_t lean_bytes(size_t nb, int64_t b, int64_t pitch) { return matrix_bytes(nb, b, pitch) + 2 * align_up(nb * b * sizeof(float)); }
+
+// Floats between the rows of a block's matrix: whole 16-byte pieces, except where that alone would take a call out of the
+// static scratch array.
+int64_t row_pitch(int64_t b, int64_t B, size_t nb) {
+  const int64_t padded = (B + 3) / 4 * 4;
+  return lean_bytes(nb, b, padded) > DISCO_STATIC_SCRATCH_BYTES && lean_bytes(nb, b, B) <= DISCO_STATIC_SCRATCH_BYTES ? B : padded;
 }
 
-size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
+// Estimated time of the small kernels: launches, products at the rate they reach (85 TFLOP/s; less with 2-byte loads and with
+// rows that are not whole 16-byte pieces), and the longest reduction that the waves of one workgroup walk (a tile of the
+// rank's own gradient rows).  Against the split kernels (measured, us, d = 512): B = 256, N = 4: 17 / 48; 2048, 16: 73 / 66;
+// 2048, 8: 83 / 66; 4096, 16: 142 / 87.
+double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
+  const double macs = 0.5 * nb * (double)b * B * d, slow = (dtype == DISCO_BF16 ? 1.4 : 1.0) * (d % 4 ? 1.9 : 1.0);
+  const bool big = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
+  const double chain = (b + B) * (big ? 32.0 * 4 / 4 : 32.0 / 8) / 2200.0;
+  return 14.0 + slow * macs * 12.0 / 85e6 + chain;
+}
 
-// Floats between the rows of a block's matrix: whole 16-byte pieces for the small kernels, except where that alone would
-// take a call out of the static scratch array.
-int64_t row_pitch(int64_t b, int64_t B, int64_t d, int dtype, size_t nb) {
-  const int64_t padded = (B + 3) / 4 * 4;
-  const size_t rows = 2 * align_up(nb * b * sizeof(float));
-  if (!small_call(b, B, d, dtype)) return B;
-  return matrix_bytes(nb, b, padded) + rows > DISCO_STATIC_SCRATCH_BYTES && matrix_bytes(nb, b, B) + rows <= DISCO_STATIC_SCRATCH_BYTES ? B : padded;
+// Workspace of the split kernels may reach this where the fp32 blocks of the small ones need less.
+constexpr size_t SPLIT_LIMIT = (size_t)8 << 30;
+
+// The split kernels' workspace where they are the faster choice, else 0.  lean_only: they keep to what the small ones take.
+size_t split_bytes(int64_t B, int64_t d, int64_t b, int dtype, int nb, bool lean_only, size_t* limit) {
+  const size_t lean = lean_bytes(nb, b, row_pitch(b, B, nb));
+  *limit = lean_only || lean > SPLIT_LIMIT ? lean : SPLIT_LIMIT;
+  if (!split_supported(B, b)) return 0;
+  size_t bytes;
+  const double us = split_estimate_us(B, d, b, dtype, nb, *limit, &bytes);
+  return bytes && us < small_us(b, B, d, dtype, nb) ? bytes : 0;
 }
 
 template <int DT>
 void small_run(const Problem& p, float* W, float* row_ce, float* row_ds, float c) {
   SmallShape f;
   f.b = p.b; f.B = p.B; f.d = p.d; f.nb = loss_blocks(p.variant);
-  f.pitch = row_pitch(p.b, p.B, p.d, DT, f.nb);
+  f.pitch = row_pitch(p.b, p.B, f.nb);
   f.rank = p.rank; f.variant = p.variant; f.accumulate = p.accumulate;
   const unsigned nb = (unsigned)f.nb;
   // 16-byte pieces of a feature row (8-byte ones in bf16)
@@ -649,45 +433,26 @@ void small_run(const Problem& p, float* W, float* row_ce, float* row_ds, float c
 
 }  // namespace
 
-size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant) {
-  int64_t b = B / N;
-  const size_t nb = (size_t)loss_blocks(variant);
-  return matrix_bytes(nb, b, row_pitch(b, B, d, dtype, nb)) + 2 * align_up(nb * b * sizeof(float));
+size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean) {
+  const int64_t b = B / N;
+  const int nb = loss_blocks(variant);
+  const size_t least = lean_bytes(nb, b, row_pitch(b, B, nb));
+  size_t limit;
+  const size_t split = split_bytes(B, d, b, dtype, nb, lean, &limit);
+  return split > least ? split : least;             // (unaligned gradients take the small kernels whatever the plan)
 }
 
 int naive_run(const Problem& p) {
-  const int64_t b = p.b, B = p.B, d = p.d;
+  const int64_t b = p.b, B = p.B;
+  const int nb = loss_blocks(p.variant);
+  size_t limit;
+  if (split_bytes(B, p.d, b, p.dtype, nb, p.lean, &limit) && split_aligned(p)) return split_run(p, limit);
   float* W = static_cast<float*>(p.ws);
-  char* base = static_cast<char*>(p.ws);
-  const unsigned nb = (unsigned)loss_blocks(p.variant);
-  float* row_ce = reinterpret_cast<float*>(base + matrix_bytes(nb, b, row_pitch(b, B, d, p.dtype, nb)));
+  float* row_ce = reinterpret_cast<float*>(static_cast<char*>(p.ws) + matrix_bytes(nb, b, row_pitch(b, B, nb)));
   float* row_ds = reinterpret_cast<float*>(reinterpret_cast<char*>(row_ce) + align_up((size_t)nb * b * sizeof(float)));
   const float c = loss_norm(B, p.variant);
-  const float cs = c * p.s;
-
-  const bool bf = p.dtype == DISCO_BF16;
-  if (small_call(b, B, d, p.dtype)) {
-    if (bf) small_run<DISCO_BF16>(p, W, row_ce, row_ds, c);
-    else small_run<DISCO_F32>(p, W, row_ce, row_ds, c);
-    return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
-  }
-  stage_mark(p.stream, 0);
-  const dim3 sim_grid(cdiv(B, TS), cdiv(b, TS), nb);
-  if (bf) naive_similarity<DISCO_BF16><<<sim_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W);
-  else naive_similarity<DISCO_F32><<<sim_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W);
-  stage_mark(p.stream, 1);
-  naive_row_softmax<<<dim3((unsigned)b, nb), 256, 0, p.stream>>>(W, b, B, B, p.rank, p.s, row_ce, row_ds, p.variant);
-  stage_mark(p.stream, 2);
-  naive_scalars<<<1, 256, 0, p.stream>>>(row_ce, row_ds, (int64_t)nb * b, c, p.accumulate, p.loss, p.gs);
-  stage_mark(p.stream, 3);
-  const dim3 key_grid(cdiv(B, TS), cdiv(d, TS), nb);
-  if (bf) naive_key_grad<DISCO_BF16><<<key_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W, cs, p.accumulate, p.gI, p.gT);
-  else naive_key_grad<DISCO_F32><<<key_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W, cs, p.accumulate, p.gI, p.gT);
-  stage_mark(p.stream, 4);
-  const dim3 query_grid(cdiv(d, TQ), cdiv(b, TQ), nb);
-  if (bf) naive_query_grad<DISCO_BF16><<<query_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W, cs, p.gI, p.gT);
-  else naive_query_grad<DISCO_F32><<<query_grid, 256, 0, p.stream>>>(p.I, p.T, p.dtype, b, B, d, p.rank, W, cs, p.gI, p.gT);
-  stage_mark(p.stream, 5);
+  if (p.dtype == DISCO_BF16) small_run<DISCO_BF16>(p, W, row_ce, row_ds, c);
+  else small_run<DISCO_F32>(p, W, row_ce, row_ds, c);
   return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
 }
 

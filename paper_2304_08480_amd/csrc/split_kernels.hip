@@ -1,0 +1,546 @@
+// The fp32 path's large calls: its four contractions on the bf16 matrix instruction, with every fp32 operand split into three
+// bf16 planes that add up to it exactly (8 significand bits each).  A product of two fp32 operands is six plane products
+// (Planes<3, 3> of mfma_tile.h), one of an fp32 operand and a bf16 one three, of two bf16 ones one: all of them exact in the
+// matrix instruction and summed in fp32, which leaves out less than 2^-26 of any product.
+//
+// What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
+// (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); the tile loop of mfma_tile.h runs six
+// bf16 products at 1.1 PFLOP/s, 180 TFLOP/s of fp32 work.  Measured (us a call, fp32 products before / these): fp32
+// features B = 8192, N = 8, d = 512: 799 / 313 (logits 95, softmax 37, both gradient sides 165-180); 32768, 8, 512: 9000 / 4650;
+// bf16 features of width 1000, B = 8192, N = 8: 1881 / 283; 300, 8192, 32: 1041 / 75.  Errors against 64 bits fall as well (gradients
+// at 8192, 8, 512: 1.8e-6 -> 0.6e-6 in 2-norm): the matrix instruction rounds its sum once per 16 terms, not per 2, and the
+// logits add the small plane products first (SWEEPS, which costs 2-5 % of a call and takes the bias of 2e-7 out of the loss).
+//
+// Per block (X: the rank's rows, Y: all rows):
+//   planes    features -> bf16 planes, rows padded with zeros to whole tiles, columns to whole 64-deep K-steps
+//   logits    S = X Y^T in fp32 (b x B)
+//   softmax   row by row against the row's true maximum: loss terms, G = softmax - onehot as three planes
+//   grads     gY = cs G^T X (key side) and the split-K partial sums of G Y (query side), one launch
+//   finalize  partial sums into the gradients, loss and d/ds
+// The rows are taken in chunks where the whole would need more memory than the fp32 blocks of the small kernels do.
+#include "common.h"
+#include "mfma_tile.h"
+
+namespace disco {
+namespace {
+
+using namespace tile;
+
+struct SplitBlock {
+  const uint16_t* X;     // planes of the rank's rows: the first of the chunk
+  const uint16_t* Y;     // planes of all rows
+  float* S;              // bp x Bp logits without the multiplier
+  uint16_t* G;           // three planes, bp x Bp each
+  float* part;           // splitk x bp x dp query-side sums
+  float* kpart;          // key_splits x Bp x dp key-side sums (only where they do not go straight to gk)
+  float* gq;             // query-side destination (the whole B x d matrix)
+  float* gk;             // key-side destination
+  float* ce;             // b: cross-entropy of the rank's rows
+  float* ds;             // b: row shares of d/ds
+};
+struct SplitArgs {
+  SplitBlock z[2];
+  int64_t b, bp;         // rows of the chunk and the same rounded up to whole tiles
+  int64_t B, Bp;         // all rows, rounded up: also the pitch of S and G
+  int64_t d, dp;         // feature width, rounded up to a multiple of 64: the pitch of the planes and of the partial sums
+  int64_t g0;            // global row of the chunk's first row
+  int64_t r0;            // local row of the chunk's first row
+  int64_t fplane, gplane;  // elements between feature planes / between planes of G
+  int nb, variant;
+  int nMq, nMk, nN;      // gradient tiles: query rows, key rows, columns
+  int splitk, ktps, key_splits, key_ktps;  // splits of the two reductions and their length in 64-deep pieces
+  int q_wgs;
+};
+
+// v = p[0] + p[1] + p[2], to the last bit while the last plane stays above the smallest bf16.  (A value whose leading plane
+// would round to infinity keeps a cut one; a value that is not finite is its own leading plane.)
+struct Three { uint16_t p[3]; };
+__device__ __forceinline__ uint16_t bf16_bits(float f) {
+  const __bf16 v = (__bf16)f;
+  return __builtin_bit_cast(uint16_t, v);
+}
+__device__ __forceinline__ float bf16_value(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+__device__ __forceinline__ Three split3(float v) {
+  Three t;
+  t.p[0] = bf16_bits(v);
+  const bool over = (t.p[0] & 0x7f80u) == 0x7f80u;                     // not finite, or rounded up to it
+  if (over) t.p[0] = (uint16_t)(__float_as_uint(v) >> 16);
+  const bool finite = (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u;
+  if (over && !finite && v != v) t.p[0] = 0x7fc0u;                     // NaN stays one
+  const float r1 = finite ? v - bf16_value(t.p[0]) : 0.f;
+  t.p[1] = bf16_bits(r1);
+  t.p[2] = bf16_bits(r1 - bf16_value(t.p[1]));
+  return t;
+}
+__device__ __forceinline__ void store_planes(uint16_t* dst, int64_t plane, const f32x4& v) {
+  u32x2 w[3];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const Three a = split3(v[2 * h]), c = split3(v[2 * h + 1]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) w[q][h] = (uint32_t)a.p[q] | (uint32_t)c.p[q] << 16;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(dst + q * plane) = w[q];
+}
+
+// Feature planes of I (z = 0) and T: rows x dp each, zero from row B and from column d on.  VEC: whole 16-byte (bf16: 8-byte)
+// pieces of a row can be read at once.  mats: 1 for the two-view loss, whose matrices are one.  Four columns per thread,
+// grid-stride.
+template <int DT, bool VEC>
+__global__ __launch_bounds__(256) void k_feature_planes(const void* I, const void* T, int64_t B, int64_t d, int64_t rows, int64_t dp,
+                                                        int mats, uint16_t* Ip,
+                                                        uint16_t* Tp) {
+  const int64_t cpr = dp >> 2, n = rows * cpr, plane = rows * dp;
+  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < mats * n; c += (int64_t)gridDim.x * 256) {
+    const bool second = c >= n;
+    const int64_t w = second ? c - n : c, row = w / cpr, k = (w - row * cpr) * 4;
+    const void* src = second ? T : I;
+    uint16_t* dst = (second ? Tp : Ip) + row * dp + k;
+    if constexpr (DT == DISCO_BF16) {
+      u32x2 v = {0u, 0u};
+      const uint16_t* p = static_cast<const uint16_t*>(src) + row * d + k;
+      if (row < B) {
+        if constexpr (VEC) {
+          if (k < d) v = *reinterpret_cast<const u32x2*>(p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k + e < d) v[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+        }
+      }
+      *reinterpret_cast<u32x2*>(dst) = v;
+    } else {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      const float* p = static_cast<const float*>(src) + row * d + k;
+      if (row < B) {
+        if constexpr (VEC) {
+          if (k < d) v = *reinterpret_cast<const f32x4*>(p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k + e < d) v[e] = p[e];
+        }
+      }
+      store_planes(dst, plane, v);
+    }
+  }
+}
+
+// S = X Y^T, one T x T tile per workgroup (rows: query, columns: key).  NP: planes of a feature (1 or 3).
+template <int T, int NP>
+__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_logits(SplitArgs a, int sbi, int sbj) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int nI = (int)(a.bp / T), nJ = (int)(a.Bp / T), total = nI * nJ, per_block = (total + 7) / 8 * 8;
+  const int z = blockIdx.x / per_block;
+  int lin, it, jt;
+  if (!xcd_linear(blockIdx.x - z * per_block, total, lin)) return;
+  superblock_tile(lin, nI, nJ, sbi, sbj, it, jt);
+  const SplitBlock& p = a.z[z];
+  const int64_t i0 = (int64_t)it * T, j0 = (int64_t)jt * T;
+  Acc<Cfg<T>::NFA> acc;
+  using PS = Planes<NP, NP, NP == 3>;
+  mainloop<T, FMT_K, FMT_K, false, true, PS>(p.X + i0 * a.dp, a.dp, p.Y + j0 * a.dp, a.dp, (int)(a.dp / BK) * PS::N, smem, acc, T, a.fplane, a.fplane);
+  store_tile_f32<T, false>(acc, smem, p.S + i0 * a.Bp + j0, a.Bp, 1.0f);
+}
+
+constexpr int SM_THREADS = 512, SM_KEEP = 8;                // softmax: threads per row, 4-column pieces a thread can keep
+
+__device__ __forceinline__ float workgroup_sum(float v, float* red) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float r = red[0];
+#pragma unroll
+  for (int w = 1; w < SM_THREADS / 64; ++w) r += red[w];
+  return r;
+}
+
+// One workgroup per row: maximum over the columns that take part, cross-entropy, the row's share of d/ds and the row of
+// G = softmax - onehot as three planes (0 in the padding columns and rows, and in a two-view row's own column).  The off-label
+// mass is summed on its own, so that P_label - 1 = -(it) / (total) does not cancel, and d/ds as
+// sum_{j != label} P_ij (S_ij - S_i,label).  KEEP: the row fits the workgroup's registers (Bp <= 16384) and is read once;
+// else it is read three times, from cache.
+template <bool KEEP>
+__global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float s) {
+  __shared__ float red[SM_THREADS / 64];
+  const int64_t i = blockIdx.x;
+  const SplitBlock& p = a.z[blockIdx.y];
+  uint16_t* G = p.G + i * a.Bp;
+  const int64_t nvec = a.Bp >> 2;
+  if (i >= a.b) {
+    for (int64_t q = threadIdx.x; q < nvec; q += SM_THREADS)
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x2*>(G + pl * a.gplane + q * 4) = u32x2{0u, 0u};
+    return;
+  }
+  const float* S = p.S + i * a.Bp;
+  const int64_t label = label_row(a.g0 + i, a.B, a.variant), self = masked_col(a.g0 + i, a.variant);
+  const float xl = S[label];
+  f32x4 keep[KEEP ? SM_KEEP : 1];
+  // f(j, v) over this thread's pieces v of columns j .. j + 3; with KEEP in registers, where f may replace them
+  auto visit = [&](auto f) {
+    if constexpr (KEEP) {
+#pragma unroll
+      for (int u = 0; u < SM_KEEP; ++u) {
+        const int64_t q = threadIdx.x + u * SM_THREADS;
+        if (q < nvec) f(q * 4, keep[u]);
+      }
+    } else {
+      for (int64_t q = threadIdx.x; q < nvec; q += SM_THREADS) {
+        f32x4 v = *reinterpret_cast<const f32x4*>(S + q * 4);
+        f(q * 4, v);
+      }
+    }
+  };
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int u = 0; u < SM_KEEP; ++u) {
+      const int64_t q = threadIdx.x + u * SM_THREADS;
+      if (q < nvec) keep[u] = *reinterpret_cast<const f32x4*>(S + q * 4);
+    }
+  }
+  float mx = -INFINITY;
+  visit([&](int64_t j, f32x4& v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (j + e < a.B && j + e != self) mx = fmaxf(mx, s * v[e]);
+  });
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < SM_THREADS / 64; ++w) mx = fmaxf(mx, red[w]);
+  float off = 0.f, ds = 0.f;
+  visit([&](int64_t j, f32x4& v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x = 0.f;
+      if (j + e < a.B && j + e != self && j + e != label) {
+        x = expf(s * v[e] - mx);
+        off += x;
+        ds = fmaf(x, v[e] - xl, ds);
+      }
+      if constexpr (KEEP) v[e] = x;
+    }
+  });
+  off = workgroup_sum(off, red);
+  ds = workgroup_sum(ds, red);
+  const float zl = s * xl, el = expf(zl - mx), tot = off + el, inv = 1.f / tot;
+  visit([&](int64_t j, f32x4& v) {
+    f32x4 g;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = j + e < a.B && j + e != self && j + e != label;
+      const float x = KEEP ? v[e] : in ? expf(s * v[e] - mx) : 0.f;
+      g[e] = j + e == label ? -off * inv : x * inv;
+    }
+    store_planes(G + j, a.gplane, g);
+  });
+  if (threadIdx.x == 0) {
+    // ce = log(tot) - (zl - mx); where the label holds most of the mass log1p(off / el) keeps the relative accuracy
+    p.ce[a.r0 + i] = (el > 0.5f * tot) ? log1pf(off / el) : logf(tot) - (zl - mx);
+    p.ds[a.r0 + i] = ds * inv;
+  }
+}
+
+enum { SPLIT_KEY_WRITE = 0, SPLIT_KEY_ADD = 1, SPLIT_KEY_PARTS = 2 };
+
+// Both gradient contractions, one T x T tile of one split per workgroup; query side first (workgroups < q_wgs, a multiple of
+// 8), as in k_grads of mfma_kernels.hip.  NP: planes of a feature.
+template <int T, int NP, int KMODE>
+__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, float cs) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  using PS = Planes<3, NP>;
+  Acc<Cfg<T>::NFA> acc;
+  if ((int)blockIdx.x < a.q_wgs) {
+    const int tiles = a.nMq * a.nN, total = tiles * a.nb * a.splitk;
+    int lin;
+    if (!xcd_linear(blockIdx.x, total, lin)) return;
+    const int slice = lin / tiles, tile = lin % tiles;               // the workgroups of one slice read the same rows of Y
+    const SplitBlock& p = a.z[slice / a.splitk];
+    const int ks = slice % a.splitk;
+    const int64_t i0 = (int64_t)(tile / a.nN) * T, k0 = (int64_t)(tile % a.nN) * T;
+    const int kt0 = ks * a.ktps, left = (int)(a.Bp / BK) - kt0, kts = left < a.ktps ? left : a.ktps;
+    const int ncols = a.dp - k0 < T ? (int)(a.dp - k0) : T;
+    mainloop<T, FMT_K, FMT_R, false, true, PS>(p.G + i0 * a.Bp + (int64_t)kt0 * BK, a.Bp, p.Y + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem,
+                                               acc, ncols, a.gplane, a.fplane);
+    store_tile_f32<T, false>(acc, smem, p.part + (int64_t)ks * a.bp * a.dp + i0 * a.dp + k0, a.dp, 1.0f, ncols);
+    return;
+  }
+  const int tiles = a.nMk * a.nN * a.key_splits, per_block = (tiles + 7) / 8 * 8;
+  const int w = blockIdx.x - a.q_wgs, z = w / per_block;
+  int lin;
+  if (!xcd_linear(w - z * per_block, tiles, lin)) return;
+  const SplitBlock& p = a.z[z];
+  const int t2 = lin / a.nN, ks = t2 / a.nMk;
+  const int64_t j0 = (int64_t)(t2 % a.nMk) * T, k0 = (int64_t)(lin % a.nN) * T;
+  const int kt0 = ks * a.key_ktps, left = (int)(a.bp / BK) - kt0, kts = left < a.key_ktps ? left : a.key_ktps;
+  const int ncols = a.dp - k0 < T ? (int)(a.dp - k0) : T;
+  mainloop<T, FMT_R, FMT_R, false, true, PS>(p.G + (int64_t)kt0 * BK * a.Bp + j0, a.Bp, p.X + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem, acc,
+                                             ncols, a.gplane, a.fplane);
+  if constexpr (KMODE == SPLIT_KEY_PARTS) {
+    store_tile_f32<T, false>(acc, smem, p.kpart + ((int64_t)ks * a.Bp + j0) * a.dp + k0, a.dp, 1.0f, ncols);
+  } else {                                                           // (d % 4 == 0: a tile's last column piece is whole)
+    const int cols = a.d - k0 < T ? (int)(a.d - k0) : T;
+    const int64_t rows = a.B - j0;
+    store_tile_f32<T, KMODE == SPLIT_KEY_ADD>(acc, smem, p.gk + j0 * a.d + k0, a.d, cs, cols, rows < T ? (int)rows : T);
+  }
+}
+
+// Partial sums into the gradients: gX[row] += cs sum_ks part[ks][row] for the chunk's rows, and with PARTS also
+// gY[j] = [add] gY[j] + cs sum_ks kpart[ks][j] for all rows; one wave per (matrix, row).  Workgroup 0 of the call's last chunk
+// (scalars = 1) adds up loss and d/ds over the rank's rows instead, in fixed order.
+// VEC: rows of the gradients can be written in 16-byte pieces.
+template <bool PARTS, bool VEC>
+__global__ __launch_bounds__(256) void k_split_finalize(SplitArgs a, float cs, float c, int add, int scalars, int accumulate, int64_t b_all,
+                                                        float* loss, float* gs) {
+  if (scalars && blockIdx.x == 0) {
+    __shared__ float red[2][4];
+    float l = 0.f, g = 0.f;
+    for (int z = 0; z < a.nb; ++z)
+      for (int64_t i0 = threadIdx.x; i0 < b_all; i0 += 1024) {
+        float u[4], v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int64_t i = i0 + q * 256;
+          u[q] = i < b_all ? a.z[z].ce[i] : 0.f;
+          v[q] = i < b_all ? a.z[z].ds[i] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { l += u[q]; g += v[q]; }
+      }
+    for (int o = 32; o > 0; o >>= 1) { l += __shfl_xor(l, o); g += __shfl_xor(g, o); }
+    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = l; red[1][threadIdx.x >> 6] = g; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      *loss = (accumulate ? *loss : 0.f) + c * ((red[0][0] + red[0][1]) + (red[0][2] + red[0][3]));
+      *gs = (accumulate ? *gs : 0.f) + c * ((red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+    }
+    return;
+  }
+  const int64_t rows = PARTS ? a.B : a.b;
+  const int64_t w = ((int64_t)blockIdx.x - scalars) * 4 + (threadIdx.x >> 6);
+  const int z = w >= rows ? 1 : 0;                                    // this wave's destination is block z's query side
+  const int64_t row = w - z * rows;
+  if (row >= rows || z >= a.nb) return;
+  const SplitBlock& p = a.z[z];
+  const SplitBlock& o = a.z[a.nb == 1 ? 0 : 1 - z];                   // whose key side lands in the same matrix
+  const int64_t i = PARTS ? row - a.g0 : row, g = PARTS ? row : a.g0 + row;
+  const bool own = i >= 0 && i < a.b;
+  float* out = p.gq + g * a.d;
+  for (int64_t k = (threadIdx.x & 63) * 4; k < a.d; k += 256) {
+    f32x4 u = {0.f, 0.f, 0.f, 0.f}, v = {0.f, 0.f, 0.f, 0.f};
+    if (own)
+      for (int ks = 0; ks < a.splitk; ++ks) u += *reinterpret_cast<const f32x4*>(p.part + ((int64_t)ks * a.bp + i) * a.dp + k);
+    if constexpr (PARTS)
+      for (int ks = 0; ks < a.key_splits; ++ks) v += *reinterpret_cast<const f32x4*>(o.kpart + ((int64_t)ks * a.Bp + row) * a.dp + k);
+    u += v;
+    if constexpr (VEC) {
+      f32x4 r = {0.f, 0.f, 0.f, 0.f};
+      if (!PARTS || add) r = *reinterpret_cast<const f32x4*>(out + k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = fmaf(cs, u[e], r[e]);
+      *reinterpret_cast<f32x4*>(out + k) = r;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < a.d) out[k + e] = fmaf(cs, u[e], !PARTS || add ? out[k + e] : 0.f);
+    }
+  }
+}
+
+struct SplitPlan {
+  int T;
+  int64_t chunk;         // rows taken at a time
+  int64_t bp, Bp, dp, frows;
+  int nMq, nMk, nN, splitk, ktps, key_splits, key_ktps;
+  bool parts;            // the key side goes through partial sums
+  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, total;
+  double us;
+};
+
+int64_t round_up(int64_t v, int64_t u) { return (v + u - 1) / u * u; }
+
+void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
+  size_t o = 0;
+  pl.off_planes = o; o += 2 * align_up((size_t)np * pl.frows * pl.dp * 2);
+  pl.off_S = o;      o += nb * align_up((size_t)pl.bp * pl.Bp * 4);
+  pl.off_G = o;      o += nb * align_up((size_t)3 * pl.bp * pl.Bp * 2);
+  pl.off_part = o;   o += nb * align_up((size_t)pl.splitk * pl.bp * pl.dp * 4);
+  pl.off_kpart = o;
+  if (pl.parts) o += nb * align_up((size_t)pl.key_splits * pl.Bp * pl.dp * 4);
+  pl.off_rows = o;   o += 2 * nb * align_up((size_t)b * 4);
+  pl.total = o;
+}
+
+// Compares estimated times over tile sizes and splits, for one chunk of rows.  (Rows of the gradients that are not whole
+// 16-byte pieces go through partial sums: the tile store writes such pieces.)
+SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64_t chunk) {
+  static const int Q_SPLITS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
+  SplitPlan best;
+  best.us = 1e300;
+  const int nl = np == 3 ? 6 : 1, ng = np == 3 ? 6 : 3;
+  for (int T = 128; T <= 256; T += 128) {
+    SplitPlan pl;
+    pl.T = T; pl.chunk = chunk;
+    pl.bp = round_up(chunk, T); pl.Bp = round_up(B, T); pl.dp = round_up(d, BK);
+    pl.frows = pl.Bp + (chunk < b ? pl.bp : T);                      // a rank's last tile (chunk) may reach past the last row
+    pl.nMq = (int)(pl.bp / T); pl.nMk = (int)(pl.Bp / T); pl.nN = (int)((pl.dp + T - 1) / T);
+    const double slots = T == 256 ? CHIP_CUS : 2 * CHIP_CUS, fix = T == 256 ? 8.0 : 3.0;
+    const double lt = (double)nb * pl.nMq * pl.nMk, lrounds = (double)(int64_t)((lt + slots - 1) / slots);
+    const double logits = lrounds * ((double)(pl.dp / BK) * nl * step_us(T, lt) + fix);
+    const double bytes = (double)nb * pl.bp * pl.Bp;
+    const double base = logits + 20.0 * bytes / BYTES_PER_US + (np * 2 + 4) * 2.0 * pl.frows * pl.dp / BYTES_PER_US;
+    const int kq = (int)(pl.Bp / BK), kk = (int)(pl.bp / BK);
+    for (int sk : Q_SPLITS) {
+      if (sk > kq) break;
+      pl.ktps = (kq + sk - 1) / sk; pl.splitk = (kq + pl.ktps - 1) / pl.ktps;
+      for (int ks : K_SPLITS) {
+        if (ks > kk) break;
+        pl.key_ktps = (kk + ks - 1) / ks; pl.key_splits = (kk + pl.key_ktps - 1) / pl.key_ktps;
+        pl.parts = pl.key_splits > 1 || d % 4 != 0;
+        const double nq = (double)nb * pl.nMq * pl.nN * pl.splitk, nk = (double)nb * pl.nMk * pl.nN * pl.key_splits;
+        const double step = step_us(T, nq + nk), lq = pl.ktps * ng * step + fix, lk = pl.key_ktps * ng * step + fix;
+        const double longest = lq > lk ? lq : lk;
+        const double grads = nq + nk <= slots ? longest : (nq * lq + nk * lk) / slots + 0.5 * longest;
+        const double part = 8.0 * nb * pl.bp * pl.dp * pl.splitk, key = 4.0 * nb * pl.Bp * pl.dp;
+        pl.us = base + grads + (part + (pl.parts ? 2.0 * key * pl.key_splits + key : key)) / BYTES_PER_US + 25.0;
+        if (pl.us < best.us) { split_layout(pl, b, nb, np); best = pl; }
+      }
+    }
+  }
+  return best;
+}
+
+template <class K>
+bool allow_lds(K kernel, int bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+}
+
+template <int T>
+constexpr int SPLIT_SMEM = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SMEM_BYTES<T> : Cfg<T>::SMEM_BYTES;
+
+template <int T, int NP>
+bool split_lds_ok() {
+  static const bool ok = allow_lds(k_split_logits<T, NP>, SPLIT_SMEM<T>) && allow_lds(k_split_grads<T, NP, SPLIT_KEY_WRITE>, SPLIT_SMEM<T>) &&
+                         allow_lds(k_split_grads<T, NP, SPLIT_KEY_ADD>, SPLIT_SMEM<T>) && allow_lds(k_split_grads<T, NP, SPLIT_KEY_PARTS>, SPLIT_SMEM<T>);
+  return ok;
+}
+
+template <int T, int NP>
+void split_products(bool grads, bool parts, bool add, const SplitArgs& a, float cs, hipStream_t st) {
+  if (!grads) {
+    const int nI = (int)(a.bp / T), nJ = (int)(a.Bp / T);
+    const int sbi = nI < 8 ? nI : 8, sbj = 32 / sbi < nJ ? 32 / sbi : nJ;
+    k_split_logits<T, NP><<<dim3((unsigned)(a.nb * ((nI * nJ + 7) / 8 * 8))), Cfg<T>::NTHREADS, SPLIT_SMEM<T>, st>>>(a, sbi, sbj);
+    return;
+  }
+  const dim3 grid((unsigned)(a.q_wgs + a.nb * ((a.nMk * a.nN * a.key_splits + 7) / 8 * 8)));
+  auto go = [&](auto kernel) { kernel<<<grid, Cfg<T>::NTHREADS, SPLIT_SMEM<T>, st>>>(a, cs); };
+  if (parts) go(k_split_grads<T, NP, SPLIT_KEY_PARTS>);
+  else if (add) go(k_split_grads<T, NP, SPLIT_KEY_ADD>);
+  else go(k_split_grads<T, NP, SPLIT_KEY_WRITE>);
+}
+
+template <int DT>
+int split_run_typed(const Problem& pr, const SplitPlan& pl) {
+  constexpr int NP = DT == DISCO_BF16 ? 1 : 3;
+  if (!(pl.T == 256 ? split_lds_ok<256, NP>() : split_lds_ok<128, NP>())) return DISCO_ERR_HIP;
+  const int nb = loss_blocks(pr.variant);
+  char* ws = static_cast<char*>(pr.ws);
+  const float c = loss_norm(pr.B, pr.variant), cs = c * pr.s;
+  hipStream_t st = pr.stream;
+  auto aligned = [](const void* p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
+  const bool fvec = pr.d % 4 == 0 && aligned(pr.I, DT == DISCO_BF16 ? 8 : 16) && aligned(pr.T, DT == DISCO_BF16 ? 8 : 16);
+  const bool gvec = pr.d % 4 == 0 && aligned(pr.gI, 16) && aligned(pr.gT, 16);
+  uint16_t* planes[2];
+  for (int z = 0; z < 2; ++z) planes[z] = reinterpret_cast<uint16_t*>(ws + pl.off_planes + z * align_up((size_t)NP * pl.frows * pl.dp * 2));
+
+  stage_mark(st, 0);
+  {
+    const int64_t pieces = nb * pl.frows * (pl.dp >> 2);
+    const dim3 grid((unsigned)(pieces < 4096 * 256 ? (pieces + 255) / 256 : 4096));
+    if (fvec) k_feature_planes<DT, true><<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1]);
+    else k_feature_planes<DT, false><<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1]);
+  }
+  for (int64_t r0 = 0; r0 < pr.b; r0 += pl.chunk) {
+    const bool last = r0 + pl.chunk >= pr.b, add = pr.accumulate || r0 > 0;
+    SplitArgs a;
+    a.b = last ? pr.b - r0 : pl.chunk; a.bp = pl.bp; a.B = pr.B; a.Bp = pl.Bp; a.d = pr.d; a.dp = pl.dp;
+    a.g0 = (int64_t)pr.rank * pr.b + r0; a.r0 = r0;
+    a.fplane = pl.frows * pl.dp; a.gplane = pl.bp * pl.Bp;
+    a.nb = nb; a.variant = pr.variant;
+    a.nMq = pl.nMq; a.nMk = pl.nMk; a.nN = pl.nN;
+    a.splitk = pl.splitk; a.ktps = pl.ktps; a.key_splits = pl.key_splits; a.key_ktps = pl.key_ktps;
+    a.q_wgs = (nb * a.nMq * a.nN * a.splitk + 7) / 8 * 8;
+    for (int z = 0; z < 2; ++z) {
+      SplitBlock& p = a.z[z];
+      p.X = planes[z] + a.g0 * pl.dp;
+      p.Y = planes[nb == 1 ? z : 1 - z];
+      const int zz = z < nb ? z : 0;
+      p.S = reinterpret_cast<float*>(ws + pl.off_S + zz * align_up((size_t)pl.bp * pl.Bp * 4));
+      p.G = reinterpret_cast<uint16_t*>(ws + pl.off_G + zz * align_up((size_t)3 * pl.bp * pl.Bp * 2));
+      p.part = reinterpret_cast<float*>(ws + pl.off_part + zz * align_up((size_t)pl.splitk * pl.bp * pl.dp * 4));
+      p.kpart = pl.parts ? reinterpret_cast<float*>(ws + pl.off_kpart + zz * align_up((size_t)pl.key_splits * pl.Bp * pl.dp * 4)) : nullptr;
+      p.ce = reinterpret_cast<float*>(ws + pl.off_rows + (2 * zz) * align_up((size_t)pr.b * 4));
+      p.ds = reinterpret_cast<float*>(ws + pl.off_rows + (2 * zz + 1) * align_up((size_t)pr.b * 4));
+      p.gq = z == 0 ? pr.gI : pr.gT;
+      p.gk = z == 0 ? pr.gT : pr.gI;
+    }
+    if (pl.T == 256) split_products<256, NP>(false, pl.parts, add, a, cs, st);
+    else split_products<128, NP>(false, pl.parts, add, a, cs, st);
+    if (r0 == 0) stage_mark(st, 1);
+    const dim3 rows((unsigned)pl.bp, (unsigned)nb);
+    if (pl.Bp <= (int64_t)SM_THREADS * SM_KEEP * 4) k_split_softmax<true><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    else k_split_softmax<false><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    if (r0 == 0) { stage_mark(st, 2); stage_mark(st, 3); }
+    if (pl.T == 256) split_products<256, NP>(true, pl.parts, add, a, cs, st);
+    else split_products<128, NP>(true, pl.parts, add, a, cs, st);
+    if (last) stage_mark(st, 4);
+    const int64_t frows = nb * (pl.parts ? pr.B : a.b);
+    const int sc = last ? 1 : 0;
+    auto fin = [&](auto kernel) {
+      kernel<<<dim3((unsigned)((frows + 3) / 4 + sc)), 256, 0, st>>>(a, cs, c, add ? 1 : 0, sc, pr.accumulate, pr.b, pr.loss, pr.gs);
+    };
+    if (pl.parts) { if (gvec) fin(k_split_finalize<true, true>); else fin(k_split_finalize<true, false>); }
+    else fin(k_split_finalize<false, true>);
+  }
+  stage_mark(st, 5);
+  return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
+}
+
+// The plan whose rows are taken in as few chunks as keep the workspace within `limit` (0 bytes in `total`: there is none).
+SplitPlan plan_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit) {
+  const int np = dtype == DISCO_BF16 ? 1 : 3;
+  for (int64_t chunks = 1;; chunks *= 2) {
+    const int64_t chunk = chunks == 1 ? b : round_up((b + chunks - 1) / chunks, 256);
+    SplitPlan pl = make_split_plan(B, d, b, nb, np, chunk);
+    if (pl.total <= limit) return pl;
+    if (chunk <= 256) { pl.total = 0; return pl; }
+  }
+}
+
+}  // namespace
+
+bool split_supported(int64_t B, int64_t b) { return B <= ((int64_t)1 << 22) && b >= 1; }   // 32-bit lane offsets over 256 rows of pitch B
+
+bool split_aligned(const Problem& pr) {
+  return pr.d % 4 != 0 || ((reinterpret_cast<uintptr_t>(pr.gI) | reinterpret_cast<uintptr_t>(pr.gT)) & 15u) == 0;
+}
+
+double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, size_t* bytes) {
+  const SplitPlan pl = plan_within(B, d, b, dtype, nb, limit);
+  *bytes = pl.total;
+  // (the model ranks plans; its sum of the parts is this much more than what a call takes: 402 against 313 us at B = 8192,
+  // N = 8, d = 512, 113 against 87 at 4096, 16, 512, 43 against 33 at 2048, 16, d = 200 in bf16)
+  return 0.77 * pl.us * (double)((b + pl.chunk - 1) / pl.chunk);
+}
+
+int split_run(const Problem& pr, size_t limit) {
+  const SplitPlan pl = plan_within(pr.B, pr.d, pr.b, pr.dtype, loss_blocks(pr.variant), limit);
+  return pr.dtype == DISCO_BF16 ? split_run_typed<DISCO_BF16>(pr, pl) : split_run_typed<DISCO_F32>(pr, pl);
+}
+
+}  // namespace disco
