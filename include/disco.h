@@ -92,7 +92,8 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  *                         call, to the MATERIALIZED kernels, so the workspace is sized for those as well.  A
  *                         batch too small to gain from it (B*B*d < 1e10) goes to those kernels at once.
  * DISCO_PATH_AUTO         the fastest path that supports the arguments: SYMMETRIC (N = 1) or
- *                         MATERIALIZED when their shape limits hold, else NAIVE.  Feature widths that are not
+ *                         MATERIALIZED when their shape limits hold (of these, calls of a few tiles run on the
+ *                         small kernels of NAIVE, in fp32 arithmetic), else NAIVE.  Feature widths that are not
  *                         a multiple of 64, fp32 inputs, and ragged shares of blocks smaller than
  *                         b*B = 2^18 logits (launch-bound either way) therefore run in fp32 arithmetic, for
  *                         large shapes three to six times slower; disco_resolve_path tells which path a

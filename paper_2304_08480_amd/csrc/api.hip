@@ -72,9 +72,14 @@ int resolve(int64_t B, int64_t d, int32_t N, int dtype, int path, int variant = 
   }
 }
 
+// AUTO calls that resolve to a bf16 tile path run on the fp32 path's small kernels where those are faster.
+bool on_small_kernels(int path, int r, int64_t B, int64_t d, int32_t N, int variant) {
+  return path == DISCO_PATH_AUTO && (r == DISCO_PATH_MATERIALIZED || r == DISCO_PATH_SYMMETRIC) && small_beats_tiles(B, d, N, variant);
+}
+
 // path: what the caller asked for, r: what it resolves to
 size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant) {
-  if (r == DISCO_PATH_NAIVE) return naive_workspace_bytes(B, d, N, dtype, variant, path == DISCO_PATH_NAIVE);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, variant)) return naive_workspace_bytes(B, d, N, dtype, variant, path == DISCO_PATH_NAIVE);
   // (the bf16 paths lay their workspace out for two blocks; the one-block loss uses the first half of each part)
   if (r == DISCO_PATH_MATERIALIZED) return mfma_stored_workspace_bytes(B, d, N, variant);
   if (r == DISCO_PATH_FUSED) return mfma_fused_workspace_bytes(B, d, N, variant);
@@ -113,7 +118,7 @@ extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64
   p.loss = loss; p.gI = gI; p.gT = gT; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
-  if (r == DISCO_PATH_NAIVE) return naive_run(p);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
   if (r == DISCO_PATH_SYMMETRIC) return mfma_sym_run(p);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
 }
@@ -154,7 +159,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   p.loss = loss; p.gI = gZ; p.gT = gZ; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
-  if (r == DISCO_PATH_NAIVE) return naive_run(p);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
 }
 

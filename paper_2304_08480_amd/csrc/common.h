@@ -47,11 +47,34 @@ __host__ __device__ inline float loss_norm(int64_t B, int variant) { return (var
 void stage_mark(hipStream_t st, int k);
 bool stage_marks_on();
 
+// The plans of a thread's last few shapes.  Comparing a few hundred candidates takes 3 to 10 us of host time and a call
+// asks for its plan two or three times (workspace check, route, launch), which a short call would wait for.
+template <class Plan, int NKEY>
+struct PlanCache {
+  struct Entry { int64_t key[NKEY]; Plan plan; bool set = false; } entry[4];
+  int next = 0;
+  template <class F>
+  Plan get(const int64_t (&key)[NKEY], F make) {
+    for (Entry& e : entry) {
+      bool same = e.set;
+      for (int i = 0; i < NKEY; ++i) same = same && e.key[i] == key[i];
+      if (same) return e.plan;
+    }
+    Entry& e = entry[next];
+    next = (next + 1) % 4;
+    e.plan = make();
+    for (int i = 0; i < NKEY; ++i) e.key[i] = key[i];
+    e.set = true;
+    return e.plan;
+  }
+};
+
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 // The fp32 path.  lean: within the memory of its fp32 logit blocks (what DISCO_PATH_NAIVE by name asks for).
 size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean);
 int naive_run(const Problem& p);
+bool small_beats_tiles(int64_t B, int64_t d, int32_t N, int variant);
 
 // Its large calls (split_kernels.hip): shapes they take, gradients they can store, their estimated time and workspace with the
 // workspace kept within `limit` (*bytes = 0: impossible), and the call in that plan.
@@ -64,6 +87,7 @@ int split_run(const Problem& p, size_t limit);
 // tiles is zero-padded in the workspace) / the share is whole tiles (what the fused and symmetric paths need too)
 bool mfma_supported(int64_t B, int64_t d, int32_t N, int dtype, int variant = LOSS_CLIP);
 bool mfma_whole_tiles(int64_t B, int32_t N);
+double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant);      // its tile kernels, without the launches
 size_t mfma_stored_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant = LOSS_CLIP);
 int mfma_stored_run(const Problem& p);
 size_t mfma_fused_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant = LOSS_CLIP);

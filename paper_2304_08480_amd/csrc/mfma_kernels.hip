@@ -1123,6 +1123,7 @@ struct Plan {
   int key_splits, key_ktps;
   size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ymax, off_flags, off_ref, off_pad, total;
   size_t rows_stride;    // bytes of one b-float row array (aligned)
+  double us;             // estimated time of the tile kernels
 };
 
 // Key panels of the fused path: at most 16384 keys wide (so that one panel of both blocks' numerators
@@ -1201,10 +1202,10 @@ void split(int total, int want, int& splits, int& per) {
 }
 
 // tile: 0, or the size that the caller's kernels are written for.
-Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2, int tile = 0) {
+Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int tile) {
   static const int Q_SPLITS[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
   Plan best;
-  double best_us = 1e300;
+  best.us = 1e300;
   bool best_fits = false;
   for (int tl = 128; tl <= 256; tl += 128)
     for (int tg = 128; tg <= 256; tg += 128) {
@@ -1221,15 +1222,20 @@ Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2, int ti
           if (ks > 1 && (fused || tile || ks > kt_k)) break;
           split(kt_k, ks, pl.key_splits, pl.key_ktps);
           const double us = base + pl.npanels * grads_us(pl, nblk, pl.ktps, pl.splitk, pl.key_ktps, pl.key_splits);
-          if (best_fits && us >= best_us) continue;
+          if (best_fits && us >= best.us) continue;
           layout(pl);
           // a call whose workspace can stay within the library's static array stays within it
           const bool fits = pl.total <= DISCO_STATIC_SCRATCH_BYTES;
-          if (fits > best_fits || (fits == best_fits && us < best_us)) { best = pl; best_us = us; best_fits = fits; }
+          if (fits > best_fits || (fits == best_fits && us < best.us)) { best = pl; best.us = us; best_fits = fits; }
         }
       }
     }
   return best;
+}
+
+Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2, int tile = 0) {
+  static thread_local PlanCache<Plan, 6> cache;
+  return cache.get({B, d, N, fused, nblk, tile}, [&] { return compare_plans(B, d, N, fused, nblk, tile); });
 }
 
 // Query tiles per super-block of the logit tile walk (superblock_tile): the largest power of two <= 8 that divides
@@ -1546,6 +1552,7 @@ bool mfma_supported(int64_t B, int64_t d, int32_t N, int dtype, int variant) {
 
 bool mfma_whole_tiles(int64_t B, int32_t N) { return N > 0 && B % N == 0 && (B / N) % 256 == 0; }
 
+double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant)).us; }
 size_t mfma_stored_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant)).total; }
 size_t mfma_fused_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, true, loss_blocks(variant)).total; }
 int mfma_stored_run(const Problem& pr) { return mfma_run(pr, false); }

@@ -1,23 +1,13 @@
-// Reference-grade GPU path: fp32 arithmetic (fp32 matrix instruction or vector-ALU FMA), any shape, either input dtype.
+// The fp32 path: fp32 arithmetic on the matrix instructions, any shape, either input dtype (large calls: split_kernels.hip).
 // The two b x B blocks of raw similarities live in the workspace in fp32 (the 2B^2/N memory model
 // of Sec. 4.1) and are turned in place into (softmax - onehot); the four gradient contractions of
 // Eq. 4-6 are plain tiled products.  Everything is deterministic (no float atomics).
 #include "common.h"
 
+#include <type_traits>
+
 namespace disco {
 namespace {
-
-
-// DT: DISCO_F32 or DISCO_BF16, a template argument of the product kernels so that no load sits behind a branch
-// (the fill loops then issue all their loads before they wait for the first).
-template <int DT>
-__device__ __forceinline__ float load_feat(const void* base, int64_t idx) {
-  if (DT == DISCO_BF16) {
-    uint32_t u = static_cast<const uint16_t*>(base)[idx];
-    return __uint_as_float(u << 16);
-  }
-  return static_cast<const float*>(base)[idx];
-}
 
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* red) {
   for (int o = 32; o > 0; o >>= 1) {
@@ -119,18 +109,11 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
-// Four consecutive values from element idx on.  VEC: they start on a 16-byte (bf16: 8-byte) boundary.
-template <int DT, bool VEC>
-__device__ __forceinline__ f32x4 load_feat4(const void* base, int64_t idx) {
-  if constexpr (!VEC) {
-    return f32x4{load_feat<DT>(base, idx), load_feat<DT>(base, idx + 1), load_feat<DT>(base, idx + 2), load_feat<DT>(base, idx + 3)};
-  } else if constexpr (DT == DISCO_BF16) {
-    const u32x2 w = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(base) + idx);
-    return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),
-                 __uint_as_float(w[1] & 0xffff0000u)};
-  } else {
-    return *reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + idx);
-  }
+// Four consecutive values from element idx on.  VEC: they start on a 16-byte boundary.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float* base, int64_t idx) {
+  if constexpr (VEC) return *reinterpret_cast<const f32x4*>(base + idx);
+  return f32x4{base[idx], base[idx + 1], base[idx + 2], base[idx + 3]};
 }
 
 __device__ __forceinline__ int upper_half() { return (threadIdx.x >> 5) & 1; }
@@ -231,37 +214,37 @@ __device__ __forceinline__ void wave_range(int64_t K, int64_t& k0, int64_t& k1) 
 }
 
 // Operand whose reduction index is contiguous: element (row, k) at base[row ld + k], one row per lane and block.
-template <int DT, bool VEC, int R>
+template <bool VEC, int R>
 struct AlongK {
-  const void* base;
+  const float* base;
   int64_t off[R];
-  __device__ __forceinline__ AlongK(const void* p, int64_t ld, int64_t row0, int64_t rows) : base(p) {
+  __device__ __forceinline__ AlongK(const float* p, int64_t ld, int64_t row0, int64_t rows) : base(p) {
 #pragma unroll
     for (int u = 0; u < R; ++u) {
       const int64_t row = row0 + u * 32 + (threadIdx.x & 31);
       off[u] = (row < rows ? row : rows - 1) * ld;       // a row past the end repeats the last; its results are not stored
     }
   }
-  __device__ __forceinline__ f32x4 get4(int u, int64_t k) const { return load_feat4<DT, VEC>(base, off[u] + upper_half() * 4 + k); }
-  __device__ __forceinline__ float get1(int u, int64_t k) const { return load_feat<DT>(base, off[u] + k); }
+  __device__ __forceinline__ f32x4 get4(int u, int64_t k) const { return load4<VEC>(base, off[u] + upper_half() * 4 + k); }
+  __device__ __forceinline__ float get1(int u, int64_t k) const { return base[off[u] + k]; }
 };
 // Operand whose row (column) index is contiguous: element (k, col) at base[k ld + col].
-template <int DT, int R>
+template <int R>
 struct AcrossK {
-  const void* base;
+  const float* base;
   int64_t ld, col[R], up;
-  __device__ __forceinline__ AcrossK(const void* p, int64_t pitch, int64_t col0, int64_t cols) : base(p), ld(pitch), up(upper_half() * 4 * pitch) {
+  __device__ __forceinline__ AcrossK(const float* p, int64_t pitch, int64_t col0, int64_t cols) : base(p), ld(pitch), up(upper_half() * 4 * pitch) {
 #pragma unroll
     for (int u = 0; u < R; ++u) {
       const int64_t c = col0 + u * 32 + (threadIdx.x & 31);
       col[u] = c < cols ? c : cols - 1;
     }
   }
-  __device__ __forceinline__ float get1(int u, int64_t k) const { return load_feat<DT>(base, k * ld + col[u]); }
+  __device__ __forceinline__ float get1(int u, int64_t k) const { return base[k * ld + col[u]]; }
   __device__ __forceinline__ f32x4 get4(int u, int64_t k) const {
     f32x4 v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = load_feat<DT>(base, (k + e) * ld + (col[u] + up));
+    for (int e = 0; e < 4; ++e) v[e] = base[(k + e) * ld + (col[u] + up)];
     return v;
   }
 };
@@ -269,7 +252,7 @@ struct AcrossK {
 // VEC: the pitch is a multiple of 4 floats.
 template <bool VEC, int R>
 struct OwnRows {
-  AlongK<DISCO_F32, VEC, R> rows;
+  AlongK<VEC, R> rows;
   bool own[R];
   __device__ __forceinline__ OwnRows(const float* W, int64_t pitch, int64_t local0, int64_t b)
       : rows(W, pitch, 0, 1) {
@@ -291,16 +274,28 @@ struct SmallShape {
   int64_t b, B, d, pitch;        // pitch: floats between the rows of a block's matrix
   int rank, nb, variant, accumulate;
 };
-__device__ __forceinline__ const void* feat_rows(const void* M, int64_t row, int64_t d, int dt) {
-  return static_cast<const char*>(M) + (size_t)(row * d) * (dt == DISCO_BF16 ? 2 : 4);
+// loss and d/ds from the rows' shares, by one workgroup in fixed order.  red: 2 NW floats of LDS.
+template <int NW>
+__device__ __forceinline__ void small_scalars(const SmallShape& f, float c, const float* row_ce, const float* row_ds, float* loss, float* gs,
+                                              float* red) {
+  float a = 0.f, g = 0.f;
+  for (int64_t i = threadIdx.x; i < f.nb * f.b; i += 64 * NW) { a += row_ce[i]; g += row_ds[i]; }
+  for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); g += __shfl_xor(g, o); }
+  if ((threadIdx.x & 63) == 0) { red[2 * (threadIdx.x >> 6)] = a; red[2 * (threadIdx.x >> 6) + 1] = g; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NW; ++w) { a += red[2 * w]; g += red[2 * w + 1]; }
+    *loss = (f.accumulate ? *loss : 0.f) + c * a;
+    *gs = (f.accumulate ? *gs : 0.f) + c * g;
+  }
 }
 
-template <int DT, bool VEC, int R, int NW>
-__global__ __launch_bounds__(64 * NW) void small_similarity(const void* I, const void* T, SmallShape f, float* ws) {
+template <bool VEC, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void small_similarity(const float* I, const float* T, SmallShape f, float* ws) {
   __shared__ float red[NW][R * R * 16][64];
   const int z = blockIdx.z;
   const int64_t m0 = (int64_t)blockIdx.y * 32 * R, n0 = (int64_t)blockIdx.x * 32 * R;
-  const AlongK<DT, VEC, R> A(feat_rows(z == 0 ? I : T, f.rank * f.b, f.d, DT), f.d, m0, f.b), Bm(z == 0 ? T : I, f.d, n0, f.B);
+  const AlongK<VEC, R> A((z == 0 ? I : T) + f.rank * f.b * f.d, f.d, m0, f.b), Bm(z == 0 ? T : I, f.d, n0, f.B);
   f32x16 acc[R][R];
   clear(acc);
   int64_t k0, k1;
@@ -316,21 +311,12 @@ __global__ __launch_bounds__(64 * NW) void small_similarity(const void* I, const
 // rows [m0, m0 + 32 R) of gT (z = 0) or gI (z = 1), key side of block z plus, in the rank's own rows, the query side of
 // the other block (of the same one for the two-view loss).  The row tiles start at the rank's own rows, whose
 // reduction is the longest.
-template <int DT, bool WVEC, int R, int NW>
-__global__ __launch_bounds__(64 * NW) void small_grads(const void* I, const void* T, SmallShape f, const float* ws, float cs, float c,
+template <bool WVEC, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void small_grads(const float* I, const float* T, SmallShape f, const float* ws, float cs, float c,
                                                        const float* row_ce, const float* row_ds, float* loss, float* gs, float* gI, float* gT) {
   __shared__ float red[NW][R * R * 16][64];
   if (blockIdx.x == 0) {
-    float a = 0.f, g = 0.f;
-    for (int64_t i = threadIdx.x; i < f.nb * f.b; i += 64 * NW) { a += row_ce[i]; g += row_ds[i]; }
-    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); g += __shfl_xor(g, o); }
-    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6][0][0] = a; red[threadIdx.x >> 6][0][1] = g; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int w = 1; w < NW; ++w) { a += red[w][0][0]; g += red[w][0][1]; }
-      *loss = (f.accumulate ? *loss : 0.f) + c * a;
-      *gs = (f.accumulate ? *gs : 0.f) + c * g;
-    }
+    small_scalars<NW>(f, c, row_ce, row_ds, loss, gs, &red[0][0][0]);
     return;
   }
   const int nM = (int)((f.B + 32 * R - 1) / (32 * R)), nN = (int)((f.d + 32 * R - 1) / (32 * R));
@@ -343,18 +329,296 @@ __global__ __launch_bounds__(64 * NW) void small_grads(const void* I, const void
   clear(acc);
   int64_t k0, k1;
   wave_range<NW>(f.b, k0, k1);
-  wave_product<R>(acc, k0, k1, AcrossK<DISCO_F32, R>(ws + (size_t)z * f.b * f.pitch, f.pitch, m0, f.B),
-                  AcrossK<DT, R>(feat_rows(z == 0 ? I : T, r0, f.d, DT), f.d, n0, f.d));
+  wave_product<R>(acc, k0, k1, AcrossK<R>(ws + (size_t)z * f.b * f.pitch, f.pitch, m0, f.B),
+                  AcrossK<R>((z == 0 ? I : T) + (int64_t)r0 * f.d, f.d, n0, f.d));
   if (m0 < r0 + f.b && m0 + 32 * R > r0) {
     const int zq = f.nb == 1 ? 0 : 1 - z;
     wave_range<NW>(f.B, k0, k1);
     wave_product<R>(acc, k0, k1, OwnRows<WVEC, R>(ws + (size_t)zq * f.b * f.pitch, f.pitch, m0 - r0, f.b),
-                    AcrossK<DT, R>(zq == 0 ? T : I, f.d, n0, f.d));
+                    AcrossK<R>(zq == 0 ? T : I, f.d, n0, f.d));
   }
   float* out = z == 0 ? gT : gI;
   join_waves<R, NW>(acc, red, [&](int r, int col, float v) {
     if (m0 + r >= f.B || n0 + col >= f.d) return;
     float* p = out + (m0 + r) * f.d + n0 + col;
+    *p = (f.accumulate ? *p : 0.f) + cs * v;
+  });
+}
+
+// ---- bf16 features: the same two launches on the bf16 matrix instruction (32 x 32 x 16), 64 x 64 tiles.  A similarity
+// is one product, exact in the instruction; a gradient entry, fp32 against bf16, is three: the fp32 value is split in
+// registers into three bf16 planes that add up to it (split3_block), so nothing is rounded that the fp32 instruction would not
+// round.  Per 16 of the reduction that is 96 or 384 matrix cycles of a wave against 2048.
+// A lane supplies 8 consecutive reduction indices (lane / 32 picks which 8 of the 16) of row 2 (lane % 32) + u of row
+// block u: the two blocks' rows are interleaved, so that two neighbouring rows of an operand stored across the
+// reduction come with one load.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) float f32x8;
+
+__device__ __forceinline__ f32x16 mfma_bf16(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// The low or the high halves of eight dwords.
+__device__ __forceinline__ bf16x8 halves(const uint32_t (&w)[8], bool high) {
+  u32x4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    r[e] = high ? __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302u) : __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x05040100u);
+  return __builtin_bit_cast(bf16x8, r);
+}
+// v = p[0] + p[1] + p[2].  (Gradient entries lie in [-1, 1] or are NaN: no plane overflows.)
+__device__ __forceinline__ void split3_block(const f32x8& v, bf16x8 (&p)[3]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    p[0][e] = (__bf16)v[e];
+    const float r1 = v[e] - (float)p[0][e];
+    p[1][e] = (__bf16)r1;
+    p[2][e] = (__bf16)(r1 - (float)p[1][e]);
+  }
+}
+
+// Eight consecutive features from element idx on, in pieces of PIECE elements (8, 4 or 1: what the row pitch and the matrix's
+// address allow).
+template <int PIECE>
+__device__ __forceinline__ bf16x8 load_row8(const uint16_t* p) {
+  u32x4 w;
+  if constexpr (PIECE == 8) {
+    w = *reinterpret_cast<const u32x4*>(p);
+  } else if constexpr (PIECE == 4) {
+    const u32x2 lo = *reinterpret_cast<const u32x2*>(p), hi = *reinterpret_cast<const u32x2*>(p + 4);
+    w = u32x4{lo[0], lo[1], hi[0], hi[1]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (uint32_t)p[2 * e] | (uint32_t)p[2 * e + 1] << 16;
+  }
+  return __builtin_bit_cast(bf16x8, w);
+}
+// The same where only `n` (1 to 8; at most 0: none) of the eight exist, zeros behind them.
+__device__ __forceinline__ bf16x8 load_row8_part(const uint16_t* p, int n) {
+  u32x4 w = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (e < n) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+// This wave's part of a reduction of length K, in 16-deep pieces dealt in runs.
+template <int NW>
+__device__ __forceinline__ void wave_range16(int K, int& k0, int& k1) {
+  const int per = ((K + 15) / 16 + NW - 1) / NW * 16;
+  k0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * per;
+  k1 = k0 + per < K ? k0 + per : K;
+}
+
+// Adds up the waves' partial 64 x 64 tiles in a fixed order, through red (NW / 2 tiles): the upper half of the waves hands
+// its sums to the lower, whose sums are then added in wave order.  out(row, column, value).
+template <int NW, class FOut>
+__device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[64][64], FOut out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto put = [&](int w) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[w][(u * 2 + v) * 16 + r][lane] = acc[u][v][r];
+  };
+  if (wave >= NW / 2) put(wave - NW / 2);
+  __syncthreads();
+  if (wave < NW / 2) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][v][r] += red[wave][(u * 2 + v) * 16 + r][lane];
+    put(wave);                                          // (each lane rewrites what it alone has just read)
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 64 / NW; ++q) {
+    const int idx = q * NW + wave, uv = idx >> 4, r = idx & 15;
+    float s = red[0][idx][lane];
+#pragma unroll
+    for (int w = 1; w < NW / 2; ++w) s += red[w][idx][lane];
+    out(2 * ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) + (uv >> 1), 2 * (lane & 31) + (uv & 1), s);
+  }
+}
+
+template <int PIECE, int NW>
+__global__ __launch_bounds__(64 * NW) void small_similarity_bf16(const uint16_t* I, const uint16_t* T, SmallShape f, float* ws) {
+  __shared__ float red[NW / 2][64][64];
+  const int z = blockIdx.z, l2 = 2 * (threadIdx.x & 31), up = upper_half() * 8, d = (int)f.d;
+  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
+  const uint16_t* X = (z == 0 ? I : T) + f.rank * f.b * f.d;
+  const uint16_t* Y = z == 0 ? T : I;
+  const uint16_t *a[2], *b[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {                         // a row past the end repeats the last; its results are not stored
+    const int64_t m = m0 + l2 + u, n = n0 + l2 + u;
+    a[u] = X + (m < f.b ? m : f.b - 1) * f.d + up;
+    b[u] = Y + (n < f.B ? n : f.B - 1) * f.d + up;
+  }
+  f32x16 acc[2][2];
+  clear(acc);
+  int k0, k1;
+  wave_range16<NW>(d, k0, k1);
+  auto product = [&](const bf16x8 (&x)[2], const bf16x8 (&y)[2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) acc[u][v] = mfma_bf16(x[u], y[v], acc[u][v]);
+  };
+  int k = k0;
+  for (; k + 64 <= k1; k += 64) {                       // four pieces in flight
+    bf16x8 x[4][2], y[4][2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) { x[c][u] = load_row8<PIECE>(a[u] + k + 16 * c); y[c][u] = load_row8<PIECE>(b[u] + k + 16 * c); }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) product(x[c], y[c]);
+  }
+  for (; k + 16 <= k1; k += 16) {
+    const bf16x8 x[2] = {load_row8<PIECE>(a[0] + k), load_row8<PIECE>(a[1] + k)}, y[2] = {load_row8<PIECE>(b[0] + k), load_row8<PIECE>(b[1] + k)};
+    product(x, y);
+  }
+  if (k < k1) {
+    const int n = k1 - k - up;
+    const bf16x8 x[2] = {load_row8_part(a[0] + k, n), load_row8_part(a[1] + k, n)}, y[2] = {load_row8_part(b[0] + k, n), load_row8_part(b[1] + k, n)};
+    product(x, y);
+  }
+  float* W = ws + (size_t)z * f.b * f.pitch;
+  join_waves_64<NW>(acc, red, [&](int r, int c, float v) {
+    if (m0 + r < f.b && n0 + c < f.B) W[(m0 + r) * f.pitch + n0 + c] = v;
+  });
+}
+
+// Two neighbouring features of one row, from an even column of a matrix of even width on a 4-byte boundary (PAIR), or one by
+// one (next: 0 where the second does not exist, the first is then repeated).
+template <bool PAIR>
+__device__ __forceinline__ uint32_t load_feature_pair(const uint16_t* p, int next) {
+  if constexpr (PAIR) return *reinterpret_cast<const uint32_t*>(p);
+  return (uint32_t)p[0] | (uint32_t)p[next] << 16;
+}
+
+// As small_grads.  PAIR: see load_feature_pair.  WVEC: the matrices' pitch is a multiple of 4 floats.
+template <bool PAIR, bool WVEC, int NW>
+__global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, const uint16_t* T, SmallShape f, const float* ws, float cs, float c,
+                                                            const float* row_ce, const float* row_ds, float* loss, float* gs, float* gI, float* gT) {
+  __shared__ float red[NW / 2][64][64];
+  if (blockIdx.x == 0) {
+    small_scalars<NW>(f, c, row_ce, row_ds, loss, gs, &red[0][0][0]);
+    return;
+  }
+  const int nM = (int)((f.B + 63) / 64), nN = (int)((f.d + 63) / 64), r0 = f.rank * (int)f.b, d = (int)f.d;
+  const int w = blockIdx.x - 1, mt_rel = w / (nN * f.nb), rest = w - mt_rel * nN * f.nb, z = rest / nN;
+  const int mt = (mt_rel + r0 / 64) % nM;               // the longest reductions, those of the own rows, first
+  const int m0 = mt * 64, n0 = (rest % nN) * 64;
+  const int l2 = 2 * (threadIdx.x & 31), up = upper_half() * 8;
+  const int n = n0 + l2 < d ? n0 + l2 : (d - 1) & ~1, next = n + 1 < d ? 1 : 0;     // columns n, n + 1 of this lane
+  f32x16 acc[2][2];
+  clear(acc);
+  // One 16-deep piece of a reduction as it comes from memory: this lane's 8 gradient entries of either row block and its 8 pairs
+  // of features.  PART: only the indices below lim exist; the features of the others repeat the last one's, their
+  // gradient entries count as 0.
+  struct Raw { f32x8 g[2]; uint32_t q[8]; };
+  auto features = [&](Raw& t, const uint16_t* M, int k, int lim, auto part) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int kk = !decltype(part)::value || k + up + e < lim ? k + e : lim - 1 - up;
+      t.q[e] = load_feature_pair<PAIR>(M + (int64_t)kk * d, next);
+    }
+  };
+  auto consume = [&](const Raw& t) {
+    const bf16x8 y[2] = {halves(t.q, false), halves(t.q, true)};
+    bf16x8 x[2][3];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) split3_block(t.g[u], x[u]);
+#pragma unroll
+    for (int q = 2; q >= 0; --q)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = mfma_bf16(x[u][q], y[v], acc[u][v]);
+  };
+  // the pieces of [k0, k1), each fetched two ahead of its use
+  auto reduce = [&](int K, auto fetch) {
+    int k0, k1;
+    wave_range16<NW>(K, k0, k1);
+    const int full = k0 < k1 ? (k1 - k0) / 16 : 0;
+    Raw t[3];
+    if (full > 0) fetch(t[0], k0, k1, std::false_type{});
+    if (full > 1) fetch(t[1], k0 + 16, k1, std::false_type{});
+    int i = 0;
+    for (; i + 3 <= full; i += 3) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        if (i + u + 2 < full) fetch(t[(u + 2) % 3], k0 + 16 * (i + u + 2), k1, std::false_type{});
+        consume(t[u]);
+      }
+    }
+    if (i < full) consume(t[0]);
+    if (i + 1 < full) consume(t[1]);
+    if (k0 + 16 * full < k1) {
+      fetch(t[0], k0 + 16 * full, k1, std::true_type{});
+      consume(t[0]);
+    }
+  };
+  {                                                     // key side: G[k][m] down the rank's rows
+    const int m = m0 + l2 < f.B ? m0 + l2 : (int)(f.B - 1) & ~1, mnext = m + 1 < f.B ? 1 : 0;
+    const float* G = ws + (size_t)z * f.b * f.pitch + up * f.pitch + m;
+    const uint16_t* X = (z == 0 ? I : T) + (int64_t)(r0 + up) * d + n;
+    reduce((int)f.b, [&](Raw& t, int k, int lim, auto part) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool in = !decltype(part)::value || k + up + e < lim;
+        const float* p = G + (int64_t)(in ? k + e : lim - 1 - up) * f.pitch;
+        f32x2 v;
+        if constexpr (WVEC) v = *reinterpret_cast<const f32x2*>(p);     // (what lies in the pitch behind a row feeds no stored entry)
+        else v = f32x2{p[0], p[mnext]};
+        t.g[0][e] = in ? v[0] : 0.f;
+        t.g[1][e] = in ? v[1] : 0.f;
+      }
+      features(t, X, k, lim, part);
+    });
+  }
+  if (m0 < r0 + f.b && m0 + 64 > r0) {                  // query side of the own rows: G[m][k] along all rows
+    const int zq = f.nb == 1 ? 0 : 1 - z;
+    const float* G[2];
+    bool own[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int64_t i = m0 + l2 + u - r0;
+      own[u] = i >= 0 && i < f.b;
+      G[u] = ws + (size_t)zq * f.b * f.pitch + (own[u] ? i : 0) * f.pitch + up;
+    }
+    const uint16_t* Y = (zq == 0 ? T : I) + (int64_t)up * d + n;
+    reduce((int)f.B, [&](Raw& t, int k, int lim, auto part) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if constexpr (WVEC && !decltype(part)::value) {
+          const f32x4 lo = *reinterpret_cast<const f32x4*>(G[u] + k), hi = *reinterpret_cast<const f32x4*>(G[u] + k + 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { t.g[u][e] = own[u] ? lo[e] : 0.f; t.g[u][4 + e] = own[u] ? hi[e] : 0.f; }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const bool in = !decltype(part)::value || k + up + e < lim;
+            const float v = G[u][in ? k + e : lim - 1 - up];
+            t.g[u][e] = own[u] && in ? v : 0.f;
+          }
+        }
+      }
+      features(t, Y, k, lim, part);
+    });
+  }
+  float* out = z == 0 ? gT : gI;
+  join_waves_64<NW>(acc, red, [&](int r, int col, float v) {
+    if (m0 + r >= f.B || n0 + col >= d) return;
+    float* p = out + (int64_t)(m0 + r) * d + n0 + col;
     *p = (f.accumulate ? *p : 0.f) + cs * v;
   });
 }
@@ -375,12 +639,13 @@ int64_t row_pitch(int64_t b, int64_t B, size_t nb) {
   return lean_bytes(nb, b, padded) > DISCO_STATIC_SCRATCH_BYTES && lean_bytes(nb, b, B) <= DISCO_STATIC_SCRATCH_BYTES ? B : padded;
 }
 
-// Estimated time of the small kernels: launches, products at the rate they reach (85 TFLOP/s; less with 2-byte loads and with
-// rows that are not whole 16-byte pieces), and the longest reduction that the waves of one workgroup walk (a tile of the
-// rank's own gradient rows).  Against the split kernels (measured, us, d = 512): B = 256, N = 4: 17 / 48; 2048, 16: 73 / 66;
+// Estimated time of the small kernels: launches, products at the rate they reach (fp32 features 85 TFLOP/s, bf16 ones 200; less
+// where rows are not whole pieces), and the longest reduction that the waves of one workgroup walk (a tile of the rank's
+// own gradient rows).  Against the split kernels (measured, us, fp32 features, d = 512): B = 256, N = 4: 17 / 48; 2048, 16: 73 / 66;
 // 2048, 8: 83 / 66; 4096, 16: 142 / 87.
 double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
-  const double macs = 0.5 * nb * (double)b * B * d, slow = (dtype == DISCO_BF16 ? 1.4 : 1.0) * (d % 4 ? 1.9 : 1.0);
+  if (dtype == DISCO_BF16) return 14.0 + 0.5 * nb * (double)b * B * d * (d % 2 ? 1.5 : 1.0) * 12.0 / 200e6 + 1.15 * (b + B) / 128;
+  const double macs = 0.5 * nb * (double)b * B * d, slow = d % 4 ? 1.9 : 1.0;
   const bool big = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
   const double chain = (b + B) * (big ? 32.0 * 4 / 4 : 32.0 / 8) / 2200.0;
   return 14.0 + slow * macs * 12.0 / 85e6 + chain;
@@ -399,34 +664,55 @@ size_t split_bytes(int64_t B, int64_t d, int64_t b, int dtype, int nb, bool lean
   return bytes && us < small_us(b, B, d, dtype, nb) ? bytes : 0;
 }
 
-template <int DT>
-void small_run(const Problem& p, float* W, float* row_ce, float* row_ds, float c) {
+void small_run(const Problem& p) {
   SmallShape f;
   f.b = p.b; f.B = p.B; f.d = p.d; f.nb = loss_blocks(p.variant);
   f.pitch = row_pitch(p.b, p.B, f.nb);
   f.rank = p.rank; f.variant = p.variant; f.accumulate = p.accumulate;
   const unsigned nb = (unsigned)f.nb;
-  // 16-byte pieces of a feature row (8-byte ones in bf16)
-  const uintptr_t align = reinterpret_cast<uintptr_t>(p.I) | reinterpret_cast<uintptr_t>(p.T);
-  const bool vec = p.d % 4 == 0 && align % (DT == DISCO_BF16 ? 8 : 16) == 0;
-  // 64 x 64 tiles (four waves) once they give every compute unit one, else 32 x 32 (eight waves)
-  auto big = [&](int64_t rows, int64_t cols) { return (int64_t)nb * cdiv(rows, 64) * cdiv(cols, 64) >= 256; };
-  auto sim = [&](auto kernel, int tile, int waves) {
-    kernel<<<dim3(cdiv(p.B, tile), cdiv(p.b, tile), nb), 64 * waves, 0, p.stream>>>(p.I, p.T, f, W);
-  };
-  auto grads = [&](auto kernel, int tile, int waves) {
-    kernel<<<dim3(1 + nb * cdiv(p.B, tile) * cdiv(p.d, tile)), 64 * waves, 0, p.stream>>>(p.I, p.T, f, W, c * p.s, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT);
+  const float c = loss_norm(p.B, p.variant), cs = c * p.s;
+  float* W = static_cast<float*>(p.ws);
+  float* row_ce = reinterpret_cast<float*>(static_cast<char*>(p.ws) + matrix_bytes(nb, p.b, f.pitch));
+  float* row_ds = reinterpret_cast<float*>(reinterpret_cast<char*>(row_ce) + align_up((size_t)nb * p.b * sizeof(float)));
+  const uintptr_t address = reinterpret_cast<uintptr_t>(p.I) | reinterpret_cast<uintptr_t>(p.T);
+  const bool wvec = f.pitch % 4 == 0;
+  auto sim_grid = [&](int tile) { return dim3(cdiv(p.B, tile), cdiv(p.b, tile), nb); };
+  auto grad_grid = [&](int tile) { return dim3(1 + nb * cdiv(p.B, tile) * cdiv(p.d, tile)); };
+  auto softmax = [&] {
+    stage_mark(p.stream, 1);
+    naive_row_softmax<<<dim3((unsigned)p.b, nb), 256, 0, p.stream>>>(W, p.b, p.B, f.pitch, p.rank, p.s, row_ce, row_ds, p.variant);
+    stage_mark(p.stream, 2);
+    stage_mark(p.stream, 3);
   };
   stage_mark(p.stream, 0);
-  if (big(p.b, p.B)) { if (vec) sim(small_similarity<DT, true, 2, 4>, 64, 4); else sim(small_similarity<DT, false, 2, 4>, 64, 4); }
-  else { if (vec) sim(small_similarity<DT, true, 1, 8>, 32, 8); else sim(small_similarity<DT, false, 1, 8>, 32, 8); }
-  stage_mark(p.stream, 1);
-  naive_row_softmax<<<dim3((unsigned)p.b, nb), 256, 0, p.stream>>>(W, p.b, p.B, f.pitch, p.rank, p.s, row_ce, row_ds, p.variant);
-  stage_mark(p.stream, 2);
-  stage_mark(p.stream, 3);
-  const bool wvec = f.pitch % 4 == 0;
-  if (big(p.B, p.d)) { if (wvec) grads(small_grads<DT, true, 2, 4>, 64, 4); else grads(small_grads<DT, false, 2, 4>, 64, 4); }
-  else { if (wvec) grads(small_grads<DT, true, 1, 8>, 32, 8); else grads(small_grads<DT, false, 1, 8>, 32, 8); }
+  if (p.dtype == DISCO_BF16) {
+    const uint16_t* I = static_cast<const uint16_t*>(p.I);
+    const uint16_t* T = static_cast<const uint16_t*>(p.T);
+    auto sim = [&](auto kernel) { kernel<<<sim_grid(64), 256, 0, p.stream>>>(I, T, f, W); };
+    auto grads = [&](auto kernel) { kernel<<<grad_grid(64), 512, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT); };
+    if (p.d % 8 == 0 && address % 16 == 0) sim(small_similarity_bf16<8, 4>);
+    else if (p.d % 4 == 0 && address % 8 == 0) sim(small_similarity_bf16<4, 4>);
+    else sim(small_similarity_bf16<1, 4>);
+    softmax();
+    const bool pair = p.d % 2 == 0 && address % 4 == 0;
+    if (pair) { if (wvec) grads(small_grads_bf16<true, true, 8>); else grads(small_grads_bf16<true, false, 8>); }
+    else { if (wvec) grads(small_grads_bf16<false, true, 8>); else grads(small_grads_bf16<false, false, 8>); }
+  } else {
+    const float* I = static_cast<const float*>(p.I);
+    const float* T = static_cast<const float*>(p.T);
+    const bool vec = p.d % 4 == 0 && address % 16 == 0;
+    // 64 x 64 tiles (four waves) once they give every compute unit one, else 32 x 32 (eight waves)
+    auto big = [&](int64_t rows, int64_t cols) { return (int64_t)nb * cdiv(rows, 64) * cdiv(cols, 64) >= 256; };
+    auto sim = [&](auto kernel, int tile, int waves) { kernel<<<sim_grid(tile), 64 * waves, 0, p.stream>>>(I, T, f, W); };
+    auto grads = [&](auto kernel, int tile, int waves) {
+      kernel<<<grad_grid(tile), 64 * waves, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT);
+    };
+    if (big(p.b, p.B)) { if (vec) sim(small_similarity<true, 2, 4>, 64, 4); else sim(small_similarity<false, 2, 4>, 64, 4); }
+    else { if (vec) sim(small_similarity<true, 1, 8>, 32, 8); else sim(small_similarity<false, 1, 8>, 32, 8); }
+    softmax();
+    if (big(p.B, p.d)) { if (wvec) grads(small_grads<true, 2, 4>, 64, 4); else grads(small_grads<false, 2, 4>, 64, 4); }
+    else { if (wvec) grads(small_grads<true, 1, 8>, 32, 8); else grads(small_grads<false, 1, 8>, 32, 8); }
+  }
   stage_mark(p.stream, 4);
   stage_mark(p.stream, 5);
 }
@@ -442,17 +728,21 @@ size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int var
   return split > least ? split : least;             // (unaligned gradients take the small kernels whatever the plan)
 }
 
+// Is a call that the bf16 tile kernels take faster on the small ones?  Few tiles leave those kernels with their seven launches,
+// 27 us on top of the tiles' estimate whatever the shape; the small ones are three.  (Measured, us, tiles / small, bf16:
+// B = 256, N = 1, d = 128: 34 / 21; 512, 2, 256: 37 / 25; 1024, 4, 512: 44 / 34; 1024, 2, 256: 41 / 38; 2048, 16, 512: 45 / 42;
+// 1024, 1, 512: 51 / 53; 2048, 4, 256: 43 / 54; 4096, 32, 512: 46 / 66.)
+bool small_beats_tiles(int64_t B, int64_t d, int32_t N, int variant) {
+  const double us = small_us(B / N, B, d, DISCO_BF16, loss_blocks(variant));
+  return us < 60.0 && us < mfma_stored_estimate_us(B, d, N, variant) + 27.0;
+}
+
 int naive_run(const Problem& p) {
   const int64_t b = p.b, B = p.B;
   const int nb = loss_blocks(p.variant);
   size_t limit;
   if (split_bytes(B, p.d, b, p.dtype, nb, p.lean, &limit) && split_aligned(p)) return split_run(p, limit);
-  float* W = static_cast<float*>(p.ws);
-  float* row_ce = reinterpret_cast<float*>(static_cast<char*>(p.ws) + matrix_bytes(nb, b, row_pitch(b, B, nb)));
-  float* row_ds = reinterpret_cast<float*>(reinterpret_cast<char*>(row_ce) + align_up((size_t)nb * b * sizeof(float)));
-  const float c = loss_norm(B, p.variant);
-  if (p.dtype == DISCO_BF16) small_run<DISCO_BF16>(p, W, row_ce, row_ds, c);
-  else small_run<DISCO_F32>(p, W, row_ce, row_ds, c);
+  small_run(p);
   return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
 }
 

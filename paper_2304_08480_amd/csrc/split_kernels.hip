@@ -512,7 +512,7 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
 }
 
 // The plan whose rows are taken in as few chunks as keep the workspace within `limit` (0 bytes in `total`: there is none).
-SplitPlan plan_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit) {
+SplitPlan compare_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit) {
   const int np = dtype == DISCO_BF16 ? 1 : 3;
   for (int64_t chunks = 1;; chunks *= 2) {
     const int64_t chunk = chunks == 1 ? b : round_up((b + chunks - 1) / chunks, 256);
@@ -520,6 +520,11 @@ SplitPlan plan_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t
     if (pl.total <= limit) return pl;
     if (chunk <= 256) { pl.total = 0; return pl; }
   }
+}
+
+SplitPlan plan_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit) {
+  static thread_local PlanCache<SplitPlan, 6> cache;
+  return cache.get({B, d, b, dtype, nb, (int64_t)limit}, [&] { return compare_within(B, d, b, dtype, nb, limit); });
 }
 
 }  // namespace

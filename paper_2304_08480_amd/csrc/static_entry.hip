@@ -38,11 +38,13 @@ extern "C" int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B
   const int r = disco_resolve_path(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = disco_workspace_bytes(B, d, N, dtype, r);
+  // what AUTO would take, or, where that is too much, the path it resolves to by name
+  size_t need = disco_workspace_bytes(B, d, N, dtype, path);
+  if (need > DISCO_STATIC_SCRATCH_BYTES) { path = r; need = disco_workspace_bytes(B, d, N, dtype, path); }
   if (need == 0 || need > DISCO_STATIC_SCRATCH_BYTES) return DISCO_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return DISCO_ERR_HIP;
-  return disco_loss_fwd_bwd(I, T, B, d, rank, N, s, dtype, r, accumulate, loss, gI, gT, gs, ws, DISCO_STATIC_SCRATCH_BYTES,
+  return disco_loss_fwd_bwd(I, T, B, d, rank, N, s, dtype, path, accumulate, loss, gI, gT, gs, ws, DISCO_STATIC_SCRATCH_BYTES,
                             hip_stream);
 }
 

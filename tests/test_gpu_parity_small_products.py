@@ -22,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (96, 63, 96, 0),        # one row per rank, odd width
     (2178, 68, 2, 0),       # 64 x 64 tiles in the similarities, 32 x 32 in the gradients, shares of 1089 rows
     (4230, 130, 6, 1),      # 64 x 64 tiles in both, shares of 705 rows that straddle them
+    (200, 48, 1, 0),        # three 16-deep pieces of d: a wave without one, rows past the last tile
+    (513, 128, 1, 0),       # an odd batch: the last row of a pair does not exist
+    (150, 77, 2, 2),        # odd width: features one by one; bf16 rows on 4-byte boundaries
 ])
 def test_small_products(B, d, N, shift, dtype):
     s = 14.285714
@@ -55,3 +58,23 @@ def test_small_products(B, d, N, shift, dtype):
     assert l2 == pytest.approx(2.0 + loss, rel=1e-6) and g2 == pytest.approx(1.0 + gs, rel=1e-6)
     np.testing.assert_allclose(a2, gI + 0.5, rtol=1e-6)
     np.testing.assert_allclose(t2, gT - 0.25, rtol=1e-6)
+
+
+@pytest.mark.parametrize("B,d,N", [(256, 128, 1), (512, 256, 2), (1024, 64, 4)])
+def test_auto_runs_a_call_of_a_few_tiles_in_fp32_arithmetic(B, d, N):
+    # such a call resolves to a bf16 tile path, whose numerators would cost 1e-5 and more of the gradients' 2-norm
+    s = 14.285714
+    I, T = clip_pairs(B, d, 32)
+    Ib, Tb = f32_to_bf16_bits(I), f32_to_bf16_bits(T)
+    I, T = bf16_bits_to_f32(Ib), bf16_bits_to_f32(Tb)
+    Id, Td, dt = to_device(I, T, Ib, Tb, "bf16")
+    assert dl.disco_resolve_path(B, d, N, dt, dl.DISCO_PATH_AUTO) != dl.DISCO_PATH_NAIVE
+    run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_AUTO)
+    run.rank(N - 1, s)
+    loss, gI, gT, gs = run.results()
+    ref = oc.disco_rank(I, T, s, N - 1, N)
+    sI, sT, fl = term_scale(oc, I, T, s, N - 1, N)
+    check_scalar("loss", loss, ref[0], TOL["f32"]["scalar"])
+    check_scalar("gs", gs, ref[3], TOL["f32"]["scalar"] * 10, abs_tol=1e-9)
+    check_tensor("gI", gI, ref[1], "f32", sI, fl)
+    check_tensor("gT", gT, ref[2], "f32", sT, fl)
