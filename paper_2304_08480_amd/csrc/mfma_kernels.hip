@@ -4,8 +4,8 @@
 //
 // For one block with query rows X (b x d, the rank's rows) and key rows Y (B x d):
 //   z_ij   = s <x_i, y_j>                      z2 = z * log2(e)   (all exponentials are base 2)
-//   ref2_i = z2 of the positive pair (i, label_i), lifted where needed so that no z2_ij - ref2_i
-//            exceeds 100 (overflow guard from the row norms, Cauchy-Schwarz)
+//   ref2_i = z2 of the positive pair (i, label_i), lifted where needed so that no key of the positive's norm gives a
+//            z2_ij - ref2_i above 100 (overflow guard, Cauchy-Schwarz)
 //   E_ij   = exp2(z2_ij - ref2_i)  for j != label_i, stored as bf16 (b x B);  E_i,label = 0 in the
 //            store and kept separately in fp32 as e_i
 //   tot_i  = sum_j E_ij + e_i,  beta_i = 1/tot_i,  P_ij = beta_i E_ij,
@@ -13,11 +13,10 @@
 //   query-side gradient  gX_i = c s [ beta_i (E Y)_i + (P_i,label - 1) y_label ]
 //   key-side gradient    gY_j = c s [ sum_i E_ij beta_i x_i  (+ (P_i,label - 1) x_i  if j = label_i) ]
 //   d/ds share           c <gX_i / (c s), x_i>  summed over i   (sum_ij G_ij S_ij = <G Y, X>)
-// Since lse_i >= z_i,label, every E_ij that underflows is negligible against the row total.  Where the guard
-// lifts ref2_i so far above every logit of the row that the row total itself falls below 2^-60 (rows of large
-// norm whose cosines are all small, positives far below the Cauchy-Schwarz bound), k_row_merge flags the row's
-// query tile and k_logit_repair redoes that tile with the true row maximum as its reference (a slow path for
-// inputs that are not CLIP-like; it returns at once when nothing is flagged).
+// Since lse_i >= z_i,label, every E_ij that underflows is negligible against the row total.  Where the guard lifts ref2_i so
+// far above every logit of the row that its total falls below 2^-60 (rows of large norm whose cosines are all small), or
+// keys of much larger norm than the positive's take it above 2^120, or the total is no number, k_row_merge redoes the row's
+// group of 64 with the true row maxima as references (a slow path for inputs that are not CLIP-like).
 //
 // One NT tile main loop (mfma_tile.h: 256x256x64 by 8 waves, or 128x128x64 by 4, of MFMA 32x32x16 blocks, operands
 // loaded global -> LDS directly into a ring of five units) serves all three contractions; operands whose
@@ -31,7 +30,8 @@ namespace {
 using namespace tile;
 
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr float REF_HEADROOM = 100.f;                    // largest exponent (base 2) a stored numerator may reach
+constexpr float REF_HEADROOM = 100.f;                    // largest exponent (base 2) a stored numerator should reach
+constexpr float ROW_TOTAL_FLOOR = 0x1p-60f, ROW_TOTAL_MAX = 0x1p120f;   // a row whose total lies outside has lost terms
 
 constexpr int BM = 256, BN = 256, NTHREADS = Cfg<256>::NTHREADS;     // the symmetric path's tiles
 
@@ -54,10 +54,7 @@ struct BlockPtrs {
   float* lpart;          // (2B/T) x b partial row sums (label column excluded) of logit tiles of size T
   float* ediag;          // b: numerator of the label column
   float* zd2;            // b: z2 of the positive pair
-  float* xnorm;          // b: |x_i|
-  float* ref2;           // b: exponent reference of the row (written by the statistics pass, replaced by a repair)
-  int* tileflag;         // b / T: set when a row of that query tile has lost its row total to underflow
-  const float* ymax_parts; // NORM_BLOCKS partial maxima of |y_j|^2
+  float* ref2;           // b: exponent reference of the row
   float* beta;           // b
   float* gdiag;          // b: P_label - 1
   float* ce;             // b
@@ -89,92 +86,48 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Exponent reference (base 2) of a row: its positive-pair logit, lifted to the row's Cauchy-Schwarz bound minus the
-// headroom where that is larger.  One explicit fma, so that every kernel that forms it gets the same bits.
-__device__ __forceinline__ float row_reference(float zd2, float xnorm, float ymax, float s2) {
-  return fmaxf(zd2, __fmaf_rn(fabsf(s2) * xnorm, ymax, -REF_HEADROOM));
-}
-
-constexpr int NORM_BLOCKS = 512;     // workgroups per matrix that take row norms = partial maxima per matrix
-static_assert(NORM_BLOCKS == 512, "the logit kernels fold the partial maxima one or two per thread");
-
-// Preparation, two kinds of workgroup in one launch (they are independent of each other):
-//  * blockIdx.x < 2 NORM_BLOCKS: partial maximum over rows of |row|^2 of I (first NORM_BLOCKS workgroups) or T,
-//    for the overflow guard, to wgmax[which * NORM_BLOCKS + index].  A wave takes 8 rows at a time (one 16-byte
-//    load per lane and row in flight, d is a multiple of 8) and reduces the 8 row sums with interleaved
-//    butterflies.  No atomics: the consumers fold the partial maxima (max is exact, so order does not matter).
-//  * the rest: positive-pair logit and query norm of every local row, one wave per (block, row); the first of
-//    these workgroups also clears the query-tile repair flags of both blocks.  The positive of local row i is
-//    key row label_row(rank b + i): the same global row for the CLIP loss, the other view's row for the two-view loss.
-//    B, b: the real sizes; bp: b rounded up to whole tiles (the padding rows get a zero logit and a zero norm).
-__global__ __launch_bounds__(256) void k_prep(Blocks bl, const uint16_t* I, const uint16_t* T, int64_t B, int64_t b, int64_t bp, int64_t d,
-                                              int rank, float s2, float* wgmax) {
+// Positive-pair logit and exponent reference of every local row, one wave per (block, row).  The positive of local row i is
+// key row label_row(rank b + i): the same global row for the CLIP loss, the other view's row for the two-view loss.
+// B, b: the real sizes; bp: b rounded up to whole tiles (the padding rows get zeros).  The guard takes the positive's norm
+// for that of every key, which unit-norm features make true: a pass over all rows for their largest norm costs 10 us of a
+// call at B = 32768, d = 512 and 75 at 196608, and k_row_merge finds the rows for which it was not true.  NORMS (symmetric
+// path): leaves |x_i| and |y_label| in beta and gdiag, which are free until the merge.
+template <bool NORMS>
+__global__ __launch_bounds__(256) void k_prep(Blocks bl, int64_t B, int64_t b, int64_t bp, int64_t d, int rank, float s2) {
   if (gated_off(bl)) return;
-  __shared__ float red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (blockIdx.x < 2 * NORM_BLOCKS) {
-    const int which = blockIdx.x / NORM_BLOCKS, idx = blockIdx.x % NORM_BLOCKS;
-    const uint16_t* M = which == 0 ? I : T;
-    float best = 0.f;
-    for (int64_t row0 = ((int64_t)idx * 4 + wave) * 8; row0 < B; row0 += (int64_t)NORM_BLOCKS * 32) {
-      float a[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) a[r] = 0.f;
-      for (int64_t k = lane * 8; k < d; k += 512) {
-        u32x4 v[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int64_t row = row0 + r < B ? row0 + r : B - 1;     // clamp: a repeated row does not change the max
-          v[r] = *reinterpret_cast<const u32x4*>(M + row * d + k);
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            a[r] = fmaf(bf16_lo(v[r][q]), bf16_lo(v[r][q]), a[r]);
-            a[r] = fmaf(bf16_hi(v[r][q]), bf16_hi(v[r][q]), a[r]);
-          }
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int r = 0; r < 8; ++r) a[r] += __shfl_xor(a[r], o);
-#pragma unroll
-      for (int r = 0; r < 8; ++r) best = fmaxf(best, a[r]);
-    }
-    if (lane == 0) red[wave] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) wgmax[which * NORM_BLOCKS + idx] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    return;
-  }
   const int64_t rb = (bp + 3) / 4;                      // row workgroups per block
-  const int64_t q = (int64_t)blockIdx.x - 2 * NORM_BLOCKS;
-  if (q == 0)
-    for (int64_t it = threadIdx.x; it < bp / 128; it += 256) { bl.z[0].tileflag[it] = 0; bl.z[1].tileflag[it] = 0; }
-  const BlockPtrs& p = bl.z[q / rb];
-  const int64_t i = (q % rb) * 4 + wave;
+  const BlockPtrs& p = bl.z[blockIdx.x / rb];
+  const int64_t i = (blockIdx.x % rb) * 4 + wave;
   if (i >= bp) return;
   if (i >= b) {
-    if (lane == 0) { p.zd2[i] = 0.f; p.xnorm[i] = 0.f; }
+    if (lane == 0) { p.zd2[i] = 0.f; p.ref2[i] = 0.f; }
     return;
   }
   const uint16_t* x = p.X + i * d;
   const uint16_t* y = p.Y + label_row((int64_t)rank * b + i, B, bl.variant) * d;
-  float dot = 0.f, nn = 0.f;
+  float dot = 0.f, xx = 0.f, yy = 0.f;
   for (int64_t k = lane * 8; k < d; k += 512) {          // 16-byte pieces (d is a multiple of 8, the rows are 16-byte aligned)
     const u32x4 xw = *reinterpret_cast<const u32x4*>(x + k), yw = *reinterpret_cast<const u32x4*>(y + k);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float x0 = bf16_lo(xw[q]), x1 = bf16_hi(xw[q]);
-      dot = fmaf(x0, bf16_lo(yw[q]), dot);
-      dot = fmaf(x1, bf16_hi(yw[q]), dot);
-      nn = fmaf(x0, x0, nn);
-      nn = fmaf(x1, x1, nn);
+      const float x0 = bf16_lo(xw[q]), x1 = bf16_hi(xw[q]), y0 = bf16_lo(yw[q]), y1 = bf16_hi(yw[q]);
+      dot = fmaf(x0, y0, dot);
+      dot = fmaf(x1, y1, dot);
+      xx = fmaf(x0, x0, xx);
+      xx = fmaf(x1, x1, xx);
+      yy = fmaf(y0, y0, yy);
+      yy = fmaf(y1, y1, yy);
     }
   }
   dot = wave_sum(dot);
-  nn = wave_sum(nn);
-  if (lane == 0) { p.zd2[i] = s2 * dot; p.xnorm[i] = sqrtf(nn); }
+  xx = sqrtf(wave_sum(xx));
+  yy = sqrtf(wave_sum(yy));
+  if (lane == 0) {
+    p.zd2[i] = s2 * dot;
+    p.ref2[i] = fmaxf(s2 * dot, fmaf(fabsf(s2) * xx, yy, -REF_HEADROOM));
+    if (NORMS) { p.beta[i] = xx; p.gdiag[i] = yy; }
+  }
 }
 
 // Operands of a ragged share (the rank's rows or the batch are not whole 256-row tiles): zero-padded copies of I and T
@@ -202,7 +155,7 @@ __global__ __launch_bounds__(256) void k_pad_operands(const uint16_t* I, const u
 // rows, inside a group key piece by key piece (formats FMT_KA / FMT_RA of mfma_tile.h).
 // (The definition of the layout; the epilogue below forms the same address piecewise, which the compiler turns into
 // a percent faster code than a call of this function.)
-[[maybe_unused]] __device__ __forceinline__ int64_t e_index(int64_t i, int64_t jl, int64_t W) {
+__device__ __forceinline__ int64_t e_index(int64_t i, int64_t jl, int64_t W) {
   return ((i >> 6) * (W >> 3) + (jl >> 3)) * 512 + (i & 63) * 8 + (jl & 7);
 }
 
@@ -216,8 +169,7 @@ __global__ __launch_bounds__(256) void k_pad_operands(const uint16_t* I, const u
 // Local query row i is global row g0 + i; its label is key row label_row(g0 + i), and for the two-view loss its own
 // key row g0 + i is left out of its softmax (stored as 0, in no sum), and so are the padding columns from key row
 // nkeys (the batch size) on (MASK_EDGE only:
-// the caller takes that variant for the tiles they fall into).  LOCAL (with STATS): the row sums and the label numerators
-// are added into rs / kept in ed (registers of the lane, indexed like ref2) instead of being written to lpart / ediag.
+// the caller takes that variant for the tiles they fall into).
 // jl0: first key column of the tile relative to the panel of width W that p.E holds.  STREAM: streaming stores
 // (written once, read by later kernels: keeps the operand tiles in L2).  STAGE: also leave the bf16 tile in LDS,
 // row-major T x T (8-byte granules XOR-swizzled with the row: conflict-free 8-byte writes and 16-byte reads),
@@ -241,10 +193,10 @@ __device__ __forceinline__ bool tile_has_marked_columns(int64_t g, int64_t B, in
 
 enum { MASK_NONE = 0, MASK_DIAG = 1, MASK_EDGE = 2 };     // MASK_EDGE: label / left-out columns and padding columns
 
-template <int T, bool STATS, bool STORE, int MASK, bool LOCAL = false, bool STAGE = false, bool STREAM = true>
+template <int T, bool STATS, bool STORE, int MASK, bool STAGE = false, bool STREAM = true>
 __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::NFA>& acc, char* smem, int64_t b, float s2, int64_t i0,
                                                int64_t j0, int64_t g0, int variant, int64_t nkeys, const float (&ref2)[2],
-                                               int64_t jl0, int64_t W, float* rs = nullptr, float* ed = nullptr) {
+                                               int64_t jl0, int64_t W) {
   constexpr bool DIAG = MASK != MASK_NONE, EDGE = MASK == MASK_EDGE;
   constexpr int WTM = Cfg<T>::WTM, NFA = Cfg<T>::NFA;      // a wave's key columns: 128 (T = 256) or 64
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -280,8 +232,7 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             if (dl == bm * 32 + q * 8 + r) {
-              if (STATS && LOCAL) ed[bn] = e[r];
-              else if (STATS) p.ediag[i] = e[r];
+              if (STATS) p.ediag[i] = e[r];
               e[r] = 0.f;
             }
 #pragma unroll
@@ -312,9 +263,7 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
         }
       }
     }
-    if (STATS && LOCAL) {
-      rs[bn] += rowsum;
-    } else if (STATS) {
+    if (STATS) {
       rowsum += __shfl_xor(rowsum, 32);
       if (half == 0) p.lpart[((T == 256 ? j0 >> 7 : j0 >> 6) + wm) * b + i] = rowsum;
     }
@@ -328,8 +277,6 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
 //   STORE: write the bf16 numerators to E (panel-relative columns, atom storage, see e_index).
 // materialized path: STATS and STORE, one panel = all keys.  fused path: a STATS-only pass over all
 // keys (nothing of size b x B is written), then STORE-only passes that recompute one panel at a time.
-// A STATS pass derives the rows' exponent references (row_reference; k_row_merge records the same values in ref2);
-// a pass without STATS reads them from ref2, so that it sees the references a repair has replaced.
 // b: the rank's rows rounded up to whole tiles; B: the key rows that exist (the panel widths cover them rounded up to
 // whole tiles); g0: global row of the rank's first row.  RAGGED: the last key tile may hold padding columns (the
 // instance without it keeps the tile walk free of that variant of the epilogue and of the registers it costs).
@@ -349,27 +296,6 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int
   const int total = nI * nJ;
   const int chunk = (total + 7) >> 3, padded = chunk << 3;
   const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) % Cfg<T>::WN;
-  // max_j |y_j| of each block's key matrix, folded from the partial maxima (one per thread, T = 128: two)
-  float ymax_z[2];
-  {
-    float* red = reinterpret_cast<float*>(smem);
-#pragma unroll
-    for (int z = 0; z < 2; ++z) {
-      float m = bl.z[z].ymax_parts[threadIdx.x];
-      if (T == 128) m = fmaxf(m, bl.z[z].ymax_parts[threadIdx.x + 256]);
-      for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-      if (lane == 0) red[z * 8 + (threadIdx.x >> 6)] = m;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int z = 0; z < 2; ++z) {
-      float m = red[z * 8];
-#pragma unroll
-      for (int w = 1; w < Cfg<T>::WAVES; ++w) m = fmaxf(m, red[z * 8 + w]);
-      ymax_z[z] = sqrtf(m);
-    }
-    __syncthreads();
-  }
   for (int v = blockIdx.x; v < nblk * padded; v += gridDim.x) {
     const int z = v >= padded ? 1 : 0;
     const int u = v - z * padded;
@@ -384,11 +310,10 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int
     // not waited for in the epilogue
     float ref2[2];
     {
-      const float ymax = z ? ymax_z[1] : ymax_z[0];
 #pragma unroll
       for (int bn = 0; bn < 2; ++bn) {
         const int64_t i = i0 + wn * 64 + bn * 32 + (lane & 31);
-        ref2[bn] = STATS ? row_reference(p.zd2[i], p.xnorm[i], ymax, s2) : p.ref2[i];
+        ref2[bn] = p.ref2[i];
       }
     }
     Acc<Cfg<T>::NFA> acc;
@@ -409,7 +334,6 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int
 }
 
 constexpr float LN2 = 0.6931471805599453f;
-constexpr float ROW_TOTAL_FLOOR = 0x1p-60f;
 
 // beta, P_label - 1 and the cross-entropy of row i from its off-label sum, its label numerator and their total.
 // ce = log(tot / ed); when the label numerator does not dominate it is taken from the exponents,
@@ -469,176 +393,167 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
     }
 }
 
-// Row totals -> beta, P_label - 1, cross-entropy.  A workgroup takes 64 rows; its 16 waves each add a
-// sixteenth of the column parts (lane = row, so the reads are coalesced), combined in fixed order.
-// nparts0 / nparts1: number of partial sums per row of block 0 / block 1.  global_ref (symmetric full loss): the one
-// exponent reference every row shares; bad_flag: where that path records that a row or column total was lost
-// (the per-rank paths flag the row's query tile for repair instead).  d > 0: the workgroup goes on to write its
-// rows of Xs = (beta x)^T (a query tile that is repaired afterwards rewrites its rows there); d = 0: not.
-// tile_rows: rows of a query tile of the logit kernel (what the repair flags count).
-__global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, int64_t b, int nparts0, int nparts1, float s2,
-                                                    const float* global_ref, int* bad_flag, int64_t d, int tile_rows) {
-  if (gated_off(bl)) return;
-  const int nparts = blockIdx.y ? nparts1 : nparts0;
-  __shared__ float red[16][64];
-  __shared__ float ymax_w[8];
-  __shared__ float beta_s[64];
-  __shared__ float tile[64][65];
-  const BlockPtrs& p = bl.z[blockIdx.y];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // max_j |y_j| folded from the partial maxima exactly as k_logit_tiles folds it (max is exact in any order)
-  if (threadIdx.x < NORM_BLOCKS) {
-    float m = p.ymax_parts[threadIdx.x];
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (lane == 0) ymax_w[wave] = m;
-  }
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-  if (i < b) {
-    int q = wave;
-    for (; q + 112 < nparts; q += 128) {                 // eight loads in flight
-      float v[8];
+// The statistics of 64 rows redone by the workgroup of k_row_merge that found one whose total is lost (inputs that are not
+// CLIP-like; nothing here is fast): a first sweep over all keys finds every row's true maximum logit, its new exponent
+// reference, a second forms the numerators (stored to E if `store`) and the row sums against it.  Operand fragments come
+// straight from memory; wave w takes the key strips w, w + 16, ... of 32 keys against all 64 rows, laid out like the tiles
+// of the logit kernel (key rows on the M side).  Local rows i0 .. i0 + 63, global row g0 + i; Bp: key rows that exist in
+// memory, a multiple of 32.  Leaves the rows' sums in off_s and their label numerators in ed_s.
+__device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool store,
+                                       float (*red)[64], float* ref_s, float* off_s, float* ed_s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, half = lane >> 5;
+  const uint16_t* x[2] = {p.X + (i0 + l32) * d + half * 8, p.X + (i0 + 32 + l32) * d + half * 8};
+  f32x16 acc[2];
+  auto strip = [&](int64_t j0) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p.lpart[(int64_t)(q + 16 * u) * b + i];
-      a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
-      a0 += v[4]; a1 += v[5]; a2 += v[6]; a3 += v[7];
+    for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+    const uint16_t* y = p.Y + (j0 + l32) * d + half * 8;
+    for (int64_t k = 0; k < d; k += 16) {
+      const u32x4 a = *reinterpret_cast<const u32x4*>(y + k);
+      mfma1(acc[0], a, *reinterpret_cast<const u32x4*>(x[0] + k));
+      mfma1(acc[1], a, *reinterpret_cast<const u32x4*>(x[1] + k));
     }
-    for (; q + 48 < nparts; q += 64) {
-      a0 += p.lpart[(int64_t)q * b + i];
-      a1 += p.lpart[(int64_t)(q + 16) * b + i];
-      a2 += p.lpart[(int64_t)(q + 32) * b + i];
-      a3 += p.lpart[(int64_t)(q + 48) * b + i];
-    }
-    for (; q < nparts; q += 16) a0 += p.lpart[(int64_t)q * b + i];
+  };
+  int64_t label[2], self[2];
+#pragma unroll
+  for (int bn = 0; bn < 2; ++bn) {
+    const int64_t g = g0 + i0 + bn * 32 + l32;
+    label[bn] = label_row(g, keys, variant);
+    self[bn] = masked_col(g, variant);
   }
-  red[wave][lane] = (a0 + a1) + (a2 + a3);
-  __syncthreads();
-  if (wave == 0 && i < b) {
-    if (i >= bl.rows) {                                 // a padding row: no weight anywhere, no flag
-      p.ref2[i] = 0.f; p.beta[i] = 0.f; p.gdiag[i] = 0.f; p.ce[i] = 0.f;
-      beta_s[lane] = 0.f;
-    } else {
-      float off = 0.f;
+  float m[2] = {-INFINITY, -INFINITY};
+  for (int64_t j0 = wave * 32; j0 < Bp; j0 += 16 * 32) {
+    strip(j0);
 #pragma unroll
-      for (int w = 0; w < 16; w += 4) off += (red[w][lane] + red[w + 1][lane]) + (red[w + 2][lane] + red[w + 3][lane]);
-      float ym = ymax_w[0];
+    for (int bn = 0; bn < 2; ++bn)
 #pragma unroll
-      for (int w = 1; w < 8; ++w) ym = fmaxf(ym, ymax_w[w]);
-      p.ref2[i] = global_ref ? *global_ref : row_reference(p.zd2[i], p.xnorm[i], sqrtf(ym), s2);   // what the statistics pass used
-      const float ed = p.ediag[i];
-      const float tot = off + ed;
-      beta_s[lane] = row_outputs(p, i, off, ed, tot);
-      // The guard lifted the reference so far above every logit of this row that its total is (next to) lost:
-      // the row's query tile is redone against the true row maximum.  Also catches non-finite totals.
-      if (!(tot >= ROW_TOTAL_FLOOR)) {
-        if (bad_flag) *bad_flag = 1;
-        else p.tileflag[i / tile_rows] = 1;
+      for (int e = 0; e < 16; ++e) {
+        const int64_t j = j0 + (e >> 2) * 8 + half * 4 + (e & 3);
+        if (j < keys && j != self[bn]) m[bn] = fmaxf(m[bn], acc[bn][e] * s2);
       }
-    }
   }
-  if (d > 0 && (int64_t)blockIdx.x * 64 + 64 <= b) scale_transpose_rows<1024>(p, b, d, (int64_t)blockIdx.x * 64, 64, beta_s, tile);
-}
-
-// The statistics kernels of a flagged query tile, redone by one workgroup per (block, query tile): a first
-// sweep over all keys finds every row's true maximum logit, which becomes its exponent reference (ref2), a
-// second sweep forms the numerators (stored to E when STORE) and the row sums against it, and the rows'
-// beta, P_label - 1 and cross-entropy are written directly.  Workgroups of tiles that are not flagged return
-// at once, which is the normal case: the kernel then costs one launch.
-template <int T, bool STORE>
-__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_repair(Blocks bl, int64_t b, int64_t B, int64_t d, int rank, float s2) {
-  if (gated_off(bl)) return;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int nI = (int)(b / T), nJ = (int)(B / T);
-  const int z = blockIdx.x / nI, it = blockIdx.x % nI;
-  const BlockPtrs& p = bl.z[z];
-  if (p.tileflag[it] == 0) return;
-  constexpr int WTM = Cfg<T>::WTM, NFA = Cfg<T>::NFA;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / Cfg<T>::WN, wn = wave % Cfg<T>::WN, half = lane >> 5;
-  const int64_t i0 = (int64_t)it * T;
-  const int64_t g0 = (int64_t)rank * bl.rows;             // global row of the rank's first row
-  float* red = reinterpret_cast<float*>(smem);            // [2][T] exchange between the two key halves
-  Acc<NFA> acc;
-  float ref2[2] = {-INFINITY, -INFINITY};
-  for (int jt = 0; jt < nJ; ++jt) {
 #pragma unroll
-    for (int i = 0; i < NFA; ++i)
+  for (int bn = 0; bn < 2; ++bn) {
+    m[bn] = fmaxf(m[bn], __shfl_xor(m[bn], 32));
+    if (half == 0) red[wave][bn * 32 + l32] = m[bn];
+  }
+  __syncthreads();
+  if (wave == 0) {
+    float r = red[0][lane];
+    for (int w = 1; w < 16; ++w) r = fmaxf(r, red[w][lane]);
+    ref_s[lane] = r;
+    p.ref2[i0 + lane] = r;
+  }
+  __syncthreads();
+  const float ref[2] = {ref_s[l32], ref_s[32 + l32]};
+  float rs[2] = {0.f, 0.f};
+  for (int64_t j0 = wave * 32; j0 < Bp; j0 += 16 * 32) {
+    strip(j0);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int bn = 0; bn < 2; ++bn)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<T, FMT_K, FMT_K, true>(p.Y + (int64_t)jt * T * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
-    const int64_t j0 = (int64_t)jt * T;
-    // the left-out column and the padding columns take no part in the maximum
-    const bool has_self = bl.variant == LOSS_NTXENT && (g0 + i0 < j0 + T) && (j0 < g0 + i0 + T);
-    const int64_t jl64 = bl.keys - (j0 + wm * WTM + half * 4);
-    const int jlim = jl64 >= WTM ? WTM : jl64 > 0 ? (int)jl64 : 0;
+      for (int q = 0; q < 4; ++q) {
+        const int64_t j = j0 + q * 8 + half * 4, i = i0 + bn * 32 + l32;
+        bf16x4 v;
 #pragma unroll
-    for (int bn = 0; bn < 2; ++bn) {
-      const int64_t dm64 = g0 + i0 + wn * 64 + bn * 32 + (lane & 31) - (j0 + wm * WTM + half * 4);
-#pragma unroll
-      for (int bm = 0; bm < NFA; ++bm)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int jl = bm * 32 + (e >> 2) * 8 + (e & 3);
-          const bool skip = (has_self && dm64 == jl) || jl >= jlim;
-          ref2[bn] = skip ? ref2[bn] : fmaxf(ref2[bn], acc[bm][bn][e] * s2);
+        for (int r = 0; r < 4; ++r) {
+          float e = j + r < keys && j + r != self[bn] ? __builtin_amdgcn_exp2f(fmaf(acc[bn][q * 4 + r], s2, -ref[bn])) : 0.f;
+          if (j + r == label[bn]) { ed_s[bn * 32 + l32] = e; e = 0.f; }
+          rs[bn] += e;
+          v[r] = (__bf16)e;
         }
-    }
+        if (store) *reinterpret_cast<bf16x4*>(p.E + e_index(i, j, Bp)) = v;
+      }
   }
-#pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    ref2[bn] = fmaxf(ref2[bn], __shfl_xor(ref2[bn], 32));
-    if (half == 0) red[wm * T + wn * 64 + bn * 32 + lane] = ref2[bn];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    const int il = wn * 64 + bn * 32 + (lane & 31);
-    ref2[bn] = fmaxf(red[il], red[T + il]);
-    if (wm == 0 && half == 0) p.ref2[i0 + il] = ref2[bn];
-  }
-  __syncthreads();                                         // red is read before the main loop reuses the LDS
-
-  float rs[2] = {0.f, 0.f}, ed[2] = {0.f, 0.f};
-  for (int jt = 0; jt < nJ; ++jt) {
-    const int64_t j0 = (int64_t)jt * T;
-#pragma unroll
-    for (int i = 0; i < NFA; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
-    const bool diag = tile_has_marked_columns<T>(g0 + i0, bl.keys, bl.variant, j0) || j0 + T > bl.keys;
-    if (diag) logit_epilogue<T, true, STORE, MASK_EDGE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
-    else logit_epilogue<T, true, STORE, MASK_NONE, true>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, bl.keys, ref2, j0, B, rs, ed);
-  }
-  // row totals: the four lanes (two key halves x two lane halves) that share a row; exactly one of them met the label
-  __syncthreads();
 #pragma unroll
   for (int bn = 0; bn < 2; ++bn) {
     rs[bn] += __shfl_xor(rs[bn], 32);
-    ed[bn] += __shfl_xor(ed[bn], 32);
-    if (half == 0) {
-      red[wm * T + wn * 64 + bn * 32 + lane] = rs[bn];
-      red[2 * T + wm * T + wn * 64 + bn * 32 + lane] = ed[bn];
+    if (half == 0) red[wave][bn * 32 + l32] = rs[bn];
+  }
+  __syncthreads();
+  if (wave == 0) {
+    float r = red[0][lane];
+    for (int w = 1; w < 16; ++w) r += red[w][lane];
+    off_s[lane] = r;
+  }
+  __syncthreads();
+}
+
+// What k_row_merge needs besides the blocks.
+struct MergeShape {
+  int64_t b, Bp, d;                // rows and key rows in memory (whole tiles)
+  int64_t g0;                      // global row of the rank's first row
+  int nparts0, nparts1;            // partial sums per row of block 0 / block 1
+  int store;                       // redone rows: numerators to E
+  int transpose;                   // go on to write the rows of Xs = (beta x)^T
+  float s2;
+  const float* global_ref;         // symmetric full loss: the one exponent reference every row shares
+  int* bad_flag;                   // and where that path records that a row or column total was lost (nullptr: rows are redone)
+};
+
+// Row totals -> beta, P_label - 1, cross-entropy.  A workgroup takes 64 rows; its 16 waves each add a
+// sixteenth of the column parts (lane = row, so the reads are coalesced), combined in fixed order.
+__global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
+  if (gated_off(bl)) return;
+  const int64_t b = f.b;
+  const int nparts = blockIdx.y ? f.nparts1 : f.nparts0;
+  __shared__ float red[16][64];
+  __shared__ float beta_s[64], ref_s[64], off_s[64], ed_s[64];
+  __shared__ int redo;
+  __shared__ float tile[64][65];
+  const BlockPtrs& p = bl.z[blockIdx.y];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+  int q = wave;
+  for (; q + 112 < nparts; q += 128) {                   // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p.lpart[(int64_t)(q + 16 * u) * b + i];
+    a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
+    a0 += v[4]; a1 += v[5]; a2 += v[6]; a3 += v[7];
+  }
+  for (; q + 48 < nparts; q += 64) {
+    a0 += p.lpart[(int64_t)q * b + i];
+    a1 += p.lpart[(int64_t)(q + 16) * b + i];
+    a2 += p.lpart[(int64_t)(q + 32) * b + i];
+    a3 += p.lpart[(int64_t)(q + 48) * b + i];
+  }
+  for (; q < nparts; q += 16) a0 += p.lpart[(int64_t)q * b + i];
+  red[wave][lane] = (a0 + a1) + (a2 + a3);
+  __syncthreads();
+  // wave 0, lane = row: outputs of the row from its off-label sum and its label numerator; is the total lost?
+  auto finish = [&](float off, float ed) {
+    if (i >= bl.rows) {                                 // a padding row: no weight anywhere
+      p.ref2[i] = 0.f; p.beta[i] = 0.f; p.gdiag[i] = 0.f; p.ce[i] = 0.f;
+      beta_s[lane] = 0.f;
+      return false;
+    }
+    const float tot = off + ed;
+    beta_s[lane] = row_outputs(p, i, off, ed, tot);
+    return !(tot >= ROW_TOTAL_FLOOR && tot <= ROW_TOTAL_MAX);             // (catches totals that are not numbers, too)
+  };
+  if (wave == 0) {
+    float off = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; w += 4) off += (red[w][lane] + red[w + 1][lane]) + (red[w + 2][lane] + red[w + 3][lane]);
+    if (f.global_ref) p.ref2[i] = *f.global_ref;
+    const bool lost = __any(finish(off, p.ediag[i]));
+    if (lane == 0) {
+      redo = lost && !f.bad_flag;
+      if (lost && f.bad_flag) *f.bad_flag = 1;
     }
   }
   __syncthreads();
-  if (wm == 0 && half == 0) {
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn) {
-      const int il = wn * 64 + bn * 32 + lane;
-      const float off = red[il] + red[T + il], e = red[2 * T + il] + red[3 * T + il];
-      p.ediag[i0 + il] = e;
-      float beta = 0.f;
-      if (i0 + il < bl.rows) beta = row_outputs(p, i0 + il, off, e, off + e);
-      else { p.beta[i0 + il] = 0.f; p.gdiag[i0 + il] = 0.f; p.ce[i0 + il] = 0.f; }
-      red[4 * T + il] = beta;
+  if (redo) {
+    redo_rows(p, bl.variant, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, f.store, red, ref_s, off_s, ed_s);
+    if (wave == 0) {
+      p.ediag[i] = ed_s[lane];
+      finish(off_s[lane], ed_s[lane]);
     }
+    __syncthreads();
   }
-  // the rows' share of Xs = (beta x)^T, written by k_row_merge with the betas that have just been replaced
-  scale_transpose_rows<Cfg<T>::NTHREADS>(p, b, d, i0, T, red + 4 * T, reinterpret_cast<float (*)[65]>(red + 5 * T));
+  if (f.transpose) scale_transpose_rows<1024>(p, b, f.d, i0, 64, beta_s, tile);
 }
 
 // Xs = X^T for one block without any scaling (the symmetric full loss folds both normalisations into the stored
@@ -945,23 +860,33 @@ __global__ __launch_bounds__(1024) void k_scalars(Blocks bl, int64_t b, float c,
 // this path return at once and the two-block path, launched behind them and gated the other way, does the call.
 
 // r of the comment above, and the hand-over flag cleared.  One workgroup.
-__global__ __launch_bounds__(1024) void k_sym_ref(const float* zd2, int64_t B, const float* wgmax, float s2, float* rglobal, int* gate) {
-  __shared__ float red[16], nrm[2][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float m = -INFINITY;
-  for (int64_t i = threadIdx.x; i < B; i += 1024) m = fmaxf(m, zd2[i]);
-  float n0 = wgmax[threadIdx.x % NORM_BLOCKS], n1 = wgmax[NORM_BLOCKS + threadIdx.x % NORM_BLOCKS];
-  for (int o = 32; o > 0; o >>= 1) {
-    m = fmaxf(m, __shfl_xor(m, o));
-    n0 = fmaxf(n0, __shfl_xor(n0, o));
-    n1 = fmaxf(n1, __shfl_xor(n1, o));
+__global__ __launch_bounds__(1024) void k_sym_ref(const float* zd2, const float* xnorm, const float* ynorm, int64_t B, float s2, float* rglobal,
+                                                   int* gate) {
+  __shared__ float red[3][16];
+  float m[3] = {-INFINITY, 0.f, 0.f};
+  const float* src[3] = {zd2, xnorm, ynorm};
+  for (int64_t i0 = threadIdx.x; i0 < B; i0 += 4096) {                 // four loads of each array in flight
+    float v[3][4];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[a][u] = src[a][i0 + u * 1024 < B ? i0 + u * 1024 : i0];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m[a] = fmaxf(m[a], v[a][u]);
   }
-  if (lane == 0) { red[wave] = m; nrm[0][wave] = n0; nrm[1][wave] = n1; }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    for (int o = 32; o > 0; o >>= 1) m[a] = fmaxf(m[a], __shfl_xor(m[a], o));
+    if ((threadIdx.x & 63) == 0) red[a][threadIdx.x >> 6] = m[a];
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    float a = red[0], x = nrm[0][0], y = nrm[1][0];
-    for (int w = 1; w < 16; ++w) { a = fmaxf(a, red[w]); x = fmaxf(x, nrm[0][w]); y = fmaxf(y, nrm[1][w]); }
-    *rglobal = row_reference(a, sqrtf(x), sqrtf(y), s2);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      for (int w = 0; w < 16; ++w) m[a] = fmaxf(m[a], red[a][w]);
+    *rglobal = fmaxf(m[0], fmaf(fabsf(s2) * m[1], m[2], -REF_HEADROOM));
     *gate = 0;
   }
 }
@@ -1003,8 +928,8 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
     // the label of query row i is key row i: only the tiles on the diagonal contain label columns
     // (ordinary stores: the matrix is read again by the combining pass and the two contractions)
     if (it == jt || (RAGGED && j0 + BM > bl.keys))
-      logit_epilogue<256, true, true, RAGGED ? MASK_EDGE : MASK_DIAG, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
-    else logit_epilogue<256, true, true, MASK_NONE, false, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
+      logit_epilogue<256, true, true, RAGGED ? MASK_EDGE : MASK_DIAG, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
+    else logit_epilogue<256, true, true, MASK_NONE, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
     lds_barrier();
     const int t = threadIdx.x;
     const int chunk16 = t & 31, r0 = t >> 5;
@@ -1108,7 +1033,7 @@ __global__ __launch_bounds__(256) void k_sym_finalize(Blocks bl, int64_t B, int6
   if (lane == 0) { p.rowds[i] = dot; bl.z[1].rowds[i] = 0.f; }
 }
 
-constexpr int NROWARRAYS = 7;
+constexpr int NROWARRAYS = 6;
 
 struct Plan {
   int64_t b, B, d;       // b and B rounded up to whole tiles: what the tile kernels and the layout below see
@@ -1121,7 +1046,7 @@ struct Plan {
   int nMq, nMk, nN;      // gradient tiles: query rows, key rows of a panel, columns
   int splitk, ktps;      // query-side split, K-steps per split
   int key_splits, key_ktps;
-  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ymax, off_flags, off_ref, off_pad, total;
+  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ref, off_pad, total;
   size_t rows_stride;    // bytes of one b-float row array (aligned)
   double us;             // estimated time of the tile kernels
 };
@@ -1140,13 +1065,11 @@ void layout(Plan& pl) {
   pl.off_E = o;      o += 2 * align_up((size_t)b * pl.W * 2);
   pl.off_lpart = o;  o += 2 * align_up((size_t)pl.nparts * b * 4);
   pl.rows_stride = align_up((size_t)b * 4);
-  pl.off_rows = o;   o += 2 * NROWARRAYS * pl.rows_stride;   // ediag, zd2, xnorm, beta, gdiag, ce, rowds
+  pl.off_rows = o;   o += 2 * NROWARRAYS * pl.rows_stride;   // ediag, zd2, beta, gdiag, ce, rowds
   pl.off_Xs = o;     o += 2 * align_up((size_t)d * b * 2);
   pl.off_part = o;   o += 2 * align_up((size_t)pl.splitk * b * d * 4);
   pl.off_kpart = o;
   if (pl.key_splits > 1) o += 2 * align_up((size_t)pl.key_splits * B * d * 4);
-  pl.off_ymax = o;   o += align_up((size_t)2 * NORM_BLOCKS * 4);         // partial maxima of the row norms
-  pl.off_flags = o;  o += 2 * align_up((size_t)(b / 128) * 4);           // repair flags, one per query tile
   pl.off_ref = o;    o += 2 * pl.rows_stride;                            // exponent references of the rows
   pl.off_pad = o;                                                        // padded I, T, I_r, T_r of a ragged share
   if (pl.ragged) o += 2 * align_up((size_t)B * d * 2) + 2 * align_up((size_t)b * d * 2);
@@ -1267,7 +1190,6 @@ struct TileKernels {
         allow_lds(k_logit_tiles<T, true, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, false>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, true, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
-        allow_lds(k_logit_repair<T, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_repair<T, true>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_WRITE, false>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_WRITE, true>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_SPLIT, false>, GEMM_SMEM_BYTES<T>);
@@ -1285,11 +1207,6 @@ struct TileKernels {
     if (stats && store) { if (pl.ragged) go(k_logit_tiles<T, true, true, true>); else go(k_logit_tiles<T, true, true>); }
     else if (stats) { if (pl.ragged) go(k_logit_tiles<T, true, false, true>); else go(k_logit_tiles<T, true, false>); }
     else { if (pl.ragged) go(k_logit_tiles<T, false, true, true>); else go(k_logit_tiles<T, false, true>); }
-  }
-  static void repair(bool store, const Plan& pl, const Blocks& bl, int rank, float s2, hipStream_t st) {
-    const dim3 grid((unsigned)(bl.nblk * (pl.b / T)));
-    auto go = [&](auto kernel) { kernel<<<grid, Cfg<T>::NTHREADS, LOGIT_SMEM_BYTES<T>, st>>>(bl, pl.b, pl.B, pl.d, rank, s2); };
-    if (store) go(k_logit_repair<T, true>); else go(k_logit_repair<T, false>);
   }
   // both gradient contractions over the key panel [jp0, jp0 + W); part: 0 both, 1 key side only, 2 query side only
   static void grads(int part, bool key_add, bool query_add, const Plan& pl, const Blocks& bl, float cs, int64_t jp0, hipStream_t st) {
@@ -1331,7 +1248,6 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   char* ws = static_cast<char*>(pr.ws);
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
   const uint16_t* T = static_cast<const uint16_t*>(pr.T);
-  float* wgmax = reinterpret_cast<float*>(ws + pl.off_ymax);   // NORM_BLOCKS partial maxima of |I_j|^2, then of |T_j|^2
 
   uint16_t* Ipad = reinterpret_cast<uint16_t*>(ws + pl.off_pad);
   uint16_t* Tpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + align_up((size_t)B * d * 2));
@@ -1355,14 +1271,11 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
     char* rows = ws + pl.off_rows + (size_t)z * NROWARRAYS * pl.rows_stride;
     p.ediag = reinterpret_cast<float*>(rows + 0 * pl.rows_stride);
     p.zd2 = reinterpret_cast<float*>(rows + 1 * pl.rows_stride);
-    p.xnorm = reinterpret_cast<float*>(rows + 2 * pl.rows_stride);
-    p.beta = reinterpret_cast<float*>(rows + 3 * pl.rows_stride);
-    p.gdiag = reinterpret_cast<float*>(rows + 4 * pl.rows_stride);
-    p.ce = reinterpret_cast<float*>(rows + 5 * pl.rows_stride);
-    p.rowds = reinterpret_cast<float*>(rows + 6 * pl.rows_stride);
+    p.beta = reinterpret_cast<float*>(rows + 2 * pl.rows_stride);
+    p.gdiag = reinterpret_cast<float*>(rows + 3 * pl.rows_stride);
+    p.ce = reinterpret_cast<float*>(rows + 4 * pl.rows_stride);
+    p.rowds = reinterpret_cast<float*>(rows + 5 * pl.rows_stride);
     p.ref2 = reinterpret_cast<float*>(ws + pl.off_ref + (size_t)z * pl.rows_stride);
-    p.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + z * align_up((size_t)(b / 128) * 4));
-    p.ymax_parts = wgmax + (z == 0 ? NORM_BLOCKS : 0);     // block A's keys are T, block C's are I
     p.Xs = reinterpret_cast<uint16_t*>(ws + pl.off_Xs + z * align_up((size_t)d * b * 2));
     p.part = reinterpret_cast<float*>(ws + pl.off_part + z * align_up((size_t)pl.splitk * b * d * 4));
     p.kpart = reinterpret_cast<float*>(ws + pl.off_kpart + z * align_up((size_t)pl.key_splits * B * d * 4));
@@ -1381,14 +1294,17 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   mark();
   if (pl.ragged)
     k_pad_operands<<<dim3((unsigned)(8 * cus)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, b, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
-  k_prep<<<dim3((unsigned)(2 * NORM_BLOCKS + nblk * ((b + 3) / 4))), 256, 0, st>>>(bl, I, T, pl.B_real, pl.b_real, b, d, pr.rank, s2, wgmax);
+  k_prep<false><<<dim3((unsigned)(nblk * ((b + 3) / 4))), 256, 0, st>>>(bl, pl.B_real, pl.b_real, b, d, pr.rank, s2);
   mark();
   if (pl.tl == 256) TileKernels<256>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
   else TileKernels<128>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
   mark();
-  k_row_merge<<<dim3((unsigned)(b / 64), (unsigned)nblk), 1024, 0, st>>>(bl, b, pl.nparts, pl.nparts, s2, nullptr, nullptr, d, pl.tl);
-  if (pl.tl == 256) TileKernels<256>::repair(!fused, pl, bl, pr.rank, s2, st);
-  else TileKernels<128>::repair(!fused, pl, bl, pr.rank, s2, st);
+  MergeShape mg;
+  mg.b = b; mg.Bp = B; mg.d = d; mg.g0 = g0;
+  mg.nparts0 = mg.nparts1 = pl.nparts;
+  mg.store = !fused; mg.transpose = 1; mg.s2 = s2;
+  mg.global_ref = nullptr; mg.bad_flag = nullptr;
+  k_row_merge<<<dim3((unsigned)(b / 64), (unsigned)nblk), 1024, 0, st>>>(bl, mg);
   mark();
   for (int pnl = 0; pnl < pl.npanels; ++pnl) {
     const int64_t jp0 = (int64_t)pnl * W;
@@ -1442,7 +1358,6 @@ int mfma_sym_run_impl(const Problem& pr) {
   float* rglobal = reinterpret_cast<float*>(ws + tail + 128);
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
   const uint16_t* T = static_cast<const uint16_t*>(pr.T);
-  float* wgmax = reinterpret_cast<float*>(ws + pl.off_ymax);
 
   // a batch that is not whole tiles: zero-padded copies of I and T (the copies of "the rank's rows" are not used)
   uint16_t* Ipad = reinterpret_cast<uint16_t*>(ws + pl.off_pad);
@@ -1464,14 +1379,11 @@ int mfma_sym_run_impl(const Problem& pr) {
   p.lpart = reinterpret_cast<float*>(ws + pl.off_lpart);
   p.ediag = reinterpret_cast<float*>(rows0 + 0 * pl.rows_stride);
   p.zd2 = reinterpret_cast<float*>(rows0 + 1 * pl.rows_stride);
-  p.xnorm = reinterpret_cast<float*>(rows0 + 2 * pl.rows_stride);
-  p.beta = reinterpret_cast<float*>(rows0 + 3 * pl.rows_stride);
-  p.gdiag = reinterpret_cast<float*>(rows0 + 4 * pl.rows_stride);
-  p.ce = reinterpret_cast<float*>(rows0 + 5 * pl.rows_stride);
-  p.rowds = reinterpret_cast<float*>(rows0 + 6 * pl.rows_stride);
+  p.beta = reinterpret_cast<float*>(rows0 + 2 * pl.rows_stride);
+  p.gdiag = reinterpret_cast<float*>(rows0 + 3 * pl.rows_stride);
+  p.ce = reinterpret_cast<float*>(rows0 + 4 * pl.rows_stride);
+  p.rowds = reinterpret_cast<float*>(rows0 + 5 * pl.rows_stride);
   p.ref2 = reinterpret_cast<float*>(ws + pl.off_ref);
-  p.tileflag = reinterpret_cast<int*>(ws + pl.off_flags);
-  p.ymax_parts = wgmax + NORM_BLOCKS;
   p.Xs = reinterpret_cast<uint16_t*>(ws + pl.off_Xs);
   p.part = reinterpret_cast<float*>(ws + pl.off_part);
   p.gq = pr.gI;
@@ -1481,12 +1393,11 @@ int mfma_sym_run_impl(const Problem& pr) {
   BlockPtrs& q = bl.z[1];
   q = p;
   q.lpart = reinterpret_cast<float*>(ws + pl.off_lpart + align_up((size_t)pl.nparts * B * 4));
-  q.beta = reinterpret_cast<float*>(rows1 + 3 * pl.rows_stride);
-  q.gdiag = reinterpret_cast<float*>(rows1 + 4 * pl.rows_stride);
-  q.ce = reinterpret_cast<float*>(rows1 + 5 * pl.rows_stride);
-  q.rowds = reinterpret_cast<float*>(rows1 + 6 * pl.rows_stride);
+  q.beta = reinterpret_cast<float*>(rows1 + 2 * pl.rows_stride);
+  q.gdiag = reinterpret_cast<float*>(rows1 + 3 * pl.rows_stride);
+  q.ce = reinterpret_cast<float*>(rows1 + 4 * pl.rows_stride);
+  q.rowds = reinterpret_cast<float*>(rows1 + 5 * pl.rows_stride);
   q.ref2 = reinterpret_cast<float*>(ws + pl.off_ref + pl.rows_stride);
-  q.tileflag = reinterpret_cast<int*>(ws + pl.off_flags + align_up((size_t)(B / 128) * 4));
 
   const float s2 = pr.s * LOG2E;
   const float c = loss_norm(Br, LOSS_CLIP);
@@ -1501,15 +1412,20 @@ int mfma_sym_run_impl(const Problem& pr) {
 
   stage_mark(st, stage++);
   if (pl.ragged) k_pad_operands<<<dim3((unsigned)(8 * persistent_wgs)), 256, 0, st>>>(I, T, Br, B, 0, 0, d, 0, Ipad, Tpad, Ipad, Tpad);
-  k_prep<<<dim3((unsigned)(2 * NORM_BLOCKS + (B + 3) / 4)), 256, 0, st>>>(bl, I, T, Br, Br, B, d, 0, s2, wgmax);
-  k_sym_ref<<<1, 1024, 0, st>>>(p.zd2, Br, wgmax, s2, rglobal, gate);
+  k_prep<true><<<dim3((unsigned)((B + 3) / 4)), 256, 0, st>>>(bl, Br, Br, B, d, 0, s2);
+  k_sym_ref<<<1, 1024, 0, st>>>(p.zd2, p.beta, p.gdiag, Br, s2, rglobal, gate);
   stage_mark(st, stage++);
   if (pl.ragged) k_sym_logit<true><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES<256>, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
   else k_sym_logit<false><<<logit_grid, NTHREADS, LOGIT_SMEM_BYTES<256>, st>>>(bl, B, d, s2, rglobal, sbi, sbj);
   stage_mark(st, stage++);
   Blocks both = bl;
   both.nblk = 2;
-  k_row_merge<<<dim3((unsigned)((B + 63) / 64), 2), 1024, 0, st>>>(both, B, pl.nparts, nT, s2, rglobal, gate, 0, BN);
+  MergeShape mg;
+  mg.b = B; mg.Bp = B; mg.d = d; mg.g0 = 0;
+  mg.nparts0 = pl.nparts; mg.nparts1 = nT;
+  mg.store = 0; mg.transpose = 0; mg.s2 = s2;
+  mg.global_ref = rglobal; mg.bad_flag = gate;
+  k_row_merge<<<dim3((unsigned)(B / 64), 2), 1024, 0, st>>>(both, mg);
   Blocks go = bl;                                   // from here on only while no total was lost
   go.gate = gate;
   go.gate_value = 0;
