@@ -77,11 +77,13 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  *                         to one inside the workspace (zero-padded copies of I, T and the rank's rows,
  *                         2*(B+b)*d*2 more bytes; the padding takes part in no softmax, sum or output),
  *                         so the call costs what the rounded-up shape costs.
- * DISCO_PATH_FUSED        bf16 MFMA tiles, streaming: a forward pass keeps the row sums on chip and
- *                         writes nothing of size b x B; the backward pass recomputes the logits one
- *                         key panel (at most 16384 keys) at a time and contracts each panel while
- *                         it is cache-resident (16*b*B*d flop, workspace 2*b*W*2 bytes for panel
- *                         width W).  Shape limits of MATERIALIZED (ragged shares padded as there).
+ * DISCO_PATH_FUSED        bf16 MFMA tiles, memory-lean: 2*b*W*2 bytes of numerators for a panel width W of at most 16384
+ *                         keys, in one of two forms, whichever is the faster for the shape: the rank's rows in chunks of
+ *                         b*W/B, each taken through logits and gradients against all keys (12*b*B*d flop, the key-side
+ *                         gradient read and written again per chunk), or streaming: a forward pass keeps the row sums on
+ *                         chip and writes nothing of size b x B, the backward pass recomputes the logits one key panel
+ *                         at a time and contracts each panel while it is cache-resident (16*b*B*d flop).
+ *                         Shape limits of MATERIALIZED (ragged shares padded as there).
  * DISCO_PATH_SYMMETRIC    bf16 MFMA tiles, N = 1 only (the non-decomposed loss, Eq. 1 / Fig. 1): the B x B
  *                         similarity matrix is computed once and serves both directions (text -> image is
  *                         its transpose); one matrix of numerators (B*B*2 bytes) against one exponent
@@ -200,9 +202,9 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
  * (Stages 4 and 5 are one launch while stage timing is off, two while it is on.)
  * Stages of DISCO_PATH_NAIVE (DISCO_STAGES_NAIVE = 5): similarity, row softmax, scalars, key grad, query grad.  (Calls whose
  *   two gradient sides share a launch have both in the fourth interval; the scalars are in that one or in the last.)
- * Stages of DISCO_PATH_FUSED (DISCO_STAGES_FUSED = 5): row norms + positive-pair logits, streaming forward
- *   (row sums only), row merge + scaled transpose, all key panels (recompute + both gradient GEMMs),
- *   query finalize + scalars.
+ * Stages of DISCO_PATH_FUSED (DISCO_STAGES_FUSED = 5): positive-pair logits, streaming forward (row sums only), row merge +
+ *   scaled transpose, all key panels (recompute + both gradient GEMMs), query finalize + scalars.  (Rows in chunks: the
+ *   second and third are the first chunk's, the fourth all the rest up to the last finalize.)
  * Stages of DISCO_PATH_SYMMETRIC (DISCO_STAGES_SYMMETRIC = 7): row norms + positive-pair logits + reference, logit
  *   tiles with row and column sums, both merges + transpose, combining pass, key-side GEMM, query-side split GEMM,
  *   finalize + scalars.

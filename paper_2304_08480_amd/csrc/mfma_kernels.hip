@@ -275,8 +275,8 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
 // accumulator quad: 8-byte pieces of an E row and an in-lane row sum.
 //   STATS: write the partial row sums and the label-column numerator (forward statistics);
 //   STORE: write the bf16 numerators to E (panel-relative columns, atom storage, see e_index).
-// materialized path: STATS and STORE, one panel = all keys.  fused path: a STATS-only pass over all
-// keys (nothing of size b x B is written), then STORE-only passes that recompute one panel at a time.
+// materialized path: STATS and STORE, one panel = all keys.  fused path: the same for a chunk of rows at a time, or a STATS-only
+// pass over all keys (nothing of size b x B is written), then STORE-only passes that recompute one panel at a time.
 // b: the rank's rows rounded up to whole tiles; B: the key rows that exist (the panel widths cover them rounded up to
 // whole tiles); g0: global row of the rank's first row.  RAGGED: the last key tile may hold padding columns (the
 // instance without it keeps the tile walk free of that variant of the epilogue and of the registers it costs).
@@ -663,10 +663,11 @@ __device__ __forceinline__ f32x4 sum_slices(const float* part, int64_t pitch, in
 
 // What the finalize kernels add up for a row, besides its own terms.
 struct FinalizeShape {
-  int64_t b, bp;        // the rank's rows; row pitch of part
+  int64_t b, bp;        // the rank's rows (of the chunk); row pitch of part
   int64_t B, Bp;        // all rows; row pitch of kpart
   int64_t d;
-  int rank, splitk, key_splits, accumulate;
+  int64_t g0;           // global row of the first of them
+  int splitk, key_splits, accumulate;
 };
 
 // Everything that lands in the rank's own rows, for both blocks at once.  With lab = label of local row i:
@@ -688,8 +689,8 @@ __global__ __launch_bounds__(256) void k_finalize(Blocks bl, FinalizeShape f, fl
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t row = ROWWG ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
   if (row >= (KSPLIT ? f.B : f.b)) return;              // ROWWG: the whole workgroup
-  const int64_t i = KSPLIT ? row - (int64_t)f.rank * f.b : row;         // local row
-  const int64_t lab = KSPLIT ? row : (int64_t)f.rank * f.b + row;       // global row
+  const int64_t i = KSPLIT ? row - f.g0 : row;         // local row
+  const int64_t lab = KSPLIT ? row : f.g0 + row;       // global row
   const bool own = !KSPLIT || (i >= 0 && i < f.b);
   float beta_a = 0.f, gd_a = 0.f, beta_c = 0.f, gd_c = 0.f;
   if (own) { beta_a = pa.beta[i]; gd_a = pa.gdiag[i]; beta_c = pc.beta[i]; gd_c = pc.gdiag[i]; }
@@ -778,10 +779,10 @@ __global__ __launch_bounds__(256) void k_finalize_ntxent(Blocks bl, FinalizeShap
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= (KSPLIT ? f.B : f.b)) return;
-  const int64_t i = KSPLIT ? row - (int64_t)f.rank * f.b : row;
-  const int64_t g = KSPLIT ? row : (int64_t)f.rank * f.b + row, lab = label_row(g, f.B, LOSS_NTXENT);
+  const int64_t i = KSPLIT ? row - f.g0 : row;
+  const int64_t g = KSPLIT ? row : f.g0 + row, lab = label_row(g, f.B, LOSS_NTXENT);
   const bool own = !KSPLIT || (i >= 0 && i < f.b);
-  const int64_t ip = lab - (int64_t)f.rank * f.b;                     // local index of the positive, if it is local
+  const int64_t ip = lab - f.g0;                     // local index of the positive, if it is local
   const bool pos_local = ip >= 0 && ip < f.b;
   const bool owes = !KSPLIT && !pos_local;                            // this wave writes its term into row lab
   const float beta = own ? p.beta[i] : 0.f, gd = own ? p.gdiag[i] : 0.f, gd_pos = pos_local ? p.gdiag[ip] : 0.f;
@@ -1036,7 +1037,9 @@ __global__ __launch_bounds__(256) void k_sym_finalize(Blocks bl, int64_t B, int6
 constexpr int NROWARRAYS = 6;
 
 struct Plan {
-  int64_t b, B, d;       // b and B rounded up to whole tiles: what the tile kernels and the layout below see
+  int64_t b, B, d;       // rows taken at a time and B, rounded up to whole tiles: what the tile kernels and the layout below see
+  int64_t b_all;         // the share rounded up to whole tiles (b, except where the fused path takes it in chunks)
+  bool chunked;          // fused path: rows in chunks, each against all keys, instead of key panels
   int64_t b_real, B_real;
   bool ragged;           // b or B was rounded up: the kernels read zero-padded copies of the operands (off_pad)
   int64_t W;             // key panel width (B for the materialized path)
@@ -1064,7 +1067,7 @@ void layout(Plan& pl) {
   size_t o = 0;
   pl.off_E = o;      o += 2 * align_up((size_t)b * pl.W * 2);
   pl.off_lpart = o;  o += 2 * align_up((size_t)pl.nparts * b * 4);
-  pl.rows_stride = align_up((size_t)b * 4);
+  pl.rows_stride = align_up((size_t)pl.b_all * 4);
   pl.off_rows = o;   o += 2 * NROWARRAYS * pl.rows_stride;   // ediag, zd2, beta, gdiag, ce, rowds
   pl.off_Xs = o;     o += 2 * align_up((size_t)d * b * 2);
   pl.off_part = o;   o += 2 * align_up((size_t)pl.splitk * b * d * 4);
@@ -1072,22 +1075,48 @@ void layout(Plan& pl) {
   if (pl.key_splits > 1) o += 2 * align_up((size_t)pl.key_splits * B * d * 4);
   pl.off_ref = o;    o += 2 * pl.rows_stride;                            // exponent references of the rows
   pl.off_pad = o;                                                        // padded I, T, I_r, T_r of a ragged share
-  if (pl.ragged) o += 2 * align_up((size_t)B * d * 2) + 2 * align_up((size_t)b * d * 2);
+  if (pl.ragged) o += 2 * align_up((size_t)B * d * 2) + 2 * align_up((size_t)pl.b_all * d * 2);
   pl.total = o;
 }
 
 // b and B rounded to whole tiles of the two tile sizes, and what follows from them.
 void round_shape(Plan& pl, bool fused) {
   const int unit = pl.tl > pl.tg ? pl.tl : pl.tg;
-  pl.b = (pl.b_real + unit - 1) / unit * unit;
+  pl.b = pl.b_all = (pl.b_real + unit - 1) / unit * unit;
+  pl.chunked = false;
   pl.B = (pl.B_real + unit - 1) / unit * unit;
-  pl.ragged = pl.b != pl.b_real || pl.B != pl.B_real;
+  pl.ragged = pl.b_all != pl.b_real || pl.B != pl.B_real;
   pl.npanels = fused ? fused_panels(pl.B, unit) : 1;
   pl.W = pl.B / pl.npanels;
   pl.nparts = (int)(pl.B / (pl.tl / 2));
   pl.nMq = (int)(pl.b / pl.tg);
   pl.nMk = (int)(pl.W / pl.tg);
   pl.nN = (int)((pl.d + pl.tg - 1) / pl.tg);
+}
+
+// Widest key panel the fused path may take: half the keys, at most 16384.
+int64_t panel_limit(const Plan& pl) {
+  const int unit = pl.tl > pl.tg ? pl.tl : pl.tg;
+  const int64_t half = (pl.B / unit + 1) / 2 * unit;
+  return half < 16384 ? half : 16384;
+}
+
+// The fused path's rows in chunks of as many numerators as the widest panel of all rows would hold: logits once instead of
+// twice, but the key-side gradient is read and written again per chunk.  Any number of tiles can be cut so, while panels need
+// one that divides the keys' tiles (B = 20000 is 79 tiles of 256: 79 panels, 1680 us at N = 20, d = 128, against 170 in
+// chunks).  shrink: take that many times smaller chunks.  False where a chunk would be less than a tile.
+bool round_to_chunks(Plan& pl, int shrink) {
+  const int unit = pl.tl > pl.tg ? pl.tl : pl.tg;
+  const int64_t most = pl.b_all * panel_limit(pl) / pl.B / unit / shrink;     // tiles
+  if (most == 0) return false;
+  const int64_t tiles = pl.b_all / unit, chunks = (tiles + most - 1) / most;
+  pl.b = (tiles + chunks - 1) / chunks * unit;
+  pl.chunked = true;
+  pl.npanels = 1;
+  pl.W = pl.B;
+  pl.nMq = (int)(pl.b / pl.tg);
+  pl.nMk = (int)(pl.W / pl.tg);
+  return true;
 }
 
 double logits_us(const Plan& pl, int nblk) {
@@ -1130,29 +1159,38 @@ Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int ti
   Plan best;
   best.us = 1e300;
   bool best_fits = false;
-  for (int tl = 128; tl <= 256; tl += 128)
-    for (int tg = 128; tg <= 256; tg += 128) {
-      if (tile && (tl != tile || tg != tile)) continue;
-      Plan pl;
-      pl.B_real = B; pl.b_real = B / N; pl.d = d; pl.tl = tl; pl.tg = tg;
-      round_shape(pl, fused);
-      const double base = logits_us(pl, nblk) * (fused ? 2 : 1);
-      const int kt_q = (int)(pl.W / BK), kt_k = (int)(pl.b / BK);
-      for (int sk : Q_SPLITS) {
-        if (sk > kt_q) break;
-        split(kt_q, sk, pl.splitk, pl.ktps);
-        for (int ks : K_SPLITS) {
-          if (ks > 1 && (fused || tile || ks > kt_k)) break;
-          split(kt_k, ks, pl.key_splits, pl.key_ktps);
-          const double us = base + pl.npanels * grads_us(pl, nblk, pl.ktps, pl.splitk, pl.key_ktps, pl.key_splits);
-          if (best_fits && us >= best.us) continue;
-          layout(pl);
-          // a call whose workspace can stay within the library's static array stays within it
-          const bool fits = pl.total <= DISCO_STATIC_SCRATCH_BYTES;
-          if (fits > best_fits || (fits == best_fits && us < best.us)) { best = pl; best.us = us; best_fits = fits; }
+  size_t most = ~(size_t)0;                                          // chunks of rows: no more memory than with the widest panels
+  // (smaller chunks are for calls that the largest would take out of the static array)
+  for (int form = 0; form < (fused ? 4 : 1); ++form) {
+    if (form == 1) most = best.total + (size_t)4 * best.b_all * (panel_limit(best) > best.W ? panel_limit(best) - best.W : 0);
+    for (int tl = 128; tl <= 256; tl += 128)
+      for (int tg = 128; tg <= 256; tg += 128) {
+        if (tile && (tl != tile || tg != tile)) continue;
+        Plan pl;
+        pl.B_real = B; pl.b_real = B / N; pl.d = d; pl.tl = tl; pl.tg = tg;
+        round_shape(pl, fused);
+        if (form > 0 && !round_to_chunks(pl, 1 << (form - 1))) continue;
+        const double base = logits_us(pl, nblk) * (fused && !pl.chunked ? 2 : 1), chunks = (double)((pl.b_all + pl.b - 1) / pl.b);
+        const int kt_q = (int)(pl.W / BK), kt_k = (int)(pl.b / BK);
+        for (int sk : Q_SPLITS) {
+          if (sk > kt_q) break;
+          split(kt_q, sk, pl.splitk, pl.ktps);
+          for (int ks : K_SPLITS) {
+            if (ks > 1 && (fused || tile || ks > kt_k)) break;
+            split(kt_k, ks, pl.key_splits, pl.key_ktps);
+            double us = base + pl.npanels * grads_us(pl, nblk, pl.ktps, pl.splitk, pl.key_ktps, pl.key_splits);
+            // a further chunk reads the key-side gradient back and has its own merge and finalize launches
+            us = chunks * us + (chunks - 1.0) * (4.0 * nblk * pl.B * d / BYTES_PER_US + 25.0);
+            if (best_fits && us >= best.us) continue;
+            layout(pl);
+            if (pl.total > most) continue;
+            // a call whose workspace can stay within the library's static array stays within it
+            const bool fits = pl.total <= DISCO_STATIC_SCRATCH_BYTES;
+            if (fits > best_fits || (fits == best_fits && us < best.us)) { best = pl; best.us = us; best_fits = fits; }
+          }
         }
       }
-    }
+  }
   return best;
 }
 
@@ -1224,12 +1262,12 @@ struct TileKernels {
   }
 };
 
-void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, float cs, hipStream_t st) {
+void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, int64_t g0, float cs, hipStream_t st) {
   FinalizeShape f;
-  f.b = pl.b_real; f.bp = pl.b; f.B = pl.B_real; f.Bp = pl.B; f.d = pl.d;
-  f.rank = pr.rank; f.splitk = pl.splitk; f.key_splits = pl.key_splits; f.accumulate = pr.accumulate;
+  f.b = bl.rows; f.bp = pl.b; f.B = pl.B_real; f.Bp = pl.B; f.d = pl.d;
+  f.g0 = g0; f.splitk = pl.splitk; f.key_splits = pl.key_splits; f.accumulate = pr.accumulate;
   const bool ks = pl.key_splits > 1;
-  const int64_t rows = ks ? pl.B_real : pl.b_real;
+  const int64_t rows = ks ? pl.B_real : bl.rows;
   const bool rowwg = pr.variant != LOSS_NTXENT && rows <= FINALIZE_ROWWG_MAX;
   auto go = [&](auto kernel) { kernel<<<dim3((unsigned)(rowwg ? rows : (rows + 3) / 4)), 256, 0, st>>>(bl, f, cs); };
   if (pr.variant == LOSS_NTXENT) { if (ks) go(k_finalize_ntxent<true>); else go(k_finalize_ntxent<false>); }
@@ -1244,7 +1282,7 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   if ((pl.tl == 256 || pl.tg == 256) && !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
   if ((pl.tl == 128 || pl.tg == 128) && !TileKernels<128>::lds_ok()) return DISCO_ERR_HIP;
   const int cus = compute_units();
-  const int64_t b = pl.b, B = pl.B, d = pl.d, W = pl.W;     // whole tiles; the real sizes are pl.b_real, pl.B_real
+  const int64_t b = pl.b, ba = pl.b_all, B = pl.B, d = pl.d, W = pl.W;     // whole tiles; the real sizes are pl.b_real, pl.B_real
   char* ws = static_cast<char*>(pr.ws);
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
   const uint16_t* T = static_cast<const uint16_t*>(pr.T);
@@ -1252,9 +1290,10 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   uint16_t* Ipad = reinterpret_cast<uint16_t*>(ws + pl.off_pad);
   uint16_t* Tpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + align_up((size_t)B * d * 2));
   uint16_t* XIpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + 2 * align_up((size_t)B * d * 2));
-  uint16_t* XTpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + 2 * align_up((size_t)B * d * 2) + align_up((size_t)b * d * 2));
+  uint16_t* XTpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + 2 * align_up((size_t)B * d * 2) + align_up((size_t)ba * d * 2));
 
-  Blocks bl;
+  Blocks bl;                                              // all rows of the share
+
   bl.variant = pr.variant;
   bl.nblk = nblk;
   bl.rows = pl.b_real;
@@ -1264,7 +1303,7 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   for (int z = 0; z < 2; ++z) {
     BlockPtrs& p = bl.z[z];
     const uint16_t* Xfull = z == 0 ? I : T;
-    p.X = pl.ragged ? (z == 0 ? XIpad : XTpad) : Xfull + (size_t)pr.rank * b * d;
+    p.X = pl.ragged ? (z == 0 ? XIpad : XTpad) : Xfull + (size_t)pr.rank * ba * d;
     p.Y = pl.ragged ? (z == 0 ? Tpad : Ipad) : (z == 0 ? T : I);
     p.E = reinterpret_cast<uint16_t*>(ws + pl.off_E + z * align_up((size_t)b * W * 2));
     p.lpart = reinterpret_cast<float*>(ws + pl.off_lpart + z * align_up((size_t)pl.nparts * b * 4));
@@ -1287,46 +1326,62 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   const float c = loss_norm(pl.B_real, pr.variant);
   const float cs = c * pr.s;
   hipStream_t st = pr.stream;
-  const int64_t g0 = (int64_t)pr.rank * pl.b_real;       // global row of the rank's first row
+  const bool panels = fused && !pl.chunked;              // statistics first, then the numerators again, panel by panel
   int stage = 0;
   auto mark = [&] { if (marks) stage_mark(st, stage++); };
 
   mark();
   if (pl.ragged)
-    k_pad_operands<<<dim3((unsigned)(8 * cus)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, b, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
-  k_prep<false><<<dim3((unsigned)(nblk * ((b + 3) / 4))), 256, 0, st>>>(bl, pl.B_real, pl.b_real, b, d, pr.rank, s2);
+    k_pad_operands<<<dim3((unsigned)(8 * cus)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, ba, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
+  k_prep<false><<<dim3((unsigned)(nblk * ((ba + 3) / 4))), 256, 0, st>>>(bl, pl.B_real, pl.b_real, ba, d, pr.rank, s2);
   mark();
-  if (pl.tl == 256) TileKernels<256>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
-  else TileKernels<128>::logits(true, !fused, pl, bl, g0, s2, 0, B, cus, st);
-  mark();
-  MergeShape mg;
-  mg.b = b; mg.Bp = B; mg.d = d; mg.g0 = g0;
-  mg.nparts0 = mg.nparts1 = pl.nparts;
-  mg.store = !fused; mg.transpose = 1; mg.s2 = s2;
-  mg.global_ref = nullptr; mg.bad_flag = nullptr;
-  k_row_merge<<<dim3((unsigned)(b / 64), (unsigned)nblk), 1024, 0, st>>>(bl, mg);
-  mark();
-  for (int pnl = 0; pnl < pl.npanels; ++pnl) {
-    const int64_t jp0 = (int64_t)pnl * W;
-    if (fused) {
-      if (pl.tl == 256) TileKernels<256>::logits(false, true, pl, bl, g0, s2, jp0, W, cus, st);
-      else TileKernels<128>::logits(false, true, pl, bl, g0, s2, jp0, W, cus, st);
+  for (int64_t r0 = 0; r0 < ba; r0 += b) {                // (one chunk except on the fused path)
+    Plan pc = pl;
+    pc.b = ba - r0 < b ? ba - r0 : b;
+    pc.nMq = (int)(pc.b / pc.tg);
+    if (pl.chunked) pc.key_ktps = (int)(pc.b / BK);
+    Blocks bc = bl;
+    bc.rows = pl.b_real - r0 < pc.b ? pl.b_real - r0 : pc.b;
+    for (int z = 0; z < 2; ++z) {
+      BlockPtrs& p = bc.z[z];
+      p.X += r0 * d;
+      p.ediag += r0; p.zd2 += r0; p.beta += r0; p.gdiag += r0; p.ce += r0; p.rowds += r0; p.ref2 += r0;
     }
-    auto grads = [&](int part) {
-      if (pl.tg == 256) TileKernels<256>::grads(part, pr.accumulate != 0, pnl > 0, pl, bl, cs, jp0, st);
-      else TileKernels<128>::grads(part, pr.accumulate != 0, pnl > 0, pl, bl, cs, jp0, st);
-    };
-    if (fused || !marks || !stage_marks_on()) {
-      grads(0);
-    } else {                                              // a launch of its own for each side, so that each can be timed
-      grads(1);
-      mark();
-      grads(2);
+    const int64_t g0 = (int64_t)pr.rank * pl.b_real + r0;  // global row of the chunk's first row
+    const bool key_add = pr.accumulate || r0 > 0;
+    auto mark_first = [&] { if (r0 == 0) mark(); };
+    if (pl.tl == 256) TileKernels<256>::logits(true, !panels, pc, bc, g0, s2, 0, B, cus, st);
+    else TileKernels<128>::logits(true, !panels, pc, bc, g0, s2, 0, B, cus, st);
+    mark_first();
+    MergeShape mg;
+    mg.b = pc.b; mg.Bp = B; mg.d = d; mg.g0 = g0;
+    mg.nparts0 = mg.nparts1 = pl.nparts;
+    mg.store = !panels; mg.transpose = 1; mg.s2 = s2;
+    mg.global_ref = nullptr; mg.bad_flag = nullptr;
+    k_row_merge<<<dim3((unsigned)(pc.b / 64), (unsigned)nblk), 1024, 0, st>>>(bc, mg);
+    mark_first();
+    for (int pnl = 0; pnl < pl.npanels; ++pnl) {
+      const int64_t jp0 = (int64_t)pnl * W;
+      if (panels) {
+        if (pl.tl == 256) TileKernels<256>::logits(false, true, pc, bc, g0, s2, jp0, W, cus, st);
+        else TileKernels<128>::logits(false, true, pc, bc, g0, s2, jp0, W, cus, st);
+      }
+      auto grads = [&](int part) {
+        if (pl.tg == 256) TileKernels<256>::grads(part, key_add, pnl > 0, pc, bc, cs, jp0, st);
+        else TileKernels<128>::grads(part, key_add, pnl > 0, pc, bc, cs, jp0, st);
+      };
+      if (fused || !marks || !stage_marks_on()) {
+        grads(0);
+      } else {                                            // a launch of its own for each side, so that each can be timed
+        grads(1);
+        mark();
+        grads(2);
+      }
     }
+    if (!fused && !stage_marks_on()) ++stage;
+    if (r0 + b >= ba) mark();
+    finalize(pr, pc, bc, g0, cs, st);
   }
-  if (!fused && !stage_marks_on()) ++stage;
-  mark();
-  finalize(pr, pl, bl, cs, st);
   k_scalars<<<1, 1024, 0, st>>>(bl, pl.b_real, c, pr.accumulate, pr.loss, pr.gs);
   mark();
   return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
