@@ -171,7 +171,7 @@ __device__ __forceinline__ int64_t e_index(int64_t i, int64_t jl, int64_t W) {
 // nkeys (the batch size) on (MASK_EDGE only:
 // the caller takes that variant for the tiles they fall into).
 // jl0: first key column of the tile relative to the panel of width W that p.E holds.  STREAM: streaming stores
-// (written once, read by later kernels: keeps the operand tiles in L2).  STAGE: also leave the bf16 tile in LDS,
+// (past the caches, which keeps the operand tiles in L2; see streaming_stores).  STAGE: also leave the bf16 tile in LDS,
 // row-major T x T (8-byte granules XOR-swizzled with the row: conflict-free 8-byte writes and 16-byte reads),
 // for a caller that wants sums down its columns.
 constexpr int64_t NO_SELF = -((int64_t)1 << 40);
@@ -280,7 +280,7 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
 // b: the rank's rows rounded up to whole tiles; B: the key rows that exist (the panel widths cover them rounded up to
 // whole tiles); g0: global row of the rank's first row.  RAGGED: the last key tile may hold padding columns (the
 // instance without it keeps the tile walk free of that variant of the epilogue and of the registers it costs).
-template <int T, bool STATS, bool STORE, bool RAGGED = false>
+template <int T, bool STATS, bool STORE, bool RAGGED = false, bool STREAM = true>
 __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, int64_t B, int64_t d, int64_t g0, float s2,
                                                           int64_t jp0, int64_t W, int sbi, int sbj, int nblk) {
   if (gated_off(bl)) return;
@@ -328,8 +328,8 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int
     // Only the tiles that the label diagonal (or the left-out diagonal) crosses, or that hold padding columns, pay
     // for finding those columns.
     const bool diag = tile_has_marked_columns<T>(g0 + i0, B, bl.variant, j0);
-    if (diag || (RAGGED && j0 + T > B)) logit_epilogue<T, STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
-    else logit_epilogue<T, STATS, STORE, MASK_NONE>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    if (diag || (RAGGED && j0 + T > B)) logit_epilogue<T, STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG, false, STREAM>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    else logit_epilogue<T, STATS, STORE, MASK_NONE, false, STREAM>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
   }
 }
 
@@ -1220,14 +1220,25 @@ bool allow_lds(K kernel, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
+// Numerators written past the caches, or kept in them for the gradient kernel?  They stay in the 256 MiB last-level cache
+// until that kernel reads them if they fill at most half of it; below 24 MiB they would sit dirty in the eight L2s, which the
+// kernel's end writes back.  (Streamed / plain, us a call: 16 MiB 68 / 69; 32 MiB 93.6 / 91.3; 64 MiB, B = 32768, N = 64: 168 / 162;
+// 128 MiB, B = 32768, N = 32: 278 / 258; 256 MiB, B = 32768, N = 16: 449 / 460; 512 MiB: 797 / 808.)
+bool streaming_stores(int nblk, int64_t b, int64_t W) {
+  const int64_t bytes = 2 * nblk * b * W;
+  return bytes < ((int64_t)24 << 20) || bytes > ((int64_t)144 << 20);
+}
+
 // Launchers of one tile size; the LDS limit of the kernels is raised once per process (one device per process here).
 template <int T>
 struct TileKernels {
   static bool lds_ok() {
     static const bool ok =
-        allow_lds(k_logit_tiles<T, true, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, false>, LOGIT_SMEM_BYTES<T>) &&
-        allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true>, LOGIT_SMEM_BYTES<T>) &&
-        allow_lds(k_logit_tiles<T, true, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, true, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, false, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, true, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, true, true, false, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true, false>, LOGIT_SMEM_BYTES<T>) &&
+        allow_lds(k_logit_tiles<T, false, true, false, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true, false>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_WRITE, false>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_WRITE, true>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_SPLIT, false>, GEMM_SMEM_BYTES<T>);
@@ -1242,9 +1253,19 @@ struct TileKernels {
     const int slots = cus * (T == 256 ? 1 : 2);
     const dim3 grid((unsigned)(tiles < slots ? tiles : slots));
     auto go = [&](auto kernel) { kernel<<<grid, Cfg<T>::NTHREADS, LOGIT_SMEM_BYTES<T>, st>>>(bl, pl.b, pl.B_real, pl.d, g0, s2, jp0, W, sbi, sbj, bl.nblk); };
-    if (stats && store) { if (pl.ragged) go(k_logit_tiles<T, true, true, true>); else go(k_logit_tiles<T, true, true>); }
-    else if (stats) { if (pl.ragged) go(k_logit_tiles<T, true, false, true>); else go(k_logit_tiles<T, true, false>); }
-    else { if (pl.ragged) go(k_logit_tiles<T, false, true, true>); else go(k_logit_tiles<T, false, true>); }
+    auto storing = [&](auto streamed, auto plain) {
+      if (streaming_stores(bl.nblk, pl.b, W)) go(streamed);
+      else go(plain);
+    };
+    if (!store) {
+      if (pl.ragged) go(k_logit_tiles<T, true, false, true>); else go(k_logit_tiles<T, true, false>);
+    } else if (stats) {
+      if (pl.ragged) storing(k_logit_tiles<T, true, true, true>, k_logit_tiles<T, true, true, true, false>);
+      else storing(k_logit_tiles<T, true, true>, k_logit_tiles<T, true, true, false, false>);
+    } else {
+      if (pl.ragged) storing(k_logit_tiles<T, false, true, true>, k_logit_tiles<T, false, true, true, false>);
+      else storing(k_logit_tiles<T, false, true>, k_logit_tiles<T, false, true, false, false>);
+    }
   }
   // both gradient contractions over the key panel [jp0, jp0 + W); part: 0 both, 1 key side only, 2 query side only
   static void grads(int part, bool key_add, bool query_add, const Plan& pl, const Blocks& bl, float cs, int64_t jp0, hipStream_t st) {
