@@ -15,8 +15,8 @@
 //   d/ds share           c <gX_i / (c s), x_i>  summed over i   (sum_ij G_ij S_ij = <G Y, X>)
 // Since lse_i >= z_i,label, every E_ij that underflows is negligible against the row total.  Where the guard lifts ref2_i so
 // far above every logit of the row that its total falls below 2^-60 (rows of large norm whose cosines are all small), or
-// keys of much larger norm than the positive's take it above 2^120, or the total is no number, k_row_merge redoes the row's
-// group of 64 with the true row maxima as references (a slow path for inputs that are not CLIP-like).
+// keys of much larger norm than the positive's take a numerator above 2^101, k_row_merge redoes the row's group of 64 with
+// the true row maxima as references (a slow path for inputs that are not CLIP-like).
 //
 // One NT tile main loop (mfma_tile.h: 256x256x64 by 8 waves, or 128x128x64 by 4, of MFMA 32x32x16 blocks, operands
 // loaded global -> LDS directly into a ring of five units) serves all three contractions; operands whose
@@ -31,7 +31,10 @@ using namespace tile;
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float REF_HEADROOM = 100.f;                    // largest exponent (base 2) a stored numerator should reach
-constexpr float ROW_TOTAL_FLOOR = 0x1p-60f, ROW_TOTAL_MAX = 0x1p120f;   // a row whose total lies outside has lost terms
+// A row whose total lies below the floor has lost terms.  One with a partial sum over a tile's keys above the limit may hold
+// numerators the guard does not allow (keys of the positive's norm reach it only if two of a tile are copies of the query and
+// the positive is nowhere near it): times a key of large features they leave fp32, and 1 / total times a short row's leave bf16.
+constexpr float ROW_TOTAL_FLOOR = 0x1p-60f, ROW_PART_MAX = 0x1p101f;
 
 constexpr int BM = 256, BN = 256, NTHREADS = Cfg<256>::NTHREADS;     // the symmetric path's tiles
 
@@ -499,12 +502,12 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
   const int nparts = blockIdx.y ? f.nparts1 : f.nparts0;
   __shared__ float red[16][64];
   __shared__ float beta_s[64], ref_s[64], off_s[64], ed_s[64];
-  __shared__ int redo;
+  __shared__ int redo, over[16];
   __shared__ float tile[64][65];
   const BlockPtrs& p = bl.z[blockIdx.y];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f, most = 0.f;           // most: the row's largest part
   int q = wave;
   for (; q + 112 < nparts; q += 128) {                   // eight loads in flight
     float v[8];
@@ -512,17 +515,28 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
     for (int u = 0; u < 8; ++u) v[u] = p.lpart[(int64_t)(q + 16 * u) * b + i];
     a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
     a0 += v[4]; a1 += v[5]; a2 += v[6]; a3 += v[7];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) most = fmaxf(most, v[u]);
   }
   for (; q + 48 < nparts; q += 64) {
-    a0 += p.lpart[(int64_t)q * b + i];
-    a1 += p.lpart[(int64_t)(q + 16) * b + i];
-    a2 += p.lpart[(int64_t)(q + 32) * b + i];
-    a3 += p.lpart[(int64_t)(q + 48) * b + i];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p.lpart[(int64_t)(q + 16 * u) * b + i];
+    a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) most = fmaxf(most, v[u]);
   }
-  for (; q < nparts; q += 16) a0 += p.lpart[(int64_t)q * b + i];
+  for (; q < nparts; q += 16) {
+    const float v = p.lpart[(int64_t)q * b + i];
+    a0 += v;
+    most = fmaxf(most, v);
+  }
   red[wave][lane] = (a0 + a1) + (a2 + a3);
+  const int wave_over = __any(most > ROW_PART_MAX);
+  if (lane == 0) over[wave] = wave_over;
   __syncthreads();
-  // wave 0, lane = row: outputs of the row from its off-label sum and its label numerator; is the total lost?
+  // wave 0, lane = row: outputs of the row from its off-label sum and its label numerator; is the total lost?  (One that is not
+  // a number comes from features that are not, or from logits past fp32: no other reference of the row's helps.)
   const bool writer = blockIdx.z == 0;                  // of several workgroups on the same rows
   auto finish = [&](float off, float ed) {
     if (i >= bl.rows) {                                 // a padding row: no weight anywhere
@@ -533,16 +547,16 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
     const float tot = off + ed;
     beta_s[lane] = 1.f / tot;
     if (writer) row_outputs(p, i, off, ed, tot);
-    return !(tot >= ROW_TOTAL_FLOOR && tot <= ROW_TOTAL_MAX);             // (catches totals that are not numbers, too)
+    return f.bad_flag ? !(tot >= ROW_TOTAL_FLOOR) : tot < ROW_TOTAL_FLOOR;
   };
   if (wave == 0) {
     float off = 0.f;
 #pragma unroll
     for (int w = 0; w < 16; w += 4) off += (red[w][lane] + red[w + 1][lane]) + (red[w + 2][lane] + red[w + 3][lane]);
     if (f.global_ref && writer) p.ref2[i] = *f.global_ref;
-    const bool lost = __any(finish(off, p.ediag[i]));
+    const bool lost = __any(finish(off, p.ediag[i])), above = __any(lane < 16 && over[lane & 15]);
     if (lane == 0) {
-      redo = lost && !f.bad_flag;
+      redo = (lost || above) && !f.bad_flag;
       if (lost && f.bad_flag) *f.bad_flag = 1;
     }
   }
