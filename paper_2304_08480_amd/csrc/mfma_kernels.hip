@@ -395,81 +395,123 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
 }
 
 // The statistics of 64 rows redone by the workgroup of k_row_merge that found one whose total is lost (inputs that are not
-// CLIP-like; nothing here is fast): a first sweep over all keys finds every row's true maximum logit, its new exponent
-// reference (recorded if `writer`), a second forms the numerators (stored to E if `store`) and the row sums against it.  Operand fragments come
-// straight from memory; wave w takes the key strips w, w + 16, ... of 32 keys against all 64 rows, laid out like the tiles
-// of the logit kernel (key rows on the M side).  Local rows i0 .. i0 + 63, global row g0 + i; Bp: key rows that exist in
-// memory, a multiple of 32.  Leaves the rows' sums in off_s and their label numerators in ed_s.
-__device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool writer, bool store,
-                                       float (*red)[64], float* ref_s, float* off_s, float* ed_s) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, half = lane >> 5;
-  const uint16_t* x[2] = {p.X + (i0 + l32) * d + half * 8, p.X + (i0 + 32 + l32) * d + half * 8};
-  f32x16 acc[2];
-  auto strip = [&](int64_t j0) {
+// CLIP-like): a first sweep over all keys finds every row's true maximum logit, its new exponent reference, a second forms the
+// numerators (stored to E if `store`) and the row sums against it.  Wave w takes the key strips w, w + 16, ... of 32 keys
+// against all 64 rows, in 16 x 16 x 32 blocks, key rows on the M side as in the logit kernel.  What bounds it is the lines of
+// the features it asks for: so the rows' go through LDS, 64 features at a time (`xt`: two such pieces, 16 KiB, 16-byte chunks
+// XOR-swizzled with the row), and a key's come straight from memory, a whole line at once.  (All rows redone, features of norm 4
+// to 8 at B = 32768, d = 512: a call takes 2.9 ms at N = 8 and 2.35 at N = 64; with both operands' fragments straight from
+// memory and every workgroup on the same rows at it, 6.1 and 5.5; a call that redoes none 0.9 and 0.16.)
+// Local rows i0 .. i0 + 63, global row g0 + i; Bp: key rows that exist in memory, a multiple of 32.  Leaves the rows' sums in
+// off_s and their label numerators in ed_s.
+__device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool store,
+                                       float (*red)[64], float* ref_s, float* off_s, float* ed_s, char* xt) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, grp = lane >> 4;
+  const uint32_t row_bytes = (uint32_t)d * 2;
+  const uint32_t y_off = l16 * row_bytes + grp * 16;                               // of a lane's piece from its 16 keys' first
+  const char* xb = uniform_ptr(p.X + i0 * d);                                      // threads 0 .. 511: row t / 8, chunk t % 8 of a piece
+  const uint32_t x_off = (uint32_t)(t >> 3) * row_bytes + (t & 7) * 16;
+  const uint32_t x_put = (uint32_t)((t >> 3) * 128 + (((t & 7) ^ ((t >> 3) & 7)) << 4));
+  int buf = 0;
+  f32x4 acc[2][4];                                        // [16 keys][16 rows]; a lane: keys 4 grp .. + 3 of row l16
+  auto strip = [&](int j0) {                              // (all waves together)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
-    const uint16_t* y = p.Y + (j0 + l32) * d + half * 8;
-    for (int64_t k = 0; k < d; k += 16) {
-      const u32x4 a = *reinterpret_cast<const u32x4*>(y + k);
-      mfma1(acc[0], a, *reinterpret_cast<const u32x4*>(x[0] + k));
-      mfma1(acc[1], a, *reinterpret_cast<const u32x4*>(x[1] + k));
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const char* yb = uniform_ptr(p.Y + (int64_t)j0 * d);
+    u32x4 next = {0u, 0u, 0u, 0u};
+    if (t < 512) next = *reinterpret_cast<const u32x4*>(xb + x_off);
+#pragma unroll 1
+    for (uint32_t k = 0; k < row_bytes; k += 128) {
+      bf16x8 a[2][2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) a[h][u] = *reinterpret_cast<const bf16x8*>(yb + (uint64_t)(16 * u) * row_bytes + k + 64 * h + y_off);
+      char* piece = xt + buf * 8192;
+      buf ^= 1;
+      if (t < 512) {
+        *reinterpret_cast<u32x4*>(piece + x_put) = next;
+        if (k + 128 < row_bytes) next = *reinterpret_cast<const u32x4*>(xb + x_off + k + 128);
+      }
+      lds_barrier();                                      // (the other piece: read before the previous barrier, written after it)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const bf16x8 q = *reinterpret_cast<const bf16x8*>(piece + (v * 16 + l16) * 128 + (((h * 4 + grp) ^ (l16 & 7)) << 4));
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][u], q, acc[u][v], 0, 0, 0);
+        }
     }
   };
-  int64_t label[2], self[2];
+  float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll 1
+  for (int base = 0; base < (int)Bp; base += 16 * 32) {
+    const int j0 = base + wave * 32;
+    strip(j0 < (int)Bp ? j0 : 0);                         // a wave without a strip works on the first one and drops it
+    if (j0 >= (int)Bp) continue;
 #pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    const int64_t g = g0 + i0 + bn * 32 + l32;
-    label[bn] = label_row(g, keys, variant);
-    self[bn] = masked_col(g, variant);
+    for (int v = 0; v < 4; ++v) {
+      const int self = (int)masked_col(g0 + i0 + v * 16 + l16, variant);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = j0 + u * 16 + grp * 4 + e;
+          if (j < (int)keys && j != self) m[v] = fmaxf(m[v], acc[u][v][e] * s2);
+        }
+    }
   }
-  float m[2] = {-INFINITY, -INFINITY};
-  for (int64_t j0 = wave * 32; j0 < Bp; j0 += 16 * 32) {
-    strip(j0);
 #pragma unroll
-    for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t j = j0 + (e >> 2) * 8 + half * 4 + (e & 3);
-        if (j < keys && j != self[bn]) m[bn] = fmaxf(m[bn], acc[bn][e] * s2);
-      }
-  }
-#pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    m[bn] = fmaxf(m[bn], __shfl_xor(m[bn], 32));
-    if (half == 0) red[wave][bn * 32 + l32] = m[bn];
+  for (int v = 0; v < 4; ++v) {
+    m[v] = fmaxf(m[v], __shfl_xor(m[v], 16));
+    m[v] = fmaxf(m[v], __shfl_xor(m[v], 32));
+    if (grp == 0) red[wave][v * 16 + l16] = m[v];
   }
   __syncthreads();
   if (wave == 0) {
     float r = red[0][lane];
     for (int w = 1; w < 16; ++w) r = fmaxf(r, red[w][lane]);
     ref_s[lane] = r;
-    if (writer) p.ref2[i0 + lane] = r;
+    p.ref2[i0 + lane] = r;
   }
   __syncthreads();
-  const float ref[2] = {ref_s[l32], ref_s[32 + l32]};
-  float rs[2] = {0.f, 0.f};
-  for (int64_t j0 = wave * 32; j0 < Bp; j0 += 16 * 32) {
-    strip(j0);
+  float rs[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int base = 0; base < (int)Bp; base += 16 * 32) {
+    const int j0 = base + wave * 32;
+    strip(j0 < (int)Bp ? j0 : 0);
+    if (j0 >= (int)Bp) continue;
+    // (element (row, key) of the group is at e_index: scalar base of the strip plus this lane's place in it)
+    char* erow = const_cast<char*>(uniform_ptr(p.E + e_index(i0, j0, Bp))) + (uint32_t)(((grp >> 1) * 512 + l16 * 8 + (grp & 1) * 4) * 2);
 #pragma unroll
-    for (int bn = 0; bn < 2; ++bn)
+    for (int v = 0; v < 4; ++v) {
+      const int row = v * 16 + l16;
+      const int64_t g = g0 + i0 + row;
+      const int label = (int)label_row(g, keys, variant), self = (int)masked_col(g, variant);
+      const float ref = ref_s[row];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t j = j0 + q * 8 + half * 4, i = i0 + bn * 32 + l32;
-        bf16x4 v;
+      for (int u = 0; u < 2; ++u) {
+        const int j = j0 + u * 16 + grp * 4;
+        bf16x4 o;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float e = j + r < keys && j + r != self[bn] ? __builtin_amdgcn_exp2f(fmaf(acc[bn][q * 4 + r], s2, -ref[bn])) : 0.f;
-          if (j + r == label[bn]) { ed_s[bn * 32 + l32] = e; e = 0.f; }
-          rs[bn] += e;
-          v[r] = (__bf16)e;
+        for (int e = 0; e < 4; ++e) {
+          float n = j + e < (int)keys && j + e != self ? __builtin_amdgcn_exp2f(fmaf(acc[u][v][e], s2, -ref)) : 0.f;
+          if (j + e == label) { ed_s[row] = n; n = 0.f; }
+          rs[v] += n;
+          o[e] = (__bf16)n;
         }
-        if (store) *reinterpret_cast<bf16x4*>(p.E + e_index(i, j, Bp)) = v;
+        if (store) *reinterpret_cast<bf16x4*>(erow + (u * 1024 + v * 128) * 2) = o;
       }
+    }
   }
 #pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    rs[bn] += __shfl_xor(rs[bn], 32);
-    if (half == 0) red[wave][bn * 32 + l32] = rs[bn];
+  for (int v = 0; v < 4; ++v) {
+    rs[v] += __shfl_xor(rs[v], 16);
+    rs[v] += __shfl_xor(rs[v], 32);
+    if (grp == 0) red[wave][v * 16 + l16] = rs[v];
   }
   __syncthreads();
   if (wave == 0) {
@@ -503,7 +545,7 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
   __shared__ float red[16][64];
   __shared__ float beta_s[64], ref_s[64], off_s[64], ed_s[64];
   __shared__ int redo, over[16];
-  __shared__ float tile[64][65];
+  __shared__ __attribute__((aligned(16))) float tile[64][65];
   const BlockPtrs& p = bl.z[blockIdx.y];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
@@ -561,13 +603,16 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
     }
   }
   __syncthreads();
-  if (redo) {
-    redo_rows(p, bl.variant, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, writer, f.store && writer, red, ref_s, off_s, ed_s);
-    if (wave == 0) finish(off_s[lane], ed_s[lane]);         // (ediag keeps the old numerators: the other workgroups read them)
+  int chunks = f.fchunks;
+  if (redo) {                                           // by the first of the workgroups on these rows, which goes on to all of their features
+    if (!writer) return;
+    chunks = 1;
+    redo_rows(p, bl.variant, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, f.store, red, ref_s, off_s, ed_s, reinterpret_cast<char*>(tile));
+    if (wave == 0) finish(off_s[lane], ed_s[lane]);
     __syncthreads();
   }
   if (f.fchunks) {
-    const int64_t per = (f.d / 64 + f.fchunks - 1) / f.fchunks * 64, k0 = blockIdx.z * per;
+    const int64_t per = (f.d / 64 + chunks - 1) / chunks * 64, k0 = blockIdx.z * per;
     scale_transpose_rows<1024>(p, b, f.d, k0, k0 + per < f.d ? k0 + per : f.d, i0, 64, beta_s, tile);
   }
 }
