@@ -217,6 +217,24 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
 DISCO_API int disco_set_stage_events(void** events, int count);
 
 /*
+ * For benchmarks and tests: which kernels a call runs and how its work is cut.  path as for the loss entry points (two_view != 0:
+ * of ntxent_loss_fwd_bwd).  workspace_limit 0: a call with a workspace of its own; else what a call may take, as
+ * disco_loss_fwd_bwd_static's may DISCO_STATIC_SCRATCH_BYTES.  Returns DISCO_OK, the status that the call would return for these
+ * arguments, or DISCO_ERR_WORKSPACE where the path has no plan within the limit (workspace_bytes is then above it).  Host only.
+ */
+enum { DISCO_KERNELS_SMALL = 0, DISCO_KERNELS_SPLIT = 1, DISCO_KERNELS_TILES = 2, DISCO_KERNELS_SYMMETRIC = 3 };
+typedef struct {
+  int32_t path;                     /* what `path` resolves to */
+  int32_t kernels;                  /* fp32 arithmetic: SMALL, or SPLIT (exact bf16 planes); bf16: TILES or SYMMETRIC */
+  int32_t logit_tile, gradient_tile;  /* 128 or 256; 0: SMALL */
+  int32_t row_chunks, key_panels;   /* the rank's rows in chunks / the keys in panels, each taken through logits and gradients */
+  int32_t query_splits, key_splits; /* of the two gradient reductions */
+  double microseconds;              /* the model's time that the plan was chosen by (not a measurement) */
+  uint64_t workspace_bytes;
+} disco_plan;
+DISCO_API int disco_describe_plan(int64_t B, int64_t d, int32_t N, int dtype, int path, int two_view, size_t workspace_limit, disco_plan* out);
+
+/*
  * Measurement only: `workgroups` workgroups of 8 waves each issue `iters` x 8 bf16 MFMA 32x32x16 instructions per
  * wave (32768 flop each) from registers, with no memory traffic: what the matrix cores sustain once the clock
  * management has settled, the ceiling under the published peak that a tile kernel works against.  varied != 0: the

@@ -22,6 +22,16 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdisco.so")
 
 
+DISCO_KERNELS_SMALL, DISCO_KERNELS_SPLIT, DISCO_KERNELS_TILES, DISCO_KERNELS_SYMMETRIC = 0, 1, 2, 3
+
+
+class DiscoPlan(ctypes.Structure):
+    _fields_ = [("path", ctypes.c_int32), ("kernels", ctypes.c_int32), ("logit_tile", ctypes.c_int32),
+                ("gradient_tile", ctypes.c_int32), ("row_chunks", ctypes.c_int32), ("key_panels", ctypes.c_int32),
+                ("query_splits", ctypes.c_int32), ("key_splits", ctypes.c_int32), ("microseconds", ctypes.c_double),
+                ("workspace_bytes", ctypes.c_uint64)]
+
+
 class DiscoError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -68,6 +78,8 @@ def _load():
     lib.disco_logit_scale_fwd.restype = ci
     lib.disco_logit_scale_bwd.argtypes = [vp, f32, vp, vp, ci, vp]
     lib.disco_logit_scale_bwd.restype = ci
+    lib.disco_describe_plan.argtypes = [i64, i64, i32, ci, ci, ci, sz, ctypes.POINTER(DiscoPlan)]
+    lib.disco_describe_plan.restype = ci
     lib.disco_mfma_probe.argtypes = [ci, ci, ci, vp, vp, vp]
     lib.disco_mfma_probe.restype = ci
     lib.disco_status_string.argtypes = [ci]
@@ -158,6 +170,14 @@ def ntxent_loss_fwd_bwd(Z, B, d, rank, N, s, dtype, path, accumulate, loss, gZ, 
 def disco_set_stage_events(events, count: int) -> int:
     """`events`: a ctypes array of c_void_p holding hipEvent_t handles (kept alive by the caller), or None."""
     return _lib.disco_set_stage_events(events, int(count))
+
+
+def disco_describe_plan(B, d, N, dtype, path, two_view=False, workspace_limit=0, check=True) -> DiscoPlan:
+    plan = DiscoPlan()
+    st = _lib.disco_describe_plan(B, d, N, dtype, path, int(two_view), workspace_limit, ctypes.byref(plan))
+    if check and st != DISCO_OK:
+        raise DiscoError(st, "disco_describe_plan")
+    return plan
 
 
 def disco_mfma_probe(workgroups, iters, varied, sink, clocks, stream=None, check=True) -> int:

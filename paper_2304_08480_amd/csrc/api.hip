@@ -77,14 +77,12 @@ bool on_small_kernels(int path, int r, int64_t B, int64_t d, int32_t N, int vari
   return path == DISCO_PATH_AUTO && (r == DISCO_PATH_MATERIALIZED || r == DISCO_PATH_SYMMETRIC) && small_beats_tiles(B, d, N, variant);
 }
 
-// path: what the caller asked for, r: what it resolves to
-size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant) {
+// path: what the caller asked for, r: what it resolves to.  limit: of the bf16 paths' plans (above it: no plan keeps to it).
+size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant, size_t limit) {
   if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, variant)) return naive_workspace_bytes(B, d, N, dtype, variant, path == DISCO_PATH_NAIVE);
   // (the bf16 paths lay their workspace out for two blocks; the one-block loss uses the first half of each part)
-  if (r == DISCO_PATH_MATERIALIZED) return mfma_stored_workspace_bytes(B, d, N, variant);
-  if (r == DISCO_PATH_FUSED) return mfma_fused_workspace_bytes(B, d, N, variant);
-  if (r == DISCO_PATH_SYMMETRIC) return mfma_sym_workspace_bytes(B, d);
-  return 0;
+  if (r == DISCO_PATH_SYMMETRIC) return mfma_sym_workspace_bytes(B, d, limit);
+  return mfma_workspace_bytes(B, d, N, variant, r == DISCO_PATH_FUSED, limit);
 }
 
 }  // namespace
@@ -93,19 +91,20 @@ extern "C" int disco_resolve_path(int64_t B, int64_t d, int32_t N, int dtype, in
   return resolve(B, d, N, dtype, path);
 }
 
-extern "C" size_t disco_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path) {
+namespace disco {
+
+size_t loss_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path, size_t limit) {
   const int r = resolve(B, d, N, dtype, path);
-  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_CLIP) : 0;
+  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_CLIP, limit) : 0;
 }
 
-extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N,
-                                  float s, int dtype, int path, int accumulate, float* loss, float* gI, float* gT,
-                                  float* gs, void* workspace, size_t workspace_bytes, void* hip_stream) {
+int loss_call(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N, float s, int dtype, int path, int accumulate,
+              float* loss, float* gI, float* gT, float* gs, void* workspace, size_t workspace_bytes, void* hip_stream, size_t limit) {
   if (!I || !T || !loss || !gI || !gT || !gs) return DISCO_ERR_NULL;
   int r = resolve(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_CLIP);
+  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_CLIP, limit);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(I) && aligned16(T) && aligned16(gI) && aligned16(gT))) return DISCO_ERR_UNSUPPORTED;
@@ -115,12 +114,25 @@ extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64
   p.I = I; p.T = T; p.B = B; p.d = d; p.rank = rank; p.N = N; p.b = B / N; p.s = s; p.dtype = dtype;
   p.accumulate = accumulate ? 1 : 0;
   p.lean = path == DISCO_PATH_NAIVE;
+  p.limit = limit;
   p.loss = loss; p.gI = gI; p.gT = gT; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
   if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
   if (r == DISCO_PATH_SYMMETRIC) return mfma_sym_run(p);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
+}
+
+}  // namespace disco
+
+extern "C" size_t disco_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path) {
+  return loss_workspace_bytes(B, d, N, dtype, path, NO_LIMIT);
+}
+
+extern "C" int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N,
+                                  float s, int dtype, int path, int accumulate, float* loss, float* gI, float* gT,
+                                  float* gs, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  return loss_call(I, T, B, d, rank, N, s, dtype, path, accumulate, loss, gI, gT, gs, workspace, workspace_bytes, hip_stream, NO_LIMIT);
 }
 
 extern "C" int clip_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64_t d, float s, int dtype, int path,
@@ -137,7 +149,7 @@ extern "C" int ntxent_resolve_path(int64_t B, int64_t d, int32_t N, int dtype, i
 
 extern "C" size_t ntxent_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path) {
   const int r = resolve(B, d, N, dtype, path, LOSS_NTXENT);
-  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT) : 0;
+  return r > 0 ? workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT, NO_LIMIT) : 0;
 }
 
 extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t rank, int32_t N, float s, int dtype,
@@ -147,7 +159,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   const int r = resolve(B, d, N, dtype, path, LOSS_NTXENT);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT);
+  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT, NO_LIMIT);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(Z) && aligned16(gZ))) return DISCO_ERR_UNSUPPORTED;
@@ -156,11 +168,26 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   p.I = Z; p.T = Z; p.B = B; p.d = d; p.rank = rank; p.N = N; p.b = B / N; p.s = s; p.dtype = dtype;
   p.accumulate = accumulate ? 1 : 0;
   p.lean = path == DISCO_PATH_NAIVE;
+  p.limit = NO_LIMIT;
   p.loss = loss; p.gI = gZ; p.gT = gZ; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
   if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
+}
+
+extern "C" int disco_describe_plan(int64_t B, int64_t d, int32_t N, int dtype, int path, int two_view, size_t workspace_limit, disco_plan* out) {
+  if (!out) return DISCO_ERR_NULL;
+  const int variant = two_view ? LOSS_NTXENT : LOSS_CLIP;
+  const size_t limit = workspace_limit ? workspace_limit : NO_LIMIT;
+  *out = disco_plan{};
+  const int r = resolve(B, d, N, dtype, path, variant);
+  if (r < 0) return -r;
+  out->path = r;
+  out->workspace_bytes = workspace_need(path, r, B, d, N, dtype, variant, limit);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, variant)) naive_describe(B, d, N, dtype, variant, path == DISCO_PATH_NAIVE, out);
+  else mfma_describe(B, d, N, variant, r == DISCO_PATH_FUSED, r == DISCO_PATH_SYMMETRIC, limit, out);
+  return out->workspace_bytes > limit ? DISCO_ERR_WORKSPACE : DISCO_OK;
 }
 
 extern "C" const char* disco_status_string(int status) {

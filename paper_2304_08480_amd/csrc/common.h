@@ -20,6 +20,7 @@ struct Problem {
   int dtype;
   int accumulate;
   bool lean;          // fp32 path: see naive_workspace_bytes
+  size_t limit;       // bf16 paths: most bytes that the plan may take (NO_LIMIT: the caller's workspace is what the plan asks for)
   float* loss;
   float* gI;
   float* gT;
@@ -32,6 +33,7 @@ struct Problem {
 };
 
 enum { LOSS_CLIP = 0, LOSS_NTXENT = 1 };
+constexpr size_t NO_LIMIT = ~(size_t)0;
 
 // Global row of the positive of global row g, and the column that is left out of row g's softmax (-1: none).
 __host__ __device__ inline int64_t label_row(int64_t g, int64_t B, int variant) {
@@ -82,17 +84,26 @@ bool split_supported(int64_t B, int64_t b);
 bool split_aligned(const Problem& p);
 double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, size_t* bytes);
 int split_run(const Problem& p, size_t limit);
+void split_describe(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, disco_plan* out);
 
 // the bf16 tile kernels can take the shape (materialized path; a rank share that is not a whole number of 256-row
 // tiles is zero-padded in the workspace) / the share is whole tiles (what the fused and symmetric paths need too)
 bool mfma_supported(int64_t B, int64_t d, int32_t N, int dtype, int variant = LOSS_CLIP);
 bool mfma_whole_tiles(int64_t B, int32_t N);
 double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant);      // its tile kernels, without the launches
-size_t mfma_stored_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant = LOSS_CLIP);
+size_t mfma_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant, bool fused, size_t limit);      // the plan's within `limit`, else more
 int mfma_stored_run(const Problem& p);
-size_t mfma_fused_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant = LOSS_CLIP);
 int mfma_fused_run(const Problem& p);
-size_t mfma_sym_workspace_bytes(int64_t B, int64_t d);
+size_t mfma_sym_workspace_bytes(int64_t B, int64_t d, size_t limit);
 int mfma_sym_run(const Problem& p);      // N = 1, the CLIP loss only
+
+// What a call would run (disco_describe_plan), without the fields that api.hip fills in itself.
+void naive_describe(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean, disco_plan* out);
+void mfma_describe(int64_t B, int64_t d, int32_t N, int variant, bool fused, bool sym, size_t limit, disco_plan* out);
+
+// disco_loss_fwd_bwd with its plan kept within `limit`.
+size_t loss_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path, size_t limit);
+int loss_call(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N, float s, int dtype, int path, int accumulate,
+              float* loss, float* gI, float* gT, float* gs, void* workspace, size_t workspace_bytes, void* hip_stream, size_t limit);
 
 }  // namespace disco

@@ -1214,16 +1214,22 @@ void split(int total, int want, int& splits, int& per) {
   splits = (total + per - 1) / per;                                  // those that are not empty
 }
 
-// tile: 0, or the size that the caller's kernels are written for.
-Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int tile) {
+// tile: 0, or the size that the caller's kernels are written for.  limit: most bytes the workspace may take (of
+// a call without one of its own: B = 24000, N = 16, d = 512 memory-lean takes 1390 us in 64 MiB and 353 in 148); where no plan
+// keeps to it the result's total is above it.
+Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int tile, size_t limit) {
   static const int Q_SPLITS[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
-  Plan best;
+  Plan best{};
   best.us = 1e300;
-  bool best_fits = false;
-  size_t most = ~(size_t)0;                                          // chunks of rows: no more memory than with the widest panels
-  // (smaller chunks are for calls that the largest would take out of the static array)
+  best.total = ~(size_t)0;
+  size_t most = limit;
+  // form 0: all rows, in one key panel or several; the memory-lean path's others: rows in chunks.  Those take no more memory than
+  // the widest panels would, or the little that a call without a workspace of its own may take.
   for (int form = 0; form < (fused ? 4 : 1); ++form) {
-    if (form == 1) most = best.total + (size_t)4 * best.b_all * (panel_limit(best) > best.W ? panel_limit(best) - best.W : 0);
+    if (form == 1 && limit == NO_LIMIT) {
+      most = best.total + (size_t)4 * best.b_all * (panel_limit(best) > best.W ? panel_limit(best) - best.W : 0);
+      if (most < DISCO_STATIC_SCRATCH_BYTES) most = DISCO_STATIC_SCRATCH_BYTES;
+    }
     for (int tl = 128; tl <= 256; tl += 128)
       for (int tg = 128; tg <= 256; tg += 128) {
         if (tile && (tl != tile || tg != tile)) continue;
@@ -1242,12 +1248,11 @@ Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int ti
             double us = base + pl.npanels * grads_us(pl, nblk, pl.ktps, pl.splitk, pl.key_ktps, pl.key_splits);
             // a further chunk reads the key-side gradient back and has its own merge and finalize launches
             us = chunks * us + (chunks - 1.0) * (4.0 * nblk * pl.B * d / BYTES_PER_US + 25.0);
-            if (best_fits && us >= best.us) continue;
+            if (us >= best.us) continue;
             layout(pl);
             if (pl.total > most) continue;
-            // a call whose workspace can stay within the library's static array stays within it
-            const bool fits = pl.total <= DISCO_STATIC_SCRATCH_BYTES;
-            if (fits > best_fits || (fits == best_fits && us < best.us)) { best = pl; best.us = us; best_fits = fits; }
+            best = pl;
+            best.us = us;
           }
         }
       }
@@ -1255,9 +1260,9 @@ Plan compare_plans(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int ti
   return best;
 }
 
-Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk = 2, int tile = 0) {
-  static thread_local PlanCache<Plan, 6> cache;
-  return cache.get({B, d, N, fused, nblk, tile}, [&] { return compare_plans(B, d, N, fused, nblk, tile); });
+Plan make_plan(int64_t B, int64_t d, int32_t N, bool fused, int nblk, int tile, size_t limit) {
+  static thread_local PlanCache<Plan, 7> cache;
+  return cache.get({B, d, N, fused, nblk, tile, (int64_t)limit}, [&] { return compare_plans(B, d, N, fused, nblk, tile, limit); });
 }
 
 // Query tiles per super-block of the logit tile walk (superblock_tile): the largest power of two <= 8 that divides
@@ -1360,7 +1365,7 @@ void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, int64_t g0, f
 // gate / gate_value: see Blocks.  marks: record the benchmark's stage events.
 int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_value = 0, bool marks = true) {
   const int nblk = loss_blocks(pr.variant);
-  const Plan pl = make_plan(pr.B, pr.d, pr.N, fused, nblk);
+  const Plan pl = make_plan(pr.B, pr.d, pr.N, fused, nblk, 0, pr.limit);
   if ((pl.tl == 256 || pl.tg == 256) && !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
   if ((pl.tl == 128 || pl.tg == 128) && !TileKernels<128>::lds_ok()) return DISCO_ERR_HIP;
   const int cus = compute_units();
@@ -1479,8 +1484,11 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
 // 3964, 256: 158 / 112; 6912, 320: 274 / 293; 8728, 320: 397 / 498.)
 bool sym_two_block(int64_t B, int64_t d) { return (double)B * B * d < 1e10; }
 
-size_t sym_tail(int64_t B, int64_t d) {
-  const size_t a = make_plan(B, d, 1, false, 1, 256).total, c = make_plan(B, d, 1, false, 2).total;
+// Behind the larger of the two plans' workspaces: the hand-over flag and the reference.
+constexpr size_t SYM_WORDS = 256;
+size_t sym_plan_limit(size_t limit) { return limit == NO_LIMIT ? NO_LIMIT : limit - SYM_WORDS; }
+size_t sym_tail(int64_t B, int64_t d, size_t limit) {
+  const size_t a = make_plan(B, d, 1, false, 1, 256, sym_plan_limit(limit)).total, c = make_plan(B, d, 1, false, 2, 0, sym_plan_limit(limit)).total;
   return a > c ? a : c;
 }
 
@@ -1488,11 +1496,11 @@ int mfma_sym_run_impl(const Problem& pr) {
   static const bool lds_ok = allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES<256>) && allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES<256>);
   if (!lds_ok || !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
   if (sym_two_block(pr.B, pr.d)) return mfma_run(pr, false);
-  const Plan pl = make_plan(pr.B, pr.d, 1, false, 1, 256);
+  const Plan pl = make_plan(pr.B, pr.d, 1, false, 1, 256, sym_plan_limit(pr.limit));
   const int persistent_wgs = compute_units();
   const int64_t B = pl.B, d = pl.d, Br = pl.B_real;        // whole tiles / the rows that exist
   char* ws = static_cast<char*>(pr.ws);
-  const size_t tail = sym_tail(Br, d);
+  const size_t tail = sym_tail(Br, d, pr.limit);
   int* gate = reinterpret_cast<int*>(ws + tail);
   float* rglobal = reinterpret_cast<float*>(ws + tail + 128);
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
@@ -1589,7 +1597,9 @@ int mfma_sym_run_impl(const Problem& pr) {
   k_scalars<<<1, 1024, 0, st>>>(go2, Br, c, pr.accumulate, pr.loss, pr.gs);
   stage_mark(st, stage++);
   if (hipGetLastError() != hipSuccess) return DISCO_ERR_HIP;
-  return mfma_run(pr, false, gate, 1, false);
+  Problem two_block = pr;
+  two_block.limit = sym_plan_limit(pr.limit);
+  return mfma_run(two_block, false, gate, 1, false);
 }
 
 }  // namespace
@@ -1607,14 +1617,31 @@ bool mfma_supported(int64_t B, int64_t d, int32_t N, int dtype, int variant) {
 
 bool mfma_whole_tiles(int64_t B, int32_t N) { return N > 0 && B % N == 0 && (B / N) % 256 == 0; }
 
-double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant)).us; }
-size_t mfma_stored_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant)).total; }
-size_t mfma_fused_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, true, loss_blocks(variant)).total; }
+double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant), 0, NO_LIMIT).us; }
+size_t mfma_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant, bool fused, size_t limit) {
+  return make_plan(B, d, N, fused, loss_blocks(variant), 0, limit).total;
+}
 int mfma_stored_run(const Problem& pr) { return mfma_run(pr, false); }
 int mfma_fused_run(const Problem& pr) { return mfma_run(pr, true); }
-size_t mfma_sym_workspace_bytes(int64_t B, int64_t d) {
-  return sym_two_block(B, d) ? make_plan(B, d, 1, false, 2).total : sym_tail(B, d) + 256;
+size_t mfma_sym_workspace_bytes(int64_t B, int64_t d, size_t limit) {
+  if (sym_two_block(B, d)) return make_plan(B, d, 1, false, 2, 0, limit).total;
+  const size_t tail = sym_tail(B, d, limit);
+  return tail == NO_LIMIT ? tail : tail + SYM_WORDS;
 }
 int mfma_sym_run(const Problem& pr) { return mfma_sym_run_impl(pr); }
+
+void mfma_describe(int64_t B, int64_t d, int32_t N, int variant, bool fused, bool sym, size_t limit, disco_plan* out) {
+  const bool one = sym && !sym_two_block(B, d);
+  const Plan pl = one ? make_plan(B, d, 1, false, 1, 256, sym_plan_limit(limit)) : make_plan(B, d, N, fused, loss_blocks(variant), 0, limit);
+  out->kernels = one ? DISCO_KERNELS_SYMMETRIC : DISCO_KERNELS_TILES;
+  if (pl.total == NO_LIMIT) return;
+  out->logit_tile = pl.tl;
+  out->gradient_tile = pl.tg;
+  out->row_chunks = (int)((pl.b_all + pl.b - 1) / pl.b);
+  out->key_panels = pl.npanels;
+  out->query_splits = pl.splitk;
+  out->key_splits = pl.key_splits;
+  out->microseconds = pl.us;
+}
 
 }  // namespace disco

@@ -728,6 +728,19 @@ size_t naive_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int var
   return split > least ? split : least;             // (unaligned gradients take the small kernels whatever the plan)
 }
 
+void naive_describe(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean, disco_plan* out) {
+  const int64_t b = B / N;
+  const int nb = loss_blocks(variant);
+  size_t limit;
+  if (split_bytes(B, d, b, dtype, nb, lean, &limit)) {
+    split_describe(B, d, b, dtype, nb, limit, out);
+    return;
+  }
+  out->kernels = DISCO_KERNELS_SMALL;
+  out->row_chunks = out->key_panels = out->query_splits = out->key_splits = 1;
+  out->microseconds = small_us(b, B, d, dtype, nb);
+}
+
 // Is a call that the bf16 tile kernels take faster on the small ones?  Few tiles leave those kernels with their seven launches,
 // 27 us on top of the tiles' estimate whatever the shape; the small ones are three.  (Measured, us, tiles / small, bf16:
 // B = 256, N = 1, d = 128: 34 / 21; 512, 2, 256: 37 / 25; 1024, 4, 512: 44 / 34; 1024, 2, 256: 41 / 38; 2048, 16, 512: 45 / 42;

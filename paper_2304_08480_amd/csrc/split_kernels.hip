@@ -543,6 +543,18 @@ double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, siz
   return 0.77 * pl.us * (double)((b + pl.chunk - 1) / pl.chunk);
 }
 
+void split_describe(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, disco_plan* out) {
+  const SplitPlan pl = plan_within(B, d, b, dtype, nb, limit);
+  size_t bytes;
+  out->kernels = DISCO_KERNELS_SPLIT;
+  out->logit_tile = out->gradient_tile = pl.T;
+  out->row_chunks = (int)((b + pl.chunk - 1) / pl.chunk);
+  out->key_panels = 1;
+  out->query_splits = pl.splitk;
+  out->key_splits = pl.key_splits;
+  out->microseconds = split_estimate_us(B, d, b, dtype, nb, limit, &bytes);
+}
+
 int split_run(const Problem& pr, size_t limit) {
   const SplitPlan pl = plan_within(pr.B, pr.d, pr.b, pr.dtype, loss_blocks(pr.variant), limit);
   return pr.dtype == DISCO_BF16 ? split_run_typed<DISCO_BF16>(pr, pl) : split_run_typed<DISCO_F32>(pr, pl);

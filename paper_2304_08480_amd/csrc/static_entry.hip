@@ -38,13 +38,12 @@ extern "C" int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B
   const int r = disco_resolve_path(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  // what AUTO would take, or, where that is too much, the path it resolves to by name
-  size_t need = disco_workspace_bytes(B, d, N, dtype, path);
-  if (need > DISCO_STATIC_SCRATCH_BYTES) { path = r; need = disco_workspace_bytes(B, d, N, dtype, path); }
+  // what AUTO would take, or, where that is too much, the path it resolves to by name; plans within the array
+  size_t need = loss_workspace_bytes(B, d, N, dtype, path, DISCO_STATIC_SCRATCH_BYTES);
+  if (need > DISCO_STATIC_SCRATCH_BYTES) { path = r; need = loss_workspace_bytes(B, d, N, dtype, path, DISCO_STATIC_SCRATCH_BYTES); }
   if (need == 0 || need > DISCO_STATIC_SCRATCH_BYTES) return DISCO_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return DISCO_ERR_HIP;
-  return disco_loss_fwd_bwd(I, T, B, d, rank, N, s, dtype, path, accumulate, loss, gI, gT, gs, ws, DISCO_STATIC_SCRATCH_BYTES,
-                            hip_stream);
+  return loss_call(I, T, B, d, rank, N, s, dtype, path, accumulate, loss, gI, gT, gs, ws, DISCO_STATIC_SCRATCH_BYTES, hip_stream,
+                   DISCO_STATIC_SCRATCH_BYTES);
 }
-
