@@ -130,7 +130,8 @@ DISCO_API size_t disco_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtyp
  *               1: the rank's results are added to what the buffers hold.
  *   loss, gs    device, one fp32 each.      gI, gT: device, row-major B x d fp32.
  *   workspace   device scratch of at least disco_workspace_bytes(...) bytes, 256-byte aligned;
- *               contents before and after the call are unspecified.
+ *               contents before and after the call are unspecified.  (DISCO_PATH_AUTO: with less than that, but enough
+ *               for the path that disco_resolve_path names, the call runs that path as if asked for by name.)
  */
 DISCO_API int disco_loss_fwd_bwd(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N,
                        float s, int dtype, int path, int accumulate,

@@ -85,6 +85,14 @@ size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtyp
   return mfma_workspace_bytes(B, d, N, variant, r == DISCO_PATH_FUSED, limit);
 }
 
+// The workspace a call takes, for as much as it was handed: where AUTO's own choice of kernels wants more, `path` becomes the path
+// that AUTO resolves to, by name (a caller may have asked disco_resolve_path and sized its workspace for that).
+size_t settle_path(int& path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant, size_t limit, size_t have) {
+  size_t need = workspace_need(path, r, B, d, N, dtype, variant, limit);
+  if (path == DISCO_PATH_AUTO && have < need) need = workspace_need(path = r, r, B, d, N, dtype, variant, limit);
+  return need;
+}
+
 }  // namespace
 
 extern "C" int disco_resolve_path(int64_t B, int64_t d, int32_t N, int dtype, int path) {
@@ -101,10 +109,10 @@ size_t loss_workspace_bytes(int64_t B, int64_t d, int32_t N, int dtype, int path
 int loss_call(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, int32_t N, float s, int dtype, int path, int accumulate,
               float* loss, float* gI, float* gT, float* gs, void* workspace, size_t workspace_bytes, void* hip_stream, size_t limit) {
   if (!I || !T || !loss || !gI || !gT || !gs) return DISCO_ERR_NULL;
-  int r = resolve(B, d, N, dtype, path);
+  const int r = resolve(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_CLIP, limit);
+  const size_t need = settle_path(path, r, B, d, N, dtype, LOSS_CLIP, limit, workspace_bytes);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(I) && aligned16(T) && aligned16(gI) && aligned16(gT))) return DISCO_ERR_UNSUPPORTED;
@@ -159,7 +167,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   const int r = resolve(B, d, N, dtype, path, LOSS_NTXENT);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  const size_t need = workspace_need(path, r, B, d, N, dtype, LOSS_NTXENT, NO_LIMIT);
+  const size_t need = settle_path(path, r, B, d, N, dtype, LOSS_NTXENT, NO_LIMIT, workspace_bytes);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(Z) && aligned16(gZ))) return DISCO_ERR_UNSUPPORTED;

@@ -38,10 +38,10 @@ extern "C" int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B
   const int r = disco_resolve_path(B, d, N, dtype, path);
   if (r < 0) return -r;
   if (rank < 0 || rank >= N) return DISCO_ERR_SHAPE;
-  // what AUTO would take, or, where that is too much, the path it resolves to by name; plans within the array
-  size_t need = loss_workspace_bytes(B, d, N, dtype, path, DISCO_STATIC_SCRATCH_BYTES);
-  if (need > DISCO_STATIC_SCRATCH_BYTES) { path = r; need = loss_workspace_bytes(B, d, N, dtype, path, DISCO_STATIC_SCRATCH_BYTES); }
-  if (need == 0 || need > DISCO_STATIC_SCRATCH_BYTES) return DISCO_ERR_WORKSPACE;
+  // (AUTO takes the kernels that fit the array, the bf16 plans keep within it: see loss_call)
+  if (loss_workspace_bytes(B, d, N, dtype, path, DISCO_STATIC_SCRATCH_BYTES) > DISCO_STATIC_SCRATCH_BYTES &&
+      loss_workspace_bytes(B, d, N, dtype, r, DISCO_STATIC_SCRATCH_BYTES) > DISCO_STATIC_SCRATCH_BYTES)
+    return DISCO_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return DISCO_ERR_HIP;
   return loss_call(I, T, B, d, rank, N, s, dtype, path, accumulate, loss, gI, gT, gs, ws, DISCO_STATIC_SCRATCH_BYTES, hip_stream,
