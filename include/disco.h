@@ -209,6 +209,8 @@ DISCO_API int disco_loss_fwd_bwd_static(const void* I, const void* T, int64_t B,
  * Stages of DISCO_PATH_SYMMETRIC (DISCO_STAGES_SYMMETRIC = 7): row norms + positive-pair logits + reference, logit
  *   tiles with row and column sums, both merges + transpose, combining pass, key-side GEMM, query-side split GEMM,
  *   finalize + scalars.
+ * A call records all events of the path it resolves to.  Where other kernels take it over (AUTO: the small ones of NAIVE;
+ * SYMMETRIC: the two-block ones of MATERIALIZED) the intervals are theirs and those left over, at the end, are empty.
  * Returns DISCO_OK, or DISCO_ERR_SHAPE if count < 0.
  */
 #define DISCO_STAGES_MATERIALIZED 6

@@ -85,6 +85,15 @@ size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtyp
   return mfma_workspace_bytes(B, d, N, variant, r == DISCO_PATH_FUSED, limit);
 }
 
+// The fp32 path's call, for the path r: AUTO calls that the small kernels take for a bf16 path record its further stage events at
+// their end (those stages are empty).
+int run_naive(const Problem& p, int r) {
+  const int status = naive_run(p);
+  const int stages = r == DISCO_PATH_MATERIALIZED ? DISCO_STAGES_MATERIALIZED : r == DISCO_PATH_SYMMETRIC ? DISCO_STAGES_SYMMETRIC : 0;
+  for (int k = DISCO_STAGES_NAIVE + 1; k <= stages; ++k) stage_mark(p.stream, k);
+  return status;
+}
+
 // The workspace a call takes, for as much as it was handed: where AUTO's own choice of kernels wants more, `path` becomes the path
 // that AUTO resolves to, by name (a caller may have asked disco_resolve_path and sized its workspace for that).
 size_t settle_path(int& path, int r, int64_t B, int64_t d, int32_t N, int dtype, int variant, size_t limit, size_t have) {
@@ -126,7 +135,7 @@ int loss_call(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, 
   p.loss = loss; p.gI = gI; p.gT = gT; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
-  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return run_naive(p, r);
   if (r == DISCO_PATH_SYMMETRIC) return mfma_sym_run(p);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
 }
@@ -180,7 +189,7 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   p.loss = loss; p.gI = gZ; p.gT = gZ; p.gs = gs;
   p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.stream = static_cast<hipStream_t>(hip_stream);
-  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return naive_run(p);
+  if (r == DISCO_PATH_NAIVE || on_small_kernels(path, r, B, d, N, p.variant)) return run_naive(p, r);
   return r == DISCO_PATH_MATERIALIZED ? mfma_stored_run(p) : mfma_fused_run(p);
 }
 

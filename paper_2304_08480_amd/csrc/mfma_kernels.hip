@@ -1495,7 +1495,11 @@ size_t sym_tail(int64_t B, int64_t d, size_t limit) {
 int mfma_sym_run_impl(const Problem& pr) {
   static const bool lds_ok = allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES<256>) && allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES<256>);
   if (!lds_ok || !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
-  if (sym_two_block(pr.B, pr.d)) return mfma_run(pr, false);
+  if (sym_two_block(pr.B, pr.d)) {
+    const int status = mfma_run(pr, false);
+    stage_mark(pr.stream, DISCO_STAGES_SYMMETRIC);
+    return status;
+  }
   const Plan pl = make_plan(pr.B, pr.d, 1, false, 1, 256, sym_plan_limit(pr.limit));
   const int persistent_wgs = compute_units();
   const int64_t B = pl.B, d = pl.d, Br = pl.B_real;        // whole tiles / the rows that exist
