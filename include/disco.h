@@ -27,9 +27,9 @@
  * nothing was launched and no output was touched.
  *
  * Stream capture: the calls enqueue kernels only (no allocation, no memset, no
- * synchronisation), so a caller may capture them in a HIP graph.  The first call of a
- * process on one of the bf16 MFMA paths also raises the dynamic-LDS limit of its kernels
- * (hipFuncSetAttribute), which is not a stream operation: make one call outside any
+ * synchronisation), so a caller may capture them in a HIP graph.  The first loss call of a
+ * process also raises the dynamic-LDS limits of the tile kernels (hipFuncSetAttribute), which
+ * is not a stream operation: make one call, of any sizes, dtype and path, outside any
  * capture first.
  *
  * Inputs: any finite values.  The features are expected L2-normalised (what CLIP feeds
@@ -174,7 +174,7 @@ DISCO_API int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t r
  * status codes as disco_loss_fwd_bwd without the workspace pair: the workspace is a static device array of
  * DISCO_STATIC_SCRATCH_BYTES inside the library (every GPU the library runs on holds its own copy until the
  * process ends).  The call allocates and frees nothing; on its first use on a device it looks the array's
- * address up once (not a stream operation: make one call outside any capture first, as for the MFMA paths).
+ * address up once (not a stream operation: make one call outside any capture first, as for the tile kernels).
  * Returns DISCO_ERR_WORKSPACE, before any launch, when the arguments need more than the array holds
  * (disco_workspace_bytes(...) of the path that the call resolves to > disco_static_scratch_bytes()), DISCO_ERR_HIP when
  * the address lookup fails.

@@ -85,6 +85,13 @@ size_t workspace_need(int path, int r, int64_t B, int64_t d, int32_t N, int dtyp
   return mfma_workspace_bytes(B, d, N, variant, r == DISCO_PATH_FUSED, limit);
 }
 
+// Done by the first loss call of a process, whatever it runs (one device per process here), for all kernels: a caller that keeps
+// what is no stream operation out of its captures needs one call of any sizes outside them.
+bool lds_limits_raised() {
+  static const bool ok = mfma_raise_lds() && split_raise_lds();
+  return ok;
+}
+
 // The fp32 path's call, for the path r: AUTO calls that the small kernels take for a bf16 path record its further stage events at
 // their end (those stages are empty).
 int run_naive(const Problem& p, int r) {
@@ -125,6 +132,8 @@ int loss_call(const void* I, const void* T, int64_t B, int64_t d, int32_t rank, 
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(I) && aligned16(T) && aligned16(gI) && aligned16(gT))) return DISCO_ERR_UNSUPPORTED;
+
+  if (!lds_limits_raised()) return DISCO_ERR_HIP;
 
   Problem p;
   p.variant = LOSS_CLIP;
@@ -180,6 +189,8 @@ extern "C" int ntxent_loss_fwd_bwd(const void* Z, int64_t B, int64_t d, int32_t 
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return DISCO_ERR_WORKSPACE;
   if (r != DISCO_PATH_NAIVE && !(aligned16(Z) && aligned16(gZ))) return DISCO_ERR_UNSUPPORTED;
+  if (!lds_limits_raised()) return DISCO_ERR_HIP;
+
   Problem p;
   p.variant = LOSS_NTXENT;
   p.I = Z; p.T = Z; p.B = B; p.d = d; p.rank = rank; p.N = N; p.b = B / N; p.s = s; p.dtype = dtype;

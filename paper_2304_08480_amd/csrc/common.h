@@ -97,6 +97,10 @@ int mfma_fused_run(const Problem& p);
 size_t mfma_sym_workspace_bytes(int64_t B, int64_t d, size_t limit);
 int mfma_sym_run(const Problem& p);      // N = 1, the CLIP loss only
 
+// Raise the dynamic-LDS limits of all their kernels (false: HIP refused).
+bool mfma_raise_lds();
+bool split_raise_lds();
+
 // What a call would run (disco_describe_plan), without the fields that api.hip fills in itself.
 void naive_describe(int64_t B, int64_t d, int32_t N, int dtype, int variant, bool lean, disco_plan* out);
 void mfma_describe(int64_t B, int64_t d, int32_t N, int variant, bool fused, bool sym, size_t limit, disco_plan* out);

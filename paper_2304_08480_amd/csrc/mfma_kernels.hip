@@ -1295,11 +1295,11 @@ bool streaming_stores(int nblk, int64_t b, int64_t W) {
   return bytes < ((int64_t)24 << 20) || bytes > ((int64_t)144 << 20);
 }
 
-// Launchers of one tile size; the LDS limit of the kernels is raised once per process (one device per process here).
+// Launchers of one tile size.
 template <int T>
 struct TileKernels {
-  static bool lds_ok() {
-    static const bool ok =
+  static bool raise_lds() {
+    return
         allow_lds(k_logit_tiles<T, true, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, false, true>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, true, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
@@ -1308,7 +1308,6 @@ struct TileKernels {
         allow_lds(k_grads<T, KEY_WRITE, false>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_WRITE, true>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true>, GEMM_SMEM_BYTES<T>) &&
         allow_lds(k_grads<T, KEY_SPLIT, false>, GEMM_SMEM_BYTES<T>);
-    return ok;
   }
   // logit tiles of the key panel [jp0, jp0 + W): statistics, stored numerators or both
   static void logits(bool stats, bool store, const Plan& pl, const Blocks& bl, int64_t g0, float s2, int64_t jp0, int64_t W, int cus, hipStream_t st) {
@@ -1366,8 +1365,6 @@ void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, int64_t g0, f
 int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_value = 0, bool marks = true) {
   const int nblk = loss_blocks(pr.variant);
   const Plan pl = make_plan(pr.B, pr.d, pr.N, fused, nblk, 0, pr.limit);
-  if ((pl.tl == 256 || pl.tg == 256) && !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
-  if ((pl.tl == 128 || pl.tg == 128) && !TileKernels<128>::lds_ok()) return DISCO_ERR_HIP;
   const int cus = compute_units();
   const int64_t b = pl.b, ba = pl.b_all, B = pl.B, d = pl.d, W = pl.W;     // whole tiles; the real sizes are pl.b_real, pl.B_real
   char* ws = static_cast<char*>(pr.ws);
@@ -1493,8 +1490,6 @@ size_t sym_tail(int64_t B, int64_t d, size_t limit) {
 }
 
 int mfma_sym_run_impl(const Problem& pr) {
-  static const bool lds_ok = allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES<256>) && allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES<256>);
-  if (!lds_ok || !TileKernels<256>::lds_ok()) return DISCO_ERR_HIP;
   if (sym_two_block(pr.B, pr.d)) {
     const int status = mfma_run(pr, false);
     stage_mark(pr.stream, DISCO_STAGES_SYMMETRIC);
@@ -1624,6 +1619,10 @@ bool mfma_whole_tiles(int64_t B, int32_t N) { return N > 0 && B % N == 0 && (B /
 double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant) { return make_plan(B, d, N, false, loss_blocks(variant), 0, NO_LIMIT).us; }
 size_t mfma_workspace_bytes(int64_t B, int64_t d, int32_t N, int variant, bool fused, size_t limit) {
   return make_plan(B, d, N, fused, loss_blocks(variant), 0, limit).total;
+}
+bool mfma_raise_lds() {
+  return TileKernels<256>::raise_lds() && TileKernels<128>::raise_lds() && allow_lds(k_sym_logit<false>, LOGIT_SMEM_BYTES<256>) &&
+         allow_lds(k_sym_logit<true>, LOGIT_SMEM_BYTES<256>);
 }
 int mfma_stored_run(const Problem& pr) { return mfma_run(pr, false); }
 int mfma_fused_run(const Problem& pr) { return mfma_run(pr, true); }

@@ -423,10 +423,9 @@ template <int T>
 constexpr int SPLIT_SMEM = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SMEM_BYTES<T> : Cfg<T>::SMEM_BYTES;
 
 template <int T, int NP>
-bool split_lds_ok() {
-  static const bool ok = allow_lds(k_split_logits<T, NP>, SPLIT_SMEM<T>) && allow_lds(k_split_grads<T, NP, SPLIT_KEY_WRITE>, SPLIT_SMEM<T>) &&
+bool raise_lds() {
+  return allow_lds(k_split_logits<T, NP>, SPLIT_SMEM<T>) && allow_lds(k_split_grads<T, NP, SPLIT_KEY_WRITE>, SPLIT_SMEM<T>) &&
                          allow_lds(k_split_grads<T, NP, SPLIT_KEY_ADD>, SPLIT_SMEM<T>) && allow_lds(k_split_grads<T, NP, SPLIT_KEY_PARTS>, SPLIT_SMEM<T>);
-  return ok;
 }
 
 template <int T, int NP>
@@ -447,7 +446,6 @@ void split_products(bool grads, bool parts, bool add, const SplitArgs& a, float 
 template <int DT>
 int split_run_typed(const Problem& pr, const SplitPlan& pl) {
   constexpr int NP = DT == DISCO_BF16 ? 1 : 3;
-  if (!(pl.T == 256 ? split_lds_ok<256, NP>() : split_lds_ok<128, NP>())) return DISCO_ERR_HIP;
   const int nb = loss_blocks(pr.variant);
   char* ws = static_cast<char*>(pr.ws);
   const float c = loss_norm(pr.B, pr.variant), cs = c * pr.s;
@@ -542,6 +540,8 @@ double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, siz
   // N = 8, d = 512, 113 against 87 at 4096, 16, 512, 43 against 33 at 2048, 16, d = 200 in bf16)
   return 0.77 * pl.us * (double)((b + pl.chunk - 1) / pl.chunk);
 }
+
+bool split_raise_lds() { return raise_lds<128, 1>() && raise_lds<128, 3>() && raise_lds<256, 1>() && raise_lds<256, 3>(); }
 
 void split_describe(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, disco_plan* out) {
   const SplitPlan pl = plan_within(B, d, b, dtype, nb, limit);
