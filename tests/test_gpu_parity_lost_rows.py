@@ -25,7 +25,7 @@ def _spoil(I, T, B):
 
 
 @pytest.mark.parametrize("path,B,d,N", [("materialized", 1024, 128, 4), ("materialized", 1010, 64, 2), ("fused", 1024, 128, 2),
-                                        ("fused", 1500, 64, 3), ("symmetric", 4608, 512, 1)])
+                                        ("fused", 1500, 64, 3), ("fused", 1581, 64, 3), ("symmetric", 4608, 512, 1)])
 def test_rows_are_redone(path, B, d, N):
     s = 14.285714
     I, T = _spoil(*clip_pairs(B, d, 51), B)
@@ -86,7 +86,7 @@ def _window(X, rows, key, length, exponent, s):
 
 @pytest.mark.parametrize("length,exponent", WINDOW)
 @pytest.mark.parametrize("path,B,d,N", [("materialized", 1024, 64, 4), ("materialized", 8100, 256, 4), ("fused", 1024, 128, 2),
-                                        ("fused", 1500, 64, 3), ("materialized", 1100, 192, 2)])
+                                        ("fused", 1500, 64, 3), ("fused", 1581, 64, 3), ("materialized", 1100, 192, 2)])
 def test_numerators_stay_within_what_the_products_hold(path, B, d, N, length, exponent):
     s, r, key = 14.285714, N - 1, 3
     I, T = clip_pairs(B, d, 53)

@@ -15,8 +15,9 @@ pytestmark = pytest.mark.gpu
 S = 14.285714
 
 
-@pytest.mark.parametrize("B,d,N", [(10100, 64, 4), (10100, 64, 2), (4990, 128, 2), (8320, 192, 5), (6500, 64, 1)])
-def test_row_chunks(B, d, N):
+@pytest.mark.parametrize("B,d,N,chunks", [(10100, 64, 4, 2), (10100, 64, 2, 2), (4990, 128, 2, 2), (6500, 64, 1, 2), (1581, 64, 3, 3)])
+def test_row_chunks(B, d, N, chunks):
+    assert dl.disco_describe_plan(B, d, N, dl.DISCO_BF16, dl.DISCO_PATH_FUSED).row_chunks == chunks
     I, T = clip_pairs(B, d, 61)
     Ib, Tb = f32_to_bf16_bits(I), f32_to_bf16_bits(T)
     I, T = bf16_bits_to_f32(Ib), bf16_bits_to_f32(Tb)
@@ -40,9 +41,10 @@ def test_row_chunks(B, d, N):
     np.testing.assert_allclose(t2, gT - 0.25, rtol=1e-6)
 
 
-@pytest.mark.parametrize("M,d,N", [(2525, 64, 1), (5050, 64, 2), (5050, 64, 4)])
-def test_two_view_row_chunks(M, d, N):
+@pytest.mark.parametrize("M,d,N,chunks", [(2525, 64, 1, 2), (5050, 64, 2, 2), (5050, 64, 4, 2), (825, 64, 3, 3)])
+def test_two_view_row_chunks(M, d, N, chunks):
     B, r = 2 * M, N - 1
+    assert dl.disco_describe_plan(B, d, N, dl.DISCO_BF16, dl.DISCO_PATH_FUSED, two_view=True).row_chunks == chunks
     Z = two_views(M, d, 7)
     bits = f32_to_bf16_bits(Z)
     Z, Zd = bf16_bits_to_f32(bits), torch.from_numpy(bits.view(np.int16)).cuda()

@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
     (200, 48, 1, 0),        # three 16-deep pieces of d: a wave without one, rows past the last tile
     (513, 128, 1, 0),       # an odd batch: the last row of a pair does not exist
     (150, 77, 2, 2),        # odd width: features one by one; bf16 rows on 4-byte boundaries
+    (4098, 68, 1, 0),       # all rows one share, a row pitch that is rounded up
 ])
 def test_small_products(B, d, N, shift, dtype):
     s = 14.285714
@@ -34,6 +35,7 @@ def test_small_products(B, d, N, shift, dtype):
         Ib, Tb = f32_to_bf16_bits(I), f32_to_bf16_bits(T)
         I, T = bf16_bits_to_f32(Ib), bf16_bits_to_f32(Tb)
     Id, Td, dt = to_device(I, T, Ib, Tb, dtype)
+    assert dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_NAIVE).kernels == dl.DISCO_KERNELS_SMALL
     if shift:
         moved = []
         for x in (Id, Td):
@@ -69,6 +71,7 @@ def test_auto_runs_a_call_of_a_few_tiles_in_fp32_arithmetic(B, d, N):
     I, T = bf16_bits_to_f32(Ib), bf16_bits_to_f32(Tb)
     Id, Td, dt = to_device(I, T, Ib, Tb, "bf16")
     assert dl.disco_resolve_path(B, d, N, dt, dl.DISCO_PATH_AUTO) != dl.DISCO_PATH_NAIVE
+    assert dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_AUTO).kernels == dl.DISCO_KERNELS_SMALL
     run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_AUTO)
     run.rank(N - 1, s)
     loss, gI, gT, gs = run.results()

@@ -57,6 +57,7 @@ def test_split_products(B, d, N, dtype, shift):
     run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_AUTO)
     # by name the path keeps to its fp32 blocks; a call that is worth it takes more memory through AUTO
     assert run.ws_bytes > dl.disco_workspace_bytes(B, d, N, dt, dl.DISCO_PATH_NAIVE)
+    assert dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_AUTO).kernels == dl.DISCO_KERNELS_SPLIT
     for r in sorted({0, N - 1}):
         print(f"case split products B={B} d={d} N={N} rank={r} dtype={dtype} shift={shift}", flush=True)
         run.rank(r, S)
@@ -72,9 +73,16 @@ def test_split_products(B, d, N, dtype, shift):
     assert l3 == loss and g3 == gs and np.array_equal(a3, gI) and np.array_equal(t3, gT)
 
 
-@pytest.mark.parametrize("B,d,N,dtype", [(4098, 68, 1, "f32"), (4098, 67, 2, "bf16")])
-def test_rows_in_chunks_within_the_papers_memory(B, d, N, dtype):
+@pytest.mark.parametrize("B,d,N,dtype,chunks", [
+    (4099, 130, 1, "f32", 6),             # a last chunk that is short and ragged, gradients through partial sums (d % 4 != 0)
+    (6000, 400, 2, "f32", 6),             # the query side added to rows that a chunk before has written
+    (5001, 500, 1, "bf16", 4),
+    (4099, 450, 1, "f32", 6),
+])
+def test_rows_in_chunks_within_the_papers_memory(B, d, N, dtype, chunks):
     I, T, (Id, Td, dt) = _features(B, d, dtype)
+    plan = dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_NAIVE)
+    assert plan.kernels == dl.DISCO_KERNELS_SPLIT and plan.row_chunks == chunks
     run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_NAIVE)
     assert run.ws_bytes <= 2 * (B // N) * (B + 3) * 4 + 64 * (B // N) + 4096
     print(f"case chunks B={B} d={d} N={N} dtype={dtype}", flush=True)
