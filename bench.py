@@ -21,6 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
+PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 MFMA
 
 # The paper's own figure where it reports this metric on this workload (context: another machine).  Table 4:
 # loss computation 1.6 ms + loss back-propagation 2.8 ms per iteration and GPU at 512 pairs per GPU of a
@@ -209,8 +210,10 @@ def main():
     # algorithmic flops of one call: 12 b B d for a rank's two blocks; the non-decomposed loss (N = 1) needs one
     # similarity matrix for both directions, 6 B^2 d.  Executed: what the path that ran multiplies.
     alg_flops_rank = 6.0 * B * B * d if N == 1 else 12.0 * b * B * d
-    # (the memory-lean path takes the headline shapes in row chunks: 12; its streaming form would recompute the logits, 16)
-    exec_flops_rank = {dl.DISCO_PATH_SYMMETRIC: 6.0}.get(resolved, 12.0) * b * B * d
+    # (the memory-lean path with its rows in chunks: 12; its streaming form recomputes the logits: 16)
+    plan = dl.disco_describe_plan(B, d, N, dt, path)
+    streaming = resolved == dl.DISCO_PATH_FUSED and plan.row_chunks == 1
+    exec_flops_rank = (6.0 if plan.kernels == dl.DISCO_KERNELS_SYMMETRIC else 16.0 if streaming else 12.0) * b * B * d
     tflops_alg = alg_flops_rank / (ms_per_rank * 1e-3) / 1e12
     tflops_exec = exec_flops_rank / (ms_per_rank * 1e-3) / 1e12
 
@@ -228,17 +231,23 @@ def main():
         peak, bound, unit = PEAK_BF16_TFLOPS, "mfma", "TFLOP/s"
         dtype = "bf16"
     elif resolved == dl.DISCO_PATH_FUSED:
-        names = ["prep", "streaming_forward", "merge_transpose", "panel_recompute_and_gemms", "finalize_scalars"]
         dom = 3
-        dom_flops = 12.0 * b * B * d                # recompute (4) + key side (4) + query side (4), both blocks
+        if streaming:
+            names = ["prep", "streaming_forward", "merge_transpose", "panel_recompute_and_gemms", "finalize_scalars"]
+            dom_flops = 12.0 * b * B * d            # recompute (4) + key side (4) + query side (4), both blocks
+        else:                                       # the first chunk's logits (4 / chunks) are a stage of their own
+            names = ["prep", "first_chunk_logits", "first_chunk_merge_transpose", "other_logits_and_gemms", "finalize_scalars"]
+            dom_flops = (12.0 - 4.0 / plan.row_chunks) * b * B * d
         peak, bound, unit = PEAK_BF16_TFLOPS, "mfma", "TFLOP/s"
         dtype = "bf16"
     else:
         names = ["similarity", "row_softmax", "scalars", "gradients", "finalize"]     # (both gradient sides are one launch)
         dom = dom_stage
         dom_flops = (8.0 if dom == 3 else 4.0) * b * B * d
-        # large calls run every fp32 product as six bf16 plane products (fp32 times bf16: three)
-        peak, bound, unit = PEAK_BF16_TFLOPS / (6 if feat_dtype != "bf16" else 3), "mfma", "TFLOP/s"
+        # large calls run every fp32 product as six bf16 plane products (fp32 times bf16: three), small ones with fp32 features
+        # on the fp32 instruction
+        peak = PEAK_BF16_TFLOPS / 3 if feat_dtype == "bf16" else PEAK_BF16_TFLOPS / 6 if plan.kernels == dl.DISCO_KERNELS_SPLIT else PEAK_FP32_TFLOPS
+        bound, unit = "mfma", "TFLOP/s"
         dtype = "f32"
     dom_ms = float(stage_avg[dom])
     achieved = dom_flops / (dom_ms * 1e-3) / 1e12
