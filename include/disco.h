@@ -34,10 +34,15 @@
  *
  * Inputs: any finite values.  The features are expected L2-normalised (what CLIP feeds
  * the loss) and that is the fast case; rows of other norms, positives that are not the
- * row maximum, duplicate and all-zero rows give the same results as the definition, and
- * on the bf16 MFMA paths a row whose every logit lies more than about 110 below its
- * Cauchy-Schwarz bound s*|x_i|*max_j|y_j| is recomputed on a slower path (its query tile of
- * 256 rows is redone).  NaN or infinity in I, T or s propagates to the outputs.
+ * row maximum, duplicate and all-zero rows give the same results as the definition.  On the
+ * MATERIALIZED and FUSED paths the exponentials of row i, with positive p, are taken against
+ * the larger of s<x_i,y_p> and s*|x_i|*|y_p| - 69.  A row whose softmax total is lost that way
+ * (every logit 42 or more under the reference) or would leave the range of the products (a
+ * logit 70 above it: keys far longer than the positives) is redone against its true maximum,
+ * with the group of 64 rows it lies in, on a slower route: features of norm 4 to 8 send every
+ * group there, and a single long key may; such a call takes 2.9 ms instead of 0.9 at
+ * B = 32768, d = 512, N = 8.  (SYMMETRIC: see DISCO_PATH_SYMMETRIC.)
+ * NaN or infinity in I, T or s propagates to the outputs.
  */
 #ifndef DISCO_H
 #define DISCO_H

@@ -1,5 +1,5 @@
 // Device-side building blocks of the bf16 MFMA path: the T x T x 64 NT tile main loop (T = 256 or 128), the operand
-// tile formats and the tile store of the fp32 outputs (through LDS).  Included by mfma_kernels.hip only.
+// tile formats and the tile store of the fp32 outputs (through LDS).  Included by mfma_kernels.hip and split_kernels.hip.
 //
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
 // 128x64 of it as 4x2 MFMA 32x32x16 bf16 blocks with fp32 accumulators.  The reduction runs in K-steps of
@@ -87,7 +87,7 @@ using Acc = f32x16[NFA][2];
 
 // Plane products of an operand pair of PA and PB planes (PS of kloop), smallest first.  Planes 0, 1, 2 of a value carry its
 // leading, middle and last 8 significand bits, so with three planes on both sides the products left out (1 x 2, 2 x 1 and
-// 2 x 2) are below 2^-26 of the value's own product, under the rounding of the fp32 sum.
+// 2 x 2) come to 2^-24 of the values' own product at most and to 2^-27.5 root mean square.
 template <int PA, int PB, bool SWEEPS_ = false>
 struct Planes {
   static constexpr bool SWEEPS = SWEEPS_;

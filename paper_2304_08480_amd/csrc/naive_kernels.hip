@@ -347,8 +347,8 @@ __global__ __launch_bounds__(64 * NW) void small_grads(const float* I, const flo
 
 // ---- bf16 features: the same two launches on the bf16 matrix instruction (32 x 32 x 16), 64 x 64 tiles.  A similarity
 // is one product, exact in the instruction; a gradient entry, fp32 against bf16, is three: the fp32 value is split in
-// registers into three bf16 planes that add up to it (split3_block), so nothing is rounded that the fp32 instruction would not
-// round.  Per 16 of the reduction that is 96 or 384 matrix cycles of a wave against 2048.
+// registers into three bf16 planes that add up to it (split3_block; entries below about 2^-109 lose the last one to bf16's
+// range), so nothing else is rounded that the fp32 instruction would not round.  Per 16 of the reduction that is 96 or 384 matrix cycles of a wave against 2048.
 // A lane supplies 8 consecutive reduction indices (lane / 32 picks which 8 of the 16) of row 2 (lane % 32) + u of row
 // block u: the two blocks' rows are interleaved, so that two neighbouring rows of an operand stored across the
 // reduction come with one load.

@@ -1,7 +1,8 @@
 // The fp32 path's large calls: its four contractions on the bf16 matrix instruction, with every fp32 operand split into three
 // bf16 planes that add up to it exactly (8 significand bits each).  A product of two fp32 operands is six plane products
 // (Planes<3, 3> of mfma_tile.h), one of an fp32 operand and a bf16 one three, of two bf16 ones one: all of them exact in the
-// matrix instruction and summed in fp32, which leaves out less than 2^-26 of any product.
+// matrix instruction and summed in fp32.  The six leave out 2^-27.5 of a product (root mean square; the worst case is 2^-24),
+// less than the fp32 instruction's rounding of its sum adds per term.
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
 // (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); the tile loop of mfma_tile.h runs six
@@ -52,7 +53,7 @@ struct SplitArgs {
   int q_wgs;
 };
 
-// v = p[0] + p[1] + p[2], to the last bit while the last plane stays above the smallest bf16.  (A value whose leading plane
+// v = p[0] + p[1] + p[2], to the last bit while the last plane stays above the smallest bf16 (a value above about 2^-109).  (A value whose leading plane
 // would round to infinity keeps a cut one; a value that is not finite is its own leading plane.)
 struct Three { uint16_t p[3]; };
 __device__ __forceinline__ uint16_t bf16_bits(float f) {
