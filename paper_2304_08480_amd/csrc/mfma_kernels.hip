@@ -18,7 +18,7 @@
 // keys of much larger norm than the positive's take a numerator above 2^101, k_row_merge redoes the row's group of 64 with
 // the true row maxima as references (a slow path for inputs that are not CLIP-like).
 //
-// One NT tile main loop (mfma_tile.h: 256x256x64 by 8 waves, or 128x128x64 by 4, of MFMA 32x32x16 blocks, operands
+// One NT tile main loop (mfma_tile.h: 256x256x64 by 8 waves, or 128x128x64 by 4, of MFMA 16x16x32 blocks, operands
 // loaded global -> LDS directly into a ring of five units) serves all three contractions; operands whose
 // reduction index is not the contiguous one in memory are read from LDS with transposing loads.
 #include "common.h"
@@ -41,11 +41,7 @@ constexpr int BM = 256, BN = 256, NTHREADS = Cfg<256>::NTHREADS;     // the symm
 // The tile kernels come in two sizes, T = 256 (one workgroup of 8 waves per compute unit) and T = 128 (4 waves, two
 // workgroups per compute unit); make_plan chooses.
 template <int T>
-constexpr int E_ROW_BYTES = T * 2;                       // row of the bf16 tile copy in LDS (swizzled, not padded)
-template <int T>
-constexpr int E_TILE_BYTES = T * E_ROW_BYTES<T>;         // 128 KiB at T = 256
-template <int T>
-constexpr int LOGIT_SMEM_BYTES = E_TILE_BYTES<T> > Cfg<T>::SMEM_BYTES ? E_TILE_BYTES<T> : Cfg<T>::SMEM_BYTES;
+constexpr int LOGIT_SMEM_BYTES = Cfg<T>::SMEM_BYTES;
 template <int T>
 constexpr int GEMM_SMEM_BYTES = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SMEM_BYTES<T> : Cfg<T>::SMEM_BYTES;
 
@@ -163,10 +159,9 @@ __device__ __forceinline__ int64_t e_index(int64_t i, int64_t jl, int64_t W) {
 }
 
 // Epilogue of one logit tile: numerators from the accumulators, row sums, the bf16 numerators to memory.
-// Each lane holds, per accumulator quad, 4 consecutive key columns of one query row, lanes l and l + 32 the two
-// halves of 8 consecutive keys; one v_permlane32_swap per register pair gives the lower lane the whole atom of an
-// even key piece and the upper lane that of the odd piece next to it, and the 32 lanes of a half-wave (32
-// consecutive query rows) then store 512 contiguous bytes of the panel (see e_index): no LDS, no barrier, so
+// Each lane holds, per fragment, 4 consecutive key columns of one query row, lanes l and l + 16 (and l + 32 and l + 48) the two
+// halves of 8 consecutive keys; one v_permlane16_swap per register pair of two neighbouring fragments gives every lane a whole
+// atom, and 16 lanes (16 consecutive query rows) then store 256 contiguous bytes of the panel (see e_index): no LDS, no barrier, so
 // the waves of a workgroup need not meet between the main loops of consecutive tiles.
 // MASK_DIAG: the tile contains label columns, which are stored as 0 and kept in fp32 in ediag.
 // Local query row i is global row g0 + i; its label is key row label_row(g0 + i), and for the two-view loss its own
@@ -174,9 +169,8 @@ __device__ __forceinline__ int64_t e_index(int64_t i, int64_t jl, int64_t W) {
 // nkeys (the batch size) on (MASK_EDGE only:
 // the caller takes that variant for the tiles they fall into).
 // jl0: first key column of the tile relative to the panel of width W that p.E holds.  STREAM: streaming stores
-// (past the caches, which keeps the operand tiles in L2; see streaming_stores).  STAGE: also leave the bf16 tile in LDS,
-// row-major T x T (8-byte granules XOR-swizzled with the row: conflict-free 8-byte writes and 16-byte reads),
-// for a caller that wants sums down its columns.
+// (past the caches, which keeps the operand tiles in L2; see streaming_stores).  COLS: also the lane's sums over its four query
+// rows, of each of its keys (col[fragment][r]; padding rows, from row nrows on, are left out under MASK_EDGE).
 constexpr int64_t NO_SELF = -((int64_t)1 << 40);
 
 // Do label columns or left-out columns of the T query rows from global row g on fall among key rows [j0, j0 + T)?
@@ -196,80 +190,88 @@ __device__ __forceinline__ bool tile_has_marked_columns(int64_t g, int64_t B, in
 
 enum { MASK_NONE = 0, MASK_DIAG = 1, MASK_EDGE = 2 };     // MASK_EDGE: label / left-out columns and padding columns
 
-template <int T, bool STATS, bool STORE, int MASK, bool STAGE = false, bool STREAM = true>
-__device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::NFA>& acc, char* smem, int64_t b, float s2, int64_t i0,
-                                               int64_t j0, int64_t g0, int variant, int64_t nkeys, const float (&ref2)[2],
-                                               int64_t jl0, int64_t W) {
+template <int T, bool STATS, bool STORE, int MASK, bool STREAM = true, bool COLS = false>
+__device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::NFA>& acc, int64_t b, float s2, int64_t i0,
+                                               int64_t j0, int64_t g0, int variant, int64_t nkeys, const float (&ref2)[4],
+                                               int64_t jl0, int64_t W, float (*col)[4] = nullptr, int64_t nrows = 0) {
   constexpr bool DIAG = MASK != MASK_NONE, EDGE = MASK == MASK_EDGE;
   constexpr int WTM = Cfg<T>::WTM, NFA = Cfg<T>::NFA;      // a wave's key columns: 128 (T = 256) or 64
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / Cfg<T>::WN, wn = wave % Cfg<T>::WN, half = lane >> 5;
+  const int wm = wave / Cfg<T>::WN, wn = wave % Cfg<T>::WN, grp = lane >> 4;
+  // the wave's first 32 keys of its rows, and in there this lane's atom: row lane % 16, key piece (0, 2, 1, 3)[grp]
+  char* e0 = nullptr;
+  if (STORE) e0 = const_cast<char*>(uniform_ptr(p.E + (((i0 >> 6) + wn) * (W >> 3) + ((jl0 + wm * WTM) >> 3)) * 512));
+  const uint32_t e_lane = (uint32_t)(((grp & 1) << 1 | grp >> 1) * 1024 + (lane & 15) * 16);
+  float sums[4];
 #pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    const int il = wn * 64 + bn * 32 + (lane & 31);
+  for (int fn = 0; fn < 4; ++fn) {
+    const int il = wn * 64 + fn * 16 + (lane & 15);
     const int64_t i = i0 + il;
-    const float ref = ref2[bn];
+    const float ref = ref2[fn];
     // label column of row i, relative to this lane's first key column of the tile (any value outside
     // [0, WTM) means the label is not among this lane's columns)
-    const int64_t dl64 = (DIAG ? label_row(g0 + i, nkeys, variant) : 0) - (j0 + wm * WTM + half * 4);
+    const int64_t dl64 = (DIAG ? label_row(g0 + i, nkeys, variant) : 0) - (j0 + wm * WTM + grp * 4);
     const int dl = dl64 >= 0 && dl64 < WTM ? (int)dl64 : -1;
-    const int64_t dm64 = (variant == LOSS_NTXENT ? g0 + i : NO_SELF) - (j0 + wm * WTM + half * 4);
+    const int64_t dm64 = (variant == LOSS_NTXENT ? g0 + i : NO_SELF) - (j0 + wm * WTM + grp * 4);
     const int dm = dm64 >= 0 && dm64 < WTM ? (int)dm64 : -1;
     // first padding column, relative like dl (WTM: none among this lane's columns)
-    const int64_t jl64 = nkeys - (j0 + wm * WTM + half * 4);
+    const int64_t jl64 = nkeys - (j0 + wm * WTM + grp * 4);
     const int jlim = jl64 >= WTM ? WTM : jl64 > 0 ? (int)jl64 : 0;
+    const bool padding_row = COLS && EDGE && i >= nrows;
     float rowsum = 0.f;
-    char* lrow = smem + il * E_ROW_BYTES<T>;
-    // this lane's atom of the wave's first key piece pair: row i, key piece (jl0 + 128 wm) / 8 + half
-    uint16_t* erow = STORE ? p.E + ((i >> 6) * (W >> 3) + ((jl0 + wm * WTM) >> 3) + half) * 512 + (i & 63) * 8 : nullptr;
 #pragma unroll
-    for (int bm = 0; bm < NFA; ++bm) {
-      const int jl = wm * WTM + bm * 32 + half * 4;
-      u32x2 pk[4];
+    for (int fp = 0; fp < NFA; fp += 2) {
+      u32x2 pk[2];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < 2; ++q) {
+        const int fm = fp + q;
         float e[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(acc[bm][bn][q * 4 + r], s2, -ref));
+        for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(acc[fm][fn][r], s2, -ref));
         if (DIAG) {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (dl == bm * 32 + q * 8 + r) {
+            if (dl == fm * 16 + r) {
               if (STATS) p.ediag[i] = e[r];
               e[r] = 0.f;
             }
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (dm == bm * 32 + q * 8 + r || (EDGE && bm * 32 + q * 8 + r >= jlim)) e[r] = 0.f;
+            if (dm == fm * 16 + r || (EDGE && fm * 16 + r >= jlim)) e[r] = 0.f;
         }
         if (STATS) rowsum += (e[0] + e[1]) + (e[2] + e[3]);
-        if (STORE || STAGE) {
+        if (COLS) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float v = padding_row ? 0.f : e[r];
+            col[fm][r] = fn == 0 ? v : col[fm][r] + v;
+          }
+        }
+        if (STORE) {
           bf16x4 v;
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = (__bf16)e[r];
           pk[q] = __builtin_bit_cast(u32x2, v);
-          // 8-byte granule g of row il lives at granule g ^ (il & 31): the 32 rows of a half-wave (same g)
-          // then cover all 64 banks once
-          if (STAGE) *reinterpret_cast<u32x2*>(lrow + ((((jl >> 2) + q * 2) ^ (il & 31)) << 3)) = pk[q];
         }
       }
       if (STORE) {
-#pragma unroll
-        for (int qp = 0; qp < 2; ++qp) {
-          // lanes 32..63 of the even piece's registers <-> lanes 0..31 of the odd piece's
-          const auto w0 = __builtin_amdgcn_permlane32_swap(pk[2 * qp][0], pk[2 * qp + 1][0], false, false);
-          const auto w1 = __builtin_amdgcn_permlane32_swap(pk[2 * qp][1], pk[2 * qp + 1][1], false, false);
-          const u32x4 atom = {w0[0], w1[0], w0[1], w1[1]};
-          u32x4* dst = reinterpret_cast<u32x4*>(erow + (bm * 4 + qp * 2) * 512);
-          if (STREAM) __builtin_nontemporal_store(atom, dst);
-          else *dst = atom;
-        }
+        // lanes 16..31 and 48..63 of the even fragment's registers <-> lanes 0..15 and 32..47 of the odd one's
+        const auto w0 = __builtin_amdgcn_permlane16_swap(pk[0][0], pk[1][0], false, false);
+        const auto w1 = __builtin_amdgcn_permlane16_swap(pk[0][1], pk[1][1], false, false);
+        const u32x4 atom = {w0[0], w1[0], w0[1], w1[1]};
+        u32x4* dst = reinterpret_cast<u32x4*>(e0 + fp * 2048 + (e_lane + fn * 256));
+        if (STREAM) __builtin_nontemporal_store(atom, dst);
+        else *dst = atom;
       }
     }
     if (STATS) {
-      rowsum += __shfl_xor(rowsum, 32);
-      if (half == 0) p.lpart[((T == 256 ? j0 >> 7 : j0 >> 6) + wm) * b + i] = rowsum;
+      rowsum += __shfl_xor(rowsum, 16);
+      sums[fn] = rowsum + __shfl_xor(rowsum, 32);
     }
+  }
+  if (STATS) {
+    const float lo = grp & 1 ? sums[1] : sums[0], hi = grp & 1 ? sums[3] : sums[2];
+    p.lpart[((T == 256 ? j0 >> 7 : j0 >> 6) + wm) * b + i0 + wn * 64 + lane] = grp & 2 ? hi : lo;
   }
 }
 
@@ -309,30 +311,23 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int
     superblock_tile(lin, nI, nJ, sbi, sbj, it, jt);
     const int64_t i0 = (int64_t)it * T, j0 = jp0 + (int64_t)jt * T;
 
-    // exponent reference of this lane's two query rows, fetched before the main loop so that the loads are
+    // exponent references of this lane's four query rows, fetched before the main loop so that the loads are
     // not waited for in the epilogue
-    float ref2[2];
-    {
+    float ref2[4];
 #pragma unroll
-      for (int bn = 0; bn < 2; ++bn) {
-        const int64_t i = i0 + wn * 64 + bn * 32 + (lane & 31);
-        ref2[bn] = p.ref2[i];
-      }
-    }
+    for (int fn = 0; fn < 4; ++fn) ref2[fn] = p.ref2[i0 + wn * 64 + fn * 16 + (lane & 15)];
     Acc<Cfg<T>::NFA> acc;
 #pragma unroll
     for (int i = 0; i < Cfg<T>::NFA; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
 
     // Only the tiles that the label diagonal (or the left-out diagonal) crosses, or that hold padding columns, pay
     // for finding those columns.
     const bool diag = tile_has_marked_columns<T>(g0 + i0, B, bl.variant, j0);
-    if (diag || (RAGGED && j0 + T > B)) logit_epilogue<T, STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG, false, STREAM>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
-    else logit_epilogue<T, STATS, STORE, MASK_NONE, false, STREAM>(p, acc, smem, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    if (diag || (RAGGED && j0 + T > B)) logit_epilogue<T, STATS, STORE, RAGGED ? MASK_EDGE : MASK_DIAG, STREAM>(p, acc, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
+    else logit_epilogue<T, STATS, STORE, MASK_NONE, STREAM>(p, acc, b, s2, i0, j0, g0, bl.variant, B, ref2, j0 - jp0, W);
   }
 }
 
@@ -953,11 +948,34 @@ __global__ __launch_bounds__(1024) void k_sym_ref(const float* zd2, const float*
   }
 }
 
+// One step of sums_over_rows: of the 2 N values per lane a lane keeps the lower or the upper N and adds its partner's, who keeps
+// the others.
+template <int CTRL, int N>
+__device__ __forceinline__ void halve_values(const float (&v)[2 * N], bool upper, float (&out)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const float keep = upper ? v[N + k] : v[k], give = upper ? v[k] : v[N + k];
+    out[k] = keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), CTRL, 0xf, 0xf, true));
+  }
+}
+// Sums of col[fm][r] over the 16 lanes of a row (the 16 query rows of a fragment): lane l receives those of fm = l / 2 % 8,
+// r = 2 (l % 2) and the next one.  Four steps of half the values each (90 instructions for 32 values), partners l and 15 - l, 7 - l
+// of a half row, l ^ 2, l ^ 1.
+__device__ __forceinline__ f32x2 sums_over_rows(const float (&col)[8][4], int lane) {
+  float v[32], a[16], c[8], e[4], o[2];
+#pragma unroll
+  for (int k = 0; k < 32; ++k) v[k] = col[k >> 2][k & 3];
+  halve_values<0x140>(v, (lane & 8) != 0, a);
+  halve_values<0x141>(a, (lane & 4) != 0, c);
+  halve_values<0x4E>(c, (lane & 2) != 0, e);
+  halve_values<0xB1>(e, (lane & 1) != 0, o);
+  return f32x2{o[0], o[1]};
+}
+
 // Logit tiles of the symmetric path: k_logit_tiles for one block (X = I on the tile's N side, Y = T on its M side)
-// with the one reference; the row sums come from the accumulators as there, the column sums (over the tile's
-// query rows) from a copy of the bf16 tile that the epilogue leaves in LDS: a thread adds up its 8 columns over its
-// 16 rows, lanes l and l + 32 join, the eight waves leave their sums in ring unit 4 and, after a barrier, 256
-// threads add the eight.  (So the text -> image normalisation is that of the stored, rounded numerators.)
+// with the one reference; row sums and column sums (over the tile's query rows) come from the accumulators, the latter
+// over a lane's four rows, then over the 16 lanes that hold a fragment's rows (sums_over_rows); the four waves that share the
+// columns leave their sums in ring unit 4 and, after a barrier, 256 threads add the four.
 // bl.z[0]: E, row partial sums, label numerators; bl.z[1].lpart: column partial sums, one per query tile, cpart[it][j].
 // B: the batch rounded up to whole tiles.  RAGGED: the batch is not whole tiles (X and Y are zero-padded copies): the
 // last key tiles leave their padding columns out (so every row sum is right) and the column sums leave the padding
@@ -971,57 +989,32 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
   const int total = nI * nJ;
   const int chunk = (total + 7) >> 3, padded = chunk << 3;
   const float ref = *rglobal;
-  const float ref2[2] = {ref, ref};
-  float* colpart = reinterpret_cast<float*>(smem + E_TILE_BYTES<256>);       // [8 waves][256 keys]
+  const float ref2[4] = {ref, ref, ref, ref};
+  float* colpart = reinterpret_cast<float*>(smem + 4 * Cfg<256>::UNIT_BYTES);       // [4 waves][256 keys]
   for (int u = blockIdx.x; u < padded; u += gridDim.x) {
     const int lin = (u & 7) * chunk + (u >> 3);
     if ((u >> 3) >= chunk || lin >= total) continue;
     int it, jt;
     superblock_tile(lin, nI, nJ, sbi, sbj, it, jt);
     const int64_t i0 = (int64_t)it * BN, j0 = (int64_t)jt * BM;
-    f32x16 acc[4][2];
+    Acc<Cfg<256>::NFA> acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Cfg<256>::NFA; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     mainloop<256, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
     // the label of query row i is key row i: only the tiles on the diagonal contain label columns
     // (ordinary stores: the matrix is read again by the combining pass and the two contractions)
-    if (it == jt || (RAGGED && j0 + BM > bl.keys))
-      logit_epilogue<256, true, true, RAGGED ? MASK_EDGE : MASK_DIAG, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
-    else logit_epilogue<256, true, true, MASK_NONE, true, false>(p, acc, smem, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B);
+    // (and of a ragged batch the last key tiles and the last query tiles contain padding)
+    float col[Cfg<256>::NFA][4];
+    if (it == jt || (RAGGED && (j0 + BM > bl.keys || i0 + BN > bl.rows)))
+      logit_epilogue<256, true, true, RAGGED ? MASK_EDGE : MASK_DIAG, false, true>(p, acc, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B, col, bl.rows);
+    else logit_epilogue<256, true, true, MASK_NONE, false, true>(p, acc, B, s2, i0, j0, 0, LOSS_CLIP, bl.keys, ref2, j0, B, col);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const f32x2 sums = sums_over_rows(col, lane);
+    *reinterpret_cast<f32x2*>(colpart + (wave % 4) * 256 + (wave / 4) * 128 + (lane >> 1 & 7) * 16 + (lane >> 4) * 4 + (lane & 1) * 2) = sums;
     lds_barrier();
-    const int t = threadIdx.x;
-    const int chunk16 = t & 31, r0 = t >> 5;
-    float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int r = 0; r < 16; ++r) {
-      const int row = r * 16 + r0;
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(smem + row * E_ROW_BYTES<256> + ((chunk16 ^ ((row & 31) >> 1)) << 4));
-      const u32x4 val = (row & 1) ? u32x4{raw[2], raw[3], raw[0], raw[1]} : raw;
-      if (RAGGED && i0 + row >= bl.rows) continue;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        cs[2 * w] += bf16_lo(val[w]);
-        cs[2 * w + 1] += bf16_hi(val[w]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) cs[k] += __shfl_xor(cs[k], 32);
-    if ((t & 63) < 32) {
-      float* cp = colpart + (t >> 6) * 256 + chunk16 * 8;
-      *reinterpret_cast<f32x4*>(cp) = f32x4{cs[0], cs[1], cs[2], cs[3]};
-      *reinterpret_cast<f32x4*>(cp + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
-    }
-    lds_barrier();
-    if (t < BM) {
-      float c = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) c += colpart[w * 256 + t];
-      bl.z[1].lpart[(int64_t)it * B + j0 + t] = c;
-    }
+    if (t < BM) bl.z[1].lpart[(int64_t)it * B + j0 + t] = (colpart[t] + colpart[256 + t]) + (colpart[512 + t] + colpart[768 + t]);
   }
 }
 

@@ -2,8 +2,11 @@
 // tile formats and the tile store of the fp32 outputs (through LDS).  Included by mfma_kernels.hip and split_kernels.hip.
 //
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
-// 128x64 of it as 4x2 MFMA 32x32x16 bf16 blocks with fp32 accumulators.  The reduction runs in K-steps of
-// 64.  Operand tiles travel global memory -> LDS directly (global_load_lds_dwordx4): no staging
+// 128x64 of it as 8x4 MFMA 16x16x32 bf16 blocks with fp32 accumulators.  What bounds the loop is power (the chip clocks at
+// 1.6-1.8 GHz in it), and the 16x16x32 form does the same multiplications with half the accumulator traffic: from registers
+// alone the whole chip runs 2.09 PFLOP/s of it against 1.86 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
+// 752 us against 821, B = 65536, d = 768 3990 against 4395.  The reduction runs in K-steps of
+// 64.  Operand tiles travel global memory -> LDS directly (buffer_load_dwordx4 ... lds): no staging
 // registers, no LDS write instructions, and the data in flight lives in LDS.  K-steps are 64 wide so that
 // a load instruction of a reduction-contiguous operand covers 8 rows x 128 bytes, i.e. whole cache lines
 // (with 32-wide steps each line is fetched in two halves and such loads cost twice as much).
@@ -29,8 +32,8 @@
 //              16 consecutive rows a quarter-wave reads (same chunk) hit 16 different bank groups of the
 //              64-bank LDS; fragments are read with ds_read_b128.
 //   format R - the operand's row index is contiguous in memory (element (r,k) at base[k*ld + r]): 64
-//              reduction rows of 512 bytes; the 32-byte group index is XOR-ed with twice the low two bits
-//              of the reduction row, so the 4 reduction rows x 2 row groups that a half-wave reads at once
+//              reduction rows of 512 bytes; the 32-byte group index is XOR-ed with bits 0, 1 and 3
+//              of the reduction row, so the 8 reduction rows (0..3 and 8..11 of 16) that a half-wave reads at once
 //              cover a 256-byte bank window exactly; fragments are read with the transposing
 //              ds_read_b64_tr_b16 (two per fragment).
 // A direct-to-LDS load puts lane l's 16 bytes at (wave-uniform LDS base) + 16*l, so a swizzle is applied by
@@ -48,8 +51,8 @@
 //          consecutive rows a quarter-wave reads with ds_read_b128 are 256 contiguous bytes, so no swizzle.
 //   FMT_RA reduces down the rows (a K-step is one row group; the tile's 256 rows are 32 column pieces of it: one
 //          contiguous 32 KiB run, and a load instruction fetches one column piece, 1 KiB).  Its LDS tile keeps that
-//          order: column piece c at 1024 c, inside it reduction row kap at 16 (kap ^ 4 (c % 4)), so that the
-//          4 reduction rows x 4 column pieces x 2 halves which a half-wave reads at once with ds_read_b64_tr_b16
+//          order: column piece c at 1024 c, inside it reduction row kap at 16 (kap ^ 4 (c % 2)), so that the
+//          8 reduction rows x 2 column pieces x 2 halves which a half-wave reads at once with ds_read_b64_tr_b16
 //          cover a 256-byte bank window exactly.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -62,8 +65,8 @@ namespace tile {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
@@ -78,12 +81,13 @@ struct Cfg {
   static constexpr int WAVES = T / 32, NTHREADS = WAVES * 64;
   static constexpr int WN = WAVES / 2;                    // waves along N; also the waves that load one operand
   static constexpr int WTM = T / 2;                       // a wave's rows of the A side (64 of the B side)
-  static constexpr int NFA = WTM / 32;                    // its 32-row fragments of the A side (2 of the B side)
+  static constexpr int NFA = WTM / 16, NFB = 4;           // its 16-row fragments of the A side and of the B side
   static constexpr int UNIT_BYTES = T * BK * 2;           // one operand, one K-step: 32 or 16 KiB
   static constexpr int SMEM_BYTES = NUNITS * UNIT_BYTES;  // the ring: all 160 KiB of the CU's LDS, or half of it
 };
+// acc[i][j][r] of lane l: row 16 i + 4 (l / 16) + r, column 16 j + l % 16 of the wave's tile
 template <int NFA>
-using Acc = f32x16[NFA][2];
+using Acc = f32x4[NFA][4];
 
 // Plane products of an operand pair of PA and PB planes (PS of kloop), smallest first.  Planes 0, 1, 2 of a value carry its
 // leading, middle and last 8 significand bits, so with three planes on both sides the products left out (1 x 2, 2 x 1 and
@@ -123,20 +127,23 @@ __device__ __forceinline__ u32x2 ds_read64_tr(uint32_t addr) {
   return v;
 }
 
-// Operand fragments of one 16-wide sub-step: NFA (4 or 2) for the A side (rows 32 i), 2 for the B side.
-template <int NFA>
-struct Frags {
-  u32x4 a[NFA], b[2];
+// Operand fragments, 16 rows x 32 of the reduction each: half of the A side's (rows 16 i of it), all of the B side's.
+template <int NH>
+struct FragsA {
+  u32x4 f[NH];
+};
+struct FragsB {
+  u32x4 f[4];
 };
 // All LDS reads issued so far have returned; ties the registers to the wait so no MFMA moves above it.
-__device__ __forceinline__ void wait_frags(Frags<4>& f) {
+__device__ __forceinline__ void wait_frags(FragsA<4>& a, FragsB& b) {
   asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1])
+               : "+v"(a.f[0]), "+v"(a.f[1]), "+v"(a.f[2]), "+v"(a.f[3]), "+v"(b.f[0]), "+v"(b.f[1]), "+v"(b.f[2]), "+v"(b.f[3])
                :
                : "memory");
 }
-__device__ __forceinline__ void wait_frags(Frags<2>& f) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]) : : "memory");
+__device__ __forceinline__ void wait_frags(FragsA<2>& a, FragsB& b) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a.f[0]), "+v"(a.f[1]), "+v"(b.f[0]), "+v"(b.f[1]), "+v"(b.f[2]), "+v"(b.f[3]) : : "memory");
 }
 
 // A pointer that is the same in every lane, handed to the compiler as scalar registers: the loads below then take
@@ -147,16 +154,25 @@ __device__ __forceinline__ const char* uniform_ptr(const void* p) {
   return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
+// The 4 GiB from p on (the same in every lane) as a buffer resource.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(uniform_ptr(p)), 0, 0xffffffffu, 0x00020000);
+}
+
+// format R: what the 32-byte group index of reduction row kap is XOR-ed with
+__device__ __forceinline__ int swizzle_r(int kap) { return (kap & 3) << 1 | (kap >> 3 & 1); }
+
 // ---- per-lane addressing of one operand of a T x T tile
 template <int T, int FMT, int NFRAG>
 struct Operand {
+  static constexpr int NRD = FMT == FMT_R ? NFRAG : FMT == FMT_KA ? 1 : 2;
   uint32_t ld_off[NLD];     // byte offset of this lane's global chunk for the wave's load instructions
-  uint32_t rd[4];           // FMT_K/KA: rd[ks] base for sub-step ks; FMT_R: rd[i] base for fragment i; FMT_RA: rd[h]
-                            // base of the fragment's first (h = 0) and second (h = 1) transposing read
+  uint32_t rd[NRD];         // FMT_K: base for the K-step's first and second half; FMT_KA: base; FMT_R: base of fragment i; FMT_RA:
+                            // base of the fragment's first and second transposing read
   uint32_t lds_q;           // LDS byte offset (inside the operand tile) of the wave's first load instruction
 
   // lw: index of this wave among the T / 64 that load this operand; row0: first tile row of this
-  // wave's fragments (multiple of 32); ld in elements; nvalid: tile rows that exist in memory (a multiple of
+  // wave's fragments (multiple of 64, of 128 for eight of them); ld in elements; nvalid: tile rows that exist in memory (a multiple of
   // 8, at most T): loads of the rows past them are redirected to the last existing rows, so that they
   // stay in bounds (the caller does not use the output rows or columns they feed)
   __device__ __forceinline__ void init(int64_t ld, int lw, int lane, int row0, int nvalid = T) {
@@ -174,122 +190,126 @@ struct Operand {
         ld_off[n] = (uint32_t)(((int64_t)wave * ld + n * 512 + lane * 8) * 2);
       } else if (FMT == FMT_RA) {
         const int c = q;                            // this instruction's column piece; lane = position in it
-        ld_off[n] = (uint32_t)((c * 512 + (lane ^ ((c & 3) << 2)) * 8) * 2);
+        ld_off[n] = (uint32_t)((c * 512 + (lane ^ ((c & 1) << 2)) * 8) * 2);
       } else {
         constexpr int PPR = T / 8;                  // 16-byte pieces per reduction row of the unit
         const int kap = (64 / PPR) * q + lane / PPR, pcw = lane % PPR;
-        const int c0 = (((pcw >> 1) ^ ((kap & 3) << 1)) << 1) | (pcw & 1);
+        const int c0 = (((pcw >> 1) ^ swizzle_r(kap)) << 1) | (pcw & 1);
         const int c = (c0 << 3) < nvalid ? c0 : (nvalid >> 3) - 1;
         ld_off[n] = (uint32_t)(((int64_t)kap * ld + (c << 3)) * 2);
       }
     }
+    // lane l supplies the 8 reduction indices 8 (l / 16) .. of row l % 16 of a fragment; for a transposing read it names 4
+    // rows' worth (`piece`) of one reduction row and receives 4 reduction indices of its own row
+    const int grp = lane >> 4, L = lane & 15;
     if (FMT == FMT_K) {
-      const int row = row0 + (lane & 31), g = (row >> 1) & 7, kc = lane >> 5;
+      const int row = row0 + L, g = (row >> 1) & 7;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) rd[ks] = (uint32_t)(row * 128 + (((ks * 2 + kc) ^ g) << 4));
+      for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(row * 128 + (((ks * 4 + grp) ^ g) << 4));
     } else if (FMT == FMT_KA) {
-      const int row = row0 + (lane & 31), kc = lane >> 5;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) rd[ks] = (uint32_t)((ks * 2 + kc) * (16 * T) + row * 16);
+      rd[0] = (uint32_t)(grp * (16 * T) + (row0 + L) * 16);
     } else if (FMT == FMT_RA) {
-      const int grp = lane >> 4, L = lane & 15, piece = L & 3;     // piece: 8-byte quarter of a 16-row (32-byte) group
-      const int c = ((row0 + (grp & 1) * 16) >> 3) + (piece >> 1);   // + 4 per fragment: c % 4 unchanged
+      const int piece = L & 3, c = (row0 >> 3) + (piece >> 1);       // + 2 per fragment: c % 2 unchanged
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int kap = (grp >> 1) * 8 + (L >> 2) + 4 * h;           // + 16 ks: bits 2..3 unchanged
-        rd[h] = (uint32_t)(c * 1024 + ((kap ^ ((c & 3) << 2)) << 4) + (piece & 1) * 8);
+        const int kap = grp * 8 + (L >> 2) + 4 * h;                  // + 32 ks: bit 2 unchanged
+        rd[h] = (uint32_t)(c * 1024 + ((kap ^ ((c & 1) << 2)) << 4) + (piece & 1) * 8);
       }
     } else {
-      const int grp = lane >> 4, L = lane & 15;
-      const int kap = (grp >> 1) * 8 + (L >> 2);  // + 16 ks + 4 h, multiples of 4: (kap & 3) unchanged
+      const int kap = grp * 8 + (L >> 2);         // + 32 ks + 4 h: the swizzle's bits unchanged
 #pragma unroll
       for (int i = 0; i < NFRAG; ++i) {
-        const int G = (row0 + 32 * i + (grp & 1) * 16) >> 4;
-        rd[i] = (uint32_t)(kap * (2 * T) + ((G ^ ((kap & 3) << 1)) << 5) + 8 * (L & 3));
+        const int G = (row0 >> 4) + i;
+        rd[i] = (uint32_t)(kap * (2 * T) + ((G ^ swizzle_r(kap)) << 5) + 8 * (L & 3));
       }
     }
   }
-  // issue this wave's loads of the K-step whose tile starts at `base` into the unit at `lds`
-  __device__ __forceinline__ void load(const uint16_t* base, char* lds) const {
-    char* l0 = lds + __builtin_amdgcn_readfirstlane(lds_q);
-    const char* ub = uniform_ptr(base);
+  // this wave's n-th load instruction of the K-step whose tile starts at `base`, into the unit at `lds`.  (The buffer form: scalar
+  // base + 32-bit lane offset.  Of a plain pointer the compiler keeps the offsets as 64-bit pairs where the tile loop runs more
+  // than once, 32 registers in the logit kernels, and adds the base in vector registers.)
+  __device__ __forceinline__ void load(int n, __amdgpu_buffer_rsrc_t base, char* lds) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(base, (__attribute__((address_space(3))) void*)(lds + __builtin_amdgcn_readfirstlane(lds_q) + n * lds_step(FMT, T)),
+                                             16, ld_off[n], 0, 0, 0);
+  }
+  __device__ __forceinline__ void load_all(const uint16_t* base, char* lds) const {
+    const __amdgpu_buffer_rsrc_t r = buffer_at(base);
 #pragma unroll
-    for (int n = 0; n < NLD; ++n) {
-      const char* gp = ub + ld_off[n];
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
-                                       (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT, T)), 16, 0, 0);
-    }
+    for (int n = 0; n < NLD; ++n) load(n, r, lds);
   }
 };
 
 __device__ __forceinline__ u32x4 join(u32x2 lo, u32x2 hi) { return u32x4{lo[0], lo[1], hi[0], hi[1]}; }
 
-// fragment i of sub-step KS from the operand tile at LDS byte address `tile`
+// fragment I of the K-step's half KS from the operand tile at LDS byte address `tile`
 template <int KS, int I, int T, int FMT, int NFRAG>
 __device__ __forceinline__ u32x4 read_frag(const Operand<T, FMT, NFRAG>& op, uint32_t tile) {
-  if constexpr (FMT == FMT_K) return ds_read128<I * 4096>(tile + op.rd[KS]);
-  else if constexpr (FMT == FMT_KA) return ds_read128<I * 512>(tile + op.rd[KS]);
-  else if constexpr (FMT == FMT_RA) return join(ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[0]), ds_read64_tr<KS * 256 + I * 4096>(tile + op.rd[1]));
-  else return join(ds_read64_tr<KS * 32 * T>(tile + op.rd[I]), ds_read64_tr<KS * 32 * T + 8 * T>(tile + op.rd[I]));
+  if constexpr (FMT == FMT_K) return ds_read128<I * 2048>(tile + op.rd[KS]);
+  else if constexpr (FMT == FMT_KA) return ds_read128<KS * 64 * T + I * 256>(tile + op.rd[0]);
+  else if constexpr (FMT == FMT_RA) return join(ds_read64_tr<KS * 512 + I * 2048>(tile + op.rd[0]), ds_read64_tr<KS * 512 + I * 2048>(tile + op.rd[1]));
+  else return join(ds_read64_tr<KS * 64 * T>(tile + op.rd[I]), ds_read64_tr<KS * 64 * T + 8 * T>(tile + op.rd[I]));
 }
-template <int KS, int T, int FA, int FB, int NFA>
-__device__ __forceinline__ void read_frags(Frags<NFA>& f, const Operand<T, FA, NFA>& a, const Operand<T, FB, 2>& b, uint32_t ta, uint32_t tb) {
-  f.a[0] = read_frag<KS, 0>(a, ta);
-  f.b[0] = read_frag<KS, 0>(b, tb);
-  f.a[1] = read_frag<KS, 1>(a, ta);
-  f.b[1] = read_frag<KS, 1>(b, tb);
-  if constexpr (NFA == 4) {
-    f.a[2] = read_frag<KS, 2>(a, ta);
-    f.a[3] = read_frag<KS, 3>(a, ta);
+// fragments of half H (rows) of the A side, of the B side's fragments J and J + 1
+template <int KS, int H, int NH, int T, int FMT>
+__device__ __forceinline__ void read_a(FragsA<NH>& a, const Operand<T, FMT, 2 * NH>& op, uint32_t tile) {
+  a.f[0] = read_frag<KS, H * NH>(op, tile);
+  a.f[1] = read_frag<KS, H * NH + 1>(op, tile);
+  if constexpr (NH == 4) {
+    a.f[2] = read_frag<KS, H * NH + 2>(op, tile);
+    a.f[3] = read_frag<KS, H * NH + 3>(op, tile);
   }
 }
-__device__ __forceinline__ void mfma1(f32x16& c, const u32x4& a, const u32x4& b) {
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+template <int KS, int J, int T, int FMT>
+__device__ __forceinline__ void read_b(FragsB& b, const Operand<T, FMT, 4>& op, uint32_t tile) {
+  b.f[J] = read_frag<KS, J>(op, tile);
+  b.f[J + 1] = read_frag<KS, J + 1>(op, tile);
 }
-// acc = a * b (the matrix instruction takes a literal zero for its addend: no registers are cleared)
-template <int NFA>
-__device__ __forceinline__ void mfma_block_first(const Frags<NFA>& f, Acc<NFA>& acc) {
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < NFA; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[i]), __builtin_bit_cast(bf16x8, f.b[j]), zero, 0, 0, 0);
+// acc (+)= a * b; FIRST: = (the matrix instruction takes a literal zero for its addend: no registers are cleared)
+template <bool FIRST>
+__device__ __forceinline__ void mfma1(f32x4& c, const u32x4& a, const u32x4& b) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), FIRST ? zero : c, 0, 0, 0);
 }
-template <int NFA>
-__device__ __forceinline__ void mfma_block(const Frags<NFA>& f, Acc<NFA>& acc) {
+// row I of the sub-step's 16 x 16 products, every other one backwards: only one operand changes from one to the next
+template <bool FIRST, int H, int I, int NH>
+__device__ __forceinline__ void mfma_row(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc) {
 #pragma unroll
-  for (int i = 0; i < NFA; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) mfma1(acc[i][j], f.a[i], f.b[j]);
+  for (int q = 0; q < 4; ++q) {
+    const int j = I & 1 ? 3 - q : q;
+    mfma1<FIRST>(acc[H * NH + I][j], a.f[I], b.f[j]);
+  }
 }
-// the 8 (4) MFMAs of a sub-step with this wave's 8 load instructions of one unit interleaved (two after each of the
-// first four: how they are spread over the sub-step makes no measurable difference).  The wave runs this
+template <bool FIRST, int H, int NH>
+__device__ __forceinline__ void mfma_block(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc) {
+  mfma_row<FIRST, H, 0>(a, b, acc);
+  mfma_row<FIRST, H, 1>(a, b, acc);
+  if constexpr (NH == 4) {
+    mfma_row<FIRST, H, 2>(a, b, acc);
+    mfma_row<FIRST, H, 3>(a, b, acc);
+  }
+}
+// the 16 (8) MFMAs of a sub-step with this wave's 8 load instructions of one unit interleaved (two after each of the
+// first pairs: how they are spread over the sub-step makes no measurable difference).  The wave runs this
 // sub-step at raised priority: it then wins the SIMD's issue slots from the other wave group's wave, its loads
 // leave early in the K-step and have the longest time to land (query-side GEMM 6 % faster, logit kernel 1 %;
 // raising the priority of every MFMA block instead is 1-4 % slower everywhere)
-template <int T, int FMT, int NFRAG, int NFA>
-__device__ __forceinline__ void mfma_block_loads(const Frags<NFA>& f, Acc<NFA>& acc, const Operand<T, FMT, NFRAG>& op,
+template <bool FIRST, int H, int T, int FMT, int NFRAG, int NH>
+__device__ __forceinline__ void mfma_block_loads(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc, const Operand<T, FMT, NFRAG>& op,
                                                  const uint16_t* base, char* lds) {
-  char* l0 = lds + __builtin_amdgcn_readfirstlane(op.lds_q);
-  const char* ub = uniform_ptr(base);
-#define DISCO_LD(n)                                                                                                         \
-  __builtin_amdgcn_global_load_lds(                                                                                         \
-      (const __attribute__((address_space(1))) void*)(ub + op.ld_off[n]),                                                   \
-      (__attribute__((address_space(3))) void*)(l0 + n * lds_step(FMT, T)), 16, 0, 0)
+  const __amdgpu_buffer_rsrc_t from = buffer_at(base);
+#define DISCO_LD(n) op.load(n, from, lds)
+#define DISCO_MM(i, j) mfma1<FIRST>(acc[H * NH + i][j], a.f[i], b.f[j])
   __builtin_amdgcn_s_setprio(1);
-  mfma1(acc[0][0], f.a[0], f.b[0]); DISCO_LD(0); DISCO_LD(1);
-  mfma1(acc[0][1], f.a[0], f.b[1]); DISCO_LD(2); DISCO_LD(3);
-  mfma1(acc[1][0], f.a[1], f.b[0]); DISCO_LD(4); DISCO_LD(5);
-  mfma1(acc[1][1], f.a[1], f.b[1]); DISCO_LD(6); DISCO_LD(7);
-  if constexpr (NFA == 4) {
-    mfma1(acc[2][0], f.a[2], f.b[0]);
-    mfma1(acc[2][1], f.a[2], f.b[1]);
-    mfma1(acc[3][0], f.a[3], f.b[0]);
-    mfma1(acc[3][1], f.a[3], f.b[1]);
+  DISCO_MM(0, 0); DISCO_MM(0, 1); DISCO_LD(0); DISCO_LD(1);
+  DISCO_MM(0, 2); DISCO_MM(0, 3); DISCO_LD(2); DISCO_LD(3);
+  DISCO_MM(1, 3); DISCO_MM(1, 2); DISCO_LD(4); DISCO_LD(5);
+  DISCO_MM(1, 1); DISCO_MM(1, 0); DISCO_LD(6); DISCO_LD(7);
+  if constexpr (NH == 4) {
+    mfma_row<FIRST, H, 2>(a, b, acc);
+    mfma_row<FIRST, H, 3>(a, b, acc);
   }
   __builtin_amdgcn_s_setprio(0);
 #undef DISCO_LD
+#undef DISCO_MM
 }
 
 __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u >= NUNITS ? u - NUNITS : u; }
@@ -297,7 +317,9 @@ __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u 
 // The K loop of one wave group.  GROUP 0 (the lower half of the waves) loads the A units, GROUP 1 the B units.
 //
 // Ring of five units; the operand tiles are laid into it in the order A0 B0 A1 B1 A2 B2 ..., item n in
-// unit n mod 5.  K-step kt computes from A(kt), B(kt) in four 16-wide sub-steps, each fetching the next
+// unit n mod 5.  K-step kt computes from A(kt), B(kt) in four sub-steps, the upper and the lower half of the wave's A
+// rows against its B rows over 32 of the reduction, then over the other 32 (so a B fragment serves two sub-steps and two
+// sets of 32 registers hold the fragments in use and the ones under way), each fetching the next
 // sub-step's fragments while its MFMAs run:
 //   sub-step 0;
 //   sub-step 1: group 0 issues the loads of A(kt+2) into the unit that held B(kt-1);
@@ -326,7 +348,7 @@ __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
 template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS>
 __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp, int64_t ldb,
                                       int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b) {
-  constexpr int NFA = Cfg<T>::NFA, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
+  constexpr int NFA = Cfg<T>::NFA, NH = NFA / 2, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t stepA = kstep_elems<FA>(lda);
   const int64_t stepB = kstep_elems<FB>(ldb);
@@ -348,75 +370,80 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     else { const auto [piece, q] = step_of(kt); return Bp + piece * stepB + (PS::B >> (2 * q) & 3) * plane_b; }
   };
   Operand<T, FA, NFA> oa;
-  Operand<T, FB, 2> ob;
+  Operand<T, FB, 4> ob;
   oa.init(lda, wave % WN, lane, (wave / WN) * Cfg<T>::WTM);
   ob.init(ldb, wave % WN, lane, (wave % WN) * 64, nvalid_b);
   const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;   // LDS byte address
   const int k1 = last < 1 ? last : 1;
   if (GROUP == 0) {
-    oa.load(tile_a(0), smem);
-    oa.load(tile_a(k1), smem + 2 * UNIT_BYTES);
+    oa.load_all(tile_a(0), smem);
+    oa.load_all(tile_a(k1), smem + 2 * UNIT_BYTES);
   } else {
-    ob.load(tile_b(0), smem + UNIT_BYTES);
-    ob.load(tile_b(k1), smem + 3 * UNIT_BYTES);
+    ob.load_all(tile_b(0), smem + UNIT_BYTES);
+    ob.load_all(tile_b(k1), smem + 3 * UNIT_BYTES);
   }
   wait_vmcnt<NLD>();
   lds_barrier();
-  Frags<NFA> f0, f1;
-  read_frags<0>(f0, oa, ob, smem_addr, smem_addr + UNIT_BYTES);
-  wait_frags(f0);
+  FragsA<NH> a0, a1;
+  FragsB b0, b1;
+  read_a<0, 0>(a0, oa, smem_addr);
+  read_b<0, 0>(b0, ob, smem_addr + UNIT_BYTES);
+  read_b<0, 2>(b0, ob, smem_addr + UNIT_BYTES);
+  wait_frags(a0, b0);
 
   int rA = 0;                                       // unit of A(kt); B(kt) is the next unit of the ring
-  // One K-step (FIRST_BLOCK: what sub-step 0 does with its fragments: mfma_block adds to the accumulators,
-  // mfma_block_first writes them).
-#define DISCO_KSTEP(FIRST_BLOCK)                                                                                             \
+  // One K-step (FIRST: its first products write the accumulators instead of adding to them).  On entry a0 and b0 hold the first
+  // half's fragments of the A side's upper rows and of the B side.
+#define DISCO_KSTEP(FIRST)                                                                                                   \
   {                                                                                                                        \
     const int rB = ring_next(rA, 1), nA = ring_next(rA, 2), nB = ring_next(rA, 3), lA = ring_next(rA, 4);                  \
     const uint32_t ta = smem_addr + (uint32_t)(rA * UNIT_BYTES), tb = smem_addr + (uint32_t)(rB * UNIT_BYTES);             \
+    const uint32_t tna = smem_addr + (uint32_t)(nA * UNIT_BYTES), tnb = smem_addr + (uint32_t)(nB * UNIT_BYTES);           \
     const int kload = kt + 2 < ktiles ? kt + 2 : last;                                                                     \
     /* sub-step 0 */                                                                                                       \
-    read_frags<1>(f1, oa, ob, ta, tb);                                                                             \
+    read_a<0, 1>(a1, oa, ta);                                                                                              \
+    read_b<1, 0>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    FIRST_BLOCK(f0, acc);                                                                                                  \
+    mfma_block<FIRST, 0>(a0, b0, acc);                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
-    wait_frags(f1);                                                                                                        \
+    wait_frags(a1, b0);                                                                                                    \
     /* sub-step 1 */                                                                                                       \
-    read_frags<2>(f0, oa, ob, ta, tb);                                                                             \
+    read_a<1, 0>(a0, oa, ta);                                                                                              \
+    read_b<1, 2>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 0) mfma_block_loads(f1, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                                  \
-    else mfma_block(f1, acc);                                                                                              \
+    if (GROUP == 0) mfma_block_loads<FIRST, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
+    else mfma_block<FIRST, 1>(a1, b0, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
-    wait_frags(f0);                                                                                                        \
+    wait_frags(a0, b1);                                                                                                    \
     /* sub-step 2 */                                                                                                       \
-    read_frags<3>(f1, oa, ob, ta, tb);                                                                             \
+    read_a<1, 1>(a1, oa, ta);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    mfma_block(f0, acc);                                                                                                   \
+    mfma_block<false, 0>(a0, b1, acc);                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     if (GROUP == 0) wait_vmcnt<NLD>(); else wait_vmcnt<0>();                                                               \
-    wait_frags(f1);                                                                                                        \
+    wait_frags(a1, b1);                                                                                                    \
     asm volatile("s_barrier" ::: "memory");                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     /* sub-step 3 */                                                                                                       \
-    read_frags<0>(f0, oa, ob, smem_addr + (uint32_t)(nA * UNIT_BYTES), smem_addr + (uint32_t)(nB * UNIT_BYTES));   \
+    read_a<0, 0>(a0, oa, tna);                                                                                             \
+    read_b<0, 0>(b0, ob, tnb);                                                                                             \
+    read_b<0, 2>(b0, ob, tnb);                                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 1) mfma_block_loads(f1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                                  \
-    else mfma_block(f1, acc);                                                                                              \
+    if (GROUP == 1) mfma_block_loads<false, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
+    else mfma_block<false, 1>(a1, b1, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
-    wait_frags(f0);                                                                                                        \
+    wait_frags(a0, b0);                                                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     rA = nA;                                                                                                               \
   }
   if constexpr (WRITE_FIRST) {
     // (the K-step as a generic lambda instantiated twice: this form, not only the peeling, is what the compiler
     // schedules 2-5 % better in the gradient GEMMs)
-    auto kstep = [&](int kt, auto first) {
-      if constexpr (decltype(first)::value) DISCO_KSTEP(mfma_block_first)
-      else DISCO_KSTEP(mfma_block)
-    };
+    auto kstep = [&](int kt, auto first) { DISCO_KSTEP(decltype(first)::value) };
     kstep(0, std::true_type{});
     for (int kt = 1; kt < ktiles; ++kt) kstep(kt, std::false_type{});
   } else {
-    for (int kt = 0; kt < ktiles; ++kt) DISCO_KSTEP(mfma_block)
+    for (int kt = 0; kt < ktiles; ++kt) DISCO_KSTEP(false)
   }
 #undef DISCO_KSTEP
   wait_vmcnt<0>();
@@ -441,11 +468,11 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, int64_t
 
 // Writes a workgroup's T x T fp32 accumulator tile to row-major global memory through LDS, so that
 // every global store is a full 1 KiB (T = 128: 512-byte) row segment (the accumulator layout would give 4-byte elements
-// per lane).  Passes of 128 rows; LDS rows padded by 32 bytes so that the two half-waves of a 4-byte
+// per lane).  Passes of 128 rows; LDS rows padded by 16 bytes so that the four rows of a wave's 4-byte
 // write land on different banks.  out points at the tile's first element; value = scale * acc (+ old);
 // only the first ncols columns (a multiple of 4) of the first nrows rows are touched.
 template <int T>
-constexpr int OUT_ROW_BYTES = T * 4 + 32;
+constexpr int OUT_ROW_BYTES = T * 4 + 16;
 template <int T>
 constexpr int OUT_SMEM_BYTES = 128 * OUT_ROW_BYTES<T>;       // 132 KiB (T = 128: 68 KiB)
 
@@ -455,7 +482,7 @@ __device__ __forceinline__ void store_tile_f32_rows(Acc<Cfg<T>::NFA>& acc, char*
   constexpr int CPR = T / 4, RSTEP = Cfg<T>::NTHREADS / CPR;      // 16-byte pieces per row, rows the workgroup stores at a time (8)
   constexpr int PASSES = T / 128;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave / WN, wn = wave % WN, half = lane >> 5;
+  const int wm = wave / WN, wn = wave % WN;
   const int chunk = t % CPR, r0 = t / CPR;
   const bool live = chunk * 4 < ncols;             // this thread's four columns exist (ncols is a multiple of 4)
 #pragma unroll
@@ -471,16 +498,13 @@ __device__ __forceinline__ void store_tile_f32_rows(Acc<Cfg<T>::NFA>& acc, char*
     lds_barrier();
     if (PASSES == 1 || wm == h) {
       const int rbase = PASSES == 1 ? wm * Cfg<T>::WTM : 0;
+      char* dst = smem + (rbase + (lane >> 4) * 4) * RB + (wn * 64 + (lane & 15)) * 4;
 #pragma unroll
-      for (int bn = 0; bn < 2; ++bn)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int bm = 0; bm < NFA; ++bm)
+        for (int i = 0; i < NFA; ++i)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int row = rbase + bm * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-            const int col = wn * 64 + bn * 32 + (lane & 31);
-            *reinterpret_cast<float*>(smem + row * RB + col * 4) = scale * acc[bm][bn][e];
-          }
+          for (int r = 0; r < 4; ++r) *reinterpret_cast<float*>(dst + (i * 16 + r) * RB + j * 64) = scale * acc[i][j][r];
     }
     lds_barrier();
 #pragma unroll

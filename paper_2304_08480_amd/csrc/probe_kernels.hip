@@ -9,7 +9,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// 512 threads = two waves per SIMD, each with eight independent 32x32 accumulators (the shape of the tile loops);
+// 512 threads = two waves per SIMD, each with eight independent 32x32 accumulators;
 // operands are pseudo-random bf16 patterns: with `varied` sign, exponent and mantissa differ from element to element,
 // so that the multipliers toggle as they do on real data; without, only the mantissas do (values in [0.5, 1)), which
 // draws less power and shows how much of the ceiling is the data's doing.
