@@ -328,8 +328,8 @@ __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u 
 //       in LDS and nobody reads the units of K-step kt any more (the last fragments are in registers);
 //   sub-step 3: group 1 issues the loads of B(kt+2) into the unit that held A(kt); the first fragments of
 //       K-step kt+1 are fetched.
-// So an A load has six sub-steps to land and a B load four.  Loads past the end are clamped to the last
-// K-step (redundant, never out of range, into a unit nobody reads again).
+// So an A load has six sub-steps to land and a B load four.  The last two K-steps are a loop of their own that loads nothing
+// (loading the last K-step again instead, for one loop, made a tile of 8 K-steps fetch 10: 1 % of a call at d = 512, 3 % at 128).
 // READS_FIRST: issue a sub-step's LDS reads ahead of its MFMAs (otherwise the compiler places them).
 //
 // PS: the operands may be kept as several bf16 planes (a value is the sum of its planes), `plane_a` / `plane_b` elements
@@ -392,9 +392,10 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   wait_frags(a0, b0);
 
   int rA = 0;                                       // unit of A(kt); B(kt) is the next unit of the ring
-  // One K-step (FIRST: its first products write the accumulators instead of adding to them).  On entry a0 and b0 hold the first
+  // One K-step (FIRST: its first products write the accumulators instead of adding to them; LOADS: it asks for K-step kt + 2, or,
+  // in a reduction of one or two, which the first K-step of WRITE_FIRST may be, for the last again, into units nobody reads).  On entry a0 and b0 hold the first
   // half's fragments of the A side's upper rows and of the B side.
-#define DISCO_KSTEP(FIRST)                                                                                                   \
+#define DISCO_KSTEP(FIRST, LOADS)                                                                                             \
   {                                                                                                                        \
     const int rB = ring_next(rA, 1), nA = ring_next(rA, 2), nB = ring_next(rA, 3), lA = ring_next(rA, 4);                  \
     const uint32_t ta = smem_addr + (uint32_t)(rA * UNIT_BYTES), tb = smem_addr + (uint32_t)(rB * UNIT_BYTES);             \
@@ -411,7 +412,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_a<1, 0>(a0, oa, ta);                                                                                              \
     read_b<1, 2>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 0) mfma_block_loads<FIRST, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
+    if (GROUP == 0 && LOADS) mfma_block_loads<FIRST, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
     else mfma_block<FIRST, 1>(a1, b0, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b1);                                                                                                    \
@@ -420,7 +421,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
     mfma_block<false, 0>(a0, b1, acc);                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
-    if (GROUP == 0) wait_vmcnt<NLD>(); else wait_vmcnt<0>();                                                               \
+    if (GROUP == 0 && LOADS) wait_vmcnt<NLD>(); else wait_vmcnt<0>();                                                               \
     wait_frags(a1, b1);                                                                                                    \
     asm volatile("s_barrier" ::: "memory");                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
@@ -429,7 +430,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_b<0, 0>(b0, ob, tnb);                                                                                             \
     read_b<0, 2>(b0, ob, tnb);                                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 1) mfma_block_loads<false, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
+    if (GROUP == 1 && LOADS) mfma_block_loads<false, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
     else mfma_block<false, 1>(a1, b1, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b0);                                                                                                    \
@@ -439,11 +440,15 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   if constexpr (WRITE_FIRST) {
     // (the K-step as a generic lambda instantiated twice: this form, not only the peeling, is what the compiler
     // schedules 2-5 % better in the gradient GEMMs)
-    auto kstep = [&](int kt, auto first) { DISCO_KSTEP(decltype(first)::value) };
-    kstep(0, std::true_type{});
-    for (int kt = 1; kt < ktiles; ++kt) kstep(kt, std::false_type{});
+    auto kstep = [&](int kt, auto first, auto loads) { DISCO_KSTEP(decltype(first)::value, decltype(loads)::value) };
+    kstep(0, std::true_type{}, std::true_type{});
+    int kt = 1;
+    for (; kt + 2 < ktiles; ++kt) kstep(kt, std::false_type{}, std::true_type{});
+    for (; kt < ktiles; ++kt) kstep(kt, std::false_type{}, std::false_type{});
   } else {
-    for (int kt = 0; kt < ktiles; ++kt) DISCO_KSTEP(false)
+    int kt = 0;
+    for (; kt + 2 < ktiles; ++kt) DISCO_KSTEP(false, true)
+    for (; kt < ktiles; ++kt) DISCO_KSTEP(false, false)
   }
 #undef DISCO_KSTEP
   wait_vmcnt<0>();
