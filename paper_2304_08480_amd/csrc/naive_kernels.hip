@@ -389,6 +389,52 @@ __global__ __launch_bounds__(64 * NW) void small_similarity(const float* I, cons
   });
 }
 
+// The same on 16 x 16 tiles (16 x 16 x 4 products: four groups of 16 lanes supply 4 reduction indices each of a 16-deep piece), for
+// the smallest calls, whose 32 x 32 tiles are fewer than the compute units: a wave's chain of matrix instructions is a quarter
+// as long.  (us a call, 32 / 16: B = 256, N = 4, d = 512: 16.2 / 14.0; 512, 8, 512: 19.2 / 16.7; 512, 4, 512: 21.6 / 20.8.)
+template <bool VEC, int NW>
+__global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, const float* T, SmallShape f, float* ws) {
+  __shared__ float red[NW][4][64];
+  constexpr int U = 4;                                  // pieces in flight
+  const int z = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, up = (lane >> 4) * 4;
+  const int64_t m0 = (int64_t)blockIdx.y * 16, n0 = (int64_t)blockIdx.x * 16, m = m0 + l16, n = n0 + l16;
+  const float* a = (z == 0 ? I : T) + (f.rank * f.b + (m < f.b ? m : f.b - 1)) * f.d;      // a row past the end repeats the last; its results are not stored
+  const float* b = (z == 0 ? T : I) + (n < f.B ? n : f.B - 1) * f.d;
+  const int pieces = (int)((f.d + 15) / 16), w = __builtin_amdgcn_readfirstlane(wave);      // dealt evenly: the shorter a wave's chain, the fewer roundings
+  const int64_t k0 = w * pieces / NW * 16, end = (w + 1) * pieces / NW * 16, k1 = end < f.d ? end : f.d;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  int64_t k = k0;
+  for (; k + 16 * U <= k1; k += 16 * U) {
+    f32x4 x[U], y[U];
+#pragma unroll
+    for (int c = 0; c < U; ++c) { x[c] = load4<VEC>(a, k + 16 * c + up); y[c] = load4<VEC>(b, k + 16 * c + up); }
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][e], y[c][e], acc, 0, 0, 0);
+  }
+  for (; k < k1; k += 16) {                             // what is left, element by element: past k1 both operands count as 0
+    float x[4], y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t kk = k + up + e, kc = kk < k1 ? kk : k1 - 1;
+      x[e] = kk < k1 ? a[kc] : 0.f;
+      y[e] = kk < k1 ? b[kc] : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[r];
+  __syncthreads();
+  if (wave >= 4) return;                                // wave r: the rows 4 (lane / 16) + r
+  float v = red[0][wave][lane];
+#pragma unroll
+  for (int q = 1; q < NW; ++q) v += red[q][wave][lane];
+  const int64_t row = m0 + up + wave, col = n0 + l16;
+  if (row < f.b && col < f.B) ws[((size_t)z * f.b + row) * f.pitch + col] = v;
+}
+
 // Workgroup 0 adds up loss and d/ds; the others take gradient tiles (row tile, column tile, block z = whose key side):
 // rows [m0, m0 + 32 R) of gT (z = 0) or gI (z = 1), key side of block z plus, in the rank's own rows, the query side of
 // the other block (of the same one for the two-view loss).  The row tiles start at the rank's own rows, whose
@@ -711,6 +757,9 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 namespace {
 
+// Up to this many 32 x 32 similarity tiles: 16 x 16 ones.  (Twice as many, us a call, 32 / 16: B = 1024, N = 4, d = 64: 26.0 / 29.1.)
+constexpr int64_t SIM16_MOST = 128;
+
 size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
 size_t lean_bytes(size_t nb, int64_t b, int64_t pitch) { return matrix_bytes(nb, b, pitch) + 2 * align_up(nb * b * sizeof(float)); }
 
@@ -796,6 +845,7 @@ void small_run(const Problem& p) {
       kernel<<<grad_grid(tile), 64 * waves, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT);
     };
     if (big(p.b, p.B)) { if (vec) sim(small_similarity<true, 2, 4>, 64, 4); else sim(small_similarity<false, 2, 4>, 64, 4); }
+    else if ((int64_t)nb * cdiv(p.b, 32) * cdiv(p.B, 32) <= SIM16_MOST) { if (vec) sim(small_similarity_16<true, 8>, 16, 8); else sim(small_similarity_16<false, 8>, 16, 8); }
     else { if (vec) sim(small_similarity<true, 1, 8>, 32, 8); else sim(small_similarity<false, 1, 8>, 32, 8); }
     softmax();
     if (big(p.B, p.d)) { if (wvec) grads(small_grads<true, 2, 4>, 64, 4); else grads(small_grads<false, 2, 4>, 64, 4); }
