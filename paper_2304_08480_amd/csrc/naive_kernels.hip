@@ -355,6 +355,7 @@ struct OwnRows {
 struct SmallShape {
   int64_t b, B, d, pitch;        // pitch: floats between the rows of a block's matrix
   int rank, nb, variant, accumulate;
+  int out_pairs;                 // rows of the gradients can be written in 8-byte pieces
 };
 // loss and d/ds from the rows' shares, by one workgroup in fixed order.  red: 2 NW floats of LDS.
 template <int NW>
@@ -541,7 +542,8 @@ __device__ __forceinline__ void wave_range16(int K, int& k0, int& k1) {
 }
 
 // Adds up the waves' partial 64 x 64 tiles in a fixed order, through red (NW / 2 tiles): the upper half of the waves hands
-// its sums to the lower, whose sums are then added in wave order.  out(row, column, value).
+// its sums to the lower, whose sums are then added in wave order.  out(row, column, two values): an even column and the next, which
+// a lane hands on together so that a half-wave stores whole lines.
 template <int NW, class FOut>
 __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[64][64], FOut out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -566,12 +568,15 @@ __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 64 / NW; ++q) {
-    const int idx = q * NW + wave, uv = idx >> 4, r = idx & 15;
-    float s = red[0][idx][lane];
+  for (int q = 0; q < 32 / NW; ++q) {
+    const int ur = q * NW + wave, u = ur >> 4, r = ur & 15, idx = u * 32 + r;
+    f32x2 s = {red[0][idx][lane], red[0][idx + 16][lane]};
 #pragma unroll
-    for (int w = 1; w < NW / 2; ++w) s += red[w][idx][lane];
-    out(2 * ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) + (uv >> 1), 2 * (lane & 31) + (uv & 1), s);
+    for (int w = 1; w < NW / 2; ++w) {
+      s[0] += red[w][idx][lane];
+      s[1] += red[w][idx + 16][lane];
+    }
+    out(2 * ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) + u, 2 * (lane & 31), s);
   }
 }
 
@@ -619,8 +624,15 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_bf16(const uint16_t*
     product(x, y);
   }
   float* W = ws + (size_t)z * f.b * f.pitch;
-  join_waves_64<NW>(acc, red, [&](int r, int c, float v) {
-    if (m0 + r < f.b && n0 + c < f.B) W[(m0 + r) * f.pitch + n0 + c] = v;
+  join_waves_64<NW>(acc, red, [&](int r, int c, const f32x2& v) {
+    if (m0 + r >= f.b || n0 + c >= f.B) return;
+    float* p = W + (m0 + r) * f.pitch + n0 + c;
+    // (streamed: up to 4 MB of it would otherwise sit dirty in the L2s, which the kernel's end writes back)
+    if (f.pitch % 4 == 0) __builtin_nontemporal_store(v, reinterpret_cast<f32x2*>(p));       // (what lies in the pitch behind a row is free)
+    else {
+      p[0] = v[0];
+      if (n0 + c + 1 < f.B) p[1] = v[1];
+    }
   });
 }
 
@@ -744,10 +756,17 @@ __global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, c
     });
   }
   float* out = z == 0 ? gT : gI;
-  join_waves_64<NW>(acc, red, [&](int r, int col, float v) {
+  join_waves_64<NW>(acc, red, [&](int r, int col, const f32x2& v) {
     if (m0 + r >= f.B || n0 + col >= d) return;
     float* p = out + (int64_t)(m0 + r) * d + n0 + col;
-    *p = (f.accumulate ? *p : 0.f) + cs * v;
+    if (f.out_pairs) {
+      f32x2 o = {0.f, 0.f};
+      if (f.accumulate) o = *reinterpret_cast<f32x2*>(p);
+      *reinterpret_cast<f32x2*>(p) = f32x2{o[0] + cs * v[0], o[1] + cs * v[1]};
+    } else {
+      p[0] = (f.accumulate ? p[0] : 0.f) + cs * v[0];
+      if (n0 + col + 1 < d) p[1] = (f.accumulate ? p[1] : 0.f) + cs * v[1];
+    }
   });
 }
 
@@ -800,6 +819,7 @@ void small_run(const Problem& p) {
   f.b = p.b; f.B = p.B; f.d = p.d; f.nb = loss_blocks(p.variant);
   f.pitch = row_pitch(p.b, p.B, f.nb);
   f.rank = p.rank; f.variant = p.variant; f.accumulate = p.accumulate;
+  f.out_pairs = p.d % 2 == 0 && (reinterpret_cast<uintptr_t>(p.gI) | reinterpret_cast<uintptr_t>(p.gT)) % 8 == 0;
   const unsigned nb = (unsigned)f.nb;
   const float c = loss_norm(p.B, p.variant), cs = c * p.s;
   float* W = static_cast<float*>(p.ws);
