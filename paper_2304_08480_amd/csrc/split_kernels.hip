@@ -160,7 +160,7 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_logits(SplitArgs a, 
   store_tile_f32<T, false>(acc, smem, p.S + i0 * a.Bp + j0, a.Bp, 1.0f);
 }
 
-constexpr int SM_THREADS = 512, SM_KEEP = 8;                // softmax: threads per row, 4-column pieces a thread can keep
+constexpr int SM_THREADS = 512;                          // softmax: threads per row
 
 __device__ __forceinline__ float workgroup_sum(float v, float* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -177,9 +177,10 @@ __device__ __forceinline__ float workgroup_sum(float v, float* red) {
 // G = softmax - onehot as three planes (0 in the padding columns and rows, and in a two-view row's own column).  The off-label
 // mass is summed on its own, so that P_label - 1 = -(it) / (total) does not cancel, and d/ds as
 // sum_{j != label} P_ij (S_ij - S_i,label).  The vector ALU bounded it, 96 % busy; without tests on the pieces that hold no special
-// column and with planes cut for values of [-1, 1], memory does (B = 8192, N = 8: 39.7 -> 33.8 us for 167 MB).  KEEP: the row fits the workgroup's registers (Bp <= 16384) and is read once;
-// else it is read three times, from cache.
-template <bool KEEP>
+// column and with planes cut for values of [-1, 1], memory does (B = 8192, N = 8: 39.7 -> 33.8 us for 167 MB).  KEEP:
+// 4-column pieces a thread keeps, 8 (Bp <= 16384) or 16 (32768): the row is then read once, else (0) three times, from cache, with
+// every exponential taken twice (us a call, 0 / 16: B = 32768, N = 8, d = 512 4394 / 4225; 20000, 8, 256 1148 / 1095).
+template <int KEEP>
 __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float s) {
   __shared__ float red[SM_THREADS / 64];
   const int64_t i = blockIdx.x;
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
   const int64_t label = label_row(a.g0 + i, a.B, a.variant), self = masked_col(a.g0 + i, a.variant);
   const float xl = S[label];
   const int B = (int)a.B, lab = (int)label, own = (int)self;
-  f32x4 keep[KEEP ? SM_KEEP : 1];
+  f32x4 keep[KEEP ? KEEP : 1];
   // f(j, v, marked) over this thread's pieces v of columns j .. j + 3; with KEEP in registers, where f may replace them.  marked:
   // the label, a left-out column or padding is among the four; the others, nearly all, take no tests.
   auto visit = [&](auto f) {
@@ -204,9 +205,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
       if ((uint32_t)(lab - j) < 4u || (uint32_t)(own - j) < 4u || j + 4 > B) f(j, v, std::true_type{});
       else f(j, v, std::false_type{});
     };
-    if constexpr (KEEP) {
+    if constexpr (KEEP > 0) {
 #pragma unroll
-      for (int u = 0; u < SM_KEEP; ++u) {
+      for (int u = 0; u < KEEP; ++u) {
         const int64_t q = threadIdx.x + u * SM_THREADS;
         if (q < nvec) one((int)q * 4, keep[u]);
       }
@@ -218,9 +219,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
     }
   };
   auto counts = [&](int j, auto marked) { return !decltype(marked)::value || (j < B && j != own && j != lab); };
-  if constexpr (KEEP) {
+  if constexpr (KEEP > 0) {
 #pragma unroll
-    for (int u = 0; u < SM_KEEP; ++u) {
+    for (int u = 0; u < KEEP; ++u) {
       const int64_t q = threadIdx.x + u * SM_THREADS;
       if (q < nvec) keep[u] = *reinterpret_cast<const f32x4*>(S + q * 4);
     }
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
         off += x;
         ds = fmaf(x, v[e] - xl, ds);
       }
-      if constexpr (KEEP) v[e] = x;
+      if constexpr (KEEP > 0) v[e] = x;
     }
   });
   off = workgroup_sum(off, red);
@@ -514,8 +515,9 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
     else split_products<128, NP>(false, pl.parts, add, a, cs, st);
     if (r0 == 0) stage_mark(st, 1);
     const dim3 rows((unsigned)pl.bp, (unsigned)nb);
-    if (pl.Bp <= (int64_t)SM_THREADS * SM_KEEP * 4) k_split_softmax<true><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
-    else k_split_softmax<false><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    if (pl.Bp <= (int64_t)SM_THREADS * 8 * 4) k_split_softmax<8><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    else if (pl.Bp <= (int64_t)SM_THREADS * 16 * 4) k_split_softmax<16><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    else k_split_softmax<0><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
     if (r0 == 0) { stage_mark(st, 2); stage_mark(st, 3); }
     if (pl.T == 256) split_products<256, NP>(true, pl.parts, add, a, cs, st);
     else split_products<128, NP>(true, pl.parts, add, a, cs, st);
