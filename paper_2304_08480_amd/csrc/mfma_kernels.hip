@@ -1283,8 +1283,8 @@ bool allow_lds(K kernel, int bytes) {
 
 // Numerators written past the caches, or kept in them for the gradient kernel?  They stay in the 256 MiB last-level cache
 // until that kernel reads them if they fill at most half of it; below 24 MiB they would sit dirty in the eight L2s, which the
-// kernel's end writes back.  (Streamed / plain, us a call: 16 MiB 68 / 69; 32 MiB 93.6 / 91.3; 64 MiB, B = 32768, N = 64: 168 / 162;
-// 128 MiB, B = 32768, N = 32: 278 / 258; 256 MiB, B = 32768, N = 16: 449 / 460; 512 MiB: 797 / 808.)
+// kernel's end writes back.  (Streamed / plain, us a call: 16 MiB 85.5 / 84.1; 32 MiB 87.5 / 86.0; 64 MiB, B = 32768, N = 64: 148 / 139;
+// 128 MiB, B = 32768, N = 32: 247 / 223; 256 MiB, B = 32768, N = 16: 394 / 410; 512 MiB: 724 / 742.)
 bool streaming_stores(int nblk, int64_t b, int64_t W) {
   const int64_t bytes = 2 * nblk * b * W;
   return bytes < ((int64_t)24 << 20) || bytes > ((int64_t)144 << 20);
@@ -1472,8 +1472,8 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
 // combined gradient matrix, two contractions; then, behind the flag, the two-block path for inputs it cannot take.
 // A small batch is not worth the path's two fixed costs, the pass over the matrix that combines the gradients and the
 // empty launches of the two-block path behind it (about 45 us together): the 6 B^2 d flop it saves pay for them from about
-// B^2 d = 1e10 on.  (Measured, symmetric / two-block in us: B = 2816, d = 640: 133 / 110; 4375, 320: 193 / 156;
-// 3964, 256: 158 / 112; 6912, 320: 274 / 293; 8728, 320: 397 / 498.)
+// B^2 d = 1e10 on.  (Measured, symmetric / two-block in us: B = 2816, d = 640: 128 / 102; 4375, 320: 182 / 146;
+// 3964, 256: 149 / 99; 6912, 320: 239 / 255; 8728, 320: 344 / 470.)
 bool sym_two_block(int64_t B, int64_t d) { return (double)B * B * d < 1e10; }
 
 // Behind the larger of the two plans' workspaces: the hand-over flag and the reference.

@@ -3,7 +3,7 @@
 //
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
 // 128x64 of it as 8x4 MFMA 16x16x32 bf16 blocks with fp32 accumulators.  What bounds the loop is power (the chip clocks at
-// 1.6-1.8 GHz in it), and the 16x16x32 form does the same multiplications with half the accumulator traffic: from registers
+// 1.7-1.9 GHz in it), and the 16x16x32 form does the same multiplications with half the accumulator traffic: from registers
 // alone the whole chip runs 2.09 PFLOP/s of it against 1.86 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
 // 752 us against 821, B = 65536, d = 768 3990 against 4395.  The reduction runs in K-steps of
 // 64.  Operand tiles travel global memory -> LDS directly (buffer_load_dwordx4 ... lds): no staging
@@ -21,10 +21,10 @@
 //
 // T = 128 is the same loop at half the size: 4 waves of 64 x 64, waves 0-1 loading A and 2-3 B, units of 16 KiB, so that
 // two workgroups share a compute unit (80 KiB of LDS each).  It moves twice the bytes per MFMA, which the compute unit's
-// load path (about 64 B/clk) cannot hide: where the chip is full a K-step of two such workgroups takes 1.03 us against
-// 1.7 us for a 256-tile of twice their work (b = 4096, B = 32768, d = 512: 1011 us a call against 835).  What it is for is
+// load path (about 64 B/clk) cannot hide: where the chip is full a K-step of two such workgroups takes 0.6 times that of a
+// 256-tile of twice their work (b = 4096, B = 32768, d = 512: 915 us a call against 730).  What it is for is
 // calls whose 256-tiles leave compute units idle, whose reductions are a few K-steps, or whose feature width fills half a
-// 256-tile: 37 us against 56 at b = 512, B = 1024, d = 256; 83 against 123 at b = 1550, B = 6200, d = 256.
+// 256-tile: 34 us against 49 at b = 512, B = 1024, d = 256; 75 against 96 at b = 1550, B = 6200, d = 256.
 //
 // Operand tile formats in one unit (T = 256; T = 128 has half the rows or half the row length):
 //   format K - the operand's reduction index is contiguous in memory (element (r,k) at base[r*ld + k]):
@@ -566,7 +566,9 @@ __device__ __forceinline__ void superblock_tile(int lin, int nI, int nJ, int sbi
 // Time estimates in microseconds that the plans compare, for a chip of 256 compute units.  What they rest on (measured):
 // a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
 // every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
-// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.
+// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.  (They are of the loop on 32x32x16 products; on
+// 16x16x32 ones both tile sizes take 8 % less, which leaves the choices as they are: forcing each of the four pairs of tile sizes on
+// 12 shapes beat the chosen plan by 4 % at most.)
 constexpr double CHIP_CUS = 256.0;
 constexpr double BYTES_PER_US = 4.5e6;
 
