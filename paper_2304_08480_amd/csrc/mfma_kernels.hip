@@ -285,8 +285,12 @@ __device__ __forceinline__ void logit_epilogue(const BlockPtrs& p, Acc<Cfg<T>::N
 // b: the rank's rows rounded up to whole tiles; B: the key rows that exist (the panel widths cover them rounded up to
 // whole tiles); g0: global row of the rank's first row.  RAGGED: the last key tile may hold padding columns (the
 // instance without it keeps the tile walk free of that variant of the epilogue and of the registers it costs).
+// Two waves per SIMD, said for both sizes: without it the compiler counts on 512 registers a lane for T = 128, keeps the accumulators
+// of the loop that loads in the accumulation file and those of the last K-steps' loop in vector registers, and copies 44 of them there
+// and back in every K-step (us: a K-step of a lone workgroup 0.63 / 0.39; a call of B = 1024, N = 4, d = 896 46.2 / 43.1;
+// 32768, 8, 64 343 / 336; 2048, 8, 704 46.5 / 44.3).
 template <int T, bool STATS, bool STORE, bool RAGGED = false, bool STREAM = true>
-__global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_logit_tiles(Blocks bl, int64_t b, int64_t B, int64_t d, int64_t g0, float s2,
+__global__ __launch_bounds__(Cfg<T>::NTHREADS, 2) void k_logit_tiles(Blocks bl, int64_t b, int64_t B, int64_t d, int64_t g0, float s2,
                                                           int64_t jp0, int64_t W, int sbi, int sbj, int nblk) {
   if (gated_off(bl)) return;
   extern __shared__ __attribute__((aligned(16))) char smem[];
