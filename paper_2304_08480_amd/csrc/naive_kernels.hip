@@ -392,7 +392,9 @@ __global__ __launch_bounds__(64 * NW) void small_similarity(const float* I, cons
 
 // The same on 16 x 16 tiles (16 x 16 x 4 products: four groups of 16 lanes supply 4 reduction indices each of a 16-deep piece), for
 // the smallest calls, whose 32 x 32 tiles are fewer than the compute units: a wave's chain of matrix instructions is a quarter
-// as long.  (us a call, 32 / 16: B = 256, N = 4, d = 512: 16.2 / 14.0; 512, 8, 512: 19.2 / 16.7; 512, 4, 512: 21.6 / 20.8.)
+// as long.  A wave's part is up to a few pieces (two at d = 256, four at 512): its whole pieces are all loaded before the first is
+// multiplied, whether they fill a block of U or not (element by element, one after the other, the rest of a block cost up to 27 %
+// of a call; us, element by element / so: B = 256, N = 1, d = 256 20.6 / 15.5; 512, 4, 256 22.8 / 17.9; 256, 4, 384 18.4 / 13.3).
 template <bool VEC, int NW>
 __global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, const float* T, SmallShape f, float* ws) {
   __shared__ float red[NW][4][64];
@@ -414,7 +416,21 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, c
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][e], y[c][e], acc, 0, 0, 0);
   }
-  for (; k < k1; k += 16) {                             // what is left, element by element: past k1 both operands count as 0
+  {                                                     // up to U - 1 whole pieces more
+    const int left = (int)(k1 - k) / 16;
+    f32x4 x[U - 1], y[U - 1];
+#pragma unroll
+    for (int c = 0; c < U - 1; ++c)
+      if (c < left) { x[c] = load4<VEC>(a, k + 16 * c + up); y[c] = load4<VEC>(b, k + 16 * c + up); }
+#pragma unroll
+    for (int c = 0; c < U - 1; ++c)
+      if (c < left) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][e], y[c][e], acc, 0, 0, 0);
+      }
+    k += 16 * left;
+  }
+  if (k < k1) {                                         // the last piece, element by element: past k1 both operands count as 0
     float x[4], y[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -776,7 +792,10 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 namespace {
 
-// Up to this many 32 x 32 similarity tiles: 16 x 16 ones.  (Twice as many, us a call, 32 / 16: B = 1024, N = 4, d = 64: 26.0 / 29.1.)
+// Up to this many 32 x 32 similarity tiles: 16 x 16 ones.  (us a call, 32 / 16.  At 32 tiles, B = 256, N = 4: d = 16 11.7 / 11.5,
+// 128 15.4 / 12.4, 256 13.8 / 12.8, 512 16.0 / 13.7, 768 18.2 / 14.8.  At 128, B = 512, N = 4: 15.5 / 15.3, 19.7 / 17.1, 18.0 / 17.9,
+// 21.2 / 20.6, 27.6 / 26.5.  At 170, B = 544, N = 4: 17.5 / 17.5, 21.7 / 19.4, 20.0 / 20.5, 25.3 / 26.2, 33.3 / 34.7.  At 256, B = 512,
+// N = 2: 16.1 / 16.4, 20.7 / 18.9, 18.5 / 20.0, 25.1 / 27.7, 33.4 / 37.4.)
 constexpr int64_t SIM16_MOST = 128;
 
 size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
