@@ -596,7 +596,8 @@ __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[
   }
 }
 
-template <int PIECE, int NW>
+// STREAM: the similarities are written past the caches (see stream_similarities).
+template <int PIECE, int NW, bool STREAM>
 __global__ __launch_bounds__(64 * NW) void small_similarity_bf16(const uint16_t* I, const uint16_t* T, SmallShape f, float* ws) {
   __shared__ float red[NW / 2][64][64];
   const int z = blockIdx.z, l2 = 2 * (threadIdx.x & 31), up = upper_half() * 8, d = (int)f.d;
@@ -643,9 +644,10 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_bf16(const uint16_t*
   join_waves_64<NW>(acc, red, [&](int r, int c, const f32x2& v) {
     if (m0 + r >= f.b || n0 + c >= f.B) return;
     float* p = W + (m0 + r) * f.pitch + n0 + c;
-    // (streamed: up to 4 MB of it would otherwise sit dirty in the L2s, which the kernel's end writes back)
-    if (f.pitch % 4 == 0) __builtin_nontemporal_store(v, reinterpret_cast<f32x2*>(p));       // (what lies in the pitch behind a row is free)
-    else {
+    if (f.pitch % 4 == 0) {                                // (what lies in the pitch behind a row is free)
+      if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x2*>(p));
+      else *reinterpret_cast<f32x2*>(p) = v;
+    } else {
       p[0] = v[0];
       if (n0 + c + 1 < f.B) p[1] = v[1];
     }
@@ -798,6 +800,14 @@ namespace {
 // N = 2: 16.1 / 16.4, 20.7 / 18.9, 18.5 / 20.0, 25.1 / 27.7, 33.4 / 37.4.)
 constexpr int64_t SIM16_MOST = 128;
 
+// bf16 features: similarities written past the caches, or kept in them for the softmax?  Up to 32 MiB fit the eight L2s, where they
+// would sit dirty until the kernel's end writes them back; up to 256 MiB stay in the last-level cache; more does not.  (Streamed /
+// plain, us a call: 4 MiB, B = 1024, N = 2, d = 256: 34.3 / 35.0; 8 MiB, 1024, 1, 100: 43.9 / 45.0; 16 MiB, 2048, 2, 256: 60.8 / 63.8;
+// 25 MiB, 2560, 2, 100: 85.7 / 85.0; 32 MiB, 4096, 4, 100: 94.6 / 95.5; 2048, 1, 256: 88.6 / 89.2; 40 MiB, 2304, 1, 100: 102.8 / 101.4;
+// 78 MiB, 3200, 1, 100: 156 / 151; 128 MiB, 4096, 1, 100: 223 / 217; 200 MiB, 5120, 1, 100: 407 / 405; 312 MiB, 6400, 1, 100: 613 / 630;
+// 512 MiB, 8192, 1, 100: 939 / 978.)
+bool stream_similarities(size_t bytes) { return bytes <= ((size_t)32 << 20) || bytes > ((size_t)256 << 20); }
+
 size_t matrix_bytes(size_t nb, int64_t b, int64_t pitch) { return align_up(nb * b * pitch * sizeof(float)); }
 size_t lean_bytes(size_t nb, int64_t b, int64_t pitch) { return matrix_bytes(nb, b, pitch) + 2 * align_up(nb * b * sizeof(float)); }
 
@@ -866,9 +876,13 @@ void small_run(const Problem& p) {
     const uint16_t* T = static_cast<const uint16_t*>(p.T);
     auto sim = [&](auto kernel) { kernel<<<sim_grid(64), 256, 0, p.stream>>>(I, T, f, W); };
     auto grads = [&](auto kernel) { kernel<<<grad_grid(64), 512, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT); };
-    if (p.d % 8 == 0 && address % 16 == 0) sim(small_similarity_bf16<8, 4>);
-    else if (p.d % 4 == 0 && address % 8 == 0) sim(small_similarity_bf16<4, 4>);
-    else sim(small_similarity_bf16<1, 4>);
+    auto similarity = [&](auto streamed, auto plain) {
+      if (stream_similarities(matrix_bytes(nb, p.b, f.pitch))) sim(streamed);
+      else sim(plain);
+    };
+    if (p.d % 8 == 0 && address % 16 == 0) similarity(small_similarity_bf16<8, 4, true>, small_similarity_bf16<8, 4, false>);
+    else if (p.d % 4 == 0 && address % 8 == 0) similarity(small_similarity_bf16<4, 4, true>, small_similarity_bf16<4, 4, false>);
+    else similarity(small_similarity_bf16<1, 4, true>, small_similarity_bf16<1, 4, false>);
     softmax();
     const bool pair = p.d % 2 == 0 && address % 4 == 0;
     if (pair) { if (wvec) grads(small_grads_bf16<true, true, 8>); else grads(small_grads_bf16<true, false, 8>); }
