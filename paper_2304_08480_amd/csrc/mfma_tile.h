@@ -567,8 +567,9 @@ __device__ __forceinline__ void superblock_tile(int lin, int nI, int nJ, int sbi
 // a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
 // every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
 // The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.  (They are of the loop on 32x32x16 products; on
-// 16x16x32 ones both tile sizes take 8 % less, which leaves the choices as they are: forcing each of the four pairs of tile sizes on
-// 12 shapes beat the chosen plan by 4 % at most.)
+// 16x16x32 ones both tile sizes take 8 % less, which leaves the choice between the sizes as it is: forcing each of the four pairs of tile
+// sizes on 12 shapes beat the chosen plan by 4 % at most.  Against other kernels that factor does not cancel: those comparisons, of the
+// small kernels with the tile paths and with the split kernels, carry allowances measured on the present kernels.)
 constexpr double CHIP_CUS = 256.0;
 constexpr double BYTES_PER_US = 4.5e6;
 

@@ -4,6 +4,8 @@
 // Eq. 4-6 are plain tiled products.  Everything is deterministic (no float atomics).
 #include "common.h"
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace disco {
@@ -820,14 +822,47 @@ int64_t row_pitch(int64_t b, int64_t B, size_t nb) {
 
 // Estimated time of the small kernels: launches, products at the rate they reach (fp32 features 85 TFLOP/s, bf16 ones 200; less
 // where rows are not whole pieces), and the longest reduction that the waves of one workgroup walk (a tile of the rank's
-// own gradient rows).  Against the split kernels (measured, us, fp32 features, d = 512): B = 256, N = 4: 17 / 48; 2048, 16: 73 / 66;
-// 2048, 8: 83 / 66; 4096, 16: 142 / 87.
-double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
+// own gradient rows).
+double small_rate_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
   if (dtype == DISCO_BF16) return 14.0 + 0.5 * nb * (double)b * B * d * (d % 2 ? 1.5 : 1.0) * 12.0 / 200e6 + 1.15 * (b + B) / 128;
   const double macs = 0.5 * nb * (double)b * B * d, slow = d % 4 ? 1.9 : 1.0;
   const bool big = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
   const double chain = (b + B) * (big ? 32.0 * 4 / 4 : 32.0 / 8) / 2200.0;
   return 14.0 + slow * macs * 12.0 / 85e6 + chain;
+}
+
+// Rows of reduction that the busiest compute unit walks in the gradient kernel on T x T tiles, one workgroup to a unit: b + B in a tile
+// of the rank's own rows, which come first, b in the others.
+double longest_walk(int64_t T, int64_t b, int64_t B, int64_t d, int nb) {
+  const double units = 256.0, all = (double)nb * cdiv(B, T) * cdiv(d, T), own = std::min(all, (double)nb * cdiv(b, T) * cdiv(d, T)), rest = all - own;
+  if (all <= units) return b + B;
+  if (rest < units / 8) return std::ceil(own / units) * (b + B);
+  return std::max((double)(b + B), (own * (b + B) + rest * b) / units + 0.5 * (own <= units ? b : b + B));
+}
+
+// The same by what each kernel's slowest compute units do, for calls that do not fill the matrix units: narrow features, whose tiles
+// are as long as wide ones', and rounds of workgroups that end nearly empty.
+double small_walk_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
+  const double pairs = 1e-6 * nb * (double)b * B, width = 1e-3 * d;
+  auto rounds = [&](int64_t T) { return std::max(1.0, (double)nb * cdiv(b, T) * cdiv(B, T) / 512); };
+  if (dtype == DISCO_BF16)
+    return 11.0 + (d % 2 ? 13.3 : 6.5) * width + 19.8 * (rounds(64) - 1) * width + 3.2 * pairs + (d % 2 ? 12.7 : 9.0) * 1e-3 * longest_walk(64, b, B, d, nb);
+  const bool similarity64 = (double)nb * cdiv(b, 64) * cdiv(B, 64) >= 256, grads64 = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
+  return 8.5 + (similarity64 ? 38.0 * rounds(64) : 10.4 * rounds(32)) * width + 3.7 * pairs +
+         1e-3 * (grads64 ? 20.0 * longest_walk(64, b, B, d, nb) : 8.2 * longest_walk(32, b, B, d, nb));
+}
+
+// Against the split kernels, whose estimate is good to about 10 %: the larger of the two estimates.  The second is a fit (8 % rms)
+// to 1500 calls of 8 to 8192 rows a share and d = 1 to 2048, times 0.9 (fp32) or 0.85 (bf16), so weighed that it moves hardly a call to
+// split kernels that are slower: of 378 drawn calls that it moves one takes 3 % longer, and half take 0.70 of the time or less.
+// (Measured, us, small / split, fp32 features: B = 256, N = 4, d = 512 13.5 / 48; 1024, 4, 512 51 / 59; 2048, 16, 128 40 / 44; 2048, 16, 512
+// 71 / 63; and small by the first estimate alone: 4096, 16, 64 66 / 47; 2560, 1, 64 187 / 108; 1536, 1, 200 145 / 84; 4096, 4, 20 88 / 69.
+// bf16: 1200, 4, 300 37 / 38; 2048, 16, 200 41 / 32; and 2560, 1, 100 115 / 88; 1024, 1, 77 55 / 42.)
+// Two kinds of calls keep the first: shares of a few rows of wide features, where the split kernels' estimate is up to 25 % short (4096,
+// 512, 1024, two views: 96 / 123, estimated 101), and those of the path by name (lean), whose split kernels take the rows in chunks.
+double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb, bool lean) {
+  const double us = small_rate_us(b, B, d, dtype, nb);
+  return lean || (b < 64 && d > 640) ? us : std::max(us, small_walk_us(b, B, d, dtype, nb));
 }
 
 // Workspace of the split kernels may reach this where the fp32 blocks of the small ones need less.
@@ -840,7 +875,7 @@ size_t split_bytes(int64_t B, int64_t d, int64_t b, int dtype, int nb, bool lean
   if (!split_supported(B, b)) return 0;
   size_t bytes;
   const double us = split_estimate_us(B, d, b, dtype, nb, *limit, &bytes);
-  return bytes && us < small_us(b, B, d, dtype, nb) ? bytes : 0;
+  return bytes && us < small_us(b, B, d, dtype, nb, lean_only) ? bytes : 0;
 }
 
 void small_run(const Problem& p) {
@@ -929,15 +964,16 @@ void naive_describe(int64_t B, int64_t d, int32_t N, int dtype, int variant, boo
   }
   out->kernels = DISCO_KERNELS_SMALL;
   out->row_chunks = out->key_panels = out->query_splits = out->key_splits = 1;
-  out->microseconds = small_us(b, B, d, dtype, nb);
+  out->microseconds = small_us(b, B, d, dtype, nb, lean);
 }
 
 // Is a call that the bf16 tile kernels take faster on the small ones?  Few tiles leave those kernels with their seven launches,
-// 27 us on top of the tiles' estimate whatever the shape; the small ones are three.  (Measured, us, tiles / small, bf16:
-// B = 256, N = 1, d = 128: 34 / 21; 512, 2, 256: 37 / 25; 1024, 4, 512: 44 / 34; 1024, 2, 256: 41 / 38; 2048, 16, 512: 45 / 42;
-// 1024, 1, 512: 51 / 53; 2048, 4, 256: 43 / 54; 4096, 32, 512: 46 / 66.)
+// about 21 us on top of the tiles' estimate whatever the shape; the small ones are three.  27 are allowed: within those 6 us a call
+// keeps the small kernels' fp32 numerators, whose gradients are 1e-5 and more of their 2-norm nearer.  (Measured, us, tiles / small,
+// bf16: B = 256, N = 1, d = 128: 29 / 18; 512, 2, 256: 29 / 23; 1024, 4, 512: 34 / 31; 1024, 2, 256: 33 / 35; 1024, 4, 1024: 44 / 36; 2048, 16,
+// 512: 35 / 41; 1024, 1, 512: 43 / 48; 2048, 4, 256: 35 / 51; 4096, 32, 512: 38 / 65.)
 bool small_beats_tiles(int64_t B, int64_t d, int32_t N, int variant) {
-  const double us = small_us(B / N, B, d, DISCO_BF16, loss_blocks(variant));
+  const double us = small_rate_us(B / N, B, d, DISCO_BF16, loss_blocks(variant));
   return us < 60.0 && us < mfma_stored_estimate_us(B, d, N, variant) + 27.0;
 }
 
