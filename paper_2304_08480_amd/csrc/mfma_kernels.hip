@@ -1286,9 +1286,12 @@ bool allow_lds(K kernel, int bytes) {
 }
 
 // Numerators written past the caches, or kept in them for the gradient kernel?  They stay in the 256 MiB last-level cache
-// until that kernel reads them if they fill at most half of it; below 24 MiB they would sit dirty in the eight L2s, which the
-// kernel's end writes back.  (Streamed / plain, us a call: 16 MiB 85.5 / 84.1; 32 MiB 87.5 / 86.0; 64 MiB, B = 32768, N = 64: 148 / 139;
-// 128 MiB, B = 32768, N = 32: 247 / 223; 256 MiB, B = 32768, N = 16: 394 / 410; 512 MiB: 724 / 742.)
+// until that kernel reads them if they fill at most half of it; what the eight L2s (32 MiB) hold would sit dirty in them, and the
+// kernel's end writes it back.  That is worth 1 % on average (12 calls each of d = 64 to 1024, streamed over plain: 16 MiB 0.987, 20 MiB 0.984, single
+// calls 0.93 to 1.04), and from 24 MiB to 32 the two are equal to within the boxes' differences (1.006, 0.989, 0.992 on one, 1.005 on
+// another), so the line lies there.  (Streamed / plain, us a call of d = 512: 16 MiB, B = 4096, N = 4 57.9 / 59.6; 16384, 64 64.5 / 69.1; 24 MiB, 6144, 6
+// 76.3 / 76.9; 32 MiB, 8192, 8 85.2 / 85.4; 64 MiB, B = 32768, N = 64: 148 / 139; 128 MiB, B = 32768, N = 32: 247 / 223; 256 MiB, B = 32768, N = 16:
+// 394 / 410; 512 MiB: 724 / 742.)
 bool streaming_stores(int nblk, int64_t b, int64_t W) {
   const int64_t bytes = 2 * nblk * b * W;
   return bytes < ((int64_t)24 << 20) || bytes > ((int64_t)144 << 20);
