@@ -310,7 +310,7 @@ def bench_mfma_peak(args, dl, np, torch):
     sink = torch.zeros(1, device=dev)
     clocks = torch.zeros(2, dtype=torch.int64, device=dev)
     stream = torch.cuda.current_stream()
-    iters = 40000                                   # x 8 MFMAs x 32768 flop per wave
+    iters = 40000                                   # x 16 MFMAs x 16384 flop per wave
     rows = []
     for varied, wgs in ((0, cus), (1, cus // 4), (1, cus)):   # quiet operands; then data-like ones on a quarter and on all of the chip
         for _ in range(max(args.warmup, 20)):
@@ -324,7 +324,7 @@ def bench_mfma_peak(args, dl, np, torch):
         torch.cuda.synchronize()
         ms = a.elapsed_time(b) / args.steps
         c = clocks.cpu().numpy()
-        flops = wgs * 8 * iters * 8 * 32768.0
+        flops = wgs * 8 * iters * 16 * 16384.0
         rows.append({"operands": "sign, exponent and mantissa vary" if varied else "mantissa varies only", "workgroups": wgs,
                      "ms_per_launch": round(ms, 4), "tflops": round(flops / (ms * 1e-3) / 1e12, 1),
                      "shader_clock_mhz": round(100.0 * float(c[0]) / float(c[1]), 1)})
@@ -332,7 +332,7 @@ def bench_mfma_peak(args, dl, np, torch):
     out = {"metric": "bf16 MFMA issue rate, registers only, all compute units", "value": full["tflops"], "unit": "TFLOP/s",
            "n_gpus": 1, "steps": args.steps, "warmup": max(args.warmup, 20), "ms_per_step": full["ms_per_launch"],
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
-           "config": {"workload": "mfma-peak", "compute_units": cus, "waves_per_simd": 2, "mfma": "v_mfma_f32_32x32x16_bf16"},
+           "config": {"workload": "mfma-peak", "compute_units": cus, "waves_per_simd": 2, "mfma": "v_mfma_f32_16x16x32_bf16"},
            "runs": rows,
            "roofline": {"bound": "mfma", "kernel": "k_mfma_probe", "achieved": full["tflops"], "peak": PEAK_BF16_TFLOPS,
                         "unit": "TFLOP/s", "frac": round(full["tflops"] / PEAK_BF16_TFLOPS, 4), "traffic": None},

@@ -243,8 +243,8 @@ typedef struct {
 DISCO_API int disco_describe_plan(int64_t B, int64_t d, int32_t N, int dtype, int path, int two_view, size_t workspace_limit, disco_plan* out);
 
 /*
- * Measurement only: `workgroups` workgroups of 8 waves each issue `iters` x 8 bf16 MFMA 32x32x16 instructions per
- * wave (32768 flop each) from registers, with no memory traffic: what the matrix cores sustain once the clock
+ * Measurement only: `workgroups` workgroups of 8 waves each issue `iters` x 16 bf16 MFMA 16x16x32 instructions per
+ * wave (16384 flop each: the instruction of the tile kernels) from registers, with no memory traffic: what the matrix cores sustain once the clock
  * management has settled, the ceiling under the published peak that a tile kernel works against.  varied != 0: the
  * operands differ in sign, exponent and mantissa from element to element (as real data does); 0: in the mantissa
  * only, which draws less power.  sink: one device

@@ -4,7 +4,7 @@
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
 // 128x64 of it as 8x4 MFMA 16x16x32 bf16 blocks with fp32 accumulators.  What bounds the loop is power (the chip clocks at
 // 1.7-1.9 GHz in it), and the 16x16x32 form does the same multiplications with half the accumulator traffic: from registers
-// alone the whole chip runs 2.09 PFLOP/s of it against 1.86 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
+// alone the whole chip runs 2.00 PFLOP/s of it (k_mfma_probe) against 1.86 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
 // 752 us against 821, B = 65536, d = 768 3990 against 4395.  The reduction runs in K-steps of
 // 64.  Operand tiles travel global memory -> LDS directly (buffer_load_dwordx4 ... lds): no staging
 // registers, no LDS write instructions, and the data in flight lives in LDS.  K-steps are 64 wide so that
