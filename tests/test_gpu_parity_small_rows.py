@@ -23,6 +23,7 @@ def test_rows_and_tiles_at_their_edges(B, N, d, dtype):
         Ib, Tb = f32_to_bf16_bits(I), f32_to_bf16_bits(T)
         I, T = bf16_bits_to_f32(Ib), bf16_bits_to_f32(Tb)
     Id, Td, dt = to_device(I, T, Ib, Tb, dtype)
+    assert dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_NAIVE).kernels == dl.DISCO_KERNELS_SMALL
     run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_NAIVE)
     for r in sorted({0, N - 1}):
         run.rank(r, 14.285714)

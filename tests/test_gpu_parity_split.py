@@ -1,6 +1,6 @@
 """The large calls of the fp32 path (operands split into bf16 planes) at the sizes where they can go wrong: shares and
 batches that are not whole tiles, widths that are not whole K-steps or 16-byte pieces, one share per 256 rows and all rows in
-one, rows too long for the softmax's registers, rows taken in chunks, operands off their 16-byte boundary.  Against the
+one, rows past the softmax's smaller set of registers, rows taken in chunks, operands off their 16-byte boundary.  Against the
 float64 oracles at the fp32 bars."""
 import numpy as np
 import pytest
@@ -45,7 +45,7 @@ def _check(I, T, run, r, N, tag):
     (4098, 300, 3, "f32", 0),          # nothing whole but the 16-byte pieces of a row
     (5000, 77, 4, "f32", 1),           # rows that are not whole pieces, features off the boundary: element loads and stores
     (4099, 130, 1, "f32", 0),          # all rows one share, an odd batch
-    (16896, 64, 66, "f32", 0),         # rows longer than the softmax keeps in registers, one K-step of d
+    (16896, 64, 66, "f32", 0),         # rows of twice the registers' first size, one K-step of d
     (2048, 200, 4, "bf16", 0),         # one plane per feature
     (4098, 100, 3, "bf16", 1),
     (6145, 333, 5, "bf16", 0),
