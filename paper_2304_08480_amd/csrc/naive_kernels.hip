@@ -840,29 +840,27 @@ double longest_walk(int64_t T, int64_t b, int64_t B, int64_t d, int nb) {
   return std::max((double)(b + B), (own * (b + B) + rest * b) / units + 0.5 * (own <= units ? b : b + B));
 }
 
-// The same by what each kernel's slowest compute units do, for calls that do not fill the matrix units: narrow features, whose tiles
-// are as long as wide ones', and rounds of workgroups that end nearly empty.
-double small_walk_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
+// The same for narrow fp32 features, by what each kernel's slowest compute units do: their tiles are as long as wide ones', and the
+// rounds of workgroups end nearly empty.
+double small_walk_us(int64_t b, int64_t B, int64_t d, int nb) {
   const double pairs = 1e-6 * nb * (double)b * B, width = 1e-3 * d;
   auto rounds = [&](int64_t T) { return std::max(1.0, (double)nb * cdiv(b, T) * cdiv(B, T) / 512); };
-  if (dtype == DISCO_BF16)
-    return 11.0 + (d % 2 ? 13.3 : 6.5) * width + 19.8 * (rounds(64) - 1) * width + 3.2 * pairs + (d % 2 ? 12.7 : 9.0) * 1e-3 * longest_walk(64, b, B, d, nb);
   const bool similarity64 = (double)nb * cdiv(b, 64) * cdiv(B, 64) >= 256, grads64 = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
   return 8.5 + (similarity64 ? 38.0 * rounds(64) : 10.4 * rounds(32)) * width + 3.7 * pairs +
          1e-3 * (grads64 ? 20.0 * longest_walk(64, b, B, d, nb) : 8.2 * longest_walk(32, b, B, d, nb));
 }
 
-// Against the split kernels, whose estimate is good to about 10 %: the larger of the two estimates.  The second is a fit (8 % rms)
-// to 1500 calls of 8 to 8192 rows a share and d = 1 to 2048, times 0.9 (fp32) or 0.85 (bf16), so weighed that it moves hardly a call to
-// split kernels that are slower: of 378 drawn calls that it moves one takes 3 % longer, and half take 0.70 of the time or less.
-// (Measured, us, small / split, fp32 features: B = 256, N = 4, d = 512 13.5 / 48; 1024, 4, 512 51 / 59; 2048, 16, 128 40 / 44; 2048, 16, 512
-// 71 / 63; and small by the first estimate alone: 4096, 16, 64 66 / 47; 2560, 1, 64 187 / 108; 1536, 1, 200 145 / 84; 4096, 4, 20 88 / 69.
-// bf16: 1200, 4, 300 37 / 38; 2048, 16, 200 41 / 32; and 2560, 1, 100 115 / 88; 1024, 1, 77 55 / 42.)
-// Two kinds of calls keep the first: shares of a few rows of wide features, where the split kernels' estimate is up to 25 % short (4096,
-// 512, 1024, two views: 96 / 123, estimated 101), and those of the path by name (lean), whose split kernels take the rows in chunks.
+// Against the split kernels, whose estimate is good to about 10 %: for shares of 32 rows and more of fp32 features under 128 columns
+// the larger of the two estimates.  The second is a fit (8 % rms) to 800 calls of 8 to 8192 rows a share, times 0.9, so weighed that it
+// moves hardly a call to split kernels that are slower.  (Measured, us, small / split, fp32 features: B = 256, N = 4, d = 512 13.5 / 48; 1024, 4,
+// 512 51 / 59; 2048, 16, 128 40 / 44; 2048, 16, 512 71 / 63; and small by the first estimate alone: 4096, 16, 64 66 / 47; 2560, 1, 64 187 / 108;
+// 2048, 1, 100 130 / 88; 4096, 4, 20 88 / 69.)  Other calls that the first estimate keeps on the small kernels stay there although many would
+// take 0.7 of the time on the split ones (1536, 1, 200 145 / 84; bf16 2560, 1, 100 115 / 88): wider ones, bf16 features and fewer rows because the
+// split kernels' gradients are further from 64 bits there (up to 2 times the error at s = 100; on the calls that move at most 0.98 times,
+// mostly 0.5 to 0.75, and of 297 drawn ones none takes longer, half 0.66 of the time or less); the path by name's (lean) because its split kernels take the rows in chunks.
 double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb, bool lean) {
   const double us = small_rate_us(b, B, d, dtype, nb);
-  return lean || (b < 64 && d > 640) ? us : std::max(us, small_walk_us(b, B, d, dtype, nb));
+  return lean || dtype == DISCO_BF16 || d >= 128 || b < 32 ? us : std::max(us, small_walk_us(b, B, d, nb));
 }
 
 // Workspace of the split kernels may reach this where the fp32 blocks of the small ones need less.
