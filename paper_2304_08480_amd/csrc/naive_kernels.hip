@@ -406,9 +406,9 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, c
   const float* a = (z == 0 ? I : T) + (f.rank * f.b + (m < f.b ? m : f.b - 1)) * f.d;      // a row past the end repeats the last; its results are not stored
   const float* b = (z == 0 ? T : I) + (n < f.B ? n : f.B - 1) * f.d;
   const int pieces = (int)((f.d + 15) / 16), w = __builtin_amdgcn_readfirstlane(wave);      // dealt evenly: the shorter a wave's chain, the fewer roundings
-  const int64_t k0 = w * pieces / NW * 16, end = (w + 1) * pieces / NW * 16, k1 = end < f.d ? end : f.d;
+  const int k0 = w * pieces / NW * 16, end = (w + 1) * pieces / NW * 16, k1 = end < (int)f.d ? end : (int)f.d;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  int64_t k = k0;
+  int k = k0;
   for (; k + 16 * U <= k1; k += 16 * U) {
     f32x4 x[U], y[U];
 #pragma unroll
@@ -418,8 +418,8 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, c
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][e], y[c][e], acc, 0, 0, 0);
   }
-  {                                                     // up to U - 1 whole pieces more
-    const int left = (int)(k1 - k) / 16;
+  if (k < k1) {                                         // up to U - 1 whole pieces more
+    const int left = (k1 - k) / 16;
     f32x4 x[U - 1], y[U - 1];
 #pragma unroll
     for (int c = 0; c < U - 1; ++c)
@@ -431,17 +431,17 @@ __global__ __launch_bounds__(64 * NW) void small_similarity_16(const float* I, c
         for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][e], y[c][e], acc, 0, 0, 0);
       }
     k += 16 * left;
-  }
-  if (k < k1) {                                         // the last piece, element by element: past k1 both operands count as 0
-    float x[4], y[4];
+    if (k < k1) {                                       // the last piece, element by element: past k1 both operands count as 0
+      float u[4], v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t kk = k + up + e, kc = kk < k1 ? kk : k1 - 1;
-      x[e] = kk < k1 ? a[kc] : 0.f;
-      y[e] = kk < k1 ? b[kc] : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        const int kk = k + up + e, kc = kk < k1 ? kk : k1 - 1;
+        u[e] = kk < k1 ? a[kc] : 0.f;
+        v[e] = kk < k1 ? b[kc] : 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(u[e], v[e], acc, 0, 0, 0);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[r];
@@ -855,9 +855,10 @@ double small_walk_us(int64_t b, int64_t B, int64_t d, int nb) {
 // moves hardly a call to split kernels that are slower.  (Measured, us, small / split, fp32 features: B = 256, N = 4, d = 512 13.5 / 48; 1024, 4,
 // 512 51 / 59; 2048, 16, 128 40 / 44; 2048, 16, 512 71 / 63; and small by the first estimate alone: 4096, 16, 64 66 / 47; 2560, 1, 64 187 / 108;
 // 2048, 1, 100 130 / 88; 4096, 4, 20 88 / 69.)  Other calls that the first estimate keeps on the small kernels stay there although many would
-// take 0.7 of the time on the split ones (1536, 1, 200 145 / 84; bf16 2560, 1, 100 115 / 88): wider ones, bf16 features and fewer rows because the
-// split kernels' gradients are further from 64 bits there (up to 2 times the error at s = 100; on the calls that move at most 0.98 times,
-// mostly 0.5 to 0.75, and of 297 drawn ones none takes longer, half 0.66 of the time or less); the path by name's (lean) because its split kernels take the rows in chunks.
+// take 0.7 of the time on the split ones (1536, 1, 200 145 / 84; bf16 2560, 1, 100 115 / 88): wider ones, bf16 features and fewer rows
+// because the split kernels' gradients are further from 64 bits there (1.0 to 1.6 times the error in most, up to 6 at s = 100; on the calls
+// that move at most 0.98 times, mostly 0.5 to 0.75, and of 297 drawn ones none takes longer, half 0.66 of the time or less); the path by
+// name's (lean) because its split kernels take the rows in chunks.
 double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb, bool lean) {
   const double us = small_rate_us(b, B, d, dtype, nb);
   return lean || dtype == DISCO_BF16 || d >= 128 || b < 32 ? us : std::max(us, small_walk_us(b, B, d, nb));
