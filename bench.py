@@ -33,10 +33,10 @@ PATH_NAMES = {1: "naive", 2: "materialized", 3: "fused", 4: "symmetric"}
 # summaries are profiles/<workload>_hbm_traffic.txt (counters cannot be read from inside this process; the fetch
 # part varies by about a quarter from run to run with what the last-level cache still holds).  Workloads and
 # paths without such a summary report null on purpose.
-MEASURED_TRAFFIC_BYTES = {("b32k_n8", "materialized", "logit_tiles"): 8.938e8,
-                          ("b196k_n64", "materialized", "logit_tiles"): 3.510e9,
-                          ("b64k_d768_n8", "materialized", "logit_tiles"): 4.590e9,
-                          ("full_n1", "symmetric", "logit_tiles_row_and_column_sums"): 3.930e9}
+MEASURED_TRAFFIC_BYTES = {("b32k_n8", "materialized", "logit_tiles"): 8.954e8,
+                          ("b196k_n64", "materialized", "logit_tiles"): 3.504e9,
+                          ("b64k_d768_n8", "materialized", "logit_tiles"): 4.613e9,
+                          ("full_n1", "symmetric", "logit_tiles_row_and_column_sums"): 3.896e9}
 
 
 def parse():

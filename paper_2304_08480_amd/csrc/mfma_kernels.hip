@@ -400,7 +400,7 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
 // the features it asks for: so the rows' go through LDS, 64 features at a time (`xt`: two such pieces, 16 KiB, 16-byte chunks
 // XOR-swizzled with the row), and a key's come straight from memory, a whole line at once.  (All rows redone, features of norm 4
 // to 8 at B = 32768, d = 512: a call takes 2.9 ms at N = 8 and 2.35 at N = 64; with both operands' fragments straight from
-// memory and every workgroup on the same rows at it, 6.1 and 5.5; a call that redoes none 0.9 and 0.16.)
+// memory and every workgroup on the same rows at it, 6.1 and 5.5; a call that redoes none 0.75 and 0.145.)
 // Local rows i0 .. i0 + 63, global row g0 + i; Bp: key rows that exist in memory, a multiple of 32.  Leaves the rows' sums in
 // off_s and their label numerators in ed_s.
 __device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool store,

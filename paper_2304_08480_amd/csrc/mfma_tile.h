@@ -4,7 +4,7 @@
 // Shape of the loop.  A workgroup of 8 waves (two per SIMD) owns a 256x256 output tile; each wave owns
 // 128x64 of it as 8x4 MFMA 16x16x32 bf16 blocks with fp32 accumulators.  What bounds the loop is power (the chip clocks at
 // 1.7-1.9 GHz in it), and the 16x16x32 form does the same multiplications with half the accumulator traffic: from registers
-// alone the whole chip runs 2.00 PFLOP/s of it (k_mfma_probe) against 1.86 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
+// alone the whole chip runs 2.00-2.12 PFLOP/s of it (k_mfma_probe) against 1.86-1.96 of 32x32x16, and a call of B = 32768, N = 8, d = 512 takes
 // 752 us against 821, B = 65536, d = 768 3990 against 4395.  The reduction runs in K-steps of
 // 64.  Operand tiles travel global memory -> LDS directly (buffer_load_dwordx4 ... lds): no staging
 // registers, no LDS write instructions, and the data in flight lives in LDS.  K-steps are 64 wide so that
@@ -566,7 +566,8 @@ __device__ __forceinline__ void superblock_tile(int lin, int nI, int nJ, int sbi
 // Time estimates in microseconds that the plans compare, for a chip of 256 compute units.  What they rest on (measured):
 // a 64-deep K-step of a workgroup takes 1.15 (T = 256) or 0.57 (T = 128) where few workgroups run and 1.7 or 1.03 where
 // every compute unit holds one (two), and prologue and store of a gradient tile another 8 or 3 (logit tiles 5.5 or 2.5).
-// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 %.  (They are of the loop on 32x32x16 products; on
+// The figures carry b = 64 .. 8192 rows of 256 .. 196608 keys to within about 15 % of the tile kernels' time; a call takes about 21 us more in
+// launches and small kernels, and the symmetric path its combining pass (3810 us against an estimate of 3009 at B = 32768, d = 512).  (They are of the loop on 32x32x16 products; on
 // 16x16x32 ones both tile sizes take 8 % less, which leaves the choice between the sizes as it is: forcing each of the four pairs of tile
 // sizes on 12 shapes beat the chosen plan by 4 % at most.  Against other kernels that factor does not cancel: those comparisons, of the
 // small kernels with the tile paths and with the split kernels, carry allowances measured on the present kernels.)

@@ -10,7 +10,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // The instruction of the tile loop, 16x16x32 (32x32x16 moves twice the accumulators per multiplication; from registers the whole chip
-// runs 1.86 PFLOP/s of it against 2.00 of this).  512 threads = two waves per SIMD, each with a 4 x 4 block of independent 16x16
+// runs 1.86-1.96 PFLOP/s of it against 2.00-2.12 of this).  512 threads = two waves per SIMD, each with a 4 x 4 block of independent 16x16
 // accumulators, taken in the tile loop's order: only one operand changes from one product to the next;
 // operands are pseudo-random bf16 patterns: with `varied` sign, exponent and mantissa differ from element to element,
 // so that the multipliers toggle as they do on real data; without, only the mantissas do (values in [0.5, 1)), which
