@@ -68,3 +68,30 @@ def test_narrow_two_view_calls_on_split_kernels(B, d, N):
     check_scalar("loss", float(loss.item()), ref[0], TOL["f32"]["scalar"])
     check_scalar("gs", float(gs.item()), ref[2], TOL["f32"]["scalar"] * 10, abs_tol=1e-9 + 1e-5 * scale[1])
     check_tensor("gZ", gZ.cpu().numpy().astype(np.float64), ref[1], "f32", scale[0], 1e-13 * S / B)
+
+
+@pytest.mark.parametrize("B,d,N,fits", [(2560, 64, 1, False), (4096, 64, 16, True)])     # (the split kernels' workspace in the static array)
+def test_less_memory_and_capture(B, d, N, fits):
+    I, T = clip_pairs(B, d, 19)
+    Id, Td, dt = to_device(I, T, None, None, "f32")
+    run, named = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_AUTO), Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_NAIVE)
+    assert (run.ws_bytes <= dl.disco_static_scratch_bytes()) == fits and named.ws_bytes < run.ws_bytes
+    run.rank(N - 1, S)
+    split = run.results()
+    named.rank(N - 1, S)
+    small = named.results()
+    print(f"case less memory B={B} d={d} N={N}", flush=True)
+    st = torch.cuda.current_stream()
+    dl.disco_loss_fwd_bwd(Id, Td, B, d, N - 1, N, S, dt, dl.DISCO_PATH_AUTO, 0, run.loss, run.gI, run.gT, run.gs, named.ws, named.ws_bytes, st)
+    assert all(np.array_equal(a, b) for a, b in zip(run.results(), small))               # what fits the path by name runs as that path
+    dl.disco_loss_fwd_bwd_static(Id, Td, B, d, N - 1, N, S, dt, dl.DISCO_PATH_AUTO, 0, run.loss, run.gI, run.gT, run.gs, st)
+    assert all(np.array_equal(a, b) for a, b in zip(run.results(), split if fits else small))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run.rank(N - 1, S)
+    for _ in range(3):
+        for o in (run.loss, run.gs, run.gI, run.gT):
+            o.fill_(float("nan"))
+        graph.replay()
+        assert all(np.array_equal(a, b) for a, b in zip(run.results(), split))
+        named.rank(0, S)                                   # eager work between the replays
