@@ -45,6 +45,27 @@ __host__ __device__ inline int loss_blocks(int variant) { return variant == LOSS
 // Normalisation: 1/(2B) for the two directions of the CLIP loss, 1/B for the single one of the two-view loss.
 __host__ __device__ inline float loss_norm(int64_t B, int variant) { return (variant == LOSS_NTXENT ? 1.0f : 0.5f) / (float)B; }
 
+// v over the wave by f (of two floats or two ints), the same in all lanes: four steps inside 16 lanes, two between them, none through
+// the LDS.  (Partners l ^ 1, l ^ 2, 7 - l, 15 - l, l ^ 16, l ^ 32.)
+template <int CTRL, class V>
+__device__ __forceinline__ V dpp(V v) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <class V, class F>
+__device__ __forceinline__ V wave_reduce(V v, F f) {
+  static_assert(sizeof(V) == 4);
+  v = f(v, dpp<0xB1>(v));
+  v = f(v, dpp<0x4E>(v));
+  v = f(v, dpp<0x141>(v));
+  v = f(v, dpp<0x140>(v));
+  const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t p0 = p[0], p1 = p[1];
+  v = f(__builtin_bit_cast(V, p0), __builtin_bit_cast(V, p1));
+  const auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t q0 = q[0], q1 = q[1];
+  return f(__builtin_bit_cast(V, q0), __builtin_bit_cast(V, q1));
+}
+
 // Benchmark stage timing (see disco_set_stage_events): records events[k] on `st` if it exists.
 void stage_mark(hipStream_t st, int k);
 bool stage_marks_on();

@@ -102,24 +102,6 @@ __global__ __launch_bounds__(256) void naive_row_softmax(float* ws, int64_t b, i
 // of four columns per lane), so that the row is read and written once and no barrier stands between its sums.  What bounds such a
 // launch is that chain of sums.  (us a call, workgroups per row / waves: fp32 B = 256, N = 4, d = 512: 17.6 / 16.2; 600 pairs of views, N = 3, d = 77:
 // 19.8 / 18.4; bf16 B = 1024, N = 2, d = 256: 37.6 / 36.6; 256 two-view rows: 19.2 / 17.0.)
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-// Over the wave, the same in all lanes.  (Partners l ^ 1, l ^ 2, 7 - l, 15 - l, l ^ 16, l ^ 32.)
-template <class F>
-__device__ __forceinline__ float wave_reduce(float v, F f) {
-  v = f(v, dpp<0xB1>(v));
-  v = f(v, dpp<0x4E>(v));
-  v = f(v, dpp<0x141>(v));
-  v = f(v, dpp<0x140>(v));
-  const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
-  const uint32_t p0 = p[0], p1 = p[1];
-  v = f(__builtin_bit_cast(float, p0), __builtin_bit_cast(float, p1));
-  const auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
-  const uint32_t q0 = q[0], q1 = q[1];
-  return f(__builtin_bit_cast(float, q0), __builtin_bit_cast(float, q1));
-}
 constexpr int WAVE_ROW_COLUMNS = 2048;
 
 template <int V>
@@ -279,12 +261,12 @@ __device__ __forceinline__ void join_waves(const f32x16 (&acc)[R][R], float (*re
   }
 }
 
-template <int R>
-__device__ __forceinline__ void clear(f32x16 (&acc)[R][R]) {
+template <int R, int C>
+__device__ __forceinline__ void clear(f32x16 (&acc)[R][C]) {
 #pragma unroll
   for (int u = 0; u < R; ++u)
 #pragma unroll
-    for (int v = 0; v < R; ++v)
+    for (int v = 0; v < C; ++v)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[u][v][r] = 0.f;
 }
@@ -492,7 +474,7 @@ __global__ __launch_bounds__(64 * NW) void small_grads(const float* I, const flo
   });
 }
 
-// ---- bf16 features: the same two launches on the bf16 matrix instruction (32 x 32 x 16), 64 x 64 tiles.  A similarity
+// ---- bf16 features: the same two launches on the bf16 matrix instruction (32 x 32 x 16), tiles of 64 or 32 x 64.  A similarity
 // is one product, exact in the instruction; a gradient entry, fp32 against bf16, is three: the fp32 value is split in
 // registers into three bf16 planes that add up to it (split3_block; entries below about 2^-109 lose the last one to bf16's
 // range), so nothing else is rounded that the fp32 instruction would not round.  Per 16 of the reduction that is 96 or 384 matrix cycles of a wave against 2048.
@@ -559,15 +541,15 @@ __device__ __forceinline__ void wave_range16(int K, int& k0, int& k1) {
   k1 = k0 + per < K ? k0 + per : K;
 }
 
-// Adds up the waves' partial 64 x 64 tiles in a fixed order, through red (NW / 2 tiles): the upper half of the waves hands
+// Adds up the waves' partial 32 RB x 64 tiles in a fixed order, through red (NW / 2 tiles): the upper half of the waves hands
 // its sums to the lower, whose sums are then added in wave order.  out(row, column, two values): an even column and the next, which
 // a lane hands on together so that a half-wave stores whole lines.
-template <int NW, class FOut>
-__device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[64][64], FOut out) {
+template <int RB, int NW, class FOut>
+__device__ __forceinline__ void join_waves_64(f32x16 (&acc)[RB][2], float (*red)[32 * RB][64], FOut out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   auto put = [&](int w) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < RB; ++u)
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
@@ -577,7 +559,7 @@ __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[
   __syncthreads();
   if (wave < NW / 2) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < RB; ++u)
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
@@ -586,7 +568,7 @@ __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 32 / NW; ++q) {
+  for (int q = 0; q < 16 * RB / NW; ++q) {
     const int ur = q * NW + wave, u = ur >> 4, r = ur & 15, idx = u * 32 + r;
     f32x2 s = {red[0][idx][lane], red[0][idx + 16][lane]};
 #pragma unroll
@@ -594,56 +576,77 @@ __device__ __forceinline__ void join_waves_64(f32x16 (&acc)[2][2], float (*red)[
       s[0] += red[w][idx][lane];
       s[1] += red[w][idx + 16][lane];
     }
-    out(2 * ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) + u, 2 * (lane & 31), s);
+    out(RB * ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) + u, 2 * (lane & 31), s);
   }
 }
 
 // STREAM: the similarities are written past the caches (see stream_similarities).
-template <int PIECE, int NW, bool STREAM>
+template <int PIECE, int RB, int NW, bool STREAM>
 __global__ __launch_bounds__(64 * NW) void small_similarity_bf16(const uint16_t* I, const uint16_t* T, SmallShape f, float* ws) {
-  __shared__ float red[NW / 2][64][64];
-  const int z = blockIdx.z, l2 = 2 * (threadIdx.x & 31), up = upper_half() * 8, d = (int)f.d;
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
+  __shared__ float red[NW / 2][32 * RB][64];
+  const int z = blockIdx.z, l32 = threadIdx.x & 31, up = upper_half() * 8, d = (int)f.d;
+  const int64_t m0 = (int64_t)blockIdx.y * 32 * RB, n0 = (int64_t)blockIdx.x * 64;
   const uint16_t* X = (z == 0 ? I : T) + f.rank * f.b * f.d;
   const uint16_t* Y = z == 0 ? T : I;
-  const uint16_t *a[2], *b[2];
+  const uint16_t *a[RB], *b[2];                         // a row past the end repeats the last; its results are not stored
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {                         // a row past the end repeats the last; its results are not stored
-    const int64_t m = m0 + l2 + u, n = n0 + l2 + u;
+  for (int u = 0; u < RB; ++u) {
+    const int64_t m = m0 + RB * l32 + u;
     a[u] = X + (m < f.b ? m : f.b - 1) * f.d + up;
-    b[u] = Y + (n < f.B ? n : f.B - 1) * f.d + up;
   }
-  f32x16 acc[2][2];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int64_t n = n0 + 2 * l32 + v;
+    b[v] = Y + (n < f.B ? n : f.B - 1) * f.d + up;
+  }
+  f32x16 acc[RB][2];
   clear(acc);
   int k0, k1;
   wave_range16<NW>(d, k0, k1);
-  auto product = [&](const bf16x8 (&x)[2], const bf16x8 (&y)[2]) {
+  // one 16-deep piece of both operands
+  struct Piece { bf16x8 x[RB], y[2]; };
+  auto product = [&](const Piece& p) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < RB; ++u)
 #pragma unroll
-      for (int v = 0; v < 2; ++v) acc[u][v] = mfma_bf16(x[u], y[v], acc[u][v]);
+      for (int v = 0; v < 2; ++v) acc[u][v] = mfma_bf16(p.x[u], p.y[v], acc[u][v]);
+  };
+  auto fetch = [&](Piece& p, int k) {
+#pragma unroll
+    for (int u = 0; u < RB; ++u) p.x[u] = load_row8<PIECE>(a[u] + k);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) p.y[v] = load_row8<PIECE>(b[v] + k);
   };
   int k = k0;
   for (; k + 64 <= k1; k += 64) {                       // four pieces in flight
-    bf16x8 x[4][2], y[4][2];
+    Piece p[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 4; ++c) fetch(p[c], k + 16 * c);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) { x[c][u] = load_row8<PIECE>(a[u] + k + 16 * c); y[c][u] = load_row8<PIECE>(b[u] + k + 16 * c); }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) product(x[c], y[c]);
+    for (int c = 0; c < 4; ++c) product(p[c]);
   }
-  for (; k + 16 <= k1; k += 16) {
-    const bf16x8 x[2] = {load_row8<PIECE>(a[0] + k), load_row8<PIECE>(a[1] + k)}, y[2] = {load_row8<PIECE>(b[0] + k), load_row8<PIECE>(b[1] + k)};
-    product(x, y);
+  const int whole = k < k1 ? (k1 - k) / 16 : 0;         // up to three more, all loaded before the first is multiplied
+  {
+    Piece p[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (c < whole) fetch(p[c], k + 16 * c);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (c < whole) product(p[c]);
   }
+  k += 16 * whole;
   if (k < k1) {
     const int n = k1 - k - up;
-    const bf16x8 x[2] = {load_row8_part(a[0] + k, n), load_row8_part(a[1] + k, n)}, y[2] = {load_row8_part(b[0] + k, n), load_row8_part(b[1] + k, n)};
-    product(x, y);
+    Piece p;
+#pragma unroll
+    for (int u = 0; u < RB; ++u) p.x[u] = load_row8_part(a[u] + k, n);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) p.y[v] = load_row8_part(b[v] + k, n);
+    product(p);
   }
   float* W = ws + (size_t)z * f.b * f.pitch;
-  join_waves_64<NW>(acc, red, [&](int r, int c, const f32x2& v) {
+  join_waves_64<RB, NW>(acc, red, [&](int r, int c, const f32x2& v) {
     if (m0 + r >= f.b || n0 + c >= f.B) return;
     float* p = W + (m0 + r) * f.pitch + n0 + c;
     if (f.pitch % 4 == 0) {                                // (what lies in the pitch behind a row is free)
@@ -664,27 +667,31 @@ __device__ __forceinline__ uint32_t load_feature_pair(const uint16_t* p, int nex
   return (uint32_t)p[0] | (uint32_t)p[next] << 16;
 }
 
-// As small_grads.  PAIR: see load_feature_pair.  WVEC: the matrices' pitch is a multiple of 4 floats.
-template <bool PAIR, bool WVEC, int NW>
+// As small_grads, on tiles of 32 RB x 64.  PAIR: see load_feature_pair.  WVEC: the matrices' pitch is a multiple of 4 floats.  RB = 1 with
+// 16 waves (flat_gradients) against RB = 2 with 8: B = 1024, N = 2, d = 256 20.0 -> 13.1 us of a call's 31.1 -> 23.6.  In those 13.1 the query side of the
+// own rows costs 5.7, the key side 3.1 and cutting the entries into planes 1.5; one list of both sides' pieces, four in flight, was no faster, nor
+// 16 x 16 x 32 products, which touch half the cache lines.
+template <bool PAIR, bool WVEC, int RB, int NW>
 __global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, const uint16_t* T, SmallShape f, const float* ws, float cs, float c,
                                                             const float* row_ce, const float* row_ds, float* loss, float* gs, float* gI, float* gT) {
-  __shared__ float red[NW / 2][64][64];
+  constexpr int ROWS = 32 * RB, AHEAD = RB == 2 ? 3 : 2;
+  __shared__ float red[NW / 2][ROWS][64];
   if (blockIdx.x == 0) {
     small_scalars<NW>(f, c, row_ce, row_ds, loss, gs, &red[0][0][0]);
     return;
   }
-  const int nM = (int)((f.B + 63) / 64), nN = (int)((f.d + 63) / 64), r0 = f.rank * (int)f.b, d = (int)f.d;
+  const int nM = (int)((f.B + ROWS - 1) / ROWS), nN = (int)((f.d + 63) / 64), r0 = f.rank * (int)f.b, d = (int)f.d;
   const int w = blockIdx.x - 1, mt_rel = w / (nN * f.nb), rest = w - mt_rel * nN * f.nb, z = rest / nN;
-  const int mt = (mt_rel + r0 / 64) % nM;               // the longest reductions, those of the own rows, first
-  const int m0 = mt * 64, n0 = (rest % nN) * 64;
-  const int l2 = 2 * (threadIdx.x & 31), up = upper_half() * 8;
+  const int mt = (mt_rel + r0 / ROWS) % nM;             // the longest reductions, those of the own rows, first
+  const int m0 = mt * ROWS, n0 = (rest % nN) * 64;
+  const int l32 = threadIdx.x & 31, l2 = 2 * l32, up = upper_half() * 8;
   const int n = n0 + l2 < d ? n0 + l2 : (d - 1) & ~1, next = n + 1 < d ? 1 : 0;     // columns n, n + 1 of this lane
-  f32x16 acc[2][2];
+  f32x16 acc[RB][2];
   clear(acc);
   // One 16-deep piece of a reduction as it comes from memory: this lane's 8 gradient entries of either row block and its 8 pairs
   // of features.  PART: only the indices below lim exist; the features of the others repeat the last one's, their
   // gradient entries count as 0.
-  struct Raw { f32x8 g[2]; uint32_t q[8]; };
+  struct Raw { f32x8 g[RB]; uint32_t q[8]; };
   auto features = [&](Raw& t, const uint16_t* M, int k, int lim, auto part) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -694,41 +701,43 @@ __global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, c
   };
   auto consume = [&](const Raw& t) {
     const bf16x8 y[2] = {halves(t.q, false), halves(t.q, true)};
-    bf16x8 x[2][3];
+    bf16x8 x[RB][3];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) split3_block(t.g[u], x[u]);
+    for (int u = 0; u < RB; ++u) split3_block(t.g[u], x[u]);
 #pragma unroll
     for (int q = 2; q >= 0; --q)
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < RB; ++u)
 #pragma unroll
         for (int v = 0; v < 2; ++v) acc[u][v] = mfma_bf16(x[u][q], y[v], acc[u][v]);
   };
-  // the pieces of [k0, k1), each fetched two ahead of its use
+  // the pieces of [k0, k1), each fetched AHEAD - 1 before its use
   auto reduce = [&](int K, auto fetch) {
     int k0, k1;
     wave_range16<NW>(K, k0, k1);
     const int full = k0 < k1 ? (k1 - k0) / 16 : 0;
-    Raw t[3];
-    if (full > 0) fetch(t[0], k0, k1, std::false_type{});
-    if (full > 1) fetch(t[1], k0 + 16, k1, std::false_type{});
-    int i = 0;
-    for (; i + 3 <= full; i += 3) {
+    Raw t[AHEAD];
 #pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        if (i + u + 2 < full) fetch(t[(u + 2) % 3], k0 + 16 * (i + u + 2), k1, std::false_type{});
+    for (int u = 0; u < AHEAD - 1; ++u)
+      if (u < full) fetch(t[u], k0 + 16 * u, k1, std::false_type{});
+    int i = 0;
+    for (; i + AHEAD <= full; i += AHEAD) {
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (i + u + AHEAD - 1 < full) fetch(t[(u + AHEAD - 1) % AHEAD], k0 + 16 * (i + u + AHEAD - 1), k1, std::false_type{});
         consume(t[u]);
       }
     }
-    if (i < full) consume(t[0]);
-    if (i + 1 < full) consume(t[1]);
+#pragma unroll
+    for (int u = 0; u < AHEAD - 1; ++u)
+      if (i + u < full) consume(t[u]);
     if (k0 + 16 * full < k1) {
       fetch(t[0], k0 + 16 * full, k1, std::true_type{});
       consume(t[0]);
     }
   };
   {                                                     // key side: G[k][m] down the rank's rows
-    const int m = m0 + l2 < f.B ? m0 + l2 : (int)(f.B - 1) & ~1, mnext = m + 1 < f.B ? 1 : 0;
+    const int m = m0 + RB * l32 < f.B ? m0 + RB * l32 : RB == 2 ? (int)(f.B - 1) & ~1 : (int)f.B - 1, mnext = m + 1 < f.B ? 1 : 0;
     const float* G = ws + (size_t)z * f.b * f.pitch + up * f.pitch + m;
     const uint16_t* X = (z == 0 ? I : T) + (int64_t)(r0 + up) * d + n;
     reduce((int)f.b, [&](Raw& t, int k, int lim, auto part) {
@@ -737,28 +746,29 @@ __global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, c
         const bool in = !decltype(part)::value || k + up + e < lim;
         const float* p = G + (int64_t)(in ? k + e : lim - 1 - up) * f.pitch;
         f32x2 v;
-        if constexpr (WVEC) v = *reinterpret_cast<const f32x2*>(p);     // (what lies in the pitch behind a row feeds no stored entry)
+        if constexpr (RB == 1) v[0] = p[0];
+        else if constexpr (WVEC) v = *reinterpret_cast<const f32x2*>(p);     // (what lies in the pitch behind a row feeds no stored entry)
         else v = f32x2{p[0], p[mnext]};
-        t.g[0][e] = in ? v[0] : 0.f;
-        t.g[1][e] = in ? v[1] : 0.f;
+#pragma unroll
+        for (int u = 0; u < RB; ++u) t.g[u][e] = in ? v[u] : 0.f;
       }
       features(t, X, k, lim, part);
     });
   }
-  if (m0 < r0 + f.b && m0 + 64 > r0) {                  // query side of the own rows: G[m][k] along all rows
+  if (m0 < r0 + f.b && m0 + ROWS > r0) {                // query side of the own rows: G[m][k] along all rows
     const int zq = f.nb == 1 ? 0 : 1 - z;
-    const float* G[2];
-    bool own[2];
+    const float* G[RB];
+    bool own[RB];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t i = m0 + l2 + u - r0;
+    for (int u = 0; u < RB; ++u) {
+      const int64_t i = m0 + RB * l32 + u - r0;
       own[u] = i >= 0 && i < f.b;
       G[u] = ws + (size_t)zq * f.b * f.pitch + (own[u] ? i : 0) * f.pitch + up;
     }
     const uint16_t* Y = (zq == 0 ? T : I) + (int64_t)up * d + n;
     reduce((int)f.B, [&](Raw& t, int k, int lim, auto part) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
+      for (int u = 0; u < RB; ++u) {
         if constexpr (WVEC && !decltype(part)::value) {
           const f32x4 lo = *reinterpret_cast<const f32x4*>(G[u] + k), hi = *reinterpret_cast<const f32x4*>(G[u] + k + 4);
 #pragma unroll
@@ -776,7 +786,7 @@ __global__ __launch_bounds__(64 * NW) void small_grads_bf16(const uint16_t* I, c
     });
   }
   float* out = z == 0 ? gT : gI;
-  join_waves_64<NW>(acc, red, [&](int r, int col, const f32x2& v) {
+  join_waves_64<RB, NW>(acc, red, [&](int r, int col, const f32x2& v) {
     if (m0 + r >= f.B || n0 + col >= d) return;
     float* p = out + (int64_t)(m0 + r) * d + n0 + col;
     if (f.out_pairs) {
@@ -820,10 +830,34 @@ int64_t row_pitch(int64_t b, int64_t B, size_t nb) {
   return lean_bytes(nb, b, padded) > DISCO_STATIC_SCRATCH_BYTES && lean_bytes(nb, b, B) <= DISCO_STATIC_SCRATCH_BYTES ? B : padded;
 }
 
+// bf16 features: tiles of half the rows by twice the waves (32 x 64, 8 waves a similarity tile, 16 a gradient tile), or 64 x 64?  Half as long
+// a chain per wave and twice the workgroups, each with the same launch and the same sum over its waves.  Gradients: for the rank's own rows,
+// whose reduction (b + B) is the longest, if their tiles leave every other compute unit idle, and unless the tiles of the
+// other rows, whose reduction is short, are so many that what they have in common outweighs it.  (us a call, 64 rows / 32; b, N, d: 32, 16, 768
+// 21.2 / 19.5; 464, 1, 500 28.0 / 23.1; 512, 2, 256 34.2 / 27.7; 88, 32, 300 52.5 / 39.9; 968, 2, 200 66.4 / 60.2; 274, 32, 200 140 / 103; own tiles
+// 132 and more: 2056, 2, 77 180 / 209; 2274, 1, 100 107 / 117; 312, 1, 1000 27.3 / 30.2; 684, 2, 512 53.6 / 56.5; 1317, 2, 200 104 / 110; many others: 68, 32, 1024 48.5 / 52.9; 100, 32, 1000 65 / 77;
+// 198, 16, 768 66 / 78; near the line: 178, 32, 1000 two views 99 / 90; 363, 4, 500 47.6 / 45.1; 396, 2, 1000 46.4 / 44.8.)
+bool flat_gradients(int64_t b, int64_t B, int64_t d, int nb) {
+  const int64_t all = nb * (int64_t)cdiv(B, 64) * cdiv(d, 64), own = nb * (int64_t)cdiv(b, 64) * cdiv(d, 64);
+  return own <= 128 && (all <= 256 || 3.3 * all < b + B);
+}
+// Similarities: while 64 x 64 tiles are fewer than half the compute units, or two to a unit where the width is few pieces.  (133, 2, 1000 25.0 / 21.6;
+// 73, 4, 1024 23.7 / 20.8; 180, 4, 500 27.1 / 25.5; 96, 4, 192 19.0 / 17.5; 287, 8, 256 54.1 / 53.0; but 365, 2, 1000 42.7 / 43.4; 396, 2, 1000
+// 46.4 / 48.6; 684, 2, 512 53.6 / 56.6.)
+bool flat_similarities(int64_t b, int64_t B, int64_t d, int nb) {
+  const int64_t all = nb * (int64_t)cdiv(b, 64) * cdiv(B, 64);
+  return all <= 128 || (all <= 512 && d <= 256);
+}
+
 // Estimated time of the small kernels: launches, products at the rate they reach (fp32 features 85 TFLOP/s, bf16 ones 200; less
 // where rows are not whole pieces), and the longest reduction that the waves of one workgroup walk (a tile of the rank's
-// own gradient rows).
-double small_rate_us(int64_t b, int64_t B, int64_t d, int dtype, int nb) {
+// own gradient rows).  bf16 features on gradient tiles of 32 rows: a fit (6 % rms over 40 calls of 13 to 74 us of whole 64-column tiles, within
+// 0.92 to 1.2 of most others').
+double small_rate_us(int64_t b, int64_t B, int64_t d, int dtype, int nb, bool flat) {
+  if (flat) {
+    const double us = (4.5 + 0.0118 * d) * 1e-6 * nb * b * B + 0.004 * (b + B) + 0.0193 * nb * cdiv(B, 64) * cdiv(d, 64);
+    return 12.3 + us * (d % 2 ? 1.7 : d % 64 ? 1.2 : 1.0);
+  }
   if (dtype == DISCO_BF16) return 14.0 + 0.5 * nb * (double)b * B * d * (d % 2 ? 1.5 : 1.0) * 12.0 / 200e6 + 1.15 * (b + B) / 128;
   const double macs = 0.5 * nb * (double)b * B * d, slow = d % 4 ? 1.9 : 1.0;
   const bool big = (double)nb * cdiv(B, 64) * cdiv(d, 64) >= 256;
@@ -860,7 +894,9 @@ double small_walk_us(int64_t b, int64_t B, int64_t d, int nb) {
 // that move at most 0.98 times, mostly 0.5 to 0.75, and of 297 drawn ones none takes longer, half 0.66 of the time or less); the path by
 // name's (lean) because its split kernels take the rows in chunks.
 double small_us(int64_t b, int64_t B, int64_t d, int dtype, int nb, bool lean) {
-  const double us = small_rate_us(b, B, d, dtype, nb);
+  double us = small_rate_us(b, B, d, dtype, nb, false);
+  // (bf16 calls that 32-row tiles move here from the split kernels: with an allowance for the two estimates)
+  if (dtype == DISCO_BF16 && !lean && flat_gradients(b, B, d, nb)) us = std::min(us, 1.15 * small_rate_us(b, B, d, dtype, nb, true));
   return lean || dtype == DISCO_BF16 || d >= 128 || b < 32 ? us : std::max(us, small_walk_us(b, B, d, nb));
 }
 
@@ -908,19 +944,29 @@ void small_run(const Problem& p) {
   if (p.dtype == DISCO_BF16) {
     const uint16_t* I = static_cast<const uint16_t*>(p.I);
     const uint16_t* T = static_cast<const uint16_t*>(p.T);
-    auto sim = [&](auto kernel) { kernel<<<sim_grid(64), 256, 0, p.stream>>>(I, T, f, W); };
-    auto grads = [&](auto kernel) { kernel<<<grad_grid(64), 512, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT); };
-    auto similarity = [&](auto streamed, auto plain) {
-      if (stream_similarities(matrix_bytes(nb, p.b, f.pitch))) sim(streamed);
-      else sim(plain);
+    const bool flat_sim = flat_similarities(p.b, p.B, p.d, nb), flat_grads = flat_gradients(p.b, p.B, p.d, nb);
+    auto sim = [&](auto kernel, int rows) { kernel<<<dim3(cdiv(p.B, 64), cdiv(p.b, rows), nb), rows == 64 ? 256 : 512, 0, p.stream>>>(I, T, f, W); };
+    auto similarity = [&](auto piece) {
+      constexpr int P = decltype(piece)::value;
+      if (flat_sim) sim(small_similarity_bf16<P, 1, 8, true>, 32);
+      else if (stream_similarities(matrix_bytes(nb, p.b, f.pitch))) sim(small_similarity_bf16<P, 2, 4, true>, 64);
+      else sim(small_similarity_bf16<P, 2, 4, false>, 64);
     };
-    if (p.d % 8 == 0 && address % 16 == 0) similarity(small_similarity_bf16<8, 4, true>, small_similarity_bf16<8, 4, false>);
-    else if (p.d % 4 == 0 && address % 8 == 0) similarity(small_similarity_bf16<4, 4, true>, small_similarity_bf16<4, 4, false>);
-    else similarity(small_similarity_bf16<1, 4, true>, small_similarity_bf16<1, 4, false>);
+    if (p.d % 8 == 0 && address % 16 == 0) similarity(std::integral_constant<int, 8>{});
+    else if (p.d % 4 == 0 && address % 8 == 0) similarity(std::integral_constant<int, 4>{});
+    else similarity(std::integral_constant<int, 1>{});
     softmax();
+    auto go = [&](auto kernel, int rows) {
+      kernel<<<dim3(1 + nb * cdiv(p.B, rows) * cdiv(p.d, 64)), rows == 64 ? 512 : 1024, 0, p.stream>>>(I, T, f, W, cs, c, row_ce, row_ds, p.loss, p.gs, p.gI, p.gT);
+    };
+    auto grads = [&](auto pair, auto vec) {
+      constexpr bool PR = decltype(pair)::value, VC = decltype(vec)::value;
+      if (flat_grads) go(small_grads_bf16<PR, VC, 1, 16>, 32);
+      else go(small_grads_bf16<PR, VC, 2, 8>, 64);
+    };
     const bool pair = p.d % 2 == 0 && address % 4 == 0;
-    if (pair) { if (wvec) grads(small_grads_bf16<true, true, 8>); else grads(small_grads_bf16<true, false, 8>); }
-    else { if (wvec) grads(small_grads_bf16<false, true, 8>); else grads(small_grads_bf16<false, false, 8>); }
+    if (pair) { if (wvec) grads(std::true_type{}, std::true_type{}); else grads(std::true_type{}, std::false_type{}); }
+    else { if (wvec) grads(std::false_type{}, std::true_type{}); else grads(std::false_type{}, std::false_type{}); }
   } else {
     const float* I = static_cast<const float*>(p.I);
     const float* T = static_cast<const float*>(p.T);
@@ -969,11 +1015,16 @@ void naive_describe(int64_t B, int64_t d, int32_t N, int dtype, int variant, boo
 // Is a call that the bf16 tile kernels take faster on the small ones?  Few tiles leave those kernels with their seven launches,
 // about 21 us on top of the tiles' estimate whatever the shape; the small ones are three.  27 are allowed: within those 6 us a call
 // keeps the small kernels' fp32 numerators, whose gradients are 1e-5 and more of their 2-norm nearer.  (Measured, us, tiles / small,
-// bf16: B = 256, N = 1, d = 128: 29 / 18; 512, 2, 256: 29 / 23; 1024, 4, 512: 34 / 31; 1024, 2, 256: 33 / 35; 1024, 4, 1024: 44 / 36; 2048, 16,
-// 512: 35 / 41; 1024, 1, 512: 43 / 48; 2048, 4, 256: 35 / 51; 4096, 32, 512: 38 / 65.)
+// bf16: B = 256, N = 1, d = 128: 29 / 14; 512, 2, 256: 29 / 17; 1024, 4, 512: 34 / 26; 1024, 2, 256: 33 / 27; 1024, 4, 1024: 44 / 33; 2048, 16,
+// 512: 35 / 41; 2048, 4, 256: 35 / 51; 4096, 32, 512: 38 / 65.)
+// That line is of 64-row tiles; where the gradients have 32-row ones, a call estimated 5 us faster than on the tile kernels moves too (417, 4, 128
+// two views 33.6 / 29.0; 274, 8, 256 40.8 / 37.5).
 bool small_beats_tiles(int64_t B, int64_t d, int32_t N, int variant) {
-  const double us = small_rate_us(B / N, B, d, DISCO_BF16, loss_blocks(variant));
-  return us < 60.0 && us < mfma_stored_estimate_us(B, d, N, variant) + 27.0;
+  const int nb = loss_blocks(variant);
+  const int64_t b = B / N;
+  const double tiles = mfma_stored_estimate_us(B, d, N, variant), us = small_rate_us(b, B, d, DISCO_BF16, nb, false);
+  if (us < 60.0 && us < tiles + 27.0) return true;
+  return flat_gradients(b, B, d, nb) && small_rate_us(b, B, d, DISCO_BF16, nb, true) < tiles + 16.0;
 }
 
 int naive_run(const Problem& p) {
