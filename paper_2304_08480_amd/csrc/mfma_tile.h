@@ -65,6 +65,8 @@ namespace tile {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(8))) _Float16 half8;
+typedef __attribute__((ext_vector_type(4))) _Float16 half4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -94,12 +96,29 @@ using Acc = f32x4[NFA][4];
 // 2 x 2) come to 2^-24 of the values' own product at most and to 2^-27.5 root mean square.
 template <int PA, int PB, bool SWEEPS_ = false>
 struct Planes {
-  static constexpr bool SWEEPS = SWEEPS_;
+  static constexpr bool HALF = false, SWEEPS = SWEEPS_;
   static_assert((PA == 1 && PB == 1) || (PA == 3 && (PB == 1 || PB == 3)));
   static constexpr int N = PA == 1 ? 1 : PB == 1 ? 3 : 6;
   // two bits per product
   static constexpr uint32_t A = PA == 1 ? 0u : PB == 1 ? (2u | 1u << 2 | 0u << 4) : (2u | 0u << 2 | 1u << 4 | 1u << 6 | 0u << 8 | 0u << 10);
   static constexpr uint32_t B = PB == 1 ? 0u : (0u | 2u << 2 | 1u << 4 | 0u << 6 | 1u << 8 | 0u << 10);
+};
+
+// The same of operands kept in fp16 planes (split_kernels.hip says what each plane holds): logits of NP planes, all four products of two, and
+// gradients, whose last product has the leading planes of both sides.
+template <int NP>
+struct HalfLogits {
+  static_assert(NP == 1 || NP == 2);
+  static constexpr bool HALF = true, SWEEPS = NP == 2;
+  static constexpr int N = NP * NP;
+  static constexpr uint32_t A = NP == 1 ? 0u : (1u | 1u << 2), B = NP == 1 ? 0u : (1u | 1u << 4);
+};
+template <int NP>
+struct HalfGrads {
+  static_assert(NP == 1 || NP == 2);
+  static constexpr bool HALF = true, SWEEPS = true;
+  static constexpr int N = NP + 1;
+  static constexpr uint32_t A = 1u, B = NP == 1 ? 1u : (2u | 1u << 2);
 };
 
 enum { FMT_K = 0, FMT_R = 1, FMT_KA = 2, FMT_RA = 3 };
@@ -264,27 +283,28 @@ __device__ __forceinline__ void read_b(FragsB& b, const Operand<T, FMT, 4>& op, 
   b.f[J + 1] = read_frag<KS, J + 1>(op, tile);
 }
 // acc (+)= a * b; FIRST: = (the matrix instruction takes a literal zero for its addend: no registers are cleared)
-template <bool FIRST>
+template <bool FIRST, bool HALF>
 __device__ __forceinline__ void mfma1(f32x4& c, const u32x4& a, const u32x4& b) {
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), FIRST ? zero : c, 0, 0, 0);
+  if constexpr (HALF) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), FIRST ? zero : c, 0, 0, 0);
+  else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), FIRST ? zero : c, 0, 0, 0);
 }
 // row I of the sub-step's 16 x 16 products, every other one backwards: only one operand changes from one to the next
-template <bool FIRST, int H, int I, int NH>
+template <bool FIRST, bool HALF, int H, int I, int NH>
 __device__ __forceinline__ void mfma_row(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int j = I & 1 ? 3 - q : q;
-    mfma1<FIRST>(acc[H * NH + I][j], a.f[I], b.f[j]);
+    mfma1<FIRST, HALF>(acc[H * NH + I][j], a.f[I], b.f[j]);
   }
 }
-template <bool FIRST, int H, int NH>
+template <bool FIRST, bool HALF, int H, int NH>
 __device__ __forceinline__ void mfma_block(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc) {
-  mfma_row<FIRST, H, 0>(a, b, acc);
-  mfma_row<FIRST, H, 1>(a, b, acc);
+  mfma_row<FIRST, HALF, H, 0>(a, b, acc);
+  mfma_row<FIRST, HALF, H, 1>(a, b, acc);
   if constexpr (NH == 4) {
-    mfma_row<FIRST, H, 2>(a, b, acc);
-    mfma_row<FIRST, H, 3>(a, b, acc);
+    mfma_row<FIRST, HALF, H, 2>(a, b, acc);
+    mfma_row<FIRST, HALF, H, 3>(a, b, acc);
   }
 }
 // the 16 (8) MFMAs of a sub-step with this wave's 8 load instructions of one unit interleaved (two after each of the
@@ -292,20 +312,20 @@ __device__ __forceinline__ void mfma_block(const FragsA<NH>& a, const FragsB& b,
 // sub-step at raised priority: it then wins the SIMD's issue slots from the other wave group's wave, its loads
 // leave early in the K-step and have the longest time to land (query-side GEMM 6 % faster, logit kernel 1 %;
 // raising the priority of every MFMA block instead is 1-4 % slower everywhere)
-template <bool FIRST, int H, int T, int FMT, int NFRAG, int NH>
+template <bool FIRST, bool HALF, int H, int T, int FMT, int NFRAG, int NH>
 __device__ __forceinline__ void mfma_block_loads(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc, const Operand<T, FMT, NFRAG>& op,
                                                  const uint16_t* base, char* lds) {
   const __amdgpu_buffer_rsrc_t from = buffer_at(base);
 #define DISCO_LD(n) op.load(n, from, lds)
-#define DISCO_MM(i, j) mfma1<FIRST>(acc[H * NH + i][j], a.f[i], b.f[j])
+#define DISCO_MM(i, j) mfma1<FIRST, HALF>(acc[H * NH + i][j], a.f[i], b.f[j])
   __builtin_amdgcn_s_setprio(1);
   DISCO_MM(0, 0); DISCO_MM(0, 1); DISCO_LD(0); DISCO_LD(1);
   DISCO_MM(0, 2); DISCO_MM(0, 3); DISCO_LD(2); DISCO_LD(3);
   DISCO_MM(1, 3); DISCO_MM(1, 2); DISCO_LD(4); DISCO_LD(5);
   DISCO_MM(1, 1); DISCO_MM(1, 0); DISCO_LD(6); DISCO_LD(7);
   if constexpr (NH == 4) {
-    mfma_row<FIRST, H, 2>(a, b, acc);
-    mfma_row<FIRST, H, 3>(a, b, acc);
+    mfma_row<FIRST, HALF, H, 2>(a, b, acc);
+    mfma_row<FIRST, HALF, H, 3>(a, b, acc);
   }
   __builtin_amdgcn_s_setprio(0);
 #undef DISCO_LD
@@ -405,21 +425,21 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_a<0, 1>(a1, oa, ta);                                                                                              \
     read_b<1, 0>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    mfma_block<FIRST, 0>(a0, b0, acc);                                                                                     \
+    mfma_block<FIRST, PS::HALF, 0>(a0, b0, acc);                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a1, b0);                                                                                                    \
     /* sub-step 1 */                                                                                                       \
     read_a<1, 0>(a0, oa, ta);                                                                                              \
     read_b<1, 2>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 0 && LOADS) mfma_block_loads<FIRST, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
-    else mfma_block<FIRST, 1>(a1, b0, acc);                                                                                \
+    if (GROUP == 0 && LOADS) mfma_block_loads<FIRST, PS::HALF, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
+    else mfma_block<FIRST, PS::HALF, 1>(a1, b0, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b1);                                                                                                    \
     /* sub-step 2 */                                                                                                       \
     read_a<1, 1>(a1, oa, ta);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    mfma_block<false, 0>(a0, b1, acc);                                                                                     \
+    mfma_block<false, PS::HALF, 0>(a0, b1, acc);                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     if (GROUP == 0 && LOADS) wait_vmcnt<NLD>(); else wait_vmcnt<0>();                                                               \
     wait_frags(a1, b1);                                                                                                    \
@@ -430,8 +450,8 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_b<0, 0>(b0, ob, tnb);                                                                                             \
     read_b<0, 2>(b0, ob, tnb);                                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 1 && LOADS) mfma_block_loads<false, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
-    else mfma_block<false, 1>(a1, b1, acc);                                                                                \
+    if (GROUP == 1 && LOADS) mfma_block_loads<false, PS::HALF, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
+    else mfma_block<false, PS::HALF, 1>(a1, b1, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b0);                                                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \

@@ -1,21 +1,27 @@
-// The fp32 path's large calls: its four contractions on the bf16 matrix instruction, with every fp32 operand split into three
-// bf16 planes that add up to it exactly (8 significand bits each).  A product of two fp32 operands is six plane products
-// (Planes<3, 3> of mfma_tile.h), one of an fp32 operand and a bf16 one three, of two bf16 ones one: all of them exact in the
-// matrix instruction and summed in fp32.  The six leave out 2^-27.5 of a product (root mean square; the worst case is 2^-24),
-// less than the fp32 instruction's rounding of its sum adds per term.
+// The fp32 path's large calls: its four contractions on the 16-bit matrix instructions, with every fp32 operand split into planes
+// whose products are exact in the instruction and summed in fp32.  Two forms:
+//   fp16   two planes of 11 significand bits each.  A logit is four plane products, a gradient entry three (bf16 features, one plane: one
+//          and two).  What the planes leave out of a value is 0 three times in four, else 2^-24 to 2^-23 of it; the product left out of a gradient is
+//          2^-24.6 (root mean square).  fp16's range is what features have to keep to (k_feature_halves tests them on the device).
+//   bf16   three planes of 8 bits, which add up to the value exactly over nearly all of fp32's range: six plane products (three against bf16
+//          features; one between them).  The six leave out 2^-27.5 of a product (root mean square; the worst case is 2^-24).  For
+//          features that the fp16 form cannot hold, and for calls too small to gain from it.
+// One product over the whole reduction follows the other, the smallest first (SWEEPS), so that only the last one rounds at the size of
+// the result: that is what decides the errors, and why the fp16 form's are no larger although its planes hold a bit less.  Against 64 bits, fp32
+// features, 2-norm of the gradients, fp16 over bf16 planes (logits in sweeps, gradients piece by piece), mean of 61 calls drawn over sizes, widths and
+// positives: 0.81 at s = 1/0.07, 0.96 at 30, 0.93 at 100; B = 8192, N = 8, d = 512 6.04e-7 -> 5.6e-7; 12288, 4, 256 4.9e-7 -> 2.7e-7.
+// (Gradients piece by piece on fp16 planes: 1.0 in the mean, but 1.33 at B = 4096, N = 16, d = 64.)
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
-// (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); the tile loop of mfma_tile.h runs six
-// bf16 products at 1.2 PFLOP/s, 200 TFLOP/s of fp32 work.  Measured (us a call, fp32 products before / these): fp32
-// features B = 8192, N = 8, d = 512: 799 / 290 (logits 85, softmax 34, both gradient sides 155-165); 32768, 8, 512: 9000 / 4225;
-// bf16 features of width 1000, B = 8192, N = 8: 1881 / 279; 300, 8192, 32: 1041 / 74.  Errors against 64 bits fall as well (gradients
-// at 8192, 8, 512: 1.8e-6 -> 0.6e-6 in 2-norm): the matrix instruction rounds its sum less often than per 2 terms, and the
-// logits add the small plane products first (SWEEPS, which costs 2-5 % of a call and takes the bias of 2e-7 out of the loss).
+// (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); six bf16 products at 1.2 PFLOP/s are 200 TFLOP/s
+// of fp32 work.  Measured, us a call, bf16 / fp16 planes: fp32 features B = 8192, N = 8, d = 512: 290 / 210 (logits 74, softmax 36, both
+// gradient sides 112); 12288, 4, 256: 806 / 561; 10416, 8, 1024: 1029 / 691; 4096, 16, 512: 83 / 70; bf16 features 12288, 8, 100: 220 / 181;
+// 110 drawn fp32 calls: 0.78 in the median.
 //
 // Per block (X: the rank's rows, Y: all rows):
-//   planes    features -> bf16 planes, rows padded with zeros to whole tiles, columns to whole 64-deep K-steps
+//   planes    features -> planes, rows padded with zeros to whole tiles, columns to whole 64-deep K-steps
 //   logits    S = X Y^T in fp32 (b x B)
-//   softmax   row by row against the row's true maximum: loss terms, G = softmax - onehot as three planes
+//   softmax   row by row against the row's true maximum: loss terms, G = softmax - onehot as planes
 //   grads     gY = cs G^T X (key side) and the split-K partial sums of G Y (query side), one launch
 //   finalize  partial sums into the gradients, loss and d/ds
 // The rows are taken in chunks where the whole would need more memory than the fp32 blocks of the small kernels do.
@@ -27,11 +33,19 @@ namespace {
 
 using namespace tile;
 
+// Written on the device by k_feature_halves and k_feature_planes: in which form the call's features and gradient entries are kept.
+struct HalfHead {
+  uint32_t half;         // 1: fp16 planes, 0: bf16 planes
+  float unscale[2];      // what undoes the power of two that the features of I (of T) are multiplied with
+};
+constexpr int HALF_FLAGS = 1024;                         // workgroups of k_feature_halves at most, a flag each
+constexpr float G_SCALE = 0x1p15f, REST_SCALE = 0x1p11f; // fp16 planes of a gradient entry: see store_unit_halves
+
 struct SplitBlock {
   const uint16_t* X;     // planes of the rank's rows: the first of the chunk
   const uint16_t* Y;     // planes of all rows
   float* S;              // bp x Bp logits without the multiplier
-  uint16_t* G;           // three planes, bp x Bp each
+  uint16_t* G;           // three (fp16: two) planes, bp x Bp each
   float* part;           // splitk x bp x dp query-side sums
   float* kpart;          // key_splits x Bp x dp key-side sums (only where they do not go straight to gk)
   float* gq;             // query-side destination (the whole B x d matrix)
@@ -51,6 +65,7 @@ struct SplitArgs {
   int nMq, nMk, nN;      // gradient tiles: query rows, key rows, columns
   int splitk, ktps, key_splits, key_ktps;  // splits of the two reductions and their length in 64-deep pieces
   int q_wgs;
+  const HalfHead* head;  // null: bf16 planes
 };
 
 // v = p[0] + p[1] + p[2], to the last bit while the last plane stays above the smallest bf16 (a value above about 2^-109).  (A value whose leading plane
@@ -100,13 +115,141 @@ __device__ __forceinline__ void store_unit_planes(uint16_t* dst, int64_t plane, 
   }
 }
 
+// The fp16 planes of four gradient entries (values of [-1, 1] or NaN): g 2^15 = h + l 2^-11, h and l of 11 significand bits each, so that
+// h keeps all of them down to |g| = 2^-29 and l down to 2^-28.
+__device__ __forceinline__ void store_unit_halves(uint16_t* dst, int64_t plane, const f32x4& v) {
+  half4 h, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float g = v[e] * G_SCALE;
+    h[e] = (_Float16)g;
+    l[e] = (_Float16)((g - (float)h[e]) * REST_SCALE);
+  }
+  *reinterpret_cast<half4*>(dst) = h;
+  *reinterpret_cast<half4*>(dst + plane) = l;
+}
+
+// Four features from column k on of a row that starts at p, as fp32; 0 from column d on.
+template <int DT, bool VEC>
+__device__ __forceinline__ f32x4 load_features(const void* src, int64_t at, int64_t k, int64_t d) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (DT == DISCO_BF16) {
+    const uint16_t* p = static_cast<const uint16_t*>(src) + at + k;
+    if constexpr (VEC) {
+      if (k < d) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(e & 1 ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < d) v[e] = bf16_value(p[e]);
+    }
+  } else {
+    const float* p = static_cast<const float*>(src) + at + k;
+    if constexpr (VEC) {
+      if (k < d) v = *reinterpret_cast<const f32x4*>(p);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < d) v[e] = p[e];
+    }
+  }
+  return v;
+}
+
+// Features as fp16 planes.  A matrix is multiplied with the power of two that brings the largest entry of its first row into [2^10, 2^11);
+// an entry x of the product is h + l, 11 significand bits each (bf16 features: h alone), and h 2^-11 is kept as well, the partner
+// of the gradient entries' second plane, which is 2^11 times what it stands for.  That loses nothing that counts where every entry is
+// under 2^15.9 and every row's largest is 0 or at least 2^3: the planes end at 2^-24, 2^-27 of that.  A workgroup that
+// sees anything else (rows whose norms differ by more than 2^5 to 2^7, what is not finite, a first row of zeros) raises its flag, and
+// k_feature_planes replaces the planes of the whole call by bf16 ones.  One wave (LPR = 64) or 16 lanes a row.
+template <int DT, bool VEC, int LPR>
+__global__ __launch_bounds__(256) void k_feature_halves(const void* I, const void* T, int64_t B, int64_t d, int64_t rows, int64_t dp, int mats,
+                                                        uint16_t* Ip, uint16_t* Tp, HalfHead* head, uint32_t* flags) {
+  __shared__ float first[2][4];
+  float m[2] = {0.f, 0.f};
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+    if (z < mats) {
+      for (int64_t k = threadIdx.x * 4; k < d; k += 1024) {
+        const f32x4 v = load_features<DT, VEC>(z ? T : I, 0, k, d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[z] = fmaxf(m[z], fabsf(v[e]));
+      }
+      m[z] = wave_reduce(m[z], [](float a, float b) { return fmaxf(a, b); });
+      if ((threadIdx.x & 63) == 0) first[z][threadIdx.x >> 6] = m[z];
+    }
+  __syncthreads();
+  int e[2] = {0, 0};
+  bool bad = false;
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+    if (z < mats) {
+      const float top = fmaxf(fmaxf(first[z][0], first[z][1]), fmaxf(first[z][2], first[z][3]));
+      e[z] = 137 - (int)(__float_as_uint(top) >> 23);                // 10 - exponent; the scales below stay far from fp32's ends
+      bad = bad || e[z] < -80 || e[z] > 80;
+    }
+  const int both = e[0] + e[mats - 1];
+  bad = bad || both < -120 || both > 120;
+  if (bad) e[0] = e[1] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) head->unscale[threadIdx.x] = __uint_as_float((uint32_t)(127 - (threadIdx.x ? e[1] : e[0])) << 23);
+  const int64_t plane = rows * dp, step = (int64_t)gridDim.x * (256 / LPR);
+  const int lane = threadIdx.x % LPR;
+  for (int64_t w = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; w < mats * rows; w += step) {
+    const bool second = w >= rows;
+    const int64_t row = second ? w - rows : w;
+    const float scale = __uint_as_float((uint32_t)(127 + (second ? e[1] : e[0])) << 23);
+    uint16_t* dst = (second ? Tp : Ip) + row * dp;
+    float top = 0.f;
+    for (int64_t k = lane * 4; k < dp; k += LPR * 4) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (row < B) v = load_features<DT, VEC>(second ? T : I, row * d, k, d);
+      half4 h, l, low;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float x = v[c] * scale, size = fabsf(x);
+        bad = bad || !(size < 61000.f);
+        top = fmaxf(top, size);
+        h[c] = (_Float16)x;
+        l[c] = (_Float16)(x - (float)h[c]);
+        low[c] = (_Float16)((float)h[c] * (1.f / REST_SCALE));
+      }
+      *reinterpret_cast<half4*>(dst + k) = h;
+      if constexpr (DT == DISCO_F32) *reinterpret_cast<half4*>(dst + plane + k) = l;
+      *reinterpret_cast<half4*>(dst + (DT == DISCO_F32 ? 2 : 1) * plane + k) = low;
+    }
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    bad = bad || (top > 0.f && top < 8.f);
+  }
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) flags[blockIdx.x] = any;
+}
+
 // Feature planes of I (z = 0) and T: rows x dp each, zero from row B and from column d on.  VEC: whole 16-byte (bf16: 8-byte)
 // pieces of a row can be read at once.  mats: 1 for the two-view loss, whose matrices are one.  Four columns per thread,
-// grid-stride.
+// grid-stride.  head: the call's features are fp16 planes unless a flag of k_feature_halves is raised; decides that for the kernels that
+// follow, and is done if none is.
 template <int DT, bool VEC>
 __global__ __launch_bounds__(256) void k_feature_planes(const void* I, const void* T, int64_t B, int64_t d, int64_t rows, int64_t dp,
                                                         int mats, uint16_t* Ip,
-                                                        uint16_t* Tp) {
+                                                        uint16_t* Tp, HalfHead* head, const uint32_t* flags, int nflags) {
+  if (head) {
+    uint32_t f[HALF_FLAGS / 256];
+#pragma unroll
+    for (int u = 0; u < HALF_FLAGS / 256; ++u) {
+      const int i = threadIdx.x + u * 256;
+      f[u] = i < nflags ? flags[i] : 0u;
+    }
+    uint32_t any = 0u;
+#pragma unroll
+    for (int u = 0; u < HALF_FLAGS / 256; ++u) any |= f[u];
+    const bool half = !__syncthreads_or((int)any);
+    if (blockIdx.x == 0 && threadIdx.x == 0) head->half = half;
+    if (half) return;
+  }
   const int64_t cpr = dp >> 2, n = rows * cpr, plane = rows * dp;
   for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < mats * n; c += (int64_t)gridDim.x * 256) {
     const bool second = c >= n;
@@ -155,9 +298,18 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_logits(SplitArgs a, 
   const SplitBlock& p = a.z[z];
   const int64_t i0 = (int64_t)it * T, j0 = (int64_t)jt * T;
   Acc<Cfg<T>::NFA> acc;
-  using PS = Planes<NP, NP, NP == 3>;
-  mainloop<T, FMT_K, FMT_K, false, true, PS>(p.X + i0 * a.dp, a.dp, p.Y + j0 * a.dp, a.dp, (int)(a.dp / BK) * PS::N, smem, acc, T, a.fplane, a.fplane);
-  store_tile_f32<T, false>(acc, smem, p.S + i0 * a.Bp + j0, a.Bp, 1.0f);
+  auto products = [&](auto ps) {
+    using PS = decltype(ps);
+    mainloop<T, FMT_K, FMT_K, false, true, PS>(p.X + i0 * a.dp, a.dp, p.Y + j0 * a.dp, a.dp, (int)(a.dp / BK) * PS::N, smem, acc, T, a.fplane, a.fplane);
+  };
+  float scale = 1.0f;
+  if (a.head && a.head->half) {
+    scale = a.head->unscale[0] * a.head->unscale[a.nb - 1];
+    products(HalfLogits<(NP + 1) / 2>{});
+  } else {
+    products(Planes<NP, NP, NP == 3>{});
+  }
+  store_tile_f32<T, false>(acc, smem, p.S + i0 * a.Bp + j0, a.Bp, scale);
 }
 
 constexpr int SM_THREADS = 512;                          // softmax: threads per row
@@ -174,7 +326,7 @@ __device__ __forceinline__ float workgroup_sum(float v, float* red) {
 }
 
 // One workgroup per row: maximum over the columns that take part, cross-entropy, the row's share of d/ds and the row of
-// G = softmax - onehot as three planes (0 in the padding columns and rows, and in a two-view row's own column).  The off-label
+// G = softmax - onehot as planes (0 in the padding columns and rows, and in a two-view row's own column).  The off-label
 // mass is summed on its own, so that P_label - 1 = -(it) / (total) does not cancel, and d/ds as
 // sum_{j != label} P_ij (S_ij - S_i,label).  The vector ALU bounded it, 96 % busy; without tests on the pieces that hold no special
 // column and with planes cut for values of [-1, 1], memory does (B = 8192, N = 8: 39.7 -> 33.8 us for 167 MB).  KEEP:
@@ -187,10 +339,10 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
   const SplitBlock& p = a.z[blockIdx.y];
   uint16_t* G = p.G + i * a.Bp;
   const int64_t nvec = a.Bp >> 2;
+  const bool half = a.head && a.head->half;
   if (i >= a.b) {
     for (int64_t q = threadIdx.x; q < nvec; q += SM_THREADS)
-#pragma unroll
-      for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x2*>(G + pl * a.gplane + q * 4) = u32x2{0u, 0u};
+      for (int pl = 0; pl < (half ? 2 : 3); ++pl) *reinterpret_cast<u32x2*>(G + pl * a.gplane + q * 4) = u32x2{0u, 0u};
     return;
   }
   const float* S = p.S + i * a.Bp;
@@ -260,7 +412,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
       const float x = KEEP ? v[e] : counts(j + e, marked) ? expf(fmaf(s, v[e], -mx)) : 0.f;
       g[e] = decltype(marked)::value && j + e == lab ? -off * inv : x * inv;
     }
-    store_unit_planes(G + j, a.gplane, g);
+    if (half) store_unit_halves(G + j, a.gplane, g);
+    else store_unit_planes(G + j, a.gplane, g);
   });
   if (threadIdx.x == 0) {
     // ce = log(tot) - (zl - mx); where the label holds most of the mass log1p(off / el) keeps the relative accuracy
@@ -276,8 +429,10 @@ enum { SPLIT_KEY_WRITE = 0, SPLIT_KEY_ADD = 1, SPLIT_KEY_PARTS = 2 };
 template <int T, int NP, int KMODE>
 __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, float cs) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  using PS = Planes<3, NP>;
   Acc<Cfg<T>::NFA> acc;
+  const bool half = a.head && a.head->half;
+  // the sums of matrix m's features in their own units
+  auto unscale = [&](int m) { return half ? a.head->unscale[m] * (1.f / G_SCALE) : 1.0f; };
   if ((int)blockIdx.x < a.q_wgs) {
     const int tiles = a.nMq * a.nN, total = tiles * a.nb * a.splitk;
     int lin;
@@ -288,9 +443,14 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, f
     const int64_t i0 = (int64_t)(tile / a.nN) * T, k0 = (int64_t)(tile % a.nN) * T;
     const int kt0 = ks * a.ktps, left = (int)(a.Bp / BK) - kt0, kts = left < a.ktps ? left : a.ktps;
     const int ncols = a.dp - k0 < T ? (int)(a.dp - k0) : T;
-    mainloop<T, FMT_K, FMT_R, false, true, PS>(p.G + i0 * a.Bp + (int64_t)kt0 * BK, a.Bp, p.Y + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem,
-                                               acc, ncols, a.gplane, a.fplane);
-    store_tile_f32<T, false>(acc, smem, p.part + (int64_t)ks * a.bp * a.dp + i0 * a.dp + k0, a.dp, 1.0f, ncols);
+    auto products = [&](auto ps) {
+      using PS = decltype(ps);
+      mainloop<T, FMT_K, FMT_R, false, true, PS>(p.G + i0 * a.Bp + (int64_t)kt0 * BK, a.Bp, p.Y + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N,
+                                                 smem, acc, ncols, a.gplane, a.fplane);
+    };
+    if (half) products(HalfGrads<(NP + 1) / 2>{});
+    else products(Planes<3, NP>{});
+    store_tile_f32<T, false>(acc, smem, p.part + (int64_t)ks * a.bp * a.dp + i0 * a.dp + k0, a.dp, unscale(a.nb == 1 ? 0 : 1 - slice / a.splitk), ncols);
     return;
   }
   const int tiles = a.nMk * a.nN * a.key_splits, per_block = (tiles + 7) / 8 * 8;
@@ -302,14 +462,19 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, f
   const int64_t j0 = (int64_t)(t2 % a.nMk) * T, k0 = (int64_t)(lin % a.nN) * T;
   const int kt0 = ks * a.key_ktps, left = (int)(a.bp / BK) - kt0, kts = left < a.key_ktps ? left : a.key_ktps;
   const int ncols = a.dp - k0 < T ? (int)(a.dp - k0) : T;
-  mainloop<T, FMT_R, FMT_R, false, true, PS>(p.G + (int64_t)kt0 * BK * a.Bp + j0, a.Bp, p.X + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem, acc,
-                                             ncols, a.gplane, a.fplane);
+  auto products = [&](auto ps) {
+    using PS = decltype(ps);
+    mainloop<T, FMT_R, FMT_R, false, true, PS>(p.G + (int64_t)kt0 * BK * a.Bp + j0, a.Bp, p.X + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem,
+                                               acc, ncols, a.gplane, a.fplane);
+  };
+  if (half) products(HalfGrads<(NP + 1) / 2>{});
+  else products(Planes<3, NP>{});
   if constexpr (KMODE == SPLIT_KEY_PARTS) {
-    store_tile_f32<T, false>(acc, smem, p.kpart + ((int64_t)ks * a.Bp + j0) * a.dp + k0, a.dp, 1.0f, ncols);
+    store_tile_f32<T, false>(acc, smem, p.kpart + ((int64_t)ks * a.Bp + j0) * a.dp + k0, a.dp, unscale(z), ncols);
   } else {                                                           // (d % 4 == 0: a tile's last column piece is whole)
     const int cols = a.d - k0 < T ? (int)(a.d - k0) : T;
     const int64_t rows = a.B - j0;
-    store_tile_f32<T, KMODE == SPLIT_KEY_ADD>(acc, smem, p.gk + j0 * a.d + k0, a.d, cs, cols, rows < T ? (int)rows : T);
+    store_tile_f32<T, KMODE == SPLIT_KEY_ADD>(acc, smem, p.gk + j0 * a.d + k0, a.d, cs * unscale(z), cols, rows < T ? (int)rows : T);
   }
 }
 
@@ -381,34 +546,38 @@ struct SplitPlan {
   int64_t bp, Bp, dp, frows;
   int nMq, nMk, nN, splitk, ktps, key_splits, key_ktps;
   bool parts;            // the key side goes through partial sums
-  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, total;
-  double us;
+  bool half;             // fp16 planes where the features allow them
+  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, off_head, total;
+  double us, exact_us;   // exact_us: of the best plan on bf16 planes
+  int feature_planes(int np) const { return half && np == 1 ? 2 : np; }
 };
 
 int64_t round_up(int64_t v, int64_t u) { return (v + u - 1) / u * u; }
 
 void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
   size_t o = 0;
-  pl.off_planes = o; o += 2 * align_up((size_t)np * pl.frows * pl.dp * 2);
+  pl.off_planes = o; o += 2 * align_up((size_t)pl.feature_planes(np) * pl.frows * pl.dp * 2);
   pl.off_S = o;      o += nb * align_up((size_t)pl.bp * pl.Bp * 4);
   pl.off_G = o;      o += nb * align_up((size_t)3 * pl.bp * pl.Bp * 2);
   pl.off_part = o;   o += nb * align_up((size_t)pl.splitk * pl.bp * pl.dp * 4);
   pl.off_kpart = o;
   if (pl.parts) o += nb * align_up((size_t)pl.key_splits * pl.Bp * pl.dp * 4);
   pl.off_rows = o;   o += 2 * nb * align_up((size_t)b * 4);
+  pl.off_head = o;
+  if (pl.half) o += align_up(sizeof(HalfHead)) + align_up(HALF_FLAGS * sizeof(uint32_t));
   pl.total = o;
 }
 
 // Compares estimated times over tile sizes and splits, for one chunk of rows.  (Rows of the gradients that are not whole
 // 16-byte pieces go through partial sums: the tile store writes such pieces.)
-SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64_t chunk) {
+SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64_t chunk, bool half) {
   static const int Q_SPLITS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
   SplitPlan best;
   best.us = 1e300;
-  const int nl = np == 3 ? 6 : 1, ng = np == 3 ? 6 : 3;
+  const int nl = np == 1 ? 1 : half ? 4 : 6, ng = np == 3 ? (half ? 3 : 6) : half ? 2 : 3;
   for (int T = 128; T <= 256; T += 128) {
     SplitPlan pl;
-    pl.T = T; pl.chunk = chunk;
+    pl.T = T; pl.chunk = chunk; pl.half = half;
     pl.bp = round_up(chunk, T); pl.Bp = round_up(B, T); pl.dp = round_up(d, BK);
     pl.frows = pl.Bp + (chunk < b ? pl.bp : T);                      // a rank's last tile (chunk) may reach past the last row
     pl.nMq = (int)(pl.bp / T); pl.nMk = (int)(pl.Bp / T); pl.nN = (int)((pl.dp + T - 1) / T);
@@ -416,7 +585,7 @@ SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64
     const double lt = (double)nb * pl.nMq * pl.nMk, lrounds = (double)(int64_t)((lt + slots - 1) / slots);
     const double logits = lrounds * ((double)(pl.dp / BK) * nl * step_us(T, lt) + fix);
     const double bytes = (double)nb * pl.bp * pl.Bp;
-    const double base = logits + 20.0 * bytes / BYTES_PER_US + (np * 2 + 4) * 2.0 * pl.frows * pl.dp / BYTES_PER_US;
+    const double base = logits + (half ? 16.0 : 20.0) * bytes / BYTES_PER_US + (pl.feature_planes(np) * 2 + 4) * 2.0 * pl.frows * pl.dp / BYTES_PER_US;
     const int kq = (int)(pl.Bp / BK), kk = (int)(pl.bp / BK);
     for (int sk : Q_SPLITS) {
       if (sk > kq) break;
@@ -478,14 +647,30 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
   const bool fvec = pr.d % 4 == 0 && aligned(pr.I, DT == DISCO_BF16 ? 8 : 16) && aligned(pr.T, DT == DISCO_BF16 ? 8 : 16);
   const bool gvec = pr.d % 4 == 0 && aligned(pr.gI, 16) && aligned(pr.gT, 16);
   uint16_t* planes[2];
-  for (int z = 0; z < 2; ++z) planes[z] = reinterpret_cast<uint16_t*>(ws + pl.off_planes + z * align_up((size_t)NP * pl.frows * pl.dp * 2));
+  for (int z = 0; z < 2; ++z) planes[z] = reinterpret_cast<uint16_t*>(ws + pl.off_planes + z * align_up((size_t)pl.feature_planes(NP) * pl.frows * pl.dp * 2));
+  HalfHead* head = nullptr;
 
   stage_mark(st, 0);
   {
     const int64_t pieces = nb * pl.frows * (pl.dp >> 2);
-    const dim3 grid((unsigned)(pieces < 4096 * 256 ? (pieces + 255) / 256 : 4096));
-    if (fvec) k_feature_planes<DT, true><<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1]);
-    else k_feature_planes<DT, false><<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1]);
+    dim3 grid((unsigned)(pieces < 4096 * 256 ? (pieces + 255) / 256 : 4096));
+    uint32_t* flags = nullptr;
+    int nflags = 0;
+    // (the gradients' scale is a power of two down to 2^-95 times cs, which has to stay a normal number)
+    if (pl.half && (cs == 0.f || fabsf(cs) >= 0x1p-30f)) {
+      head = reinterpret_cast<HalfHead*>(ws + pl.off_head);
+      flags = reinterpret_cast<uint32_t*>(ws + pl.off_head + align_up(sizeof(HalfHead)));
+      const int lanes = pl.dp <= 128 ? 16 : 64;
+      const int64_t groups = (nb * pl.frows * lanes + 255) / 256;
+      nflags = (int)(groups < HALF_FLAGS ? groups : HALF_FLAGS);
+      auto halves = [&](auto kernel) { kernel<<<dim3((unsigned)nflags), 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1], head, flags); };
+      if (fvec) { if (lanes == 16) halves(k_feature_halves<DT, true, 16>); else halves(k_feature_halves<DT, true, 64>); }
+      else { if (lanes == 16) halves(k_feature_halves<DT, false, 16>); else halves(k_feature_halves<DT, false, 64>); }
+      if (grid.x > 256) grid.x = 256;                                // (in nearly every call they have nothing to do)
+    }
+    auto exact = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1], head, flags, nflags); };
+    if (fvec) exact(k_feature_planes<DT, true>);
+    else exact(k_feature_planes<DT, false>);
   }
   for (int64_t r0 = 0; r0 < pr.b; r0 += pl.chunk) {
     const bool last = r0 + pl.chunk >= pr.b, add = pr.accumulate || r0 > 0;
@@ -493,7 +678,7 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
     a.b = last ? pr.b - r0 : pl.chunk; a.bp = pl.bp; a.B = pr.B; a.Bp = pl.Bp; a.d = pr.d; a.dp = pl.dp;
     a.g0 = (int64_t)pr.rank * pr.b + r0; a.r0 = r0;
     a.fplane = pl.frows * pl.dp; a.gplane = pl.bp * pl.Bp;
-    a.nb = nb; a.variant = pr.variant;
+    a.nb = nb; a.variant = pr.variant; a.head = head;
     a.nMq = pl.nMq; a.nMk = pl.nMk; a.nN = pl.nN;
     a.splitk = pl.splitk; a.ktps = pl.ktps; a.key_splits = pl.key_splits; a.key_ktps = pl.key_ktps;
     a.q_wgs = (nb * a.nMq * a.nN * a.splitk + 7) / 8 * 8;
@@ -534,13 +719,24 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
   return hipGetLastError() == hipSuccess ? DISCO_OK : DISCO_ERR_HIP;
 }
 
+// fp16 planes are one more launch and one more plane of the features than their products read as leading ones, and the estimates overrate
+// short calls' products: by how much their plan has to be the shorter one.  (us a call, bf16 / fp16 planes, by the estimates' difference: fp32 features 7.6: 47.9 / 46.8;
+// 11 51.0 / 48.0; 12 51.1 / 50.6; 14 57.1 / 52.2; bf16 features 6.0: 54.4 / 60.2; 10 59.3 / 60.5; 12 76.0 / 77.9; 14.5 58.5 / 60.4; 16.4 98.8 / 96.6; 19 84.0 / 79.6;
+// 25 94.0 / 90.0.)
+double half_allowance_us(int np) { return np == 3 ? 6.0 : 16.0; }
+
 // The plan whose rows are taken in as few chunks as keep the workspace within `limit` (0 bytes in `total`: there is none).
 SplitPlan compare_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit) {
   const int np = dtype == DISCO_BF16 ? 1 : 3;
   for (int64_t chunks = 1;; chunks *= 2) {
     const int64_t chunk = chunks == 1 ? b : round_up((b + chunks - 1) / chunks, 256);
-    SplitPlan pl = make_split_plan(B, d, b, nb, np, chunk);
-    if (pl.total <= limit) return pl;
+    SplitPlan pl = make_split_plan(B, d, b, nb, np, chunk, false);
+    pl.exact_us = pl.us;
+    if (pl.total <= limit) {
+      SplitPlan hp = make_split_plan(B, d, b, nb, np, chunk, true);
+      hp.exact_us = pl.us;
+      return hp.total <= limit && hp.us + half_allowance_us(np) < pl.us ? hp : pl;
+    }
     if (chunk <= 256) { pl.total = 0; return pl; }
   }
 }
@@ -563,7 +759,7 @@ double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, siz
   *bytes = pl.total;
   // (the model ranks plans; its sum of the parts is this much more than what a call takes: 402 against 313 us at B = 8192,
   // N = 8, d = 512, 113 against 87 at 4096, 16, 512, 43 against 33 at 2048, 16, d = 200 in bf16)
-  return 0.77 * pl.us * (double)((b + pl.chunk - 1) / pl.chunk);
+  return 0.77 * pl.exact_us * (double)((b + pl.chunk - 1) / pl.chunk);
 }
 
 bool split_raise_lds() { return raise_lds<128, 1>() && raise_lds<128, 3>() && raise_lds<256, 1>() && raise_lds<256, 3>(); }
