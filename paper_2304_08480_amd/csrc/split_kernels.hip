@@ -14,8 +14,8 @@
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
 // (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); six bf16 products at 1.2 PFLOP/s are 200 TFLOP/s
-// of fp32 work.  Measured, us a call, bf16 / fp16 planes: fp32 features B = 8192, N = 8, d = 512: 290 / 210 (logits 74, softmax 36, both
-// gradient sides 112); 12288, 4, 256: 806 / 561; 10416, 8, 1024: 1029 / 691; 4096, 16, 512: 83 / 70; bf16 features 12288, 8, 100: 220 / 181;
+// of fp32 work.  Measured, us a call, bf16 / fp16 planes: fp32 features B = 8192, N = 8, d = 512: 290 / 210, now 201 (logits 68, softmax 28, both
+// gradient sides 102); 12288, 4, 256: 806 / 561; 10416, 8, 1024: 1029 / 691; 4096, 16, 512: 83 / 70; bf16 features 12288, 8, 100: 220 / 181;
 // 110 drawn fp32 calls: 0.78 in the median.
 //
 // Per block (X: the rank's rows, Y: all rows):
@@ -115,17 +115,21 @@ __device__ __forceinline__ void store_unit_planes(uint16_t* dst, int64_t plane, 
   }
 }
 
-// The fp16 planes of four gradient entries (values of [-1, 1] or NaN): g 2^15 = h + l 2^-11, h and l of 11 significand bits each, so that
-// h keeps all of them down to |g| = 2^-29 and l down to 2^-28.
-__device__ __forceinline__ void store_unit_halves(uint16_t* dst, int64_t plane, const f32x4& v) {
+// The fp16 planes of four gradient entries x m / 2^15 (values of [-1, 1] or NaN): g 2^15 = h + l 2^-11, h and l of 11 significand bits each, so
+// that h keeps all of them down to |g| = 2^-29 and l down to 2^-28.  (x m 2^11 is rounded as x m is, so the fused product-sum below is exact; it
+// and the conversion are one instruction.  h passes through an empty asm statement because the compiler would otherwise form the h
+// that l is taken from a second time, by an instruction that rounds x m once where the stored one is rounded twice.)
+__device__ __forceinline__ void store_unit_halves(uint16_t* dst, int64_t plane, const f32x4& x, float m) {
+  const float m2 = m * REST_SCALE;
   half4 h, l;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float g = v[e] * G_SCALE;
-    h[e] = (_Float16)g;
-    l[e] = (_Float16)((g - (float)h[e]) * REST_SCALE);
-  }
-  *reinterpret_cast<half4*>(dst) = h;
+  for (int e = 0; e < 4; ++e) h[e] = (_Float16)(x[e] * m);
+  u32x2 w = __builtin_bit_cast(u32x2, h);
+  asm("" : "+v"(w));
+  h = __builtin_bit_cast(half4, w);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) l[e] = (_Float16)fmaf((float)h[e], -REST_SCALE, x[e] * m2);
+  *reinterpret_cast<u32x2*>(dst) = w;
   *reinterpret_cast<half4*>(dst + plane) = l;
 }
 
@@ -313,28 +317,20 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_logits(SplitArgs a, 
 }
 
 constexpr int SM_THREADS = 512;                          // softmax: threads per row
-
-__device__ __forceinline__ float workgroup_sum(float v, float* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = red[0];
-#pragma unroll
-  for (int w = 1; w < SM_THREADS / 64; ++w) r += red[w];
-  return r;
-}
+constexpr int SM_WAVES = SM_THREADS / 64;
 
 // One workgroup per row: maximum over the columns that take part, cross-entropy, the row's share of d/ds and the row of
 // G = softmax - onehot as planes (0 in the padding columns and rows, and in a two-view row's own column).  The off-label
 // mass is summed on its own, so that P_label - 1 = -(it) / (total) does not cancel, and d/ds as
-// sum_{j != label} P_ij (S_ij - S_i,label).  The vector ALU bounded it, 96 % busy; without tests on the pieces that hold no special
-// column and with planes cut for values of [-1, 1], memory does (B = 8192, N = 8: 39.7 -> 33.8 us for 167 MB).  KEEP:
-// 4-column pieces a thread keeps, 8 (Bp <= 16384) or 16 (32768): the row is then read once, else (0) three times, from cache, with
-// every exponential taken twice (us a call, 0 / 16: B = 32768, N = 8, d = 512 4394 / 4225; 20000, 8, 256 1148 / 1095).
+// sum_{j != label} P_ij (S_ij - S_i,label).  134 MB at B = 8192, N = 8 take 28.5 us, 4.7 TB/s (33 with a product in every step of
+// the maximum, 68 registers, five barriers instead of two and eight instructions for a value's planes instead of five): memory and the 26
+// vector instructions an element about even.  Pieces that hold no special column take no tests.  KEEP: 4-column pieces a thread keeps, the
+// smallest of 4 (Bp <= 8192; 44 registers, so that four workgroups share a compute unit, not three), 8 (16384) and 16 (32768) that holds
+// the row, which is then read once; else (0) three times, from cache, with every exponential taken twice (us a call, 0 / 16: B = 32768,
+// N = 8, d = 512 4394 / 4225; 20000, 8, 256 1148 / 1095).
 template <int KEEP>
 __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float s) {
-  __shared__ float red[SM_THREADS / 64];
+  __shared__ float red[3][SM_WAVES];
   const int64_t i = blockIdx.x;
   const SplitBlock& p = a.z[blockIdx.y];
   uint16_t* G = p.G + i * a.Bp;
@@ -378,17 +374,21 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
       if (q < nvec) keep[u] = *reinterpret_cast<const f32x4*>(S + q * 4);
     }
   }
-  float mx = s * xl;
+  // the largest s v is s times the largest v, or with s < 0 the smallest
+  const float up = s < 0.f ? -1.f : 1.f;
+  float top = up * xl;
   visit([&](int j, f32x4& v, auto marked) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (counts(j + e, marked)) mx = fmaxf(mx, s * v[e]);
+      if (counts(j + e, marked)) top = fmaxf(top, up * v[e]);
   });
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  top = wave_reduce(top, [](float p, float q) { return fmaxf(p, q); });
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (lane == 0) red[0][wave] = top;
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < SM_THREADS / 64; ++w) mx = fmaxf(mx, red[w]);
+  for (int w = 0; w < SM_WAVES; ++w) top = fmaxf(top, red[0][w]);
+  const float mx = s * (up * top);
   float off = 0.f, ds = 0.f;
   visit([&](int j, f32x4& v, auto marked) {
 #pragma unroll
@@ -402,18 +402,30 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
       if constexpr (KEEP > 0) v[e] = x;
     }
   });
-  off = workgroup_sum(off, red);
-  ds = workgroup_sum(ds, red);
+  auto plus = [](float p, float q) { return p + q; };
+  off = wave_reduce(off, plus);
+  ds = wave_reduce(ds, plus);
+  if (lane == 0) { red[1][wave] = off; red[2][wave] = ds; }
+  __syncthreads();
+  off = red[1][0]; ds = red[2][0];
+#pragma unroll
+  for (int w = 1; w < SM_WAVES; ++w) { off += red[1][w]; ds += red[2][w]; }
   const float zl = s * xl, el = expf(fmaf(s, xl, -mx)), tot = off + el, inv = 1.f / tot;
+  const float m = half ? inv * G_SCALE : inv;
   visit([&](int j, f32x4& v, auto marked) {
-    f32x4 g;
+    f32x4 x;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = KEEP ? v[e] : counts(j + e, marked) ? expf(fmaf(s, v[e], -mx)) : 0.f;
-      g[e] = decltype(marked)::value && j + e == lab ? -off * inv : x * inv;
+      x[e] = KEEP ? v[e] : counts(j + e, marked) ? expf(fmaf(s, v[e], -mx)) : 0.f;
+      if (decltype(marked)::value && j + e == lab) x[e] = -off;
     }
-    if (half) store_unit_halves(G + j, a.gplane, g);
-    else store_unit_planes(G + j, a.gplane, g);
+    if (half) {
+      store_unit_halves(G + j, a.gplane, x, m);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] *= m;
+      store_unit_planes(G + j, a.gplane, x);
+    }
   });
   if (threadIdx.x == 0) {
     // ce = log(tot) - (zl - mx); where the label holds most of the mass log1p(off / el) keeps the relative accuracy
@@ -700,7 +712,8 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
     else split_products<128, NP>(false, pl.parts, add, a, cs, st);
     if (r0 == 0) stage_mark(st, 1);
     const dim3 rows((unsigned)pl.bp, (unsigned)nb);
-    if (pl.Bp <= (int64_t)SM_THREADS * 8 * 4) k_split_softmax<8><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    if (pl.Bp <= (int64_t)SM_THREADS * 4 * 4) k_split_softmax<4><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
+    else if (pl.Bp <= (int64_t)SM_THREADS * 8 * 4) k_split_softmax<8><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
     else if (pl.Bp <= (int64_t)SM_THREADS * 16 * 4) k_split_softmax<16><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
     else k_split_softmax<0><<<rows, SM_THREADS, 0, st>>>(a, pr.s);
     if (r0 == 0) { stage_mark(st, 2); stage_mark(st, 3); }
