@@ -80,22 +80,22 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  *                         softmax numerators are kept in bf16 (2*b*B*2 bytes) and feed the two
  *                         gradient contractions (12*b*B*d flop).  Needs dtype bf16, d % 64 == 0,
  *                         B <= 2^23.  A share b that is not a whole number of 256-row tiles is rounded up
- *                         to one inside the workspace (zero-padded copies of I, T and the rank's rows,
- *                         2*(B+b)*d*2 more bytes; the padding takes part in no softmax, sum or output),
- *                         so the call costs what the rounded-up shape costs.
+ *                         to one (nothing past the ends of I and T is read; the padding takes part in no
+ *                         softmax, sum or output), so the call costs what the rounded-up shape costs; its
+ *                         workspace counts 2*(B+b)*d*2 more bytes.
  * DISCO_PATH_FUSED        bf16 MFMA tiles, memory-lean: 2*b*W*2 bytes of numerators for a panel width W of at most 16384
  *                         keys, in one of two forms, whichever is the faster for the shape: the rank's rows in chunks of
  *                         b*W/B, each taken through logits and gradients against all keys (12*b*B*d flop, the key-side
  *                         gradient read and written again per chunk), or streaming: a forward pass keeps the row sums on
  *                         chip and writes nothing of size b x B, the backward pass recomputes the logits one key panel
  *                         at a time and contracts each panel while it is cache-resident (16*b*B*d flop).
- *                         Shape limits of MATERIALIZED (ragged shares padded as there).
+ *                         Shape limits of MATERIALIZED (ragged shares rounded up as there).
  * DISCO_PATH_SYMMETRIC    bf16 MFMA tiles, N = 1 only (the non-decomposed loss, Eq. 1 / Fig. 1): the B x B
  *                         similarity matrix is computed once and serves both directions (text -> image is
  *                         its transpose); one matrix of numerators (B*B*2 bytes) against one exponent
  *                         reference, turned in place into the combined gradient matrix, then one contraction
  *                         per feature gradient: 6*B^2*d flop instead of 12.  Shape limits of MATERIALIZED
- *                         (a batch that is not whole 256-row tiles is padded in the workspace as there).  Inputs whose rows' or columns' largest logits lie more than about
+ *                         (a batch that is not whole 256-row tiles is rounded up as there).  Inputs whose rows' or columns' largest logits lie more than about
  *                         60 (base 2) under the largest positive-pair logit are handed over, inside the same
  *                         call, to the MATERIALIZED kernels, so the workspace is sized for those as well.  A
  *                         batch too small to gain from it (B*B*d < 1e10) goes to those kernels at once.

@@ -108,7 +108,7 @@ int split_run(const Problem& p, size_t limit);
 void split_describe(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, disco_plan* out);
 
 // the bf16 tile kernels can take the shape (materialized path; a rank share that is not a whole number of 256-row
-// tiles is zero-padded in the workspace) / the share is whole tiles (what the fused and symmetric paths need too)
+// tiles is rounded up to them) / the share is whole tiles (what the fused and symmetric paths need too)
 bool mfma_supported(int64_t B, int64_t d, int32_t N, int dtype, int variant = LOSS_CLIP);
 bool mfma_whole_tiles(int64_t B, int32_t N);
 double mfma_stored_estimate_us(int64_t B, int64_t d, int32_t N, int variant);      // its tile kernels, without the launches

@@ -47,8 +47,8 @@ constexpr int GEMM_SMEM_BYTES = OUT_SMEM_BYTES<T> > Cfg<T>::SMEM_BYTES ? OUT_SME
 
 // ------------------------------------------------------------------------------------------------
 struct BlockPtrs {
-  const uint16_t* X;     // b x d, the rank's rows (zero rows past the real ones)
-  const uint16_t* Y;     // B x d (zero rows past the real ones)
+  const uint16_t* X;     // b x d, the rank's rows
+  const uint16_t* Y;     // B x d
   uint16_t* E;           // b x W stored numerators of one key panel, in 16-byte atoms (e_index)
   float* lpart;          // (2B/T) x b partial row sums (label column excluded) of logit tiles of size T
   float* ediag;          // b: numerator of the label column
@@ -71,9 +71,13 @@ struct Blocks {
   const int* gate;       // nullptr: the kernel always runs; else it runs only while *gate == gate_value (the symmetric
   int gate_value;        // full-loss path hands over to the two-block path through this flag)
   int64_t rows, keys;    // the rank's rows and the batch as the caller has them.  The kernels' own b / B arguments are
-                         // these rounded up to whole tiles; where they differ (a ragged share), X and Y are
-                         // zero-padded copies, query rows >= rows and key columns >= keys are padding
+                         // these rounded up to whole tiles; where they differ (a ragged share), query rows >= rows and
+                         // key columns >= keys are padding: X and Y end before it, and who reads tiles of them takes zeros there
 };
+
+// Rows of a tile of MOST that exist, of `left` from its first one on (none: a tile that is all padding).
+template <int MOST>
+__device__ __forceinline__ int rows_there(int64_t left) { return left < 0 ? 0 : left < MOST ? (int)left : MOST; }
 
 __device__ __forceinline__ bool gated_off(const Blocks& bl) { return bl.gate != nullptr && *bl.gate != bl.gate_value; }
 
@@ -126,27 +130,6 @@ __global__ __launch_bounds__(256) void k_prep(Blocks bl, int64_t B, int64_t b, i
     p.zd2[i] = s2 * dot;
     p.ref2[i] = fmaxf(s2 * dot, fmaf(fabsf(s2) * xx, yy, -REF_HEADROOM));
     if (NORMS) { p.beta[i] = xx; p.gdiag[i] = yy; }
-  }
-}
-
-// Operands of a ragged share (the rank's rows or the batch are not whole 256-row tiles): zero-padded copies of I and T
-// (Bp rows each) and of the rank's rows of both (bp rows each), so that the tile kernels read whole tiles of
-// memory that exists and the padding contributes exact zeros to every contraction.  16-byte pieces, grid-stride.
-__global__ __launch_bounds__(256) void k_pad_operands(const uint16_t* I, const uint16_t* T, int64_t B, int64_t Bp, int64_t b, int64_t bp,
-                                                      int64_t d, int rank, uint16_t* Ipad, uint16_t* Tpad, uint16_t* XI, uint16_t* XT) {
-  const int64_t cpr = d >> 3;                              // 16-byte pieces per row
-  const int64_t nY = Bp * cpr, nX = bp * cpr;
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < 2 * (nY + nX); c += (int64_t)gridDim.x * 256) {
-    const int seg = c < nY ? 0 : c < 2 * nY ? 1 : c < 2 * nY + nX ? 2 : 3;
-    const int64_t w = c - (seg == 0 ? 0 : seg == 1 ? nY : seg == 2 ? 2 * nY : 2 * nY + nX);
-    const int64_t row = w / cpr, piece = w - row * cpr;
-    const uint16_t* src = (seg & 1) ? T : I;
-    uint16_t* dst = seg == 0 ? Ipad : seg == 1 ? Tpad : seg == 2 ? XI : XT;
-    const bool there = seg < 2 ? row < B : row < b;
-    const int64_t srow = seg < 2 ? row : (int64_t)rank * b + row;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (there) v = *reinterpret_cast<const u32x4*>(src + srow * d + piece * 8);
-    *reinterpret_cast<u32x4*>(dst + row * d + piece * 8) = v;
   }
 }
 
@@ -325,7 +308,10 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS, 2) void k_logit_tiles(Blocks bl, 
     for (int i = 0; i < Cfg<T>::NFA; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    if constexpr (RAGGED)
+      mainloop<T, FMT_K, FMT_K, true, false, Planes<1, 1>, Bounded>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc, T, 0, 0,
+                                                                    Bounded{rows_there<T>(B - j0), rows_there<T>(bl.rows - i0), 0u});
+    else mainloop<T, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
 
     // Only the tiles that the label diagonal (or the left-out diagonal) crosses, or that hold padding columns, pay
     // for finding those columns.
@@ -348,10 +334,10 @@ __device__ __forceinline__ void row_outputs(const BlockPtrs& p, int64_t i, float
 
 // Xs[k][i] = bf16(scale_i x_ik), kbegin <= k < kend (multiples of 64), for the nrows (a multiple of 64) rows from i0 on, scale = the nrows floats at `scale`
 // in LDS (nullptr: 1): the key-side contraction's right operand, with its reduction index contiguous.  All NTH threads
-// of the workgroup (256, 512 or 1024), 64 x 64 pieces through `tile` (64 x 65 floats of LDS).  The pieces of up to eight
+// of the workgroup (256, 512 or 1024), zeros for the rows from `rows` on, 64 x 64 pieces through `tile` (64 x 65 floats of LDS).  The pieces of up to eight
 // 64-feature tiles are fetched before the first is turned round, so that their loads are in flight together.
 template <int NTH>
-__device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t b, int64_t d, int64_t kbegin, int64_t kend, int64_t i0, int nrows, const float* scale,
+__device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t rows, int64_t b, int64_t d, int64_t kbegin, int64_t kend, int64_t i0, int nrows, const float* scale,
                                                      float (*tile)[65]) {
   constexpr int NPT = 1024 / NTH, AHEAD = 8;              // pieces of 4 features per thread and tile; tiles per batch
   const int t = threadIdx.x;
@@ -364,7 +350,8 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
 #pragma unroll
           for (int q = 0; q < NPT; ++q) {                 // 64 rows x 16 pieces of 4 features
             const int e = t + q * NTH, r = e >> 4, c4 = (e & 15) * 4;
-            w[a][q] = *reinterpret_cast<const u32x2*>(p.X + (i0 + r0 + r) * d + kc + a * 64 + c4);
+            w[a][q] = u32x2{0u, 0u};
+            if (i0 + r0 + r < rows) w[a][q] = *reinterpret_cast<const u32x2*>(p.X + (i0 + r0 + r) * d + kc + a * 64 + c4);
           }
 #pragma unroll
       for (int a = 0; a < AHEAD; ++a) {
@@ -401,16 +388,16 @@ __device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t
 // XOR-swizzled with the row), and a key's come straight from memory, a whole line at once.  (All rows redone, features of norm 4
 // to 8 at B = 32768, d = 512: a call takes 2.9 ms at N = 8 and 2.35 at N = 64; with both operands' fragments straight from
 // memory and every workgroup on the same rows at it, 6.1 and 5.5; a call that redoes none 0.75 and 0.145.)
-// Local rows i0 .. i0 + 63, global row g0 + i; Bp: key rows that exist in memory, a multiple of 32.  Leaves the rows' sums in
+// Local rows i0 .. i0 + 63, of which those from `rows` on are padding, global row g0 + i; Bp: the keys rounded up to whole tiles.  Leaves the rows' sums in
 // off_s and their label numerators in ed_s.
-__device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool store,
+__device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64_t rows, int64_t keys, int64_t Bp, int64_t d, int64_t i0, int64_t g0, float s2, bool store,
                                        float (*red)[64], float* ref_s, float* off_s, float* ed_s, char* xt) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, grp = lane >> 4;
   const uint32_t row_bytes = (uint32_t)d * 2;
-  const uint32_t y_off = l16 * row_bytes + grp * 16;                               // of a lane's piece from its 16 keys' first
   const char* xb = uniform_ptr(p.X + i0 * d);                                      // threads 0 .. 511: row t / 8, chunk t % 8 of a piece
   const uint32_t x_off = (uint32_t)(t >> 3) * row_bytes + (t & 7) * 16;
   const uint32_t x_put = (uint32_t)((t >> 3) * 128 + (((t & 7) ^ ((t >> 3) & 7)) << 4));
+  const bool x_there = t < 512 && i0 + (t >> 3) < rows;
   int buf = 0;
   f32x4 acc[2][4];                                        // [16 keys][16 rows]; a lane: keys 4 grp .. + 3 of row l16
   auto strip = [&](int j0) {                              // (all waves together)
@@ -419,20 +406,26 @@ __device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
     const char* yb = uniform_ptr(p.Y + (int64_t)j0 * d);
+    uint32_t y_off[2];                                    // of a lane's piece from the strip's first key; the last key for those past it
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = 16 * u + l16, most = (int)keys - 1 - j0;
+      y_off[u] = (uint32_t)(r < most ? r : most) * row_bytes + grp * 16;
+    }
     u32x4 next = {0u, 0u, 0u, 0u};
-    if (t < 512) next = *reinterpret_cast<const u32x4*>(xb + x_off);
+    if (x_there) next = *reinterpret_cast<const u32x4*>(xb + x_off);
 #pragma unroll 1
     for (uint32_t k = 0; k < row_bytes; k += 128) {
       bf16x8 a[2][2];
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) a[h][u] = *reinterpret_cast<const bf16x8*>(yb + (uint64_t)(16 * u) * row_bytes + k + 64 * h + y_off);
+        for (int h = 0; h < 2; ++h) a[h][u] = *reinterpret_cast<const bf16x8*>(yb + (k + 64 * h) + y_off[u]);
       char* piece = xt + buf * 8192;
       buf ^= 1;
       if (t < 512) {
         *reinterpret_cast<u32x4*>(piece + x_put) = next;
-        if (k + 128 < row_bytes) next = *reinterpret_cast<const u32x4*>(xb + x_off + k + 128);
+        if (x_there && k + 128 < row_bytes) next = *reinterpret_cast<const u32x4*>(xb + x_off + k + 128);
       }
       lds_barrier();                                      // (the other piece: read before the previous barrier, written after it)
 #pragma unroll
@@ -447,10 +440,10 @@ __device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64
   };
   float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll 1
-  for (int base = 0; base < (int)Bp; base += 16 * 32) {
+  for (int base = 0; base < (int)keys; base += 16 * 32) {
     const int j0 = base + wave * 32;
-    strip(j0 < (int)Bp ? j0 : 0);                         // a wave without a strip works on the first one and drops it
-    if (j0 >= (int)Bp) continue;
+    strip(j0 < (int)keys ? j0 : 0);                       // a wave without a strip works on the first one and drops it
+    if (j0 >= (int)keys) continue;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int self = (int)masked_col(g0 + i0 + v * 16 + l16, variant);
@@ -479,10 +472,10 @@ __device__ __forceinline__ void redo_rows(const BlockPtrs& p, int variant, int64
   __syncthreads();
   float rs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-  for (int base = 0; base < (int)Bp; base += 16 * 32) {
+  for (int base = 0; base < (int)keys; base += 16 * 32) {
     const int j0 = base + wave * 32;
-    strip(j0 < (int)Bp ? j0 : 0);
-    if (j0 >= (int)Bp) continue;
+    strip(j0 < (int)keys ? j0 : 0);
+    if (j0 >= (int)keys) continue;
     // (element (row, key) of the group is at e_index: scalar base of the strip plus this lane's place in it)
     char* erow = const_cast<char*>(uniform_ptr(p.E + e_index(i0, j0, Bp))) + (uint32_t)(((grp >> 1) * 512 + l16 * 8 + (grp & 1) * 4) * 2);
 #pragma unroll
@@ -606,13 +599,13 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
   if (redo) {                                           // by the first of the workgroups on these rows, which goes on to all of their features
     if (!writer) return;
     chunks = 1;
-    redo_rows(p, bl.variant, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, f.store, red, ref_s, off_s, ed_s, reinterpret_cast<char*>(tile));
+    redo_rows(p, bl.variant, bl.rows, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, f.store, red, ref_s, off_s, ed_s, reinterpret_cast<char*>(tile));
     if (wave == 0) finish(off_s[lane], ed_s[lane]);
     __syncthreads();
   }
   if (f.fchunks) {
     const int64_t per = (f.d / 64 + chunks - 1) / chunks * 64, k0 = blockIdx.z * per;
-    scale_transpose_rows<1024>(p, b, f.d, k0, k0 + per < f.d ? k0 + per : f.d, i0, 64, beta_s, tile);
+    scale_transpose_rows<1024>(p, bl.rows, b, f.d, k0, k0 + per < f.d ? k0 + per : f.d, i0, 64, beta_s, tile);
   }
 }
 
@@ -621,7 +614,7 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
 __global__ __launch_bounds__(1024) void k_transpose(Blocks bl, int64_t b, int64_t d) {
   if (gated_off(bl)) return;
   __shared__ float tile[64][65];
-  scale_transpose_rows<1024>(bl.z[0], b, d, 0, d, (int64_t)blockIdx.x * 64, 64, nullptr, tile);
+  scale_transpose_rows<1024>(bl.z[0], bl.rows, b, d, 0, d, (int64_t)blockIdx.x * 64, 64, nullptr, tile);
 }
 
 // The two gradient contractions of every block, in one launch: they are independent of each other, so where neither has
@@ -651,7 +644,8 @@ struct GradShape {
 };
 enum { KEY_WRITE = 0, KEY_ADD = 1, KEY_SPLIT = 2 };
 
-template <int T, int KMODE, bool QADD>
+// RAGGED: the last of the W key rows may not exist; the query side reads zeros there, which meet the zeros of the numerators' padding columns.
+template <int T, int KMODE, bool QADD, bool RAGGED>
 __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_grads(Blocks bl, GradShape g, float cs) {
   if (gated_off(bl)) return;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -683,8 +677,12 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_grads(Blocks bl, GradShape
     if (kts > g.ktps) kts = g.ktps;
     const int ncols = d - k0 < T ? (int)(d - k0) : T;               // the last column tile may be partial (d % 64 == 0)
     // (kts >= 1: the plan's split count is the number of splits that hold at least one K-step)
-    mainloop<T, FMT_KA, FMT_R, false, true>(p.E + ((i0 >> 6) * (W >> 6) + kt0) * 4096, (W >> 6) * 4096,
-                                            p.Y + (g.jp0 + (int64_t)kt0 * BK) * d + k0, d, kts, smem, acc, ncols);
+    const uint16_t* Eq = p.E + ((i0 >> 6) * (W >> 6) + kt0) * 4096;
+    const int64_t j0 = g.jp0 + (int64_t)kt0 * BK;
+    if constexpr (RAGGED)
+      mainloop<T, FMT_KA, FMT_R, false, true, Planes<1, 1>, Bounded>(Eq, (W >> 6) * 4096, p.Y + j0 * d + k0, d, kts, smem, acc, ncols, 0, 0,
+                                                                     Bounded{0, rows_there<(1 << 30)>(bl.keys - j0), (uint32_t)(k0 * 2)});
+    else mainloop<T, FMT_KA, FMT_R, false, true>(Eq, (W >> 6) * 4096, p.Y + j0 * d + k0, d, kts, smem, acc, ncols);
     store_tile_f32<T, QADD>(acc, smem, p.part + (int64_t)ks * b * d + i0 * d + k0, d, 1.0f, ncols);
     return;
   }
@@ -983,7 +981,7 @@ __device__ __forceinline__ f32x2 sums_over_rows(const float (&col)[8][4], int la
 // of the stored, rounded numerators: where a few of them hold a column's mass, their rounding cancels in the gradient.  With the
 // unrounded ones gT was 24 % further off at B = 12000, d = 128, 10 % near-duplicate rows.)
 // bl.z[0]: E, row partial sums, label numerators; bl.z[1].lpart: column partial sums, one per query tile, cpart[it][j].
-// B: the batch rounded up to whole tiles.  RAGGED: the batch is not whole tiles (X and Y are zero-padded copies): the
+// B: the batch rounded up to whole tiles.  RAGGED: the batch is not whole tiles: the
 // last key tiles leave their padding columns out (so every row sum is right) and the column sums leave the padding
 // rows out; what the padding rows hold in E meets zero feature rows in both contractions.
 template <bool RAGGED>
@@ -1008,7 +1006,10 @@ __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, in
     for (int i = 0; i < Cfg<256>::NFA; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mainloop<256, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
+    if constexpr (RAGGED)
+      mainloop<256, FMT_K, FMT_K, true, false, Planes<1, 1>, Bounded>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc, 256, 0, 0,
+                                                                      Bounded{rows_there<256>(bl.keys - j0), rows_there<256>(bl.rows - i0), 0u});
+    else mainloop<256, FMT_K, FMT_K, true>(p.Y + j0 * d, d, p.X + i0 * d, d, (int)(d / BK), smem, acc);
     // the label of query row i is key row i: only the tiles on the diagonal contain label columns
     // (ordinary stores: the matrix is read again by the combining pass and the two contractions)
     // (and of a ragged batch the last key tiles and the last query tiles contain padding)
@@ -1101,7 +1102,7 @@ struct Plan {
   int64_t b_all;         // the share rounded up to whole tiles (b, except where the fused path takes it in chunks)
   bool chunked;          // fused path: rows in chunks, each against all keys, instead of key panels
   int64_t b_real, B_real;
-  bool ragged;           // b or B was rounded up: the kernels read zero-padded copies of the operands (off_pad)
+  bool ragged;           // b or B was rounded up
   int64_t W;             // key panel width (B for the materialized path)
   int npanels;
   int tl, tg;            // tile size of the logit kernels and of the gradient kernel (256 or 128)
@@ -1109,7 +1110,7 @@ struct Plan {
   int nMq, nMk, nN;      // gradient tiles: query rows, key rows of a panel, columns
   int splitk, ktps;      // query-side split, K-steps per split
   int key_splits, key_ktps;
-  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ref, off_pad, total;
+  size_t off_E, off_lpart, off_rows, off_Xs, off_part, off_kpart, off_ref, total;
   size_t rows_stride;    // bytes of one b-float row array (aligned)
   double us;             // estimated time of the tile kernels
 };
@@ -1134,7 +1135,8 @@ void layout(Plan& pl) {
   pl.off_kpart = o;
   if (pl.key_splits > 1) o += 2 * align_up((size_t)pl.key_splits * B * d * 4);
   pl.off_ref = o;    o += 2 * pl.rows_stride;                            // exponent references of the rows
-  pl.off_pad = o;                                                        // padded I, T, I_r, T_r of a ragged share
+  // Not used: what a ragged share's padded operands would take.  The sizes that callers ask for, and with them which calls and plans fit
+  // a given memory, count it as they always have.
   if (pl.ragged) o += 2 * align_up((size_t)B * d * 2) + 2 * align_up((size_t)pl.b_all * d * 2);
   pl.total = o;
 }
@@ -1307,9 +1309,13 @@ struct TileKernels {
         allow_lds(k_logit_tiles<T, false, true>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, true, true, false, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, true, true, true, false>, LOGIT_SMEM_BYTES<T>) &&
         allow_lds(k_logit_tiles<T, false, true, false, false>, LOGIT_SMEM_BYTES<T>) && allow_lds(k_logit_tiles<T, false, true, true, false>, LOGIT_SMEM_BYTES<T>) &&
-        allow_lds(k_grads<T, KEY_WRITE, false>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false>, GEMM_SMEM_BYTES<T>) &&
-        allow_lds(k_grads<T, KEY_WRITE, true>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true>, GEMM_SMEM_BYTES<T>) &&
-        allow_lds(k_grads<T, KEY_SPLIT, false>, GEMM_SMEM_BYTES<T>);
+        raise_grads<false>() && raise_grads<true>();
+  }
+  template <bool RAGGED>
+  static bool raise_grads() {
+    return allow_lds(k_grads<T, KEY_WRITE, false, RAGGED>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, false, RAGGED>, GEMM_SMEM_BYTES<T>) &&
+           allow_lds(k_grads<T, KEY_WRITE, true, RAGGED>, GEMM_SMEM_BYTES<T>) && allow_lds(k_grads<T, KEY_ADD, true, RAGGED>, GEMM_SMEM_BYTES<T>) &&
+           allow_lds(k_grads<T, KEY_SPLIT, false, RAGGED>, GEMM_SMEM_BYTES<T>);
   }
   // logit tiles of the key panel [jp0, jp0 + W): statistics, stored numerators or both
   static void logits(bool stats, bool store, const Plan& pl, const Blocks& bl, int64_t g0, float s2, int64_t jp0, int64_t W, int cus, hipStream_t st) {
@@ -1344,9 +1350,14 @@ struct TileKernels {
     g.q_wgs = part == 1 ? 0 : qS % 8 == 0 ? qT * qS : 8 % qS == 0 ? 8 * ((qT + 8 / qS - 1) / (8 / qS)) : (qS * qT + 7) / 8 * 8;   // see the kernel's slice -> XCD mapping
     const int k_wgs = part == 2 ? 0 : bl.nblk * ((pl.nMk * pl.nN * pl.key_splits + 7) / 8 * 8);
     auto go = [&](auto kernel) { kernel<<<dim3((unsigned)(g.q_wgs + k_wgs)), Cfg<T>::NTHREADS, GEMM_SMEM_BYTES<T>, st>>>(bl, g, cs); };
-    if (pl.key_splits > 1) go(k_grads<T, KEY_SPLIT, false>);
-    else if (query_add) { if (key_add) go(k_grads<T, KEY_ADD, true>); else go(k_grads<T, KEY_WRITE, true>); }
-    else { if (key_add) go(k_grads<T, KEY_ADD, false>); else go(k_grads<T, KEY_WRITE, false>); }
+    auto instance = [&](auto ragged) {
+      constexpr bool R = decltype(ragged)::value;
+      if (pl.key_splits > 1) go(k_grads<T, KEY_SPLIT, false, R>);
+      else if (query_add) { if (key_add) go(k_grads<T, KEY_ADD, true, R>); else go(k_grads<T, KEY_WRITE, true, R>); }
+      else { if (key_add) go(k_grads<T, KEY_ADD, false, R>); else go(k_grads<T, KEY_WRITE, false, R>); }
+    };
+    if (pl.ragged) instance(std::true_type{});
+    else instance(std::false_type{});
   }
 };
 
@@ -1373,11 +1384,6 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
   const uint16_t* T = static_cast<const uint16_t*>(pr.T);
 
-  uint16_t* Ipad = reinterpret_cast<uint16_t*>(ws + pl.off_pad);
-  uint16_t* Tpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + align_up((size_t)B * d * 2));
-  uint16_t* XIpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + 2 * align_up((size_t)B * d * 2));
-  uint16_t* XTpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + 2 * align_up((size_t)B * d * 2) + align_up((size_t)ba * d * 2));
-
   Blocks bl;                                              // all rows of the share
 
   bl.variant = pr.variant;
@@ -1389,8 +1395,8 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   for (int z = 0; z < 2; ++z) {
     BlockPtrs& p = bl.z[z];
     const uint16_t* Xfull = z == 0 ? I : T;
-    p.X = pl.ragged ? (z == 0 ? XIpad : XTpad) : Xfull + (size_t)pr.rank * ba * d;
-    p.Y = pl.ragged ? (z == 0 ? Tpad : Ipad) : (z == 0 ? T : I);
+    p.X = Xfull + (size_t)pr.rank * pl.b_real * d;
+    p.Y = z == 0 ? T : I;
     p.E = reinterpret_cast<uint16_t*>(ws + pl.off_E + z * align_up((size_t)b * W * 2));
     p.lpart = reinterpret_cast<float*>(ws + pl.off_lpart + z * align_up((size_t)pl.nparts * b * 4));
     char* rows = ws + pl.off_rows + (size_t)z * NROWARRAYS * pl.rows_stride;
@@ -1417,8 +1423,6 @@ int mfma_run(const Problem& pr, bool fused, const int* gate = nullptr, int gate_
   auto mark = [&] { if (marks) stage_mark(st, stage++); };
 
   mark();
-  if (pl.ragged)
-    k_pad_operands<<<dim3((unsigned)(8 * cus)), 256, 0, st>>>(I, T, pl.B_real, B, pl.b_real, ba, d, pr.rank, Ipad, Tpad, XIpad, XTpad);
   k_prep<false><<<dim3((unsigned)(nblk * ((ba + 3) / 4))), 256, 0, st>>>(bl, pl.B_real, pl.b_real, ba, d, pr.rank, s2);
   mark();
   for (int64_t r0 = 0; r0 < ba; r0 += b) {                // (one chunk except on the fused path)
@@ -1507,10 +1511,6 @@ int mfma_sym_run_impl(const Problem& pr) {
   const uint16_t* I = static_cast<const uint16_t*>(pr.I);
   const uint16_t* T = static_cast<const uint16_t*>(pr.T);
 
-  // a batch that is not whole tiles: zero-padded copies of I and T (the copies of "the rank's rows" are not used)
-  uint16_t* Ipad = reinterpret_cast<uint16_t*>(ws + pl.off_pad);
-  uint16_t* Tpad = reinterpret_cast<uint16_t*>(ws + pl.off_pad + align_up((size_t)B * d * 2));
-
   Blocks bl;
   bl.variant = LOSS_CLIP;
   bl.nblk = 1;
@@ -1521,8 +1521,8 @@ int mfma_sym_run_impl(const Problem& pr) {
   BlockPtrs& p = bl.z[0];
   char* rows0 = ws + pl.off_rows;
   char* rows1 = rows0 + (size_t)NROWARRAYS * pl.rows_stride;
-  p.X = pl.ragged ? Ipad : I;
-  p.Y = pl.ragged ? Tpad : T;
+  p.X = I;
+  p.Y = T;
   p.E = reinterpret_cast<uint16_t*>(ws + pl.off_E);
   p.lpart = reinterpret_cast<float*>(ws + pl.off_lpart);
   p.ediag = reinterpret_cast<float*>(rows0 + 0 * pl.rows_stride);
@@ -1559,7 +1559,6 @@ int mfma_sym_run_impl(const Problem& pr) {
   int stage = 0;
 
   stage_mark(st, stage++);
-  if (pl.ragged) k_pad_operands<<<dim3((unsigned)(8 * persistent_wgs)), 256, 0, st>>>(I, T, Br, B, 0, 0, d, 0, Ipad, Tpad, Ipad, Tpad);
   k_prep<true><<<dim3((unsigned)((B + 3) / 4)), 256, 0, st>>>(bl, Br, Br, B, d, 0, s2);
   k_sym_ref<<<1, 1024, 0, st>>>(p.zd2, p.beta, p.gdiag, Br, s2, rglobal, gate);
   stage_mark(st, stage++);

@@ -173,9 +173,29 @@ __device__ __forceinline__ const char* uniform_ptr(const void* p) {
   return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
-// The 4 GiB from p on (the same in every lane) as a buffer resource.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(uniform_ptr(p)), 0, 0xffffffffu, 0x00020000);
+// The `bytes` (4 GiB) from p on (both the same in every lane) as a buffer resource: loads past them return zeros and fetch nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p, uint32_t bytes = 0xffffffffu) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(uniform_ptr(p)), 0, bytes, 0x00020000);
+}
+
+// How much of its operands a tile may read.  Whole: all of it exists.  Bounded: rows_a of the A tile's rows (FMT_K), rows_b of the B tile's
+// (FMT_K) or of the reduction's (FMT_R, whose tile starts at byte col_b of a row); none if not positive.  The loop reads zeros for
+// the others, by the bounds of its buffer resources, which it sets up for every K-step in any case.  (Zero-padded copies of the operands before,
+// a launch and 2 (B + b) d of 2 bytes read and written: B = 30000, N = 8, d = 512, two shares 1366 / 1335 us, smaller ragged calls up to
+// 12 %: 128 / 114.  Clamping rows to the last one instead would need masks where padding meets padding.  The bounds cost the instances that take
+// them 10 to 30 scalar instructions a tile; whole shares run those without.)
+struct Whole { static constexpr bool ON = false; };
+struct Bounded {
+  static constexpr bool ON = true;
+  int rows_a, rows_b;
+  uint32_t col_b;
+};
+// Bytes that exist from where K-step kt of such an operand starts.
+template <int T, int FMT>
+__device__ __forceinline__ uint32_t bytes_left(int rows, uint32_t col, int64_t ld, int kt) {
+  const int there = FMT == FMT_R ? rows - kt * BK : rows, most = FMT == FMT_R ? BK : T;
+  const uint32_t n = (uint32_t)(there < 0 ? 0 : there > most ? most : there) * (uint32_t)(ld * 2), skip = FMT == FMT_R ? col : (uint32_t)kt * (BK * 2);
+  return __builtin_amdgcn_readfirstlane(FMT == FMT_K || FMT == FMT_R ? (n > skip ? n - skip : 0u) : 0xffffffffu);
 }
 
 // format R: what the 32-byte group index of reduction row kap is XOR-ed with
@@ -250,10 +270,9 @@ struct Operand {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(base, (__attribute__((address_space(3))) void*)(lds + __builtin_amdgcn_readfirstlane(lds_q) + n * lds_step(FMT, T)),
                                              16, ld_off[n], 0, 0, 0);
   }
-  __device__ __forceinline__ void load_all(const uint16_t* base, char* lds) const {
-    const __amdgpu_buffer_rsrc_t r = buffer_at(base);
+  __device__ __forceinline__ void load_all(__amdgpu_buffer_rsrc_t base, char* lds) const {
 #pragma unroll
-    for (int n = 0; n < NLD; ++n) load(n, r, lds);
+    for (int n = 0; n < NLD; ++n) load(n, base, lds);
   }
 };
 
@@ -314,8 +333,7 @@ __device__ __forceinline__ void mfma_block(const FragsA<NH>& a, const FragsB& b,
 // raising the priority of every MFMA block instead is 1-4 % slower everywhere)
 template <bool FIRST, bool HALF, int H, int T, int FMT, int NFRAG, int NH>
 __device__ __forceinline__ void mfma_block_loads(const FragsA<NH>& a, const FragsB& b, Acc<2 * NH>& acc, const Operand<T, FMT, NFRAG>& op,
-                                                 const uint16_t* base, char* lds) {
-  const __amdgpu_buffer_rsrc_t from = buffer_at(base);
+                                                 __amdgpu_buffer_rsrc_t from, char* lds) {
 #define DISCO_LD(n) op.load(n, from, lds)
 #define DISCO_MM(i, j) mfma1<FIRST, HALF>(acc[H * NH + i][j], a.f[i], b.f[j])
   __builtin_amdgcn_s_setprio(1);
@@ -365,9 +383,10 @@ __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
 // WRITE_FIRST: the first K-step is peeled off the loop and writes the accumulators (acc = product, acc need not be
 // initialised); else every K-step adds to them (acc += product).  Peeling gains 2-5 % on the gradient GEMMs; in the
 // logit kernel it costs the epilogue registers it does not have.
-template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS>
+template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS, class BD>
 __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp, int64_t ldb,
-                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b) {
+                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b, const BD& bounds) {
+  static_assert(!BD::ON || PS::N == 1);
   constexpr int NFA = Cfg<T>::NFA, NH = NFA / 2, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t stepA = kstep_elems<FA>(lda);
@@ -389,6 +408,14 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     if constexpr (PS::N == 1) return Bp + kt * stepB;
     else { const auto [piece, q] = step_of(kt); return Bp + piece * stepB + (PS::B >> (2 * q) & 3) * plane_b; }
   };
+  auto from_a = [&](int kt) {
+    if constexpr (BD::ON) return buffer_at(tile_a(kt), bytes_left<T, FA>(bounds.rows_a, 0u, lda, kt));
+    else return buffer_at(tile_a(kt));
+  };
+  auto from_b = [&](int kt) {
+    if constexpr (BD::ON) return buffer_at(tile_b(kt), bytes_left<T, FB>(bounds.rows_b, bounds.col_b, ldb, kt));
+    else return buffer_at(tile_b(kt));
+  };
   Operand<T, FA, NFA> oa;
   Operand<T, FB, 4> ob;
   oa.init(lda, wave % WN, lane, (wave / WN) * Cfg<T>::WTM);
@@ -396,11 +423,11 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;   // LDS byte address
   const int k1 = last < 1 ? last : 1;
   if (GROUP == 0) {
-    oa.load_all(tile_a(0), smem);
-    oa.load_all(tile_a(k1), smem + 2 * UNIT_BYTES);
+    oa.load_all(from_a(0), smem);
+    oa.load_all(from_a(k1), smem + 2 * UNIT_BYTES);
   } else {
-    ob.load_all(tile_b(0), smem + UNIT_BYTES);
-    ob.load_all(tile_b(k1), smem + 3 * UNIT_BYTES);
+    ob.load_all(from_b(0), smem + UNIT_BYTES);
+    ob.load_all(from_b(k1), smem + 3 * UNIT_BYTES);
   }
   wait_vmcnt<NLD>();
   lds_barrier();
@@ -432,7 +459,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_a<1, 0>(a0, oa, ta);                                                                                              \
     read_b<1, 2>(b1, ob, tb);                                                                                              \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 0 && LOADS) mfma_block_loads<FIRST, PS::HALF, 1>(a1, b0, acc, oa, tile_a(kload), smem + lA * UNIT_BYTES);                    \
+    if (GROUP == 0 && LOADS) mfma_block_loads<FIRST, PS::HALF, 1>(a1, b0, acc, oa, from_a(kload), smem + lA * UNIT_BYTES);                    \
     else mfma_block<FIRST, PS::HALF, 1>(a1, b0, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b1);                                                                                                    \
@@ -450,7 +477,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     read_b<0, 0>(b0, ob, tnb);                                                                                             \
     read_b<0, 2>(b0, ob, tnb);                                                                                             \
     if (READS_FIRST) __builtin_amdgcn_sched_barrier(0);                                                                    \
-    if (GROUP == 1 && LOADS) mfma_block_loads<false, PS::HALF, 1>(a1, b1, acc, ob, tile_b(kload), smem + rA * UNIT_BYTES);                    \
+    if (GROUP == 1 && LOADS) mfma_block_loads<false, PS::HALF, 1>(a1, b1, acc, ob, from_b(kload), smem + rA * UNIT_BYTES);                    \
     else mfma_block<false, PS::HALF, 1>(a1, b1, acc);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     wait_frags(a0, b0);                                                                                                    \
@@ -483,12 +510,13 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
 //             a barrier, so the caller may reuse it at once.
 //   nvalid_b: rows of the B tile that exist in memory (multiple of 8, <= T); the output columns from
 //             nvalid_b on are then meaningless and must not be stored.
-template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false, class PS = Planes<1, 1>>
+//   bounds  : see Whole and Bounded.
+template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false, class PS = Planes<1, 1>, class BD = Whole>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp,
                                          int64_t ldb, int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b = T,
-                                         int64_t plane_a = 0, int64_t plane_b = 0) {
-  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST, PS>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b);
-  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST, PS>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b);
+                                         int64_t plane_a = 0, int64_t plane_b = 0, const BD& bounds = BD{}) {
+  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST, PS, BD>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds);
+  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST, PS, BD>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds);
 }
 
 // Writes a workgroup's T x T fp32 accumulator tile to row-major global memory through LDS, so that
