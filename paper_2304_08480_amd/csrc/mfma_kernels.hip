@@ -704,19 +704,28 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_grads(Blocks bl, GradShape
   store_tile_f32<T, KMODE == KEY_ADD>(acc, smem, out, d, KMODE == KEY_SPLIT ? 1.0f : cs, ncols, left < T ? (int)left : T);
 }
 
-// Sum over the split-K slices ks0, ks0 + step, ... (< splitk), in that order, of the 16-byte piece of row i at feature
-// k of each slice (part[(ks * pitch + i) * d + k]); four loads in flight at a time (a plain loop waits for every load).
-__device__ __forceinline__ f32x4 sum_slices(const float* part, int64_t pitch, int64_t i, int64_t d, int64_t k, int ks0, int step,
-                                            int splitk) {
-  auto piece = [&](int ks) { return *reinterpret_cast<const f32x4*>(part + ((int64_t)ks * pitch + i) * d + k); };
-  f32x4 u = {0.f, 0.f, 0.f, 0.f};
-  int ks = ks0;
-  for (; ks + 3 * step < splitk; ks += 4 * step) {
-    const f32x4 v0 = piece(ks), v1 = piece(ks + step), v2 = piece(ks + 2 * step), v3 = piece(ks + 3 * step);
-    u += v0; u += v1; u += v2; u += v3;
+// u[n]: sum over the split-K slices ks0, ks0 + step, ... (< splitk), in that order, of the 16-byte piece at from[n], slices `pitch` elements
+// apart.  DEPTH slices of every piece are in flight at a time, the last ones too (a plain loop waits for every load).
+template <int N, int DEPTH = 4>
+__device__ __forceinline__ void sum_slices(const float* const (&from)[N], int64_t pitch, int ks0, int step, int splitk, f32x4 (&u)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) u[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int ks = ks0; ks < splitk; ks += DEPTH * step) {
+    f32x4 v[DEPTH][N];
+#pragma unroll
+    for (int q = 0; q < DEPTH; ++q) {
+      const int at = ks + q * step;
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        v[q][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (at < splitk) v[q][n] = *reinterpret_cast<const f32x4*>(from[n] + at * pitch);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < DEPTH; ++q)
+#pragma unroll
+      for (int n = 0; n < N; ++n) u[n] += v[q][n];
   }
-  for (; ks < splitk; ks += step) u += piece(ks);
-  return u;
 }
 
 // What the finalize kernels add up for a row, besides its own terms.
@@ -735,13 +744,17 @@ struct FinalizeShape {
 // and the rows' shares of d/ds, <query-side vector, x_i>, per block.  Fixed summation order.
 // KSPLIT (the key-side contraction was split, k_grads<.., KEY_SPLIT>): the kernel runs over all B rows and starts each from
 //   gI[j] = [accumulate] gI[j] + cs sum_ks kpart^C[ks][j],  gT[j] likewise from kpart^A.
-// One wave per row; ROWWG (few rows, where rows / 4 workgroups would leave most of the chip idle while each wave walks
-// all the split-K slices): one workgroup per row, its four waves each add every fourth slice and wave 0 combines them.
-template <bool ROWWG, bool KSPLIT>
-__global__ __launch_bounds__(256) void k_finalize(Blocks bl, FinalizeShape f, float cs) {
+// One wave per row: memory's rate bounds it, so what counts is how many waves fit (64 registers; with the loads below 108, and 22.2 us
+// instead of 20.6 at b = 4096, B = 32768, d = 512).  ROWWG (few rows, where rows / 4 workgroups would leave most of the chip idle while
+// each wave walks all the split-K slices): one workgroup per row, its four waves each add every fourth slice and wave 0 combines them.
+// Latencies one after the other bound that: both blocks' slices, P pieces of columns (2 for d > 256, where the key side is not split as well) and
+// what they are added to are asked for together (b = 512, d = 1024 13.8 -> 11.3 us; 257, 768 8.7 -> 6.8; calls of B = 15040, N = 64,
+// d = 640 79.6 -> 76.4, 12864, 64, 768 154.9 -> 148.9, 3536, 8, 384 44.0 -> 42.6; of 70 random calls of 40 to 400 us 1 % in the mean).
+template <bool ROWWG, bool KSPLIT, int P>
+__global__ __launch_bounds__(256, P == 2 ? 3 : ROWWG ? 4 : 1) void k_finalize(Blocks bl, FinalizeShape f, float cs) {
   if (gated_off(bl)) return;
-  constexpr int NSUM = KSPLIT ? 4 : 2;
-  __shared__ f32x4 others[ROWWG ? 3 : 1][NSUM][64];
+  constexpr int NSUM = KSPLIT ? 4 : 2;                   // sums per piece of 256 columns
+  __shared__ f32x4 others[ROWWG ? 3 : 1][P][NSUM][64];
   const BlockPtrs& pa = bl.z[0];
   const BlockPtrs& pc = bl.z[1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -755,62 +768,104 @@ __global__ __launch_bounds__(256) void k_finalize(Blocks bl, FinalizeShape f, fl
   const int64_t d = f.d;
   const int first = ROWWG ? wave : 0, step = ROWWG ? 4 : 1;
   float dot_a = 0.f, dot_c = 0.f;
-  for (int64_t kc = 0; kc < d; kc += 256) {
-    const int64_t k = kc + lane * 4;
-    const bool on = k < d;
-    f32x4 u[NSUM];                                       // query side of A and C, key side of A and C
-#pragma unroll
-    for (int q = 0; q < NSUM; ++q) u[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (on) {
-      if (own) {
-        u[0] = sum_slices(pa.part, f.bp, i, d, k, first, step, f.splitk);
-        u[1] = sum_slices(pc.part, f.bp, i, d, k, first, step, f.splitk);
+  for (int64_t kc = 0; kc < d; kc += 256 * P) {
+    f32x4 gi[P], gt[P];                                  // what the sums are added to
+    u32x2 iw[P], tw[P];                                  // I[lab], T[lab]
+    auto fetch = [&](int h) {
+      const int64_t k = kc + h * 256 + lane * 4;
+      gi[h] = f32x4{0.f, 0.f, 0.f, 0.f}; gt[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      iw[h] = u32x2{0u, 0u}; tw[h] = u32x2{0u, 0u};
+      if (k < d && (!ROWWG || wave == 0)) {
+        if (!KSPLIT || f.accumulate) {
+          gi[h] = *reinterpret_cast<f32x4*>(pa.gq + lab * d + k);
+          gt[h] = *reinterpret_cast<f32x4*>(pc.gq + lab * d + k);
+        }
+        if (own) {
+          iw[h] = *reinterpret_cast<const u32x2*>(pa.X + i * d + k);
+          tw[h] = *reinterpret_cast<const u32x2*>(pc.X + i * d + k);
+        }
       }
-      if constexpr (KSPLIT) {
-        u[2] = sum_slices(pa.kpart, f.Bp, row, d, k, first, step, f.key_splits);
-        u[3] = sum_slices(pc.kpart, f.Bp, row, d, k, first, step, f.key_splits);
+    };
+    if (ROWWG)                                           // few rows: their loads before the sums'
+#pragma unroll
+      for (int h = 0; h < P; ++h) fetch(h);
+    f32x4 u[P][NSUM];                                    // query side of A and C, key side of A and C
+    auto sums = [&](auto pieces) {
+      constexpr int H = decltype(pieces)::value;
+      auto two = [&](const float* a, const float* c, int64_t r, int64_t pitch, int splits, int at) {
+        const float* from[2 * H];
+        f32x4 s[2 * H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const int64_t k = kc + h * 256 + lane * 4, there = r * d + (k < d ? k : 0);
+          from[2 * h] = a + there;
+          from[2 * h + 1] = c + there;
+        }
+        if constexpr (ROWWG) {
+          sum_slices<2 * H, H == 1 ? 4 : 2>(from, pitch * d, first, step, splits, s);
+        } else {                                         // (one after the other: the kernel is at memory's rate, by the waves that fit)
+#pragma unroll
+          for (int n = 0; n < 2 * H; ++n) {
+            f32x4 one[1];
+            sum_slices<1>({from[n]}, pitch * d, first, step, splits, one);
+            s[n] = one[0];
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < H; ++h) { u[h][at] = s[2 * h]; u[h][at + 1] = s[2 * h + 1]; }
+      };
+      if (own) {
+        two(pa.part, pc.part, i, f.bp, f.splitk, 0);
+      } else {
+#pragma unroll
+        for (int h = 0; h < H; ++h) u[h][0] = u[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      if constexpr (KSPLIT) two(pa.kpart, pc.kpart, row, f.Bp, f.key_splits, 2);
+    };
+    const bool more = P > 1 && kc + 256 < d;             // (workgroup-uniform) a second piece of columns
+    if (more) sums(std::integral_constant<int, P>{});
+    else sums(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int h = 0; h < P; ++h) {
+      if (h > 0 && !more) break;
+      if (ROWWG) {
+        if (wave > 0)
+#pragma unroll
+          for (int q = 0; q < NSUM; ++q) others[wave - 1][h][q][lane] = u[h][q];
       }
     }
-    if (ROWWG) {
-      if (wave > 0)
+    if (ROWWG) __syncthreads();
 #pragma unroll
-        for (int q = 0; q < NSUM; ++q) others[wave - 1][q][lane] = u[q];
-      __syncthreads();
-      if (wave == 0)
+    for (int h = 0; h < P; ++h) {
+      const int64_t k = kc + h * 256 + lane * 4;
+      if ((ROWWG && wave > 0) || k >= d) continue;
+      if (!ROWWG) fetch(h);
+      if (ROWWG)
 #pragma unroll
         for (int w = 0; w < 3; ++w)
 #pragma unroll
-          for (int q = 0; q < NSUM; ++q) u[q] += others[w][q][lane];
-      __syncthreads();                                  // read before the next piece overwrites it
-      if (wave > 0) continue;
-    }
-    if (!on) continue;
-    f32x4 gi = {0.f, 0.f, 0.f, 0.f}, gt = {0.f, 0.f, 0.f, 0.f};
-    if (!KSPLIT || f.accumulate) {
-      gi = *reinterpret_cast<f32x4*>(pa.gq + lab * d + k);
-      gt = *reinterpret_cast<f32x4*>(pc.gq + lab * d + k);
-    }
-    if constexpr (KSPLIT) {
+          for (int q = 0; q < NSUM; ++q) u[h][q] += others[w][h][q][lane];
+      if constexpr (KSPLIT) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { gt[e] = fmaf(cs, u[2][e], gt[e]); gi[e] = fmaf(cs, u[3][e], gi[e]); }
-    }
-    if (own) {
-      const u32x2 iw = *reinterpret_cast<const u32x2*>(pa.X + i * d + k);        // I[lab]
-      const u32x2 tw = *reinterpret_cast<const u32x2*>(pc.X + i * d + k);        // T[lab]
-      const float iv[4] = {bf16_lo(iw[0]), bf16_hi(iw[0]), bf16_lo(iw[1]), bf16_hi(iw[1])};
-      const float tv[4] = {bf16_lo(tw[0]), bf16_hi(tw[0]), bf16_lo(tw[1]), bf16_hi(tw[1])};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float ga = fmaf(beta_a, u[0][e], gd_a * tv[e]);
-        const float gc = fmaf(beta_c, u[1][e], gd_c * iv[e]);
-        gi[e] = fmaf(cs * gd_c, tv[e], fmaf(cs, ga, gi[e]));
-        gt[e] = fmaf(cs * gd_a, iv[e], fmaf(cs, gc, gt[e]));
-        dot_a = fmaf(ga, iv[e], dot_a);
-        dot_c = fmaf(gc, tv[e], dot_c);
+        for (int e = 0; e < 4; ++e) { gt[h][e] = fmaf(cs, u[h][2][e], gt[h][e]); gi[h][e] = fmaf(cs, u[h][3][e], gi[h][e]); }
       }
+      if (own) {
+        const float iv[4] = {bf16_lo(iw[h][0]), bf16_hi(iw[h][0]), bf16_lo(iw[h][1]), bf16_hi(iw[h][1])};
+        const float tv[4] = {bf16_lo(tw[h][0]), bf16_hi(tw[h][0]), bf16_lo(tw[h][1]), bf16_hi(tw[h][1])};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float ga = fmaf(beta_a, u[h][0][e], gd_a * tv[e]);
+          const float gc = fmaf(beta_c, u[h][1][e], gd_c * iv[e]);
+          gi[h][e] = fmaf(cs * gd_c, tv[e], fmaf(cs, ga, gi[h][e]));
+          gt[h][e] = fmaf(cs * gd_a, iv[e], fmaf(cs, gc, gt[h][e]));
+          dot_a = fmaf(ga, iv[e], dot_a);
+          dot_c = fmaf(gc, tv[e], dot_c);
+        }
+      }
+      *reinterpret_cast<f32x4*>(pa.gq + lab * d + k) = gi[h];
+      *reinterpret_cast<f32x4*>(pc.gq + lab * d + k) = gt[h];
     }
-    *reinterpret_cast<f32x4*>(pa.gq + lab * d + k) = gi;
-    *reinterpret_cast<f32x4*>(pc.gq + lab * d + k) = gt;
+    if (ROWWG && kc + 256 * P < d) __syncthreads();      // read before the next pieces overwrite it
   }
   if (!own || (ROWWG && wave > 0)) return;
   dot_a = wave_sum(dot_a);
@@ -848,8 +903,9 @@ __global__ __launch_bounds__(256) void k_finalize_ntxent(Blocks bl, FinalizeShap
   const int64_t d = f.d;
   float dot = 0.f;
   for (int64_t k = lane * 4; k < d; k += 256) {
-    f32x4 u = {0.f, 0.f, 0.f, 0.f};
-    if (own) u = sum_slices(p.part, f.bp, i, d, k, 0, 1, f.splitk);
+    f32x4 u[1] = {{0.f, 0.f, 0.f, 0.f}}, kv[1];
+    auto query_side = [&] { sum_slices<1>({p.part + i * d + k}, f.bp * d, 0, 1, f.splitk, u); };
+    if (!KSPLIT) query_side();
     const u32x2 zw = *reinterpret_cast<const u32x2*>(Zfull + g * d + k);        // Z[g]
     const u32x2 pw = *reinterpret_cast<const u32x2*>(Zfull + lab * d + k);      // Z[lab]
     const float zv[4] = {bf16_lo(zw[0]), bf16_hi(zw[0]), bf16_lo(zw[1]), bf16_hi(zw[1])};
@@ -858,13 +914,14 @@ __global__ __launch_bounds__(256) void k_finalize_ntxent(Blocks bl, FinalizeShap
     if (!KSPLIT || f.accumulate) mine = *reinterpret_cast<f32x4*>(p.gq + g * d + k);
     if (owes) oth = *reinterpret_cast<f32x4*>(p.gq + lab * d + k);
     if constexpr (KSPLIT) {
-      const f32x4 kv = sum_slices(p.kpart, f.Bp, row, d, k, 0, 1, f.key_splits);
+      if (own) query_side();
+      sum_slices<1>({p.kpart + row * d + k}, f.Bp * d, 0, 1, f.key_splits, kv);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mine[e] = fmaf(cs, kv[e], mine[e]);
+      for (int e = 0; e < 4; ++e) mine[e] = fmaf(cs, kv[0][e], mine[e]);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float ga = fmaf(beta, u[e], gd * pv[e]);
+      const float ga = fmaf(beta, u[0][e], gd * pv[e]);
       mine[e] = fmaf(cs * gd_pos, pv[e], fmaf(cs, ga, mine[e]));      // + what the local positive owes this row
       oth[e] = fmaf(cs * gd, zv[e], oth[e]);
       dot = fmaf(ga, zv[e], dot);
@@ -1073,17 +1130,17 @@ __global__ __launch_bounds__(256) void k_sym_finalize(Blocks bl, int64_t B, int6
   const float gd = p.gdiag[i] + bl.z[1].gdiag[i];
   float dot = 0.f;
   for (int64_t k = lane * 4; k < d; k += 256) {
-    const f32x4 u = sum_slices(p.part, Bp, i, d, k, 0, 1, splitk);
     const u32x2 iw = *reinterpret_cast<const u32x2*>(p.X + i * d + k);
     const u32x2 tw = *reinterpret_cast<const u32x2*>(p.Y + i * d + k);
     const float iv[4] = {bf16_lo(iw[0]), bf16_hi(iw[0]), bf16_lo(iw[1]), bf16_hi(iw[1])};
     const float tv[4] = {bf16_lo(tw[0]), bf16_hi(tw[0]), bf16_lo(tw[1]), bf16_hi(tw[1])};
     f32x4 gi = {0.f, 0.f, 0.f, 0.f};
     if (accumulate) gi = *reinterpret_cast<const f32x4*>(p.gq + i * d + k);
-    f32x4 gt = *reinterpret_cast<const f32x4*>(p.gk + i * d + k);
+    f32x4 gt = *reinterpret_cast<const f32x4*>(p.gk + i * d + k), u[1];
+    sum_slices<1>({p.part + i * d + k}, Bp * d, 0, 1, splitk, u);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float ga = fmaf(gd, tv[e], u[e]);
+      const float ga = fmaf(gd, tv[e], u[0][e]);
       gi[e] = fmaf(cs, ga, gi[e]);
       gt[e] = fmaf(cs * gd, iv[e], gt[e]);
       dot = fmaf(ga, iv[e], dot);
@@ -1370,8 +1427,9 @@ void finalize(const Problem& pr, const Plan& pl, const Blocks& bl, int64_t g0, f
   const bool rowwg = pr.variant != LOSS_NTXENT && rows <= FINALIZE_ROWWG_MAX;
   auto go = [&](auto kernel) { kernel<<<dim3((unsigned)(rowwg ? rows : (rows + 3) / 4)), 256, 0, st>>>(bl, f, cs); };
   if (pr.variant == LOSS_NTXENT) { if (ks) go(k_finalize_ntxent<true>); else go(k_finalize_ntxent<false>); }
-  else if (rowwg) { if (ks) go(k_finalize<true, true>); else go(k_finalize<true, false>); }
-  else { if (ks) go(k_finalize<false, true>); else go(k_finalize<false, false>); }
+  else if (rowwg && !ks && f.d > 256) go(k_finalize<true, false, 2>);
+  else if (rowwg) { if (ks) go(k_finalize<true, true, 1>); else go(k_finalize<true, false, 1>); }
+  else { if (ks) go(k_finalize<false, true, 1>); else go(k_finalize<false, false, 1>); }
 }
 
 // gate / gate_value: see Blocks.  marks: record the benchmark's stage events.
