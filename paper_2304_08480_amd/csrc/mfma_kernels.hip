@@ -325,59 +325,70 @@ constexpr float LN2 = 0.6931471805599453f;
 
 // beta, P_label - 1 and the cross-entropy of row i, from its off-label sum, its label numerator and their total, to memory.
 // ce = log(tot / ed); when the label numerator does not dominate it is taken from the exponents,
-// log(tot) - (z2_label - ref2) ln 2, which stays finite when ed itself has underflowed.
-__device__ __forceinline__ void row_outputs(const BlockPtrs& p, int64_t i, float off, float ed, float tot) {
+// log(tot) - z_label ln 2 with z_label = z2_label - ref2, which stays finite when ed itself has underflowed.
+__device__ __forceinline__ void row_outputs(const BlockPtrs& p, int64_t i, float off, float ed, float tot, float z_label) {
   p.beta[i] = 1.f / tot;
   p.gdiag[i] = -off / tot;
-  p.ce[i] = (ed > 0.5f * tot) ? log1pf(off / ed) : logf(tot) - (p.zd2[i] - p.ref2[i]) * LN2;
+  p.ce[i] = (ed > 0.5f * tot) ? log1pf(off / ed) : logf(tot) - z_label * LN2;
 }
 
-// Xs[k][i] = bf16(scale_i x_ik), kbegin <= k < kend (multiples of 64), for the nrows (a multiple of 64) rows from i0 on, scale = the nrows floats at `scale`
+// Xs[k][i] = bf16(scale_i x_ik), kbegin <= k < kend (multiples of 64), for the 64 rows from i0 on, scale = the 64 floats at `scale`
 // in LDS (nullptr: 1): the key-side contraction's right operand, with its reduction index contiguous.  All NTH threads
 // of the workgroup (256, 512 or 1024), zeros for the rows from `rows` on, 64 x 64 pieces through `tile` (64 x 65 floats of LDS).  The pieces of up to eight
 // 64-feature tiles are fetched before the first is turned round, so that their loads are in flight together.
+constexpr int TURN_AHEAD = 8;                             // 64-feature tiles fetched together
 template <int NTH>
-__device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t rows, int64_t b, int64_t d, int64_t kbegin, int64_t kend, int64_t i0, int nrows, const float* scale,
-                                                     float (*tile)[65]) {
-  constexpr int NPT = 1024 / NTH, AHEAD = 8;              // pieces of 4 features per thread and tile; tiles per batch
-  const int t = threadIdx.x;
-  for (int r0 = 0; r0 < nrows; r0 += 64)
-    for (int64_t kc = kbegin; kc < kend; kc += 64 * AHEAD) {
-      u32x2 w[AHEAD][NPT];
+using TurnPieces = u32x2[TURN_AHEAD][1024 / NTH];         // pieces of 4 features per thread and tile
+
+// the pieces of the 64 rows from i0 on (64 rows x 16 pieces a tile), features kc .. of those below kend
+template <int NTH>
+__device__ __forceinline__ void fetch_rows(const BlockPtrs& p, int64_t rows, int64_t d, int64_t kc, int64_t kend, int64_t i0, TurnPieces<NTH>& w) {
 #pragma unroll
-      for (int a = 0; a < AHEAD; ++a)
-        if (kc + a * 64 < kend)
+  for (int a = 0; a < TURN_AHEAD; ++a)
+    if (kc + a * 64 < kend)
 #pragma unroll
-          for (int q = 0; q < NPT; ++q) {                 // 64 rows x 16 pieces of 4 features
-            const int e = t + q * NTH, r = e >> 4, c4 = (e & 15) * 4;
-            w[a][q] = u32x2{0u, 0u};
-            if (i0 + r0 + r < rows) w[a][q] = *reinterpret_cast<const u32x2*>(p.X + (i0 + r0 + r) * d + kc + a * 64 + c4);
-          }
-#pragma unroll
-      for (int a = 0; a < AHEAD; ++a) {
-        const int64_t k0 = kc + a * 64;
-        if (k0 >= kend) break;
-        __syncthreads();                                  // the tile's previous contents have been read
-#pragma unroll
-        for (int q = 0; q < NPT; ++q) {
-          const int e = t + q * NTH, r = e >> 4, c4 = (e & 15) * 4;
-          const float sc = scale ? scale[r0 + r] : 1.f;
-          tile[r][c4 + 0] = sc * bf16_lo(w[a][q][0]);
-          tile[r][c4 + 1] = sc * bf16_hi(w[a][q][0]);
-          tile[r][c4 + 2] = sc * bf16_lo(w[a][q][1]);
-          tile[r][c4 + 3] = sc * bf16_hi(w[a][q][1]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < NPT; ++q) {                   // 64 features x 16 pieces of 4 rows
-          const int e = t + q * NTH, k = e >> 4, i4 = (e & 15) * 4;
-          bf16x4 v;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = (__bf16)tile[i4 + j][k];
-          *reinterpret_cast<bf16x4*>(p.Xs + (k0 + k) * b + i0 + r0 + i4) = v;
-        }
+      for (int q = 0; q < 1024 / NTH; ++q) {
+        const int e = threadIdx.x + q * NTH, r = e >> 4, c4 = (e & 15) * 4;
+        w[a][q] = u32x2{0u, 0u};
+        if (i0 + r < rows) w[a][q] = *reinterpret_cast<const u32x2*>(p.X + (i0 + r) * d + kc + a * 64 + c4);
       }
+}
+template <int NTH>
+__device__ __forceinline__ void turn_rows(const BlockPtrs& p, int64_t b, int64_t kc, int64_t kend, int64_t i0, const float* scale, float (*tile)[65], const TurnPieces<NTH>& w) {
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int a = 0; a < TURN_AHEAD; ++a) {
+    const int64_t k0 = kc + a * 64;
+    if (k0 >= kend) break;
+    __syncthreads();                                      // the tile's previous contents have been read
+#pragma unroll
+    for (int q = 0; q < 1024 / NTH; ++q) {
+      const int e = t + q * NTH, r = e >> 4, c4 = (e & 15) * 4;
+      const float sc = scale ? scale[r] : 1.f;
+      tile[r][c4 + 0] = sc * bf16_lo(w[a][q][0]);
+      tile[r][c4 + 1] = sc * bf16_hi(w[a][q][0]);
+      tile[r][c4 + 2] = sc * bf16_lo(w[a][q][1]);
+      tile[r][c4 + 3] = sc * bf16_hi(w[a][q][1]);
     }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 1024 / NTH; ++q) {                // 64 features x 16 pieces of 4 rows
+      const int e = t + q * NTH, k = e >> 4, i4 = (e & 15) * 4;
+      bf16x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = (__bf16)tile[i4 + j][k];
+      *reinterpret_cast<bf16x4*>(p.Xs + (k0 + k) * b + i0 + i4) = v;
+    }
+  }
+}
+template <int NTH>
+__device__ __forceinline__ void scale_transpose_rows(const BlockPtrs& p, int64_t rows, int64_t b, int64_t d, int64_t kbegin, int64_t kend, int64_t i0, const float* scale,
+                                                     float (*tile)[65]) {
+  for (int64_t kc = kbegin; kc < kend; kc += 64 * TURN_AHEAD) {
+    TurnPieces<NTH> w;
+    fetch_rows<NTH>(p, rows, d, kc, kend, i0, w);
+    turn_rows<NTH>(p, b, kc, kend, i0, scale, tile, w);
+  }
 }
 
 // The statistics of 64 rows redone by the workgroup of k_row_merge that found one whose total is lost (inputs that are not
@@ -530,6 +541,8 @@ struct MergeShape {
 // sixteenth of the column parts (lane = row, so the reads are coalesced), combined in fixed order.  A small share has few
 // such workgroups, each of which would turn round all of its rows' features: fchunks of them then share the features of
 // the same rows, and all but the first add up the totals for themselves only (b = 512, d = 512: 9.3 -> 6.8 us with eight).
+// Latencies bound it: the features and the row's own values do not wait for the totals (us a call: B = 4096, N = 16, d = 192 35.1 -> 33.0; 5072,
+// 16, 256 40.2 -> 38.7; 2048, 2, 320 43.2 -> 42.4; of 39 random calls of 33 to 540 us 1 % in the mean).
 __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
   if (gated_off(bl)) return;
   const int64_t b = f.b;
@@ -541,6 +554,16 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
   const BlockPtrs& p = bl.z[blockIdx.y];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+  // The features that the end of the kernel turns round and what wave 0 needs of a row, asked for before the totals.
+  const int64_t per = f.fchunks ? (f.d / 64 + f.fchunks - 1) / f.fchunks * 64 : 0, kz = blockIdx.z * per, kend = kz + per < f.d ? kz + per : f.d;
+  TurnPieces<1024> w;
+  if (f.fchunks) fetch_rows<1024>(p, bl.rows, f.d, kz, kend, i0, w);
+  float ed0 = 0.f, zd = 0.f, ref = 0.f;
+  if (wave == 0) {
+    ed0 = p.ediag[i];
+    zd = p.zd2[i];
+    ref = f.global_ref ? *f.global_ref : p.ref2[i];
+  }
   float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f, most = 0.f;           // most: the row's largest part
   int q = wave;
   for (; q + 112 < nparts; q += 128) {                   // eight loads in flight
@@ -580,32 +603,35 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
     }
     const float tot = off + ed;
     beta_s[lane] = 1.f / tot;
-    if (writer) row_outputs(p, i, off, ed, tot);
+    if (writer) row_outputs(p, i, off, ed, tot, zd - ref);
     return f.bad_flag ? !(tot >= ROW_TOTAL_FLOOR) : tot < ROW_TOTAL_FLOOR;
   };
   if (wave == 0) {
     float off = 0.f;
 #pragma unroll
     for (int w = 0; w < 16; w += 4) off += (red[w][lane] + red[w + 1][lane]) + (red[w + 2][lane] + red[w + 3][lane]);
-    if (f.global_ref && writer) p.ref2[i] = *f.global_ref;
-    const bool lost = __any(finish(off, p.ediag[i])), above = __any(lane < 16 && over[lane & 15]);
+    if (f.global_ref && writer) p.ref2[i] = ref;
+    const bool lost = __any(finish(off, ed0)), above = __any(lane < 16 && over[lane & 15]);
     if (lane == 0) {
       redo = (lost || above) && !f.bad_flag;
       if (lost && f.bad_flag) *f.bad_flag = 1;
     }
   }
   __syncthreads();
-  int chunks = f.fchunks;
   if (redo) {                                           // by the first of the workgroups on these rows, which goes on to all of their features
     if (!writer) return;
-    chunks = 1;
     redo_rows(p, bl.variant, bl.rows, bl.keys, f.Bp, f.d, i0, f.g0, f.s2, f.store, red, ref_s, off_s, ed_s, reinterpret_cast<char*>(tile));
-    if (wave == 0) finish(off_s[lane], ed_s[lane]);
+    if (wave == 0) {
+      ref = ref_s[lane];
+      finish(off_s[lane], ed_s[lane]);
+    }
     __syncthreads();
+    if (f.fchunks) scale_transpose_rows<1024>(p, bl.rows, b, f.d, 0, f.d, i0, beta_s, tile);
+    return;
   }
   if (f.fchunks) {
-    const int64_t per = (f.d / 64 + chunks - 1) / chunks * 64, k0 = blockIdx.z * per;
-    scale_transpose_rows<1024>(p, bl.rows, b, f.d, k0, k0 + per < f.d ? k0 + per : f.d, i0, 64, beta_s, tile);
+    turn_rows<1024>(p, b, kz, kend, i0, beta_s, tile, w);
+    scale_transpose_rows<1024>(p, bl.rows, b, f.d, kz + 64 * TURN_AHEAD, kend, i0, beta_s, tile);
   }
 }
 
@@ -614,7 +640,7 @@ __global__ __launch_bounds__(1024) void k_row_merge(Blocks bl, MergeShape f) {
 __global__ __launch_bounds__(1024) void k_transpose(Blocks bl, int64_t b, int64_t d) {
   if (gated_off(bl)) return;
   __shared__ float tile[64][65];
-  scale_transpose_rows<1024>(bl.z[0], bl.rows, b, d, 0, d, (int64_t)blockIdx.x * 64, 64, nullptr, tile);
+  scale_transpose_rows<1024>(bl.z[0], bl.rows, b, d, 0, d, (int64_t)blockIdx.x * 64, nullptr, tile);
 }
 
 // The two gradient contractions of every block, in one launch: they are independent of each other, so where neither has
