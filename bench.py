@@ -244,9 +244,13 @@ def main():
         names = ["similarity", "row_softmax", "scalars", "gradients", "finalize"]     # (both gradient sides are one launch)
         dom = dom_stage
         dom_flops = (8.0 if dom == 3 else 4.0) * b * B * d
-        # large calls run every fp32 product as six bf16 plane products (fp32 times bf16: three), small ones with fp32 features
-        # on the fp32 instruction
-        peak = PEAK_BF16_TFLOPS / 3 if feat_dtype == "bf16" else PEAK_BF16_TFLOPS / 6 if plan.kernels == dl.DISCO_KERNELS_SPLIT else PEAK_FP32_TFLOPS
+        # large calls run every fp32 product as fp16 plane products, four a logit and three a gradient entry (bf16 features: one and
+        # two; on the bf16 planes of smaller large calls it is six, so the fraction is then too low, not too high); small ones with
+        # bf16 features as three bf16 plane products, with fp32 features on the fp32 instruction
+        if plan.kernels == dl.DISCO_KERNELS_SPLIT:
+            peak = PEAK_BF16_TFLOPS / ((2 if dom == 3 else 1) if feat_dtype == "bf16" else (3 if dom == 3 else 4))
+        else:
+            peak = PEAK_BF16_TFLOPS / 3 if feat_dtype == "bf16" else PEAK_FP32_TFLOPS
         bound, unit = "mfma", "TFLOP/s"
         dtype = "f32"
     dom_ms = float(stage_avg[dom])

@@ -234,7 +234,7 @@ DISCO_API int disco_set_stage_events(void** events, int count);
 enum { DISCO_KERNELS_SMALL = 0, DISCO_KERNELS_SPLIT = 1, DISCO_KERNELS_TILES = 2, DISCO_KERNELS_SYMMETRIC = 3 };
 typedef struct {
   int32_t path;                     /* what `path` resolves to */
-  int32_t kernels;                  /* fp32 arithmetic: SMALL, or SPLIT (exact bf16 planes); bf16: TILES or SYMMETRIC */
+  int32_t kernels;                  /* fp32 arithmetic: SMALL, or SPLIT (16-bit planes); bf16: TILES or SYMMETRIC */
   int32_t logit_tile, gradient_tile;  /* 128 or 256; 0: SMALL */
   int32_t row_chunks, key_panels;   /* the rank's rows in chunks / the keys in panels, each taken through logits and gradients */
   int32_t query_splits, key_splits; /* of the two gradient reductions */
