@@ -71,7 +71,9 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
 
 /*
  * DISCO_PATH_NAIVE        fp32 arithmetic, either on the fp32 matrix instruction or (large calls) on the 16-bit ones with
- *                         every fp32 operand split into two fp16 planes, or exactly into three bf16 ones where
+ *                         every fp32 operand split into two fp16 planes (22 bits of it at least; gradients as near to
+ *                         64 bits as with the exact planes relative to their largest rows, not to every entry), or
+ *                         exactly into three bf16 ones where
  *                         rows of very different norms leave fp16's range.  Any B, d, N; either dtype.  Asked
  *                         for by name it stays within the fp32 logit blocks' memory (2*b*B*4 bytes, rows rounded up
  *                         to whole 16-byte pieces: the paper's 2B^2/N memory model, Sec. 4.1); where AUTO resolves to

@@ -198,6 +198,51 @@ __device__ __forceinline__ uint32_t bytes_left(int rows, uint32_t col, int64_t l
   return __builtin_amdgcn_readfirstlane(FMT == FMT_K || FMT == FMT_R ? (n > skip ? n - skip : 0u) : 0xffffffffu);
 }
 
+// Rows of the reduction may carry a factor: of the B operand (FMT_R, fp16 planes), row k is multiplied by 2^-(shift[k] - least), at most by 1 and at
+// least by 2^-48, when its 64-deep piece has come and before the barrier hands it on.  In the LDS, by the lanes that loaded it: each 16-byte
+// piece there is one row's, so a lane's factors are its own and nothing else of the loop changes; fp16 ends at 2^-24, so a factor is taken in
+// two halves.  (A copy of the operand made by a launch of its own cost every call 7 us of 201, B = 8192, N = 8, d = 512, mostly for finding nothing to do.)
+struct Unshifted { static constexpr bool ON = false; };
+struct RowShifts {
+  static constexpr bool ON = true;
+  const uint8_t* shift;   // 16-byte aligned; memory that the kernel does not write
+  int least;
+};
+// 2^-k as fp16, 0 <= k <= 24
+__device__ __forceinline__ _Float16 half_power(int k) { return __builtin_bit_cast(_Float16, (uint16_t)(k < 15 ? (15 - k) << 10 : 1 << (24 - k))); }
+
+// The exponents of the rows of piece `piece` that loading wave lw has, 16 (T = 256) or 32 consecutive ones (scalar loads), and their use on what
+// it has loaded into the unit at `lds`.
+template <int T>
+struct Exponents { u32x4 v[256 / T]; };
+template <int T>
+__device__ __forceinline__ Exponents<T> fetch_exponents(const RowShifts& s, int piece, int lw) {
+  typedef const __attribute__((address_space(4))) u32x4* from;
+  const uint64_t at = reinterpret_cast<uint64_t>(uniform_ptr(s.shift + piece * BK + lw * (4096 / T)));
+  Exponents<T> e;
+#pragma unroll
+  for (int i = 0; i < 256 / T; ++i) e.v[i] = reinterpret_cast<from>(at)[i];
+  return e;
+}
+template <int T>
+__device__ __forceinline__ void shift_rows(const Exponents<T>& e, int least, char* lds, int lw, int lane) {
+  // the n-th load instruction brings 64 / PPR rows, PPR = T / 8 pieces each (Operand::init)
+  const int mine = lane / (T / 8) * 8;
+  half8* at = reinterpret_cast<half8*>(lds + NLD * lw * 1024 + lane * 16);
+#pragma unroll
+  for (int h = 0; h < NLD; h += 4) {
+    half8 v[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) v[n] = at[(h + n) * 64];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int byte = (h + n) * (512 / T), below = (int)(e.v[byte / 16][byte % 16 / 4] >> (byte % 4 * 8 + mine) & 255u) - least;
+      const int k = below < 0 ? 0 : below < 48 ? below : 48;
+      at[(h + n) * 64] = v[n] * half_power(k / 2) * half_power(k - k / 2);
+    }
+  }
+}
+
 // format R: what the 32-byte group index of reduction row kap is XOR-ed with
 __device__ __forceinline__ int swizzle_r(int kap) { return (kap & 3) << 1 | (kap >> 3 & 1); }
 
@@ -383,10 +428,11 @@ __device__ __forceinline__ int64_t kstep_elems(int64_t ld) {
 // WRITE_FIRST: the first K-step is peeled off the loop and writes the accumulators (acc = product, acc need not be
 // initialised); else every K-step adds to them (acc += product).  Peeling gains 2-5 % on the gradient GEMMs; in the
 // logit kernel it costs the epilogue registers it does not have.
-template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS, class BD>
+template <int T, int FA, int FB, int GROUP, bool READS_FIRST, bool WRITE_FIRST, class PS, class BD, class SH>
 __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp, int64_t ldb,
-                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b, const BD& bounds) {
+                                      int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b, int64_t plane_a, int64_t plane_b, const BD& bounds, const SH& shifts) {
   static_assert(!BD::ON || PS::N == 1);
+  static_assert(!SH::ON || (PS::HALF && FB == FMT_R));
   constexpr int NFA = Cfg<T>::NFA, NH = NFA / 2, WN = Cfg<T>::WN, UNIT_BYTES = Cfg<T>::UNIT_BYTES;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t stepA = kstep_elems<FA>(lda);
@@ -430,6 +476,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     ob.load_all(from_b(k1), smem + 3 * UNIT_BYTES);
   }
   wait_vmcnt<NLD>();
+  if constexpr (SH::ON && GROUP == 1) shift_rows<T>(fetch_exponents<T>(shifts, step_of(0).piece, wave % WN), shifts.least, smem + UNIT_BYTES, wave % WN, lane);
   lds_barrier();
   FragsA<NH> a0, a1;
   FragsB b0, b1;
@@ -438,6 +485,10 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   read_b<0, 2>(b0, ob, smem_addr + UNIT_BYTES);
   wait_frags(a0, b0);
 
+  auto next_exponents = [&](int kt) {               // of the K-step after kt
+    if constexpr (SH::ON && GROUP == 1) return fetch_exponents<T>(shifts, step_of(kt < last ? kt + 1 : last).piece, wave % WN);
+    else return 0;
+  };
   int rA = 0;                                       // unit of A(kt); B(kt) is the next unit of the ring
   // One K-step (FIRST: its first products write the accumulators instead of adding to them; LOADS: it asks for K-step kt + 2, or,
   // in a reduction of one or two, which the first K-step of WRITE_FIRST may be, for the last again, into units nobody reads).  On entry a0 and b0 hold the first
@@ -448,6 +499,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     const uint32_t ta = smem_addr + (uint32_t)(rA * UNIT_BYTES), tb = smem_addr + (uint32_t)(rB * UNIT_BYTES);             \
     const uint32_t tna = smem_addr + (uint32_t)(nA * UNIT_BYTES), tnb = smem_addr + (uint32_t)(nB * UNIT_BYTES);           \
     const int kload = kt + 2 < ktiles ? kt + 2 : last;                                                                     \
+    const auto exponents = next_exponents(kt);                                                                             \
     /* sub-step 0 */                                                                                                       \
     read_a<0, 1>(a1, oa, ta);                                                                                              \
     read_b<1, 0>(b1, ob, tb);                                                                                              \
@@ -470,6 +522,10 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     if (GROUP == 0 && LOADS) wait_vmcnt<NLD>(); else wait_vmcnt<0>();                                                               \
     wait_frags(a1, b1);                                                                                                    \
+    if constexpr (SH::ON && GROUP == 1) {                                                                                  \
+      shift_rows<T>(exponents, shifts.least, smem + nB * UNIT_BYTES, wave % WN, lane);                                     \
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                                                   \
+    }                                                                                                                      \
     asm volatile("s_barrier" ::: "memory");                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                                     \
     /* sub-step 3 */                                                                                                       \
@@ -511,12 +567,13 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
 //   nvalid_b: rows of the B tile that exist in memory (multiple of 8, <= T); the output columns from
 //             nvalid_b on are then meaningless and must not be stored.
 //   bounds  : see Whole and Bounded.
-template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false, class PS = Planes<1, 1>, class BD = Whole>
+//   shifts  : see Unshifted and RowShifts.
+template <int T, int FA, int FB, bool READS_FIRST, bool WRITE_FIRST = false, class PS = Planes<1, 1>, class BD = Whole, class SH = Unshifted>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ Bp,
                                          int64_t ldb, int ktiles, char* smem, Acc<Cfg<T>::NFA>& acc, int nvalid_b = T,
-                                         int64_t plane_a = 0, int64_t plane_b = 0, const BD& bounds = BD{}) {
-  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST, PS, BD>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds);
-  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST, PS, BD>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds);
+                                         int64_t plane_a = 0, int64_t plane_b = 0, const BD& bounds = BD{}, const SH& shifts = SH{}) {
+  if (threadIdx.x < Cfg<T>::NTHREADS / 2) kloop<T, FA, FB, 0, READS_FIRST, WRITE_FIRST, PS, BD, SH>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds, shifts);
+  else kloop<T, FA, FB, 1, READS_FIRST, WRITE_FIRST, PS, BD, SH>(A, lda, Bp, ldb, ktiles, smem, acc, nvalid_b, plane_a, plane_b, bounds, shifts);
 }
 
 // Writes a workgroup's T x T fp32 accumulator tile to row-major global memory through LDS, so that

@@ -2,15 +2,20 @@
 // whose products are exact in the instruction and summed in fp32.  Two forms:
 //   fp16   two planes of 11 significand bits each.  A logit is four plane products, a gradient entry three (bf16 features, one plane: one
 //          and two).  What the planes leave out of a value is 0 three times in four, else 2^-24 to 2^-23 of it; the product left out of a gradient is
-//          2^-24.6 (root mean square).  fp16's range is what features have to keep to (k_feature_halves tests them on the device).
+//          2^-24.6 (root mean square).  fp16's range is what features have to keep to (k_feature_halves tests them on the device).  Rows of
+//          gradient entries that it would be too narrow for are multiplied by a power of two of their own (row_shift).
 //   bf16   three planes of 8 bits, which add up to the value exactly over nearly all of fp32's range: six plane products (three against bf16
 //          features; one between them).  The six leave out 2^-27.5 of a product (root mean square; the worst case is 2^-24).  For
 //          features that the fp16 form cannot hold, and for calls too small to gain from it.
 // One product over the whole reduction follows the other, the smallest first (SWEEPS), so that only the last one rounds at the size of
-// the result: that is what decides the errors, and why the fp16 form's are no larger although its planes hold a bit less.  Against 64 bits, fp32
-// features, 2-norm of the gradients, fp16 over bf16 planes (logits in sweeps, gradients piece by piece), mean of 61 calls drawn over sizes, widths and
-// positives: 0.81 at s = 1/0.07, 0.96 at 30, 0.93 at 100; B = 8192, N = 8, d = 512 6.04e-7 -> 5.6e-7; 12288, 4, 256 4.9e-7 -> 2.7e-7.
-// (Gradients piece by piece on fp16 planes: 1.0 in the mean, but 1.33 at B = 4096, N = 16, d = 64.)
+// the result: that is what decides the errors where logits are small, and why the fp16 form's are mostly no larger although its planes hold a bit less.
+// Against 64 bits, 2-norm of the gradients, fp16 over bf16 planes (logits in sweeps, gradients piece by piece), mean over 8 shapes, B = 2048 to 12288,
+// d = 64 to 2560, both dtypes, by the positives' cosine and s = 1/0.07, 30, 50, 100:
+//   0.89  1.00 1.03 0.97 0.98      0.64  0.93 1.01 0.96 0.95      0.38  0.72 0.95 0.90 0.96      0.27  0.69 0.88 1.00 0.97
+// Large multipliers show the features' lost bits where nothing larger hides them: fp32 features, cosines up to 0.4, s = 100: 1.23 at d = 64, 1.1 at 100 to 192, 1.05 from
+// 256 on (4e-7 to 2e-6 of the gradient's norm either way).
+// What is relative to the largest rows is a gradient as a whole: entries and rows of it as far below them as 2^-35 of a row of G (2^-51 of 1 in rows of
+// more than 2^-16) keep fewer bits than bf16 planes leave them, and can be 0.  (s = 100, d = 64, keys of other ranks.)
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
 // (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); six bf16 products at 1.2 PFLOP/s are 200 TFLOP/s
@@ -21,7 +26,7 @@
 // Per block (X: the rank's rows, Y: all rows):
 //   planes    features -> planes, rows padded with zeros to whole tiles, columns to whole 64-deep K-steps
 //   logits    S = X Y^T in fp32 (b x B)
-//   softmax   row by row against the row's true maximum: loss terms, G = softmax - onehot as planes
+//   softmax   row by row against the row's true maximum: loss terms, G = softmax - onehot as planes (fp16: times the row's own power of two)
 //   grads     gY = cs G^T X (key side) and the split-K partial sums of G Y (query side), one launch
 //   finalize  partial sums into the gradients, loss and d/ds
 // The rows are taken in chunks where the whole would need more memory than the fp32 blocks of the small kernels do.
@@ -33,13 +38,19 @@ namespace {
 
 using namespace tile;
 
-// Written on the device by k_feature_halves and k_feature_planes: in which form the call's features and gradient entries are kept.
+// Written on the device by k_feature_halves, k_feature_planes and the softmax: in which form the call's features and gradient entries are kept.
 struct HalfHead {
   uint32_t half;         // 1: fp16 planes, 0: bf16 planes
   float unscale[2];      // what undoes the power of two that the features of I (of T) are multiplied with
+  uint32_t shifted;      // some row of G is multiplied by a power of two of its own
 };
 constexpr int HALF_FLAGS = 1024;                         // workgroups of k_feature_halves at most, a flag each
 constexpr float G_SCALE = 0x1p15f, REST_SCALE = 0x1p11f; // fp16 planes of a gradient entry: see store_unit_halves
+// Rows of G whose largest entry is below 2^-16 are multiplied by the power of two that brings it to [2^-12, 2^-11) (by 2^100 at most: an entry
+// of 2^-112, about where bf16 planes end).  Higher up they would keep more of their own small entries, but a row that lies beside undecided ones moves
+// that much of its power of two into the features' planes (RowShifts of mfma_tile.h).
+constexpr int ROW_LEAST_EXP = -16, ROW_SHIFTED_EXP = -12, ROW_SHIFT_MOST = 100;
+constexpr uint8_t NO_ROW = 255;
 
 struct SplitBlock {
   const uint16_t* X;     // planes of the rank's rows: the first of the chunk
@@ -52,6 +63,7 @@ struct SplitBlock {
   float* gk;             // key-side destination
   float* ce;             // b: cross-entropy of the rank's rows
   float* ds;             // b: row shares of d/ds
+  uint8_t* shift;        // (fp16) rows of the chunk: the exponent of the row's power of two, 255 for a row of zeros
 };
 struct SplitArgs {
   SplitBlock z[2];
@@ -65,7 +77,7 @@ struct SplitArgs {
   int nMq, nMk, nN;      // gradient tiles: query rows, key rows, columns
   int splitk, ktps, key_splits, key_ktps;  // splits of the two reductions and their length in 64-deep pieces
   int q_wgs;
-  const HalfHead* head;  // null: bf16 planes
+  HalfHead* head;        // null: bf16 planes
 };
 
 // v = p[0] + p[1] + p[2], to the last bit while the last plane stays above the smallest bf16 (a value above about 2^-109).  (A value whose leading plane
@@ -116,7 +128,8 @@ __device__ __forceinline__ void store_unit_planes(uint16_t* dst, int64_t plane, 
 }
 
 // The fp16 planes of four gradient entries x m / 2^15 (values of [-1, 1] or NaN): g 2^15 = h + l 2^-11, h and l of 11 significand bits each, so
-// that h keeps all of them down to |g| = 2^-29 and l down to 2^-28.  (x m 2^11 is rounded as x m is, so the fused product-sum below is exact; it
+// that h keeps all of them down to |g| = 2^-29 and l down to 2^-28.  What both leave out of an entry is 2^-51 at most, so rows of nothing larger than 2^-16
+// are multiplied up first (row_shift): it is then 2^-35 of a row's largest entry at most.  (x m 2^11 is rounded as x m is, so the fused product-sum below is exact; it
 // and the conversion are one instruction.  h passes through an empty asm statement because the compiler would otherwise form the h
 // that l is taken from a second time, by an instruction that rounds x m once where the stored one is rounded twice.)
 __device__ __forceinline__ void store_unit_halves(uint16_t* dst, int64_t plane, const f32x4& x, float m) {
@@ -132,6 +145,14 @@ __device__ __forceinline__ void store_unit_halves(uint16_t* dst, int64_t plane, 
   *reinterpret_cast<u32x2*>(dst) = w;
   *reinterpret_cast<half4*>(dst + plane) = l;
 }
+
+// The exponent of the power of two that a row of G is multiplied with, from its largest entry: the label's, off-label mass / total.
+__device__ __forceinline__ int row_shift(float top) {
+  const int x = (int)(__float_as_uint(top) >> 23) - 127, e = ROW_SHIFTED_EXP - x;
+  return !(top > 0.f) || x >= ROW_LEAST_EXP ? 0 : e < ROW_SHIFT_MOST ? e : ROW_SHIFT_MOST;
+}
+// 2^e, -126 <= e <= 127
+__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // Four features from column k on of a row that starts at p, as fp32; 0 from column d on.
 template <int DT, bool VEC>
@@ -251,7 +272,7 @@ __global__ __launch_bounds__(256) void k_feature_planes(const void* I, const voi
 #pragma unroll
     for (int u = 0; u < HALF_FLAGS / 256; ++u) any |= f[u];
     const bool half = !__syncthreads_or((int)any);
-    if (blockIdx.x == 0 && threadIdx.x == 0) head->half = half;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { head->half = half; head->shifted = 0u; }
     if (half) return;
   }
   const int64_t cpr = dp >> 2, n = rows * cpr, plane = rows * dp;
@@ -411,7 +432,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
 #pragma unroll
   for (int w = 1; w < SM_WAVES; ++w) { off += red[1][w]; ds += red[2][w]; }
   const float zl = s * xl, el = expf(fmaf(s, xl, -mx)), tot = off + el, inv = 1.f / tot;
-  const float m = half ? inv * G_SCALE : inv;
+  const float top_g = off * inv;
+  const int shift = half ? row_shift(top_g) : 0;
+  const float m = half ? inv * (G_SCALE * power_of_two(shift)) : inv;
   visit([&](int j, f32x4& v, auto marked) {
     f32x4 x;
 #pragma unroll
@@ -431,7 +454,33 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
     // ce = log(tot) - (zl - mx); where the label holds most of the mass log1p(off / el) keeps the relative accuracy
     p.ce[a.r0 + i] = (el > 0.5f * tot) ? log1pf(off / el) : logf(tot) - (zl - mx);
     p.ds[a.r0 + i] = ds * inv;
+    if (a.head) p.shift[i] = top_g == 0.f ? NO_ROW : (uint8_t)shift;
+    if (shift) a.head->shifted = 1u;                                 // (whoever does stores the same)
   }
+}
+
+// The least exponent of the rows (0 if all are zeros) and whether there is another, the same in all threads; through LDS.
+template <int NTHREADS>
+__device__ __forceinline__ bool rows_differ(const uint8_t* shift, int64_t rows, char* smem, int& least) {
+  int lo = NO_ROW, hi = -1;
+  for (int64_t i = threadIdx.x * 4; i < rows; i += NTHREADS * 4) {   // (the array is whole pieces)
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(shift + i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int x = (int)(v >> (8 * e) & 255u);
+      if (i + e < rows && x != NO_ROW) { lo = min(lo, x); hi = max(hi, x); }
+    }
+  }
+  lo = wave_reduce(lo, [](int x, int y) { return min(x, y); });
+  hi = wave_reduce(hi, [](int x, int y) { return max(x, y); });
+  int* red = reinterpret_cast<int*>(smem);
+  if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = lo; red[16 + (threadIdx.x >> 6)] = hi; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NTHREADS / 64; ++w) { lo = min(lo, red[w]); hi = max(hi, red[16 + w]); }
+  __syncthreads();
+  least = __builtin_amdgcn_readfirstlane(hi < 0 ? 0 : lo);
+  return lo < hi;
 }
 
 enum { SPLIT_KEY_WRITE = 0, SPLIT_KEY_ADD = 1, SPLIT_KEY_PARTS = 2 };
@@ -443,7 +492,7 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, f
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Acc<Cfg<T>::NFA> acc;
   const bool half = a.head && a.head->half;
-  // the sums of matrix m's features in their own units
+  // the sums of matrix m's features in their own units (the rows' powers of two on the query side: k_split_finalize)
   auto unscale = [&](int m) { return half ? a.head->unscale[m] * (1.f / G_SCALE) : 1.0f; };
   if ((int)blockIdx.x < a.q_wgs) {
     const int tiles = a.nMq * a.nN, total = tiles * a.nb * a.splitk;
@@ -474,13 +523,29 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, f
   const int64_t j0 = (int64_t)(t2 % a.nMk) * T, k0 = (int64_t)(lin % a.nN) * T;
   const int kt0 = ks * a.key_ktps, left = (int)(a.bp / BK) - kt0, kts = left < a.key_ktps ? left : a.key_ktps;
   const int ncols = a.dp - k0 < T ? (int)(a.dp - k0) : T;
-  auto products = [&](auto ps) {
+  auto products = [&](auto ps, auto shifts) {
     using PS = decltype(ps);
-    mainloop<T, FMT_R, FMT_R, false, true, PS>(p.G + (int64_t)kt0 * BK * a.Bp + j0, a.Bp, p.X + (int64_t)kt0 * BK * a.dp + k0, a.dp, kts * PS::N, smem,
-                                               acc, ncols, a.gplane, a.fplane);
+    mainloop<T, FMT_R, FMT_R, false, true, PS, Whole, decltype(shifts)>(p.G + (int64_t)kt0 * BK * a.Bp + j0, a.Bp, p.X + (int64_t)kt0 * BK * a.dp + k0, a.dp,
+                                                                        kts * PS::N, smem, acc, ncols, a.gplane, a.fplane, Whole{}, shifts);
   };
-  if (half) products(HalfGrads<(NP + 1) / 2>{});
-  else products(Planes<3, NP>{});
+  // Rows of G with powers of two of their own: what they have in common is undone behind the sum, what they differ by goes into the features.
+  // (Of fixed planes, the gradients of a batch whose positives have cosine 0.89 were off by 8e-4 at s = 40, 0.1 at 50 and were all zero from 70 on; now 5e-6
+  // throughout.  us a call, bf16 planes / these with rows that differ / that do not: fp32 B = 8192, N = 8, d = 512 279 / 218 / 200; 4096, 16, 512
+  // 81 / 77 / 70; 2048, 4, 512 77 / 77 / 63; 12288, 4, 256 762 / 567 / 534; bf16 12288, 8, 100 216 / 190 / 176.)
+  if (half && a.head->shifted) {
+    int least;
+    if (rows_differ<Cfg<T>::NTHREADS>(p.shift, a.b, smem, least)) products(HalfGrads<(NP + 1) / 2>{}, RowShifts{p.shift + (int64_t)kt0 * BK, least});
+    else products(HalfGrads<(NP + 1) / 2>{}, Unshifted{});
+    const float common = power_of_two(-least);
+#pragma unroll
+    for (int i = 0; i < Cfg<T>::NFA; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] *= common;               // (on its own: with `unscale` below it can leave fp32's range)
+  } else if (half) {
+    products(HalfGrads<(NP + 1) / 2>{}, Unshifted{});
+  } else {
+    products(Planes<3, NP>{}, Unshifted{});
+  }
   if constexpr (KMODE == SPLIT_KEY_PARTS) {
     store_tile_f32<T, false>(acc, smem, p.kpart + ((int64_t)ks * a.Bp + j0) * a.dp + k0, a.dp, unscale(z), ncols);
   } else {                                                           // (d % 4 == 0: a tile's last column piece is whole)
@@ -530,6 +595,8 @@ __global__ __launch_bounds__(256) void k_split_finalize(SplitArgs a, float cs, f
   const SplitBlock& o = a.z[a.nb == 1 ? 0 : 1 - z];                   // whose key side lands in the same matrix
   const int64_t i = PARTS ? row - a.g0 : row, g = PARTS ? row : a.g0 + row;
   const bool own = i >= 0 && i < a.b;
+  const uint8_t shift = own && a.head && a.head->half ? p.shift[i] : 0;
+  const float unscale = shift == NO_ROW ? 0.f : power_of_two(-(int)shift);
   float* out = p.gq + g * a.d;
   for (int64_t k = (threadIdx.x & 63) * 4; k < a.d; k += 256) {
     f32x4 u = {0.f, 0.f, 0.f, 0.f}, v = {0.f, 0.f, 0.f, 0.f};
@@ -537,7 +604,8 @@ __global__ __launch_bounds__(256) void k_split_finalize(SplitArgs a, float cs, f
       for (int ks = 0; ks < a.splitk; ++ks) u += *reinterpret_cast<const f32x4*>(p.part + ((int64_t)ks * a.bp + i) * a.dp + k);
     if constexpr (PARTS)
       for (int ks = 0; ks < a.key_splits; ++ks) v += *reinterpret_cast<const f32x4*>(o.kpart + ((int64_t)ks * a.Bp + row) * a.dp + k);
-    u += v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[e] = fmaf(u[e], unscale, v[e]);
     if constexpr (VEC) {
       f32x4 r = {0.f, 0.f, 0.f, 0.f};
       if (!PARTS || add) r = *reinterpret_cast<const f32x4*>(out + k);
@@ -559,7 +627,7 @@ struct SplitPlan {
   int nMq, nMk, nN, splitk, ktps, key_splits, key_ktps;
   bool parts;            // the key side goes through partial sums
   bool half;             // fp16 planes where the features allow them
-  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, off_head, total;
+  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, off_shift, off_head, total;
   double us, exact_us;   // exact_us: of the best plan on bf16 planes
   int feature_planes(int np) const { return half && np == 1 ? 2 : np; }
 };
@@ -575,6 +643,8 @@ void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
   pl.off_kpart = o;
   if (pl.parts) o += nb * align_up((size_t)pl.key_splits * pl.Bp * pl.dp * 4);
   pl.off_rows = o;   o += 2 * nb * align_up((size_t)b * 4);
+  pl.off_shift = o;
+  if (pl.half) o += nb * align_up((size_t)pl.bp);
   pl.off_head = o;
   if (pl.half) o += align_up(sizeof(HalfHead)) + align_up(HALF_FLAGS * sizeof(uint32_t));
   pl.total = o;
@@ -701,6 +771,7 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
       const int zz = z < nb ? z : 0;
       p.S = reinterpret_cast<float*>(ws + pl.off_S + zz * align_up((size_t)pl.bp * pl.Bp * 4));
       p.G = reinterpret_cast<uint16_t*>(ws + pl.off_G + zz * align_up((size_t)3 * pl.bp * pl.Bp * 2));
+      p.shift = pl.half ? reinterpret_cast<uint8_t*>(ws + pl.off_shift + zz * align_up((size_t)pl.bp)) : nullptr;
       p.part = reinterpret_cast<float*>(ws + pl.off_part + zz * align_up((size_t)pl.splitk * pl.bp * pl.dp * 4));
       p.kpart = pl.parts ? reinterpret_cast<float*>(ws + pl.off_kpart + zz * align_up((size_t)pl.key_splits * pl.Bp * pl.dp * 4)) : nullptr;
       p.ce = reinterpret_cast<float*>(ws + pl.off_rows + (2 * zz) * align_up((size_t)pr.b * 4));
