@@ -222,7 +222,8 @@ __global__ __launch_bounds__(256) void k_feature_halves(const void* I, const voi
   if (blockIdx.x == 0 && threadIdx.x < 2) head->unscale[threadIdx.x] = __uint_as_float((uint32_t)(127 - (threadIdx.x ? e[1] : e[0])) << 23);
   const int64_t plane = rows * dp, step = (int64_t)gridDim.x * (256 / LPR);
   const int lane = threadIdx.x % LPR;
-  for (int64_t w = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; w < mats * rows; w += step) {
+  const int64_t todo = bad ? 0 : mats * rows;                         // (a test in the loop, for rows further on, cost the others 1 us of 18)
+  for (int64_t w = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; w < todo; w += step) {
     const bool second = w >= rows;
     const int64_t row = second ? w - rows : w;
     const float scale = __uint_as_float((uint32_t)(127 + (second ? e[1] : e[0])) << 23);
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_split_softmax(SplitArgs a, float
 #pragma unroll
   for (int w = 1; w < SM_WAVES; ++w) { off += red[1][w]; ds += red[2][w]; }
   const float zl = s * xl, el = expf(fmaf(s, xl, -mx)), tot = off + el, inv = 1.f / tot;
-  const float top_g = off * inv;
+  const float top_g = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(off * inv)));   // (the same in all lanes: scalar from here on)
   const int shift = half ? row_shift(top_g) : 0;
   const float m = half ? inv * (G_SCALE * power_of_two(shift)) : inv;
   visit([&](int j, f32x4& v, auto marked) {
@@ -595,7 +596,7 @@ __global__ __launch_bounds__(256) void k_split_finalize(SplitArgs a, float cs, f
   const SplitBlock& o = a.z[a.nb == 1 ? 0 : 1 - z];                   // whose key side lands in the same matrix
   const int64_t i = PARTS ? row - a.g0 : row, g = PARTS ? row : a.g0 + row;
   const bool own = i >= 0 && i < a.b;
-  const uint8_t shift = own && a.head && a.head->half ? p.shift[i] : 0;
+  const uint8_t shift = own && a.head ? p.shift[i] : 0;               // (0 on bf16 planes)
   const float unscale = shift == NO_ROW ? 0.f : power_of_two(-(int)shift);
   float* out = p.gq + g * a.d;
   for (int64_t k = (threadIdx.x & 63) * 4; k < a.d; k += 256) {
@@ -748,8 +749,12 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
       auto halves = [&](auto kernel) { kernel<<<dim3((unsigned)nflags), 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1], head, flags); };
       if (fvec) { if (lanes == 16) halves(k_feature_halves<DT, true, 16>); else halves(k_feature_halves<DT, true, 64>); }
       else { if (lanes == 16) halves(k_feature_halves<DT, false, 16>); else halves(k_feature_halves<DT, false, 64>); }
-      if (grid.x > 256) grid.x = 256;                                // (in nearly every call they have nothing to do)
     }
+    // Behind the halves these workgroups nearly always have nothing to do, and where they have, 1024 take no longer than 4096, which cost other calls
+    // 1 us more.  (us a call whose features leave fp16's range, bf16 planes alone / 256 workgroups / 1024: fp32 B = 8192, N = 8, d = 512, norms
+    // from 2^-10 to 1 301 / 327 / 321, one row 100 times longer 307 / 333 / 327, a first row of zeros 305 / 331 / 312; 4096, 16, 512 86 / 101 / 98, 86 / 103 / 99, 87 / 103 / 93.
+    // What is left is the launch, the halves up to where it shows, and tiles and splits chosen for three products where six run.)
+    if (head && grid.x > 1024) grid.x = 1024;
     auto exact = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(pr.I, pr.T, pr.B, pr.d, pl.frows, pl.dp, nb, planes[0], planes[1], head, flags, nflags); };
     if (fvec) exact(k_feature_planes<DT, true>);
     else exact(k_feature_planes<DT, false>);
