@@ -39,11 +39,14 @@ namespace {
 using namespace tile;
 
 // Written on the device by k_feature_halves, k_feature_planes and the softmax: in which form the call's features and gradient entries are kept.
+// At the front of the workspace, where tests read which form a call took.
 struct HalfHead {
+  uint32_t mark;         // HEAD_MARK: the plan is one for fp16 planes
   uint32_t half;         // 1: fp16 planes, 0: bf16 planes
   float unscale[2];      // what undoes the power of two that the features of I (of T) are multiplied with
   uint32_t shifted;      // some row of G is multiplied by a power of two of its own
 };
+constexpr uint32_t HEAD_MARK = 0x666c6168u;
 constexpr int HALF_FLAGS = 1024;                         // workgroups of k_feature_halves at most, a flag each
 constexpr float G_SCALE = 0x1p15f, REST_SCALE = 0x1p11f; // fp16 planes of a gradient entry: see store_unit_halves
 // Rows of G whose largest entry is below 2^-16 are multiplied by the power of two that brings it to [2^-12, 2^-11) (by 2^100 at most: an entry
@@ -273,7 +276,7 @@ __global__ __launch_bounds__(256) void k_feature_planes(const void* I, const voi
 #pragma unroll
     for (int u = 0; u < HALF_FLAGS / 256; ++u) any |= f[u];
     const bool half = !__syncthreads_or((int)any);
-    if (blockIdx.x == 0 && threadIdx.x == 0) { head->half = half; head->shifted = 0u; }
+    if (blockIdx.x == 0 && threadIdx.x == 0) { head->mark = HEAD_MARK; head->half = half; head->shifted = 0u; }
     if (half) return;
   }
   const int64_t cpr = dp >> 2, n = rows * cpr, plane = rows * dp;
@@ -628,7 +631,7 @@ struct SplitPlan {
   int nMq, nMk, nN, splitk, ktps, key_splits, key_ktps;
   bool parts;            // the key side goes through partial sums
   bool half;             // fp16 planes where the features allow them
-  size_t off_planes, off_S, off_G, off_part, off_kpart, off_rows, off_shift, off_head, total;
+  size_t off_head, off_planes, off_S, off_G, off_part, off_kpart, off_rows, off_shift, total;
   double us, exact_us;   // exact_us: of the best plan on bf16 planes
   int feature_planes(int np) const { return half && np == 1 ? 2 : np; }
 };
@@ -637,6 +640,8 @@ int64_t round_up(int64_t v, int64_t u) { return (v + u - 1) / u * u; }
 
 void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
   size_t o = 0;
+  pl.off_head = o;
+  if (pl.half) o += align_up(sizeof(HalfHead)) + align_up(HALF_FLAGS * sizeof(uint32_t));
   pl.off_planes = o; o += 2 * align_up((size_t)pl.feature_planes(np) * pl.frows * pl.dp * 2);
   pl.off_S = o;      o += nb * align_up((size_t)pl.bp * pl.Bp * 4);
   pl.off_G = o;      o += nb * align_up((size_t)3 * pl.bp * pl.Bp * 2);
@@ -646,8 +651,6 @@ void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
   pl.off_rows = o;   o += 2 * nb * align_up((size_t)b * 4);
   pl.off_shift = o;
   if (pl.half) o += nb * align_up((size_t)pl.bp);
-  pl.off_head = o;
-  if (pl.half) o += align_up(sizeof(HalfHead)) + align_up(HALF_FLAGS * sizeof(uint32_t));
   pl.total = o;
 }
 

@@ -13,6 +13,18 @@ def to_device(I_f32, T_f32, I_bits, T_bits, dtype):
     return torch.from_numpy(I_f32).cuda(), torch.from_numpy(T_f32).cuda(), dl.DISCO_F32
 
 
+def planes_taken(ws):
+    """Which planes the last call on the split kernels kept its features and gradient entries in, from the front of its workspace
+    (HalfHead of split_kernels.hip): "fp16"; "bf16 instead", planned as fp16 ones that the features or gradients' scale did not allow;
+    or "bf16", planned so.  Call forget_planes before the call."""
+    mark, half = ws[:8].cpu().numpy().view(np.uint32)
+    return "bf16" if mark != 0x666c6168 else "fp16" if half else "bf16 instead"
+
+
+def forget_planes(ws):
+    ws[:8].zero_()
+
+
 def term_scale(oc, I, T, s, rank, N):
     """(scale_gI, scale_gT, oracle_floor) for check_tensor."""
     sI, sT = oc.disco_rank_term_scale(I, T, s, rank, N)

@@ -8,7 +8,7 @@ import torch
 import paper_2304_08480_amd as dl
 from oracle import clip_oracle as oc
 from synth import clip_pairs, f32_to_bf16_bits, bf16_bits_to_f32
-from tests.gpu_util import Runner, term_scale, check_scalar, check_tensor, to_device, TOL
+from tests.gpu_util import Runner, forget_planes, planes_taken, term_scale, check_scalar, check_tensor, to_device, TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +52,7 @@ CHANGES = {
     "first row zero": _zero_row(0),        # no power of two to go by
     "other row zero": _zero_row(5),
 }
+PLANES = {"unit": "fp16", "inside": "fp16", "short rows": "bf16 instead", "long row": "bf16 instead", "first row zero": "bf16 instead", "other row zero": "fp16"}
 
 
 @pytest.mark.parametrize("change", sorted(CHANGES))
@@ -63,8 +64,10 @@ def test_norms_inside_and_outside_the_range(B, d, N, dtype, change):
     s = 14.285714 / max(1.0, float(np.abs((I * T).sum(1)).max()))
     run = Runner(Id, Td, B, d, N, dt, dl.DISCO_PATH_AUTO)
     print(f"case halves {change} B={B} d={d} N={N} dtype={dtype}", flush=True)
+    forget_planes(run.ws)
     run.rank(N - 1, s)
     loss, gI, gT, gs = run.results()
+    assert planes_taken(run.ws) == PLANES[change]
     ref = oc.disco_rank(I, T, s, N - 1, N)
     sI, sT, fl = term_scale(oc, I, T, s, N - 1, N)
     check_scalar("loss", loss, ref[0], TOL["f32"]["scalar"])

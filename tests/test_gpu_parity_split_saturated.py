@@ -11,7 +11,7 @@ import torch
 
 import paper_2304_08480_amd as dl
 from synth import bf16_bits_to_f32, clip_pairs, f32_to_bf16_bits
-from tests.gpu_util import Runner, to_device
+from tests.gpu_util import Runner, forget_planes, planes_taken, to_device
 
 pytestmark = pytest.mark.gpu
 BAR = 1e-4
@@ -73,8 +73,10 @@ def test_decided_rows(B, d, N, dtype, path, kind, s):
     assert dl.disco_describe_plan(B, d, N, dt, path).kernels == dl.DISCO_KERNELS_SPLIT
     run, r = Runner(Id, Td, B, d, N, dt, path), N - 1
     print(f"case decided {kind} B={B} d={d} N={N} dtype={dtype} path={path} s={s}", flush=True)
+    forget_planes(run.ws)
     run.rank(r, s)
     loss, gI, gT, _ = run.results()
+    assert planes_taken(run.ws) == "fp16"
     ref = _reference(I, T, s, r, N)
     assert abs(loss - ref[0]) <= BAR * ref[0]
     _check("gI", gI, ref[1], ref[3])
@@ -94,8 +96,10 @@ def test_rows_decided_alike(s):
     assert dl.disco_describe_plan(B, B, N, dt, dl.DISCO_PATH_AUTO).kernels == dl.DISCO_KERNELS_SPLIT
     run = Runner(Id, Td, B, B, N, dt, dl.DISCO_PATH_AUTO)
     print(f"case decided alike s={s}", flush=True)
+    forget_planes(run.ws)
     run.rank(r, s)
     loss, gI, gT, _ = run.results()
+    assert planes_taken(run.ws) == "fp16"
     ref = _reference(I, I, s, r, N)
     assert abs(loss - ref[0]) <= BAR * ref[0]
     _check("gI", gI, ref[1], ref[3])
@@ -111,9 +115,11 @@ def test_decided_rows_two_view(M, d, N, s):
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     loss, gs, gZ = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda"), torch.full((B, d), float("nan"), device="cuda")
     print(f"case decided two views M={M} d={d} N={N} s={s}", flush=True)
+    forget_planes(ws)
     dl.ntxent_loss_fwd_bwd(torch.from_numpy(Z).cuda(), B, d, r, N, s, dl.DISCO_F32, dl.DISCO_PATH_AUTO, 0, loss, gZ, gs, ws, need,
                            torch.cuda.current_stream())
     torch.cuda.synchronize()
+    assert planes_taken(ws) == "fp16"
     Z, b = Z.astype(np.float64), B // N
     own = np.arange(r * b, (r + 1) * b)
     G, l, t = _gradient_matrix(Z[own], Z, (own + M) % B, own, s)
