@@ -440,7 +440,7 @@ __device__ __forceinline__ void kloop(const uint16_t* __restrict__ A, int64_t ld
   const int last = ktiles - 1;
   // operand tiles of step kt: with several planes, product q of a 64-deep piece
   const int pieces = ktiles / PS::N;
-  const uint32_t inv = 0xffffffffu / (uint32_t)pieces + 1u;      // (kt pieces < 2^32: the high half of kt inv is the quotient)
+  const uint32_t inv = 0xffffffffu / (uint32_t)pieces + 1u;      // (kt pieces < 2^32, which who makes the plans sees to: the high half of kt inv is the quotient)
   struct Step { int piece, q; };
   auto step_of = [&](int kt) {
     const int x = !PS::SWEEPS ? kt / PS::N : pieces == 1 ? kt : (int)__umulhi((uint32_t)kt, inv), y = kt - x * (PS::SWEEPS ? pieces : PS::N);

@@ -660,6 +660,10 @@ SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64
   static const int Q_SPLITS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}, K_SPLITS[] = {1, 2, 3, 4, 6, 8};
   SplitPlan best;
   best.us = 1e300;
+  // the tile loop's quotient of a step by the pieces of a reduction taken in sweeps (mfma_tile.h) is exact below 2^32 steps times pieces
+  // (it first fails at 37927 pieces and three sweeps); logits have 1024 pieces at most
+  constexpr int64_t SWEEP_PIECES_MOST = 32768;
+  static_assert(HalfGrads<2>::N * SWEEP_PIECES_MOST * SWEEP_PIECES_MOST < (int64_t)1 << 32);
   const int nl = np == 1 ? 1 : half ? 4 : 6, ng = np == 3 ? (half ? 3 : 6) : half ? 2 : 3;
   for (int T = 128; T <= 256; T += 128) {
     SplitPlan pl;
@@ -676,9 +680,11 @@ SplitPlan make_split_plan(int64_t B, int64_t d, int64_t b, int nb, int np, int64
     for (int sk : Q_SPLITS) {
       if (sk > kq) break;
       pl.ktps = (kq + sk - 1) / sk; pl.splitk = (kq + pl.ktps - 1) / pl.ktps;
+      if (half && pl.ktps > SWEEP_PIECES_MOST) continue;
       for (int ks : K_SPLITS) {
         if (ks > kk) break;
         pl.key_ktps = (kk + ks - 1) / ks; pl.key_splits = (kk + pl.key_ktps - 1) / pl.key_ktps;
+        if (half && pl.key_ktps > SWEEP_PIECES_MOST) continue;
         pl.parts = pl.key_splits > 1 || d % 4 != 0;
         const double nq = (double)nb * pl.nMq * pl.nN * pl.splitk, nk = (double)nb * pl.nMk * pl.nN * pl.key_splits;
         const double step = step_us(T, nq + nk), lq = pl.ktps * ng * step + fix, lk = pl.key_ktps * ng * step + fix;
