@@ -852,26 +852,30 @@ bool split_aligned(const Problem& pr) {
   return pr.d % 4 != 0 || ((reinterpret_cast<uintptr_t>(pr.gI) | reinterpret_cast<uintptr_t>(pr.gT)) & 15u) == 0;
 }
 
+// (The model ranks plans; its sum of the parts is this much more than what a call takes: 402 against 313 us at B = 8192,
+// N = 8, d = 512, 113 against 87 at 4096, 16, 512, 43 against 33 at 2048, 16, d = 200 in bf16.)
+constexpr double MODEL_SHARE = 0.77;
+static double chunks_of(const SplitPlan& pl, int64_t b) { return (double)((b + pl.chunk - 1) / pl.chunk); }
+
+// What the choice against the small kernels goes by: the time on bf16 planes, which the line between them was measured with (and which a call
+// takes whose features fp16 cannot hold).
 double split_estimate_us(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, size_t* bytes) {
   const SplitPlan pl = plan_within(B, d, b, dtype, nb, limit);
   *bytes = pl.total;
-  // (the model ranks plans; its sum of the parts is this much more than what a call takes: 402 against 313 us at B = 8192,
-  // N = 8, d = 512, 113 against 87 at 4096, 16, 512, 43 against 33 at 2048, 16, d = 200 in bf16)
-  return 0.77 * pl.exact_us * (double)((b + pl.chunk - 1) / pl.chunk);
+  return MODEL_SHARE * pl.exact_us * chunks_of(pl, b);
 }
 
 bool split_raise_lds() { return raise_lds<128, 1>() && raise_lds<128, 3>() && raise_lds<256, 1>() && raise_lds<256, 3>(); }
 
 void split_describe(int64_t B, int64_t d, int64_t b, int dtype, int nb, size_t limit, disco_plan* out) {
   const SplitPlan pl = plan_within(B, d, b, dtype, nb, limit);
-  size_t bytes;
   out->kernels = DISCO_KERNELS_SPLIT;
   out->logit_tile = out->gradient_tile = pl.T;
   out->row_chunks = (int)((b + pl.chunk - 1) / pl.chunk);
   out->key_panels = 1;
   out->query_splits = pl.splitk;
   out->key_splits = pl.key_splits;
-  out->microseconds = split_estimate_us(B, d, b, dtype, nb, limit, &bytes);
+  out->microseconds = MODEL_SHARE * pl.us * chunks_of(pl, b);
 }
 
 int split_run(const Problem& pr, size_t limit) {

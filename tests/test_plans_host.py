@@ -75,6 +75,12 @@ def test_the_static_entry_point_takes_what_it_took(B, d, N, dt, path):
     assert dl.disco_describe_plan(B, d, N, dt, path, workspace_limit=STATIC).workspace_bytes <= STATIC
 
 
+# fp32 path, large calls: (B, d, N, dtype) and the measured time, us, on the planes that the plan is for.  The model is rough: within a quarter.
+@pytest.mark.parametrize("B,d,N,dt,us", [(8192, 512, 8, F32, 201), (12288, 256, 4, F32, 535), (10416, 1024, 8, F32, 691), (12288, 100, 8, BF16, 177)])
+def test_the_described_time_is_that_of_the_plan_that_runs(B, d, N, dt, us):
+    assert 0.75 * us <= dl.disco_describe_plan(B, d, N, dt, AUTO).microseconds <= 1.25 * us
+
+
 def test_plan_query_arguments():
     q = dl.DiscoPlan()
     call = dl.binding._lib.disco_describe_plan
