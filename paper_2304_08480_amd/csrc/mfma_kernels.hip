@@ -1066,7 +1066,8 @@ __device__ __forceinline__ f32x2 sums_over_rows(const float (&col)[8][4], int la
 // bl.z[0]: E, row partial sums, label numerators; bl.z[1].lpart: column partial sums, one per query tile, cpart[it][j].
 // B: the batch rounded up to whole tiles.  RAGGED: the batch is not whole tiles: the
 // last key tiles leave their padding columns out (so every row sum is right) and the column sums leave the padding
-// rows out; what the padding rows hold in E meets zero feature rows in both contractions.
+// rows out; what the padding rows hold in E meets zero feature rows in both contractions.  The loads' bounds spill three more registers there (B = 30000,
+// d = 512 1088 -> 1134 us), which the copies that they replace cost more than: us a call 3338 -> 3325, 6145, 320 252 -> 243, 16000, 768 1419 -> 1368, 10241, 128 385 -> 379.
 template <bool RAGGED>
 __global__ __launch_bounds__(NTHREADS) void k_sym_logit(Blocks bl, int64_t B, int64_t d, float s2, const float* rglobal, int sbi, int sbj) {
   if (gated_off(bl)) return;

@@ -415,7 +415,7 @@ __device__ __forceinline__ int ring_next(int u, int step) { u += step; return u 
 // (loading the last K-step again instead, for one loop, made a tile of 8 K-steps fetch 10: 1 % of a call at d = 512, 3 % at 128).
 // READS_FIRST: issue a sub-step's LDS reads ahead of its MFMAs (otherwise the compiler places them).
 //
-// PS: the operands may be kept as several bf16 planes (a value is the sum of its planes), `plane_a` / `plane_b` elements
+// PS: the operands may be kept as several 16-bit planes (a value is the sum of its planes, to their last bit), `plane_a` / `plane_b` elements
 // apart, and PS lists the plane products that make up one K-step's worth of the reduction: the loop then runs PS::N
 // times the K-steps: the products of one 64-deep piece one after the other, so that each plane's piece comes from L2 when it
 // is read again, or (PS::SWEEPS) one product over the whole reduction after the other, so that the smallest products are

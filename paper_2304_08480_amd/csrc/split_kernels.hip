@@ -189,8 +189,8 @@ __device__ __forceinline__ f32x4 load_features(const void* src, int64_t at, int6
 
 // Features as fp16 planes.  A matrix is multiplied with the power of two that brings the largest entry of its first row into [2^10, 2^11);
 // an entry x of the product is h + l, 11 significand bits each (bf16 features: h alone), and h 2^-11 is kept as well, the partner
-// of the gradient entries' second plane, which is 2^11 times what it stands for.  That loses nothing that counts where every entry is
-// under 2^15.9 and every row's largest is 0 or at least 2^3: the planes end at 2^-24, 2^-27 of that.  A workgroup that
+// of the gradient entries' second plane, which is 2^11 times what it stands for.  Beyond the planes' own bits that loses 2^-28 of a row's largest
+// entry at most where every entry is under 2^15.9 and every row's largest is 0 or at least 2^3: the planes end at 2^-24.  A workgroup that
 // sees anything else (rows whose norms differ by more than 2^5 to 2^7, what is not finite, a first row of zeros) raises its flag, and
 // k_feature_planes replaces the planes of the whole call by bf16 ones.  One wave (LPR = 64) or 16 lanes a row.
 template <int DT, bool VEC, int LPR>
