@@ -9,11 +9,12 @@
 //          features that the fp16 form cannot hold, and for calls too small to gain from it.
 // One product over the whole reduction follows the other, the smallest first (SWEEPS), so that only the last one rounds at the size of
 // the result: that is what decides the errors where logits are small, and why the fp16 form's are mostly no larger although its planes hold a bit less.
-// Against 64 bits, 2-norm of the gradients, fp16 over bf16 planes (logits in sweeps, gradients piece by piece), mean over 8 shapes, B = 2048 to 12288,
-// d = 64 to 2560, both dtypes, by the positives' cosine and s = 1/0.07, 30, 50, 100:
-//   0.89  1.00 1.03 0.97 0.98      0.64  0.93 1.01 0.96 0.95      0.38  0.72 0.95 0.90 0.96      0.27  0.69 0.88 1.00 0.97
-// Large multipliers show the features' lost bits where nothing larger hides them: fp32 features, cosines up to 0.4, s = 100: 1.23 at d = 64, 1.1 at 100 to 192, 1.05 from
-// 256 on (4e-7 to 2e-6 of the gradient's norm either way).
+// Against 64 bits, 2-norm of the gradients, fp16 over bf16 planes (logits in sweeps, gradients piece by piece), geometric mean over inputs, unit rows:
+//   bf16 features  d = 100 to 1000, s = 1/0.07 to 100, positives of cosine 0.27 to 0.89: 0.72 to 1.02
+//   fp32 features  d = 192 to 1024, by cosine 0.89 / 0.64 / 0.38 / 0.27:  s = 1/0.07 0.98 / 0.95 / 0.66 / 0.62;  30 0.99 / 0.98 / 0.96 / 0.84
+//                  and where rounding of single logits decides (few rows hold the gradient) 1.0 in the mean, one input 0.2 to 5
+// Where a logit is short of terms and multiplied by much, the features' lost bits show: fp32 features, cosine 0.27, s = 50 1.18 at d = 64, 1.1 at 77 and 100, 1.0 at 192;
+// s = 100 1.27, 1.2, 1.11, 1.06 at 256 and 320; cosine 0.89, s = 30 1.27 at 64, 1.08 at 100 and 128.  Such calls stay on bf16 planes (halves_hold).
 // What is relative to the largest rows is a gradient as a whole: entries and rows of it as far below them as 2^-35 of a row of G (2^-51 of 1 in rows of
 // more than 2^-16) keep fewer bits than bf16 planes leave them, and can be 0.  (s = 100, d = 64, keys of other ranks.)
 //
@@ -636,6 +637,13 @@ struct SplitPlan {
   int feature_planes(int np) const { return half && np == 1 ? 2 : np; }
 };
 
+// fp32 features in two fp16 planes lose the last bit of one value in four: about 2^-24 sqrt(2 / d) of a logit of unit rows, times s of an exponent.
+// The lines lie where the gradients are as near to 64 bits as on bf16 planes (the measurements are at the top of this file); under the first the
+// fp16 form gains little (us a call, bf16 / fp16 planes: B = 4096, N = 4, d = 64 73 / 70; 8192, 8, 128 136 / 127); calls past the second run six products on
+// tiles and splits chosen for three (8192, 8, 320 184 at s = 50, 271 at 100; 12288, 4, 256 549, 831; planned for six 762).
+bool halves_planned(int64_t d, int np) { return np == 1 || d >= 192; }
+bool halves_hold(float s, int64_t d, int np) { return np == 1 || 5.f * fabsf(s) <= (float)d; }
+
 int64_t round_up(int64_t v, int64_t u) { return (v + u - 1) / u * u; }
 
 void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
@@ -749,7 +757,7 @@ int split_run_typed(const Problem& pr, const SplitPlan& pl) {
     uint32_t* flags = nullptr;
     int nflags = 0;
     // (the gradients' scale is a power of two down to 2^-95 times cs, which has to stay a normal number)
-    if (pl.half && (cs == 0.f || fabsf(cs) >= 0x1p-30f)) {
+    if (pl.half && (cs == 0.f || fabsf(cs) >= 0x1p-30f) && halves_hold(pr.s, pr.d, NP)) {
       head = reinterpret_cast<HalfHead*>(ws + pl.off_head);
       flags = reinterpret_cast<uint32_t*>(ws + pl.off_head + align_up(sizeof(HalfHead)));
       const int lanes = pl.dp <= 128 ? 16 : 64;
@@ -831,6 +839,7 @@ SplitPlan compare_within(int64_t B, int64_t d, int64_t b, int dtype, int nb, siz
     SplitPlan pl = make_split_plan(B, d, b, nb, np, chunk, false);
     pl.exact_us = pl.us;
     if (pl.total <= limit) {
+      if (!halves_planned(d, np)) return pl;
       SplitPlan hp = make_split_plan(B, d, b, nb, np, chunk, true);
       hp.exact_us = pl.us;
       return hp.total <= limit && hp.us + half_allowance_us(np) < pl.us ? hp : pl;

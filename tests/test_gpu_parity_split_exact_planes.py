@@ -56,7 +56,7 @@ def test_small_multiplier(B, d, N, dtype):
 
 
 @pytest.mark.parametrize("kind,planes", [("unit", "fp16"), ("long row", "bf16 instead"), ("first row zero", "bf16 instead")])
-@pytest.mark.parametrize("B,d,N,dtype,chunks", [(6000, 400, 2, "f32", 6), (4099, 130, 1, "f32", 6), (5001, 500, 1, "bf16", 4)])
+@pytest.mark.parametrize("B,d,N,dtype,chunks", [(6000, 400, 2, "f32", 6), (4099, 330, 1, "f32", 6), (5001, 500, 1, "bf16", 4)])
 def test_rows_in_chunks(B, d, N, dtype, chunks, kind, planes):
     dt = dl.DISCO_F32 if dtype == "f32" else dl.DISCO_BF16
     assert dl.disco_describe_plan(B, d, N, dt, dl.DISCO_PATH_NAIVE).row_chunks == chunks
@@ -64,7 +64,7 @@ def test_rows_in_chunks(B, d, N, dtype, chunks, kind, planes):
 
 
 @pytest.mark.parametrize("kind,planes", [("unit", "fp16"), ("long row", "bf16 instead"), ("first row zero", "bf16 instead")])
-@pytest.mark.parametrize("M,d,N,dtype", [(2049, 130, 3, "f32"), (4096, 256, 1, "f32"), (4100, 333, 2, "bf16")])
+@pytest.mark.parametrize("M,d,N,dtype", [(2049, 230, 3, "f32"), (4096, 256, 1, "f32"), (4100, 333, 2, "bf16")])
 def test_two_views(M, d, N, dtype, kind, planes):
     B, r = 2 * M, N - 1
     Z = _change(two_views(M, d, 48), kind)

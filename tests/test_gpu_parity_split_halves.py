@@ -67,7 +67,7 @@ def test_norms_inside_and_outside_the_range(B, d, N, dtype, change):
     forget_planes(run.ws)
     run.rank(N - 1, s)
     loss, gI, gT, gs = run.results()
-    assert planes_taken(run.ws) == PLANES[change]
+    assert planes_taken(run.ws) == (PLANES[change] if d >= 192 else "bf16")      # (narrow fp32 features stay on bf16 planes)
     ref = oc.disco_rank(I, T, s, N - 1, N)
     sI, sT, fl = term_scale(oc, I, T, s, N - 1, N)
     check_scalar("loss", loss, ref[0], TOL["f32"]["scalar"])

@@ -64,6 +64,18 @@ def _pairs(kind, B, d):
                                               (6145, 333, 5, "bf16", dl.DISCO_PATH_AUTO)])
 @pytest.mark.parametrize("kind,s", [("near", 30.0), ("near", 40.0), ("near", 50.0), ("near", 70.0), ("mixed", 50.0)])
 def test_decided_rows(B, d, N, dtype, path, kind, s):
+    _decided(B, d, N, dtype, path, kind, s, "bf16" if dtype == "f32" and (d < 192 or 5 * s > d) else "fp16")
+
+
+# fp32 features: fp16 planes from d = 192 on while 5 |s| <= d; bf16 features lose nothing in them
+@pytest.mark.parametrize("B,d,N,dtype,s,planes", [
+    (4096, 191, 4, "f32", 14.0, "bf16"), (4096, 192, 4, "f32", 14.0, "fp16"), (4096, 192, 4, "f32", 38.0, "fp16"), (4096, 192, 4, "f32", -39.0, "bf16"),
+    (4098, 320, 3, "f32", 64.0, "fp16"), (4098, 320, 3, "f32", 65.0, "bf16"), (2048, 512, 4, "f32", 100.0, "fp16"), (12288, 100, 8, "bf16", 70.0, "fp16")])
+def test_large_multipliers_and_narrow_features(B, d, N, dtype, s, planes):
+    _decided(B, d, N, dtype, dl.DISCO_PATH_AUTO, "near", s, planes)
+
+
+def _decided(B, d, N, dtype, path, kind, s, planes):
     I, T = _pairs(kind, B, d)
     Ib = Tb = None
     if dtype == "bf16":
@@ -76,7 +88,7 @@ def test_decided_rows(B, d, N, dtype, path, kind, s):
     forget_planes(run.ws)
     run.rank(r, s)
     loss, gI, gT, _ = run.results()
-    assert planes_taken(run.ws) == "fp16"
+    assert planes_taken(run.ws) == planes
     ref = _reference(I, T, s, r, N)
     assert abs(loss - ref[0]) <= BAR * ref[0]
     _check("gI", gI, ref[1], ref[3])
@@ -106,7 +118,7 @@ def test_rows_decided_alike(s):
     _check("gT", gT, ref[2], ref[3])
 
 
-@pytest.mark.parametrize("M,d,N,s", [(2048, 256, 1, 40.0), (2049, 130, 3, 60.0)])
+@pytest.mark.parametrize("M,d,N,s", [(2048, 256, 1, 40.0), (2049, 330, 3, 60.0), (2049, 130, 3, 60.0)])
 def test_decided_rows_two_view(M, d, N, s):
     B, r = 2 * M, N - 1
     Z = np.concatenate(clip_pairs(M, d, 62))
@@ -119,7 +131,7 @@ def test_decided_rows_two_view(M, d, N, s):
     dl.ntxent_loss_fwd_bwd(torch.from_numpy(Z).cuda(), B, d, r, N, s, dl.DISCO_F32, dl.DISCO_PATH_AUTO, 0, loss, gZ, gs, ws, need,
                            torch.cuda.current_stream())
     torch.cuda.synchronize()
-    assert planes_taken(ws) == "fp16"
+    assert planes_taken(ws) == ("fp16" if d >= 5 * s else "bf16")
     Z, b = Z.astype(np.float64), B // N
     own = np.arange(r * b, (r + 1) * b)
     G, l, t = _gradient_matrix(Z[own], Z, (own + M) % B, own, s)
