@@ -49,6 +49,8 @@ struct HalfHead {
 };
 constexpr uint32_t HEAD_MARK = 0x666c6168u;
 constexpr int HALF_FLAGS = 1024;                         // workgroups of k_feature_halves at most, a flag each
+constexpr size_t HEAD_BYTES = 8192;                      // head and flags (in 4352, at no multiple of 4 KiB, the arrays behind them cost a call of B = 8192, N = 8, d = 512 0.6 us of 202)
+static_assert(sizeof(HalfHead) <= 256 && 256 + HALF_FLAGS * sizeof(uint32_t) <= HEAD_BYTES);
 constexpr float G_SCALE = 0x1p15f, REST_SCALE = 0x1p11f; // fp16 planes of a gradient entry: see store_unit_halves
 // Rows of G whose largest entry is below 2^-16 are multiplied by the power of two that brings it to [2^-12, 2^-11) (by 2^100 at most: an entry
 // of 2^-112, about where bf16 planes end).  Higher up they would keep more of their own small entries, but a row that lies beside undecided ones moves
@@ -496,9 +498,11 @@ template <int T, int NP, int KMODE>
 __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, float cs) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Acc<Cfg<T>::NFA> acc;
-  const bool half = a.head && a.head->half;
+  // (all of it at once: a load for each of what follows costs a call of B = 8192, N = 8, d = 512 1.8 us of 202)
+  const HalfHead head = a.head ? *a.head : HalfHead{};
+  const bool half = head.half;
   // the sums of matrix m's features in their own units (the rows' powers of two on the query side: k_split_finalize)
-  auto unscale = [&](int m) { return half ? a.head->unscale[m] * (1.f / G_SCALE) : 1.0f; };
+  auto unscale = [&](int m) { return half ? (m ? head.unscale[1] : head.unscale[0]) * (1.f / G_SCALE) : 1.0f; };
   if ((int)blockIdx.x < a.q_wgs) {
     const int tiles = a.nMq * a.nN, total = tiles * a.nb * a.splitk;
     int lin;
@@ -537,7 +541,7 @@ __global__ __launch_bounds__(Cfg<T>::NTHREADS) void k_split_grads(SplitArgs a, f
   // (Of fixed planes, the gradients of a batch whose positives have cosine 0.89 were off by 8e-4 at s = 40, 0.1 at 50 and were all zero from 70 on; now 5e-6
   // throughout.  us a call, bf16 planes / these with rows that differ / that do not: fp32 B = 8192, N = 8, d = 512 279 / 218 / 200; 4096, 16, 512
   // 81 / 77 / 70; 2048, 4, 512 77 / 77 / 63; 12288, 4, 256 762 / 567 / 534; bf16 12288, 8, 100 216 / 190 / 176.)
-  if (half && a.head->shifted) {
+  if (half && head.shifted) {
     int least;
     if (rows_differ<Cfg<T>::NTHREADS>(p.shift, a.b, smem, least)) products(HalfGrads<(NP + 1) / 2>{}, RowShifts{p.shift + (int64_t)kt0 * BK, least});
     else products(HalfGrads<(NP + 1) / 2>{}, Unshifted{});
@@ -649,7 +653,7 @@ int64_t round_up(int64_t v, int64_t u) { return (v + u - 1) / u * u; }
 void split_layout(SplitPlan& pl, int64_t b, int nb, int np) {
   size_t o = 0;
   pl.off_head = o;
-  if (pl.half) o += align_up(sizeof(HalfHead)) + align_up(HALF_FLAGS * sizeof(uint32_t));
+  if (pl.half) o += HEAD_BYTES;
   pl.off_planes = o; o += 2 * align_up((size_t)pl.feature_planes(np) * pl.frows * pl.dp * 2);
   pl.off_S = o;      o += nb * align_up((size_t)pl.bp * pl.Bp * 4);
   pl.off_G = o;      o += nb * align_up((size_t)3 * pl.bp * pl.Bp * 2);
