@@ -74,7 +74,8 @@ typedef enum { DISCO_F32 = 0, DISCO_BF16 = 1 } disco_dtype;
  *                         every fp32 operand split into two fp16 planes (22 bits of it at least; gradients as near to
  *                         64 bits as with the exact planes relative to their largest rows, not to every entry), or
  *                         exactly into three bf16 ones where
- *                         rows of very different norms leave fp16's range.  Any B, d, N; either dtype.  Asked
+ *                         rows of very different norms leave fp16's range, or fp32 features are narrow (d < 192)
+ *                         or s is large for their width (5 |s| > d).  Any B, d, N; either dtype.  Asked
  *                         for by name it stays within the fp32 logit blocks' memory (2*b*B*4 bytes, rows rounded up
  *                         to whole 16-byte pieces: the paper's 2B^2/N memory model, Sec. 4.1); where AUTO resolves to
  *                         it, a large call takes up to 8 GiB where the blocks need less, and is faster.

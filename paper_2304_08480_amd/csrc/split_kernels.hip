@@ -14,15 +14,15 @@
 //   fp32 features  d = 192 to 1024, by cosine 0.89 / 0.64 / 0.38 / 0.27:  s = 1/0.07 0.98 / 0.95 / 0.66 / 0.62;  30 0.99 / 0.98 / 0.96 / 0.84
 //                  and where rounding of single logits decides (few rows hold the gradient) 1.0 in the mean, one input 0.2 to 5
 // Where a logit is short of terms and multiplied by much, the features' lost bits show: fp32 features, cosine 0.27, s = 50 1.18 at d = 64, 1.1 at 77 and 100, 1.0 at 192;
-// s = 100 1.27, 1.2, 1.11, 1.06 at 256 and 320; cosine 0.89, s = 30 1.27 at 64, 1.08 at 100 and 128.  Such calls stay on bf16 planes (halves_hold).
+// s = 100 1.27, 1.2, 1.11, 1.06 at 256 and 320; cosine 0.89, s = 30 1.27 at 64, 1.08 at 100 and 128.  Such calls stay on bf16 planes (halves_planned, halves_hold).
 // What is relative to the largest rows is a gradient as a whole: entries and rows of it as far below them as 2^-35 of a row of G (2^-51 of 1 in rows of
 // more than 2^-16) keep fewer bits than bf16 planes leave them, and can be 0.  (s = 100, d = 64, keys of other ranks.)
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
 // (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); six bf16 products at 1.2 PFLOP/s are 200 TFLOP/s
-// of fp32 work.  Measured, us a call, bf16 / fp16 planes: fp32 features B = 8192, N = 8, d = 512: 290 / 210, now 201 (logits 68, softmax 28, both
+// of fp32 work.  Measured, us a call, bf16 / fp16 planes: fp32 features B = 8192, N = 8, d = 512: 290 / 210, now 204 (logits 68, softmax 28, both
 // gradient sides 102); 12288, 4, 256: 806 / 561; 10416, 8, 1024: 1029 / 691; 4096, 16, 512: 83 / 70; bf16 features 12288, 8, 100: 220 / 181;
-// 110 drawn fp32 calls: 0.78 in the median.
+// 110 drawn fp32 calls: 0.78 in the median, with those of narrow features and large multipliers that halves_hold has since kept on bf16 planes.
 //
 // Per block (X: the rank's rows, Y: all rows):
 //   planes    features -> planes, rows padded with zeros to whole tiles, columns to whole 64-deep K-steps
