@@ -642,9 +642,10 @@ struct SplitPlan {
 };
 
 // fp32 features in two fp16 planes lose the last bit of one value in four: about 2^-24 sqrt(2 / d) of a logit of unit rows, times s of an exponent.
-// The lines lie where the gradients are as near to 64 bits as on bf16 planes (the measurements are at the top of this file); under the first the
-// fp16 form gains little (us a call, bf16 / fp16 planes: B = 4096, N = 4, d = 64 73 / 70; 8192, 8, 128 136 / 127); calls past the second run six products on
-// tiles and splits chosen for three (8192, 8, 320 184 at s = 50, 271 at 100; 12288, 4, 256 549, 831; planned for six 762).
+// The lines lie where the gradients are as near to 64 bits as on bf16 planes (errors at B = 8192, N = 8, fp16 over bf16 planes, mean of 24 inputs, cosine 0.27: past
+// the second d = 256, s = 60 / 80 / 100 0.99 / 1.04 / 1.07, 320, 100 1.05, 384, 90 1.05, 448, 100 1.04, and 192, 50 at 0.38 1.02; within it 512, 100 1.005;
+// further ones at the top of this file); under the first the fp16 form gains little (us a call, bf16 / fp16 planes: B = 4096, N = 4, d = 64 73 / 70; 8192, 8, 128 136 / 127); calls past the second run six products on
+// tiles and splits chosen for three (8192, 8, 320 184 at s = 1/0.07, 271 at 100; 12288, 4, 256 549 at 50, 831 at 100, planned for six 762).
 bool halves_planned(int64_t d, int np) { return np == 1 || d >= 192; }
 bool halves_hold(float s, int64_t d, int np) { return np == 1 || 5.f * fabsf(s) <= (float)d; }
 
