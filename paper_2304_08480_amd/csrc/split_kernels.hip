@@ -16,7 +16,7 @@
 // Where a logit is short of terms and multiplied by much, the features' lost bits show: fp32 features, cosine 0.27, s = 50 1.18 at d = 64, 1.1 at 77 and 100, 1.0 at 192;
 // s = 100 1.27, 1.2, 1.11, 1.06 at 256 and 320; cosine 0.89, s = 30 1.27 at 64, 1.08 at 100 and 128.  Such calls stay on bf16 planes (halves_planned, halves_hold).
 // What is relative to the largest rows is a gradient as a whole: entries and rows of it as far below them as 2^-35 of a row of G (2^-51 of 1 in rows of
-// more than 2^-16) keep fewer bits than bf16 planes leave them, and can be 0.  (s = 100, d = 64, keys of other ranks.)
+// more than 2^-16) keep fewer bits than bf16 planes leave them, and can be 0.  (s = 100, keys of other ranks.)
 //
 // What bounds the fp32 matrix instruction is its rate, 157 TFLOP/s, of which the products straight from memory
 // (naive_kernels.hip) reach 80 and LDS-tiled ones reached 91 (58 % at their largest); six bf16 products at 1.2 PFLOP/s are 200 TFLOP/s
